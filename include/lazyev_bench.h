@@ -23,9 +23,9 @@ extern "C" {
  *     64..256; default 128).
  *   lazyev_set_target_blocks: stream blocks per layer call the single-launch attention kernel
  *     aims for, taken literally: each unit gets round(n_blocks / units) blocks, at least one
- *     and at most 64.  Until this is called the library sizes the split from the cache length
- *     (about 16 sub-tiles of 16 entries per wave, at least one block per compute unit, at most
- *     two).
+ *     and at most 64 (8 from 64 units on, ceil(512 / units) between: as many as the workspace holds
+ *     records for).  Until this is called the library sizes the split from the number of units
+ *     and the cache length (about one block per compute unit).
  * Errors: EINVAL. */
 int lazyev_set_chunk(lazyev_ctx *ctx, int32_t chunk);
 int lazyev_set_target_blocks(lazyev_ctx *ctx, int32_t n_blocks);
@@ -45,9 +45,9 @@ int lazyev_set_target_blocks(lazyev_ctx *ctx, int32_t n_blocks);
  * 2 and 3 are not assigned.  Errors: EINVAL. */
 int lazyev_set_variant(lazyev_ctx *ctx, int32_t variant);
 
-/* Kernel 4, units of 2..4 blocks: the unit's last block waits for the partial results of the
+/* Kernel 4, units of several blocks: the last block of a group waits for the partial results of the
  * others; the wait is bounded by `ticks` of the GPU's constant 100 MHz counter (default 2000000
- * = 20 ms; the others never wait themselves, so the bound is not reached).  When it is, the block
+ * = 20 ms; a block only waits for blocks started before it, so the bound is not reached).  When it is, the block
  * goes on with what it has and the next lazyev_stats returns LAZYEV_EEXCHANGE.  0 makes a block
  * give up when its first look finds a partial missing (a test of that path).  Errors: EINVAL. */
 int lazyev_set_spin_ticks(lazyev_ctx *ctx, uint32_t ticks);

@@ -20,14 +20,14 @@
 // What follows the stream is serial code of single waves, where instructions, not bytes, set
 // the time: no branches where a select does, addresses worked out beforehand.
 //
-// Partials of a unit.  One block: its partial is the result.  2 .. 4 blocks (the usual split):
-// the unit's last block finishes the unit, the others hand it their partial as a record of
-// stamped 64-bit words (see "hand-over" below): no acknowledgement is waited for, nothing is
-// signalled, one memory round trip.  More blocks: partials are published with device-scope
-// stores, and the block that takes the LAST ticket of its unit (a counter in the workspace,
-// taken after the block's stores have completed) merges them; the ticket resets itself.  In all
-// cases the partials are merged in block order, and the finishing block leaves the unit's
-// softmax statistics (max, 1 / sum per head) for the tracking.
+// Partials of a unit.  One block: its partial is the result.  More (decode_fused_split): a block hands
+// its partial to the last block of its group of up to eight as a record of stamped 64-bit words, the
+// groups' last blocks hand theirs to the unit's last block, which finishes the unit (see
+// "hand-over" below): no acknowledgement is waited for, nothing is signalled, one memory round trip
+// a hop.  (Until this replaced a ticket counter for more than four blocks, whose holder loaded four
+// partials per round trip: 8 units x 2112 entries 14.8 -> 8.6 us per call, 32 x 1056 9.4 -> 7.9.)
+// The partials are merged in an order that depends on the split alone, and the finishing block
+// leaves the unit's softmax statistics (max, 1 / sum per head) for the tracking.
 //
 // Tracking.  The activation test of Alg. 1 needs p = exp(s - m) / l with the statistics of the
 // WHOLE unit, which exist only when the unit's last block is done.  Doing it there puts a
@@ -97,10 +97,22 @@ __host__ __device__ inline int fused_wave_run(int n_sub, int n_split) {
   return (n_sub + kWaves * n_split - 1) / (kWaves * n_split);
 }
 
+// Unit and place in the unit of stream block b.  The units' last blocks, which finish them, come
+// after all others: a block then waits for blocks of lower indices only, and the finishing blocks,
+// which read what all the others hand over, are dealt to the eight XCDs in turn (blocks go to the
+// XCDs round robin; with the blocks of a unit side by side and 8 per unit every finishing block sat
+// on the same XCD: 10.5 instead of 8.5 us per call at 32 units and 1024 entries).
+struct BlockPlace { int unit, split; };
+__device__ __forceinline__ BlockPlace block_place(int b, int n_split, int units) {
+  const int others = (n_split - 1) * units;
+  if (n_split == 1 || b >= others) return {b - others, n_split - 1};
+  return {b / (n_split - 1), b % (n_split - 1)};
+}
+
 #ifdef LAZYEV_TIMELINE
 // Measuring build only (liblazyev_timeline.so, see build.py): every block of the LAST launch
 // leaves time stamps of the constant 100 MHz counter: 0 block start, 1 first sub-tile multiplied,
-// 2 end of wave 0's stream, 3 all four waves done, 4 ticket taken, 5 block end; word 6: the XCD the
+// 2 end of wave 0's stream, 3 all four waves done, 4 all partials there, 5 block end; word 6: the XCD the
 // block ran on (hardware register XCC_ID); word 7: 1 if the block finished its unit.  Read with
 // lazyev_timeline_read.
 __device__ unsigned long long lz_stamp[2048 * 8];
@@ -152,28 +164,6 @@ struct SubTile {
   u32x4_t k[KC];
   u32x4_t v[4];
 };
-
-// What one block writes for another block of the SAME launch to read (the partials) is
-// stored at device ("agent") scope: the stores write through the XCD-local L2, so no whole-cache
-// write-back is needed to publish them.  Publishing is: every wave waits until its stores have
-// completed (wait_own_stores), the block barrier, then one relaxed device-scope atomic on the
-// unit's ticket.  The block that takes the last ticket reads the partials with device-scope loads
-// (which do not use possibly stale cached copies); a cache-invalidating acquire fence followed
-// by ordinary loads measured five times slower.
-// Waits until every global store (and load) this wave has issued is complete.  A block barrier
-// alone does not: the compiler only drains the LDS counter before s_barrier.
-__device__ __forceinline__ void wait_own_stores() {
-  __asm__ volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0); expcnt and lgkmcnt untouched
-  __asm__ volatile("" ::: "memory");
-}
-
-__device__ __forceinline__ void store_f32_device(float *p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float load_f32_device(const float *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // ----------------------------------------------------------------------------- tracking
 // Alg. 1 (first loop) and Eq. 1 for a share of one unit of a finished decode call:
@@ -463,55 +453,7 @@ __global__ __launch_bounds__(kBlock) void track_flush_kernel(const FlushArgs f) 
   }
 }
 
-// --------------------------------------------------------------------- last block of a unit
-// A block's partial as another block reads it: four consecutive output elements (one head) and
-// that head's (max, sum).  The loads are device-scope (sc1) like load_f32_device, but 16 bytes
-// wide, which the atomic builtins do not offer; one asm statement issues all loads of a group
-// and waits for them, so no register is touched while a load is still in flight.
-template <int GW>
-struct PartialGroup {
-  f32x4_t o[GW];
-  float m[GW], l[GW];
-};
-
-__device__ __forceinline__ void load_partials(PartialGroup<2> &g, const float *const (&po)[2],
-                                              const float *const (&pm)[2], const float *const (&pl)[2]) {
-  __asm__ volatile(
-      "global_load_dwordx4 %0, %6, off sc1\n"
-      "global_load_dwordx4 %1, %7, off sc1\n"
-      "global_load_dword %2, %8, off sc1\n"
-      "global_load_dword %3, %9, off sc1\n"
-      "global_load_dword %4, %10, off sc1\n"
-      "global_load_dword %5, %11, off sc1\n"
-      "s_waitcnt vmcnt(0)\n"
-      : "=&v"(g.o[0]), "=&v"(g.o[1]), "=&v"(g.m[0]), "=&v"(g.m[1]), "=&v"(g.l[0]), "=&v"(g.l[1])
-      : "v"(po[0]), "v"(po[1]), "v"(pm[0]), "v"(pm[1]), "v"(pl[0]), "v"(pl[1])
-      : "memory");
-}
-
-__device__ __forceinline__ void load_partials(PartialGroup<4> &g, const float *const (&po)[4],
-                                              const float *const (&pm)[4], const float *const (&pl)[4]) {
-  __asm__ volatile(
-      "global_load_dwordx4 %0, %12, off sc1\n"
-      "global_load_dwordx4 %1, %13, off sc1\n"
-      "global_load_dwordx4 %2, %14, off sc1\n"
-      "global_load_dwordx4 %3, %15, off sc1\n"
-      "global_load_dword %4, %16, off sc1\n"
-      "global_load_dword %5, %17, off sc1\n"
-      "global_load_dword %6, %18, off sc1\n"
-      "global_load_dword %7, %19, off sc1\n"
-      "global_load_dword %8, %20, off sc1\n"
-      "global_load_dword %9, %21, off sc1\n"
-      "global_load_dword %10, %22, off sc1\n"
-      "global_load_dword %11, %23, off sc1\n"
-      "s_waitcnt vmcnt(0)\n"
-      : "=&v"(g.o[0]), "=&v"(g.o[1]), "=&v"(g.o[2]), "=&v"(g.o[3]), "=&v"(g.m[0]), "=&v"(g.m[1]),
-        "=&v"(g.m[2]), "=&v"(g.m[3]), "=&v"(g.l[0]), "=&v"(g.l[1]), "=&v"(g.l[2]), "=&v"(g.l[3])
-      : "v"(po[0]), "v"(po[1]), "v"(po[2]), "v"(po[3]), "v"(pm[0]), "v"(pm[1]), "v"(pm[2]),
-        "v"(pm[3]), "v"(pl[0]), "v"(pl[1]), "v"(pl[2]), "v"(pl[3])
-      : "memory");
-}
-
+// ------------------------------------------------------------- merging the partials of a unit
 // Running merge of partials in block order.  Every product and sum is written out with its
 // rounding (no contraction left to the compiler), so that all kernel instances produce the same
 // bits from the same partials.
@@ -552,86 +494,103 @@ __device__ __forceinline__ void write_unit_row(const DecodeArgs &a, int unit, co
   }
 }
 
-// ------------------------------------------------ hand-over of partials, units of 2..4 blocks
-// The unit's LAST block (highest block index) always finishes the unit; the others hand their
-// partial over as a record of 64-bit words, each = (number of the launch << 32) | value bits,
-// written and read with 64-bit device-scope atomics.  A word that shows this launch's number
-// holds this launch's value, whatever else is still on its way, so the writer neither waits for
-// its stores nor signals, and the reader needs no second round trip after a flag: it reads the
-// words it needs until all of them carry the number.  Blocks are started in index order and the
-// writers wait for nothing, so the reader's wait ends; it is bounded all the same (spin_ticks of
-// the 100 MHz counter), after which the block raises the workspace's fault word and goes on.
-// Rows 0..3 of 256 words hold the output elements (element 4 t + i of thread t in word
-// i * 256 + t: one store instruction of a wave writes 512 contiguous bytes), row 4 the heads'
-// maxima (words 0..7) and sums (words 8..15).
-constexpr int kRecWords = 5 * kBlock;
-constexpr int kHandOverMax = 4;                    // blocks per unit up to which partials are handed over
+// ------------------------------------------------------------------- hand-over of partials
+// A block hands its partial over to a block of a higher index as a record of 64-bit words, each =
+// (number of the launch << 32) | value bits, written and read with 64-bit device-scope atomics.  A
+// word that shows this launch's number holds this launch's value, whatever else is still on its way,
+// so the writer neither waits for its stores nor signals, and the reader needs no second round
+// trip after a flag: it reads the words it needs until all of them carry the number.  Blocks are
+// started in index order and a block waits for blocks of lower indices only, so every wait ends;
+// it is bounded all the same (spin_ticks of the 100 MHz counter), after which the block raises the
+// workspace's fault word and goes on.
+// A unit's blocks form groups of kMergeRadix; the last block of a group (its leader) merges the
+// group, and the unit's last block, a leader itself, merges what the other leaders hand over: one
+// hop for up to kMergeRadix blocks, two for up to kFusedSplitMax.  A hop is one memory round trip
+// whatever the number of records, because all of them are requested together.
+// Record of a block: for each of the four waves six rows of 64 words; rows 0..3 hold the output
+// elements (element 4 t + i of thread t in row i: one store instruction of a wave writes 512
+// contiguous bytes), rows 4 and 5 the maximum and the sum of thread t's head (each thread its own
+// copy: what the reader needs of a head then never waits for another wave's store).  A thread's six
+// words lie within the reach of a load's constant offset.
+constexpr int kRecWords = 6 * kBlock;
+__device__ __forceinline__ unsigned rec_at(int t) { return static_cast<unsigned>(t >> 6) * (6 * 64) + (t & 63); }
+constexpr int kMergeRadix = 8;
 
-__device__ __forceinline__ void rec_store(unsigned long long *p, float v, unsigned seq) {
+__device__ __forceinline__ void rec_word_store(unsigned long long *p, float v, unsigned seq) {
   __hip_atomic_store(p, (static_cast<unsigned long long>(seq) << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void rec_store(unsigned long long *rec, int t_own, const f32x4_t &o, float m, float l, unsigned seq) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) rec_word_store(rec + rec_at(t_own) + i * 64, o[i], seq);
+  rec_word_store(rec + rec_at(t_own) + 4 * 64, m, seq);
+  rec_word_store(rec + rec_at(t_own) + 5 * 64, l, seq);
+}
 // What one thread reads of another block's record: its four output elements, its head's max and sum.
 struct RecPart { unsigned long long w[6]; };
-__device__ __forceinline__ void rec_load(RecPart &r, const unsigned long long *rec, int t_own, int h) {
+__device__ __forceinline__ void rec_load(RecPart &r, const unsigned long long *rec, unsigned at) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    r.w[i] = __hip_atomic_load(rec + i * kBlock + t_own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  r.w[4] = __hip_atomic_load(rec + 4 * kBlock + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  r.w[5] = __hip_atomic_load(rec + 4 * kBlock + kHeadPad + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int i = 0; i < 6; ++i)
+    r.w[i] = __hip_atomic_load(rec + at + i * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ bool rec_valid(const RecPart &r, unsigned seq) {
   bool ok = true;
 #pragma unroll
-  for (int i = 0; i < 6; ++i) ok = ok && static_cast<unsigned>(r.w[i] >> 32) == seq;
+  for (int i = 0; i < 6; ++i) ok = ok & (static_cast<unsigned>(r.w[i] >> 32) == seq);
   return ok;
 }
 __device__ __forceinline__ float rec_value(unsigned long long w) { return __uint_as_float(static_cast<unsigned>(w)); }
+__device__ __forceinline__ f32x4_t rec_values(const RecPart &r) {
+  return f32x4_t{rec_value(r.w[0]), rec_value(r.w[1]), rec_value(r.w[2]), rec_value(r.w[3])};
+}
+
+// What one thread needs of n <= N records at rec, rec + stride, ..., all requested together, again
+// until every word carries the launch's number; then the records and (m, l, o) merged in this order.
+// The running merge starts from the first record as it is: folding it into the empty state would
+// reproduce exactly its bits (factors 0 and exp(0) = 1) at the price of a dozen instructions.
+template <int N>
+__device__ __forceinline__ Merge merge_records(const DecodeArgs &a, const unsigned long long *rec, int stride, int n,
+                                               int t_own, float m, float l, const f32x4_t &o) {
+  Merge mg;
+  if (n == 0) {                                    // uniform
+    mg.m = m; mg.l = l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) mg.o[i] = o[i];
+    return mg;
+  }
+  RecPart r[N];
+  const unsigned at = rec_at(t_own);
+  unsigned long long t_first = 0;
+  for (;;) {
+#pragma unroll
+    for (int j = 0; j < N; ++j)                    // (beyond n: the last record once more, no branches among the loads)
+      rec_load(r[j], rec + min(j, n - 1) * stride, at);
+    bool ok = true;
+#pragma unroll
+    for (int j = 0; j < N; ++j) ok = ok & rec_valid(r[j], a.seq);
+    if (__builtin_amdgcn_ballot_w64(!ok) == 0) break;   // (the wave goes on together)
+    const unsigned long long now = wall_clock64();
+    if (t_first == 0) t_first = now;
+    if (now - t_first >= a.spin_ticks) {           // (a limit of 0: no second look)
+      atomicOr(a.ws.fault, 1);                     // (cannot happen otherwise, see above; the row is then wrong)
+      break;
+    }
+  }
+  mg.m = rec_value(r[0].w[4]);
+  mg.l = rec_value(r[0].w[5]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) mg.o[i] = rec_value(r[0].w[i]);
+#pragma unroll
+  for (int j = 1; j < N; ++j)
+    if (j < n) mg.fold(rec_value(r[j].w[4]), rec_value(r[j].w[5]), rec_values(r[j]));
+  mg.fold(m, l, o);
+  return mg;
+}
 
 __global__ void clear_records_kernel(unsigned long long *rec, size_t n_words) {
   for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n_words;
        i += static_cast<size_t>(gridDim.x) * blockDim.x)
     rec[i] = 0;
-}
-
-// Merges the unit's block partials (in block order, so the result does not depend on which
-// block came last) into the output row and stores the unit's softmax statistics.  Thread t
-// owns output elements 4t .. 4t+3 (all of one head); GW partials per memory round trip.
-// The calling block is partial `own_j` itself and has it in registers (own_o: its four output
-// elements, own_m / own_l: its head's max and sum): those are used instead of what memory holds
-// in that place.  kOwn: the unit has no other block and nothing is loaded at all.
-template <int GW, bool kOwn>
-__device__ void finish_unit(const DecodeArgs &a, int unit, int n_split, int own_j, const f32x4_t &own_o,
-                            float own_m, float own_l) {
-  const int tid = threadIdx.x;
-  const int G = a.group;
-  const float *ml = a.ws.part_ml + static_cast<size_t>(unit) * a.n_split_max * (2 * G);
-  const float *pa = a.ws.part_acc + static_cast<size_t>(unit) * a.n_split_max * (G * D);
-  const int e0 = 4 * tid;
-  const int ec = min(e0, G * D - 4);               // threads beyond the group's rows load a valid place
-  const int h = ec / D;
-
-  Merge mg;
-  for (int j0 = 0; j0 < n_split; j0 += GW) {
-    // all loads unconditional (indices clamped to real partials) and issued together
-    PartialGroup<GW> g;
-    const float *po[GW], *pm[GW], *pl[GW];
-#pragma unroll
-    for (int jj = 0; jj < GW; ++jj) {
-      const int j = min(j0 + jj, n_split - 1);
-      po[jj] = pa + static_cast<size_t>(j) * (G * D) + ec;
-      pm[jj] = ml + j * (2 * G) + h;
-      pl[jj] = ml + j * (2 * G) + G + h;
-    }
-    if (!kOwn) load_partials(g, po, pm, pl);
-#pragma unroll
-    for (int jj = 0; jj < GW; ++jj) {
-      if (j0 + jj >= n_split) break;               // uniform
-      if (j0 + jj == own_j) { g.o[jj] = own_o; g.m[jj] = own_m; g.l[jj] = own_l; }   // (never read back)
-      mg.fold(g.m[jj], g.l[jj], g.o[jj]);
-    }
-  }
-  write_unit_row(a, unit, mg, e0, h);
 }
 
 // ------------------------------------------------------------------------------- the kernel
@@ -650,10 +609,11 @@ __device__ void finish_unit(const DecodeArgs &a, int unit, int n_split, int own_
 // all blocks of the launch are resident at once with eight waves each (a stream block and a
 // tracking block per compute unit: every instance keeps to 128 registers per lane); a launch of
 // more blocks runs four-wave blocks whose stream waves build their own lists.
-// kSplit > 0: the instance is for units of exactly kSplit blocks (the benchmark workloads' 2 and
-// 4).  What follows the stream is serial code of single waves, and a split known at compile
-// time takes the ticket route, the loops over a variable number of partials and the divisions
-// by the split out of it.
+// kSplit > 0: the instance is for units of exactly kSplit blocks (1 .. 8, with list waves).  What
+// precedes and follows the stream is serial code of single waves, and a split known at compile time takes the
+// second hop, the loads of a variable number of records and the divisions by the split out of it
+// (us per call with an instance of its own / with the one for any split: 32 units x 600 entries, 3 blocks 6.4
+// / 7.7, 4 6.3 / 7.2, 6 6.5 / 7.0).
 template <bool kCompact, bool kLong = false, bool kListWaves = false, int kSplit = 0>
 __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fused_kernel(
     const bf16_t *k_cache, const bf16_t *v_cache, const bf16_t *k_new_all, const bf16_t *v_new_all, const int n_old_call, const int n_split_call, const int capacity,
@@ -664,7 +624,6 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
   __shared__ u32x4_t stage_lds[kWaves][16 * 16];
   extern __shared__ float logit_lds[];             // [kWaves][min(run, kRunMax)][16 entries][8 heads]
   __shared__ unsigned cnt_lds[kWaves];
-  __shared__ int last_flag;
   __shared__ unsigned cand_total;                  // candidate records of this block so far
   __shared__ float run_lse[kWaves][kHeadPad];      // kLong: each wave's latest log-sum-exp per head (one word: no torn reads)
 
@@ -677,7 +636,9 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
     // like the stream blocks
     if (kListWaves && threadIdx.x >= kBlock) return;  // (the tracking has no use for list waves)
     const int tb = blockIdx.x - n_split * units_call;
-    const int unit = tb / n_split, part = tb % n_split;
+    const int n_track = a.n_track;
+    const BlockPlace at = block_place(tb, n_track, units_call);
+    const int unit = at.unit, part = at.split;
     TrackArgs k;
     if (!track_for_unit(a.track, unit, k)) return;
     float m[kHeadPad], invl[kHeadPad];
@@ -692,26 +653,26 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
       __syncthreads();
     }
     if (k.compact) {
-      n_act = track_records(k, unit, part, n_split, m, invl, log_mask);
+      n_act = track_records(k, unit, part, n_track, m, invl, log_mask);
     } else {
-      const int rounds = track_rounds((k.n_old + 1 + 15) >> 4, n_split);
+      const int rounds = track_rounds((k.n_old + 1 + 15) >> 4, n_track);
       for (int r0 = 0; r0 < rounds; r0 += kTrackRows) {
         TrackBatch b;
-        track_load(k, unit, part, n_split, r0, b);
-        n_act += track_apply(k, unit, part, n_split, r0, b, m, invl, log_mask);
+        track_load(k, unit, part, n_track, r0, b);
+        n_act += track_apply(k, unit, part, n_track, r0, b, m, invl, log_mask);
       }
     }
     if (k.bitlog) {
       // ... and every word of the unit is written by the one block whose entries it covers: word
       // j holds sub-tiles 2j and 2j + 1, which the wave map gives to one block (an even wave and
       // the next one); with candidate records that is a block of the logged call's own split,
-      // whose records this tracking block reads if the block's index is its own modulo n_split
+      // whose records this tracking block reads if the block's index is its own modulo n_track
       __syncthreads();
-      const int parts = k.compact ? k.n_parts : n_split;
+      const int parts = k.compact ? k.n_parts : n_track;
       uint32_t *dst = k.bitlog + static_cast<size_t>(unit) * k.log_unit_stride;
       for (int j = threadIdx.x; j < k.log_words; j += kBlock) {
         const int wv = (2 * j) % (kWaves * parts);
-        const int owner = (parts - 1 - wv / kWaves) % n_split;
+        const int owner = (parts - 1 - wv / kWaves) % n_track;
         if (owner == part) dst[j] = log_mask[j];
       }
     }
@@ -727,7 +688,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
     __syncthreads();
   }
   const int c = lane & 15, g = lane >> 4;
-  const int unit = blockIdx.x / n_split, split = blockIdx.x % n_split;
+  const BlockPlace place = block_place(blockIdx.x, n_split, units_call);
+  const int unit = place.unit, split = place.split;
   int n_old = n_old_call;
   if (slots_on) {                                  // per-sequence timing: this unit's own length
     const int seq_s = unit / a.n_kv_heads;
@@ -737,11 +699,6 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
   }
   const int n1 = n_old + 1;
   const int n_sub = (n1 + 15) >> 4;
-  // A unit of one block needs no exchange: its partial is the whole result.  Units of up to
-  // kHandOverMax blocks hand their partials over to the unit's last block; longer splits take
-  // tickets and the block with the last one finishes.
-  const bool alone = n_split == 1;
-  const bool hand_over = n_split >= 2 && n_split <= kHandOverMax;
 
   // the appended row goes to slot N (the stream waves read it from k_new / v_new, nobody from the slot)
   auto append_row = [&]() {
@@ -858,7 +815,6 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
     __syncthreads();                               // the stream has ended, the waves' statistics are in LDS
     run_scan(sp);
     __syncthreads();                               // cand_total is complete
-    if (!hand_over) __syncthreads();               // (the ticket route has one more)
     return;
   }
 
@@ -1120,55 +1076,12 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
     for (int i = 0; i < 4; ++i) v_own[i] = fmaf(f, x[i], v_own[i]);
     l_own = fmaf(f, lsum_lds[w][h_own], l_own);
   }
-  // the block's max and sum of head lane % 8 (what lanes 0 .. G - 1 of wave 0 store for the unit's
-  // other blocks)
-  const int hh = lane & 7;
-  float mbh = m_lds[0][hh];
-#pragma unroll
-  for (int w = 1; w < kWaves; ++w) mbh = fmaxf(mbh, m_lds[w][hh]);
-  float lbh = 0.f;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    const float mw = m_lds[w][hh];
-    lbh = fmaf(mw == -INFINITY ? 0.f : __expf(mw - mbh), lsum_lds[w][hh], lbh);
-  }
-  const bool finisher = split == n_split - 1;
+  const bool finisher = split == n_split - 1;      // the unit's last block
+  const int group0 = split / kMergeRadix * kMergeRadix;   // the blocks group0 .. of this block's group
+  const bool leader = finisher || split - group0 == kMergeRadix - 1;
   const int t_own = ec >> 2;                       // (threads beyond the group's rows read a valid place)
-  const unsigned long long *recs =
-      a.ws.part_rec + static_cast<size_t>(unit) * ((kHandOverMax - 1) * kRecWords);
-  RecPart r[kHandOverMax - 1];                     // (read only where loaded: the finishing block's j < n_split - 1)
-  if (hand_over || !alone) {
-    // the heads' max and sum of this block go out from ONE wave (lane h of wave 0 holds head h's):
-    // dword stores of several waves into the one cache line they share were seen to reach a
-    // device-scope load late
-    const float mb = mbh, l = lbh;
-    if (hand_over && !finisher) {
-      unsigned long long *rec = const_cast<unsigned long long *>(recs) + static_cast<size_t>(split) * kRecWords;
-      if (e0 < G * D) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) rec_store(rec + i * kBlock + tid, v_own[i], a.seq);
-      }
-      if (tid < G) {
-        rec_store(rec + 4 * kBlock + tid, mb, a.seq);
-        rec_store(rec + 4 * kBlock + kHeadPad + tid, l, a.seq);
-      }
-    } else if (hand_over) {
-      // a first look at the other blocks' records, requested before the work below
-#pragma unroll
-      for (int j = 0; j < kHandOverMax - 1; ++j)
-        if (j < n_split - 1) rec_load(r[j], recs + static_cast<size_t>(j) * kRecWords, t_own, h_own);
-    } else {
-      // publish the partial with device-scope (write-through) stores, 16 bytes wide for the values
-      const size_t part = static_cast<size_t>(unit) * a.n_split_max + split;
-      float *pacc = a.ws.part_acc + part * (G * D);
-      if (e0 < G * D) __asm__ volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(pacc + e0), "v"(v_own) : "memory");
-      if (tid < G) {
-        float *ml = a.ws.part_ml + part * (2 * G);
-        store_f32_device(ml + tid, mb);
-        store_f32_device(ml + G + tid, l);
-      }
-    }
-  }
+  unsigned long long *recs = a.ws.part_rec + static_cast<size_t>(unit) * a.rec_per_unit * kRecWords;
+  if (!leader && e0 < G * D) rec_store(recs + static_cast<size_t>(split) * kRecWords, tid, v_own, mb_own, l_own, a.seq);
   // what only the NEXT launch needs, while the partial travels: the appended row and this wave's
   // candidate list (list waves, where the block has them, do both meanwhile)
   if constexpr (!kListWaves) {
@@ -1179,74 +1092,37 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
       run_scan(sp);
     }
   }
-  const size_t count_at = (static_cast<size_t>(unit) * a.p_stride +
-                           static_cast<size_t>(split) * fused_part_cap(n_old, n_split)) * kHeadPad;
-  if (hand_over) {
-    if (finisher) {
-      // wait until every word this thread needs carries this launch's number
-      unsigned long long t_first = 0;
-      for (;;) {
-        bool ok = true;
-#pragma unroll
-        for (int j = 0; j < kHandOverMax - 1; ++j)
-          if (j < n_split - 1) ok = ok && rec_valid(r[j], a.seq);
-        if (ok) break;
-        const unsigned long long now = wall_clock64();
-        if (t_first == 0) t_first = now;
-        if (now - t_first >= a.spin_ticks) {       // (a limit of 0: no second look)
-          atomicOr(a.ws.fault, 1);                 // (cannot happen otherwise, see above; the row is then wrong)
-          break;
-        }
-#pragma unroll
-        for (int j = 0; j < kHandOverMax - 1; ++j)
-          if (j < n_split - 1 && !rec_valid(r[j], a.seq))
-            rec_load(r[j], recs + static_cast<size_t>(j) * kRecWords, t_own, h_own);
-      }
+  if (leader) {
+    constexpr int kIn = kSplit > 1 ? kSplit - 1 : kMergeRadix - 1;   // (instances of a fixed split have one group)
+    // (for six records and more the count is kept from the compiler, which would otherwise hold so
+    // many addresses at once that registers spill: 8 blocks per unit of 2048 entries, 14.4 us instead of 8.0)
+    int n_in = kSplit > 0 ? kSplit - 1 : split - group0;
+    if (kSplit > 6) __asm__("" : "+s"(n_in));
+    const Merge mg = merge_records<kIn>(a, recs + static_cast<size_t>(group0) * kRecWords, kRecWords, n_in, t_own,
+                                        mb_own, l_own, v_own);
+    const f32x4_t o4 = {mg.o[0], mg.o[1], mg.o[2], mg.o[3]};
+    if (kSplit > 0 || n_split <= kMergeRadix) {
       STAMP(4);
-      // in block order: the others', then this block's own.  The running merge starts from block
-      // 0's partial as it is: folding it into the empty state would reproduce exactly its bits
-      // (factors 0 and exp(0) = 1) at the price of a dozen instructions.
-      Merge mg;
-      mg.m = rec_value(r[0].w[4]);
-      mg.l = rec_value(r[0].w[5]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) mg.o[i] = rec_value(r[0].w[i]);
-#pragma unroll
-      for (int j = 1; j < kHandOverMax - 1; ++j)
-        if (j < n_split - 1) {
-          const f32x4_t oj = {rec_value(r[j].w[0]), rec_value(r[j].w[1]), rec_value(r[j].w[2]), rec_value(r[j].w[3])};
-          mg.fold(rec_value(r[j].w[4]), rec_value(r[j].w[5]), oj);
-        }
-      mg.fold(mb_own, l_own, v_own);
       write_unit_row(a, unit, mg, e0, h_own);
+    } else if (!finisher) {
+      if (e0 < G * D) rec_store(recs + static_cast<size_t>(split) * kRecWords, tid, o4, mg.m, mg.l, a.seq);
+    } else {
+      // the other leaders' records (blocks kMergeRadix - 1, 2 kMergeRadix - 1, ...)
+      const Merge all = merge_records<kFusedSplitMax / kMergeRadix - 1>(
+          a, recs + static_cast<size_t>(kMergeRadix - 1) * kRecWords, kMergeRadix * kRecWords, group0 / kMergeRadix, t_own,
+          mg.m, mg.l, o4);
+      STAMP(4);
+      write_unit_row(a, unit, all, e0, h_own);
     }
-    if (kCompact) {
-      __syncthreads();                             // cand_total is complete
-      if (tid == 0) *reinterpret_cast<int32_t *>(a.logits_out + count_at) = static_cast<int32_t>(cand_total);
-    }
-    STAMPV(7, static_cast<unsigned long long>(finisher));
-    STAMP(5);
-    return;
   }
-  // ---- ticket: the last block of the unit finishes it
-  if (!alone) wait_own_stores();                   // every wave's partial stores have completed ...
-  __syncthreads();
-  if (tid == 0) {
-    int prev = 0;
-    if (!alone)
-      prev = __hip_atomic_fetch_add(a.ticket + unit, 1, __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_AGENT);   // ... before its ticket is taken
-    last_flag = (prev == n_split - 1);
-    if (!alone && prev == n_split - 1) a.ticket[unit] = 0;   // ready for the next launch
-    if (kCompact) *reinterpret_cast<int32_t *>(a.logits_out + count_at) = static_cast<int32_t>(cand_total);
+  if (kCompact) {
+    __syncthreads();                               // cand_total is complete
+    if (tid == 0)
+      *reinterpret_cast<int32_t *>(a.logits_out + (static_cast<size_t>(unit) * a.p_stride +
+                                                   static_cast<size_t>(split) * fused_part_cap(n_old, n_split)) * kHeadPad) =
+          static_cast<int32_t>(cand_total);
   }
-  __syncthreads();
-  STAMP(4);
-  STAMPV(7, static_cast<unsigned long long>(last_flag));
-  if (!last_flag) { STAMP(5); return; }
-  // merge the unit's partials (this block's own from its registers) into the output row
-  if (alone) finish_unit<2, true>(a, unit, n_split, split, v_own, mb_own, l_own);
-  else finish_unit<4, false>(a, unit, n_split, split, v_own, mb_own, l_own);
+  STAMPV(7, static_cast<unsigned long long>(finisher));
   STAMP(5);
 }
 
@@ -1264,6 +1140,38 @@ int decode_fused_wave_run(int n_sub, int n_split) { return fused_wave_run(n_sub,
 int decode_fused_run_max() { return kRunMax; }
 int decode_fused_head_pad() { return kHeadPad; }
 size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * sizeof(unsigned long long); }
+
+// Blocks per unit.  Measured on 28 query / 4 KV heads, us per call:
+//   * no more blocks than compute units: a second stream block on some of them holds up the whole
+//     launch (80 units x 2200 entries: 3 blocks per unit 17.4, 4 22.1; 48 units: 5 12.6, 6 16.6), and with
+//     two on all of them the bytes in flight only widen the spread of the blocks' ends (128 units x
+//     4144 entries: 44.5 with one, 46.4 with two).
+//   * only a long cache pays for the second hop that more than kMergeRadix blocks need (8 units x 2200
+//     entries: 8 blocks 8.0, 16 9.6, 32 9.7; x 6200 entries: 14.6, 12.8, 11.9).
+//   * seven or eight blocks only where they do not fill the chip to the last compute unit (32 units x
+//     1200 / 2200 / 6200 entries: 6 blocks 7.9 / 10.6 / 21.4, 8 8.6 / 11.1 / 22.0; 24 units x 6200: 6 19.0, 8 18.0).
+//   * two sub-tiles or more per wave (8 units x 600 entries: 4 blocks 6.0, 5 6.0; x 350: 2 5.3, 4 5.5),
+//     but two blocks from a unit's fifth sub-tile on.
+//   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to
+//     two per compute unit (96 units x 6200 entries: 2 blocks per unit 61.8, 5 58.1; 144 units: 1 98.9, 3 88.5;
+//     with 2200 entries still 20.1 against 23.6 and 33.1 against 31.1: from 32 sub-tiles per wave on).
+int decode_fused_split(int units, int n_sub) {
+  constexpr int kUnitsOfChip = 256;
+  int n = kUnitsOfChip / units;
+  if (n < 1) n = 1;
+  if (n > kMergeRadix && n_sub <= kWaves * kMergeRadix * 8) n = kMergeRadix;
+  if (n > 6 && n <= kMergeRadix && n * units > 216) n = 6;
+  const int n2 = 2 * kUnitsOfChip / units;
+  if (units < kUnitsOfChip && n_sub >= 32 * kWaves * n && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2;
+  const int by_work = n_sub <= kWaves ? 1 : n_sub < 4 * kWaves ? 2 : (n_sub + kWaves) / (2 * kWaves);
+  return n < by_work ? n : by_work;
+}
+
+int decode_fused_records_per_unit(int units) {
+  // as many as a unit can have blocks, as long as that keeps the records of all units within a few MB
+  const int r = (2 * 256 + units - 1) / units;
+  return r < kMergeRadix ? kMergeRadix : r > kFusedSplitMax ? kFusedSplitMax : r;
+}
 
 hipError_t launch_clear_records(unsigned long long *rec, size_t n_words, hipStream_t stream) {
   hipLaunchKernelGGL(clear_records_kernel, dim3(256), dim3(256), 0, stream, rec, n_words);
@@ -1317,7 +1225,7 @@ static int compute_units() {
 hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) {
   const int units = a.batch * a.n_kv_heads;
   if (a.dtype != 1 || a.head_dim != D || a.group > kHeadPad || a.n_split < 1 ||
-      a.n_split > kFusedSplitMax || a.n_split > a.n_split_max || !a.ticket || !a.logits_out ||
+      a.n_split > kFusedSplitMax || a.n_split > a.rec_per_unit || !a.logits_out ||
       !a.ws.part_rec || !a.ws.fault || a.seq == 0 ||
       !a.stat_out || a.p_stride < (a.n_old + 16) / 16 * 16 ||
       (a.track.valid && (a.track.units != units || !a.track.logits || !a.track.stat ||
@@ -1342,19 +1250,34 @@ hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent
   const bool long_run = fused_wave_run(n_sub, a.n_split) > kRunMax;
   // list waves (blocks of eight waves) where every block of the launch is resident at once: two
   // such blocks fit a compute unit
-  const int n_blocks = sb + (a.track.valid ? sb : 0);
-  const bool list_waves = n_blocks <= 2 * compute_units();
+  const int n_blocks = sb + (a.track.valid ? a.n_track * units : 0);
+  const bool list_waves = n_blocks <= 2 * compute_units() ;
   const dim3 grid(n_blocks), b4(kBlock), b8(2 * kBlock);
 #define LAZYEV_LAUNCH(instance, block) \
   hipLaunchKernelGGL(instance, grid, block, lds_all, stream, kc, vc, kn, vn, a.n_old, a.n_split, a.capacity, units, slots_on, a)
-  if (a.variant == 6 && long_run && list_waves && a.n_split == 2) LAZYEV_LAUNCH((decode_fused_kernel<true, true, true, 2>), b8);
-  else if (a.variant == 6 && long_run && list_waves) LAZYEV_LAUNCH((decode_fused_kernel<true, true, true>), b8);
-  else if (a.variant == 6 && long_run) LAZYEV_LAUNCH((decode_fused_kernel<true, true, false>), b4);
-  else if (a.variant == 6 && list_waves && a.n_split == 2) LAZYEV_LAUNCH((decode_fused_kernel<true, false, true, 2>), b8);
-  else if (a.variant == 6 && list_waves) LAZYEV_LAUNCH((decode_fused_kernel<true, false, true>), b8);
-  else if (a.variant == 6 && a.n_split == 4) LAZYEV_LAUNCH((decode_fused_kernel<true, false, false, 4>), b4);
+#define LAZYEV_SPLIT(n) \
+  case n: \
+    if (long_run) LAZYEV_LAUNCH((decode_fused_kernel<true, true, true, n>), b8); \
+    else LAZYEV_LAUNCH((decode_fused_kernel<true, false, true, n>), b8); \
+    break;
+  if (a.variant == 6 && list_waves) {
+    switch (a.n_split) {
+      LAZYEV_SPLIT(1)
+      LAZYEV_SPLIT(2)
+      LAZYEV_SPLIT(3)
+      LAZYEV_SPLIT(4)
+      LAZYEV_SPLIT(5)
+      LAZYEV_SPLIT(6)
+      LAZYEV_SPLIT(7)
+      LAZYEV_SPLIT(8)
+      default:
+        if (long_run) LAZYEV_LAUNCH((decode_fused_kernel<true, true, true>), b8);
+        else LAZYEV_LAUNCH((decode_fused_kernel<true, false, true>), b8);
+    }
+  } else if (a.variant == 6 && long_run) LAZYEV_LAUNCH((decode_fused_kernel<true, true, false>), b4);
   else if (a.variant == 6) LAZYEV_LAUNCH((decode_fused_kernel<true, false, false>), b4);
   else LAZYEV_LAUNCH((decode_fused_kernel<false, false, false>), b4);
+#undef LAZYEV_SPLIT
 #undef LAZYEV_LAUNCH
   const hipError_t e = hipGetLastError();
   if (ev) { (void)hipEventRecord(ev[1], stream); (void)hipEventRecord(ev[2], stream); }

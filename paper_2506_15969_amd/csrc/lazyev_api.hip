@@ -110,7 +110,7 @@ int32_t capacity_of(const lazyev_config *c) {
 size_t fused_p_stride(int32_t capacity) { return static_cast<size_t>((capacity + 15) / 16 * 16) + 65 * 64; }
 
 struct Layout {
-  size_t part_acc, part_ml, p_tilde, logits1, stat, prefill_stat, src_index, sel_keys, bitlog, activations, rows_moved, ticket, records, fault, hist, slots, total;
+  size_t part_acc, part_ml, p_tilde, logits1, stat, prefill_stat, src_index, sel_keys, bitlog, activations, rows_moved, records, fault, hist, slots, total;
   int32_t log_words, log_slots;     // 0: no activation log for this shape
   int32_t n_split_max;
 };
@@ -150,10 +150,10 @@ Layout layout_of(const lazyev_config *c) {
   }
   l.activations = off; off = align_up(off + static_cast<size_t>(c->n_layers) * units * lazyev::decode_slice_max() * sizeof(unsigned long long));
   l.rows_moved = off; off = align_up(off + static_cast<size_t>(c->n_layers) * units * sizeof(unsigned long long));
-  l.ticket = off; off = align_up(off + units * sizeof(int32_t));
-  // fused kernel, units of 2..4 blocks: three stamped records of partials per unit (zero at first:
+  // fused kernel: stamped records of the partials that a unit's blocks hand over (zero at first:
   // no launch has the number 0), and the word a block raises when it gives up waiting for one
-  l.records = off; off = align_up(off + units * 3 * lazyev::decode_fused_record_bytes());
+  l.records = off;
+  off = align_up(off + units * lazyev::decode_fused_records_per_unit(static_cast<int>(units)) * lazyev::decode_fused_record_bytes());
   l.fault = off; off = align_up(off + sizeof(int32_t));
   l.hist = off; off = align_up(off + LAZYEV_MAX_HIST_BINS * sizeof(unsigned long long));
   l.slots = off; off = align_up(off + 3 * static_cast<size_t>(c->batch) * sizeof(int32_t));
@@ -400,7 +400,6 @@ int lazyev_init(const lazyev_config *cfg, lazyev_ctx **out) {
   ctx->pend_layer = -1;
   ctx->ws.activations = reinterpret_cast<unsigned long long *>(base + l.activations);
   ctx->ws.rows_moved = reinterpret_cast<unsigned long long *>(base + l.rows_moved);
-  ctx->ws.ticket = reinterpret_cast<int32_t *>(base + l.ticket);
   ctx->ws.part_rec = reinterpret_cast<unsigned long long *>(base + l.records);
   ctx->ws.fault = reinterpret_cast<int32_t *>(base + l.fault);
   ctx->launch_seq = 0;
@@ -415,7 +414,7 @@ int lazyev_init(const lazyev_config *cfg, lazyev_ctx **out) {
   if (ctx->chunk > lazyev::decode_chunk_max()) { delete ctx; return LAZYEV_EINVAL; }
   if (static_scratch_of(&ctx->device, &ctx->static_scratch) != hipSuccess) { delete ctx; return LAZYEV_EHIP; }
 
-  // activation counters, moved-row counters, tickets, records and the fault word lie next to each other
+  // activation counters, moved-row counters, records and the fault word lie next to each other
   hipError_t e = hipMemsetAsync(ctx->ws.activations, 0, l.total - l.activations, ctx->stream);
   if (e == hipSuccess)
     e = lazyev::launch_init_state(cfg->ts, cfg->mri, cfg->pos,
@@ -496,22 +495,14 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
     // fused kernel: n_split blocks of four waves per unit, every wave a run of 16-entry sub-tiles
     const int n_sub = (n_old + 1 + 15) / 16;
     int n_split = (ctx->target_blocks + ctx->units / 2) / ctx->units;
-    if (!ctx->target_blocks_set) {
-      // one block per compute unit, whatever the cache length: measured at 128 units over caches
-      // of 1088 .. 6144 entries against 1.5 and 2 blocks per compute unit (2448 / 3248 / 4144 /
-      // 5048 entries: 28.3 / 36.5 / 44.5 / 55.9 us per call against 30.2 / 37.4 / 46.4 / 57.0 with
-      // two per compute unit; three blocks per two compute units are worst, 39.3 at 3248).  A
-      // second stream block on a compute unit doubles the bytes its waves keep in flight, which
-      // this memory system answers with a wider spread of the blocks' ends, not with more
-      // bandwidth; a wave whose run then exceeds the sub-tiles it keeps logits of in LDS leaves
-      // its candidate lists segment by segment.
-      n_split = (256 + ctx->units - 1) / ctx->units;
-    }
+    if (!ctx->target_blocks_set) n_split = lazyev::decode_fused_split(ctx->units, n_sub);
     if (n_split > (n_sub + 3) / 4) n_split = (n_sub + 3) / 4;
     if (n_split > lazyev::decode_fused_split_max()) n_split = lazyev::decode_fused_split_max();
-    if (n_split > ctx->n_split_max) n_split = ctx->n_split_max;
+    a.rec_per_unit = lazyev::decode_fused_records_per_unit(ctx->units);
+    if (n_split > a.rec_per_unit) n_split = a.rec_per_unit;
     if (n_split < 1) n_split = 1;
     a.n_split = n_split;
+    a.n_track = n_split;
     a.chunk = 16;
     a.logits_out = ctx->ws.logits[ctx->cur_buf];
     a.stat_out = ctx->ws.stat[ctx->cur_buf];
@@ -560,13 +551,12 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
   a.pos = c.pos + static_cast<size_t>(layer) * slab;
   a.p_out = p_out; a.p_override = p_override;
   a.ws = ctx->ws;
-  a.ticket = ctx->ws.ticket;
   if (kind == 4) {
     // the number of this launch stamps the partials its blocks hand over; 0 is what the records
     // hold before any launch, so after a wrap-around they are cleared and the count restarts
     if (++ctx->launch_seq == 0) {
       const hipError_t ec = lazyev::launch_clear_records(
-          ctx->ws.part_rec, static_cast<size_t>(ctx->units) * 3 * lazyev::decode_fused_record_bytes() / 8, ctx->stream);
+          ctx->ws.part_rec, static_cast<size_t>(ctx->units) * a.rec_per_unit * lazyev::decode_fused_record_bytes() / 8, ctx->stream);
       if (ec != hipSuccess) return fail_hip(ctx, ec);
       ctx->launch_seq = 1;
     }

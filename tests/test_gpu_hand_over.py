@@ -1,0 +1,77 @@
+"""Partials of a unit handed over between its blocks: one hop for up to 8 blocks (an instance of the
+kernel each), two for up to 64, the groups' leaders at 7, 15, ... and a last group of any size."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(lazyev_lib, blocks, N, steps, group):
+    H = 2
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    eng = lazyev_lib.LazyEviction(1, 1, group * H, H, 128, N + 100, 64, N, 8.0 / N)
+    eng.k_cache[:, :, :, :N].normal_(generator=gen)
+    eng.v_cache[:, :, :, :N].normal_(generator=gen)
+    eng.init()
+    if blocks:
+        eng.set_target_blocks(blocks * H)
+    x = [torch.empty((steps, 1, h, 128), device="cuda").normal_(generator=gen).to(torch.bfloat16)
+         for h in (group * H, H, H)]
+    out = torch.zeros((steps, 1, group * H, 128), dtype=torch.bfloat16, device="cuda")
+    for t in range(1, steps + 1):
+        eng.decode_step(0, t, x[0][t - 1], x[1][t - 1], x[2][t - 1], out[t - 1])
+    eng.stats()
+    k, v = eng.k_cache[0, 0].double(), eng.v_cache[0, 0].double()
+    for t in range(1, steps + 1):
+        n = N + t
+        q = x[0][t - 1, 0].double().view(H, group, 128)
+        p = torch.softmax(torch.matmul(q, k[:, :n].transpose(1, 2).contiguous()) / np.sqrt(128.0), dim=-1)
+        ref = torch.matmul(p, v[:, :n]).view(group * H, 128)
+        # bf16 weights and a bf16 result: two roundings of relative size 2^-9, independent per element
+        err = (out[t - 1, 0].double() - ref).norm(dim=1) / ref.norm(dim=1)
+        assert float(err.max()) < 2 * 2.0 ** -8, (blocks, t, float(err.max()))
+    state = [y[0, 0, :, :N + steps].clone() for y in (eng.ts, eng.mri, eng.pos)]
+    eng.close()
+    return state
+
+
+@pytest.mark.parametrize("N,group,blocks", [(4080, 7, (1, 2, 3, 5, 6, 7, 8, 9, 15, 16, 17, 24, 63, 64, 0)),
+                                            (150, 4, (1, 2, 3, 0)), (3, 1, (1, 0)), (62, 7, (2, 0))])
+def test_every_number_of_blocks_gives_the_same_result(lazyev_lib, N, group, blocks):
+    """Outputs against fp64 softmax attention; TS / MRI / pos equal whatever the split (a decision
+    within rounding of alpha could differ: about one in 1e7, of 1e5 here)."""
+    first = None
+    for b in blocks:
+        state = _run(lazyev_lib, b, N, 6, group)
+        if first is None:
+            first = state
+        for x, y in zip(state, first):
+            assert torch.equal(x, y), b
+
+
+@pytest.mark.parametrize("batch,N", [(12, 700), (20, 700), (24, 6200), (36, 700), (36, 2200)])
+def test_more_units_than_blocks_fit_evenly(lazyev_lib, batch, N):
+    """48, 80, 96 and 144 units of one launch (3, 2, 5, 1 and 3 blocks per unit; with and without list
+    waves): outputs of sampled sequences against fp64 softmax attention."""
+    H, group, steps = 4, 7, 3
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    eng = lazyev_lib.LazyEviction(1, batch, group * H, H, 128, N + 100, 64, N, 8.0 / N)
+    eng.k_cache[:, :, :, :N].normal_(generator=gen)
+    eng.v_cache[:, :, :, :N].normal_(generator=gen)
+    eng.init()
+    out = torch.zeros((batch, group * H, 128), dtype=torch.bfloat16, device="cuda")
+    for t in range(1, steps + 1):
+        q, kn, vn = (torch.empty((batch, h, 128), device="cuda").normal_(generator=gen).to(torch.bfloat16)
+                     for h in (group * H, H, H))
+        eng.decode_step(0, t, q, kn, vn, out)
+        n = N + t
+        for s in (0, batch // 2, batch - 1):
+            k, v = eng.k_cache[0, s, :, :n].double(), eng.v_cache[0, s, :, :n].double()
+            p = torch.softmax(torch.matmul(q[s].double().view(H, group, 128), k.transpose(1, 2).contiguous()) /
+                              np.sqrt(128.0), dim=-1)
+            ref = torch.matmul(p, v).view(group * H, 128)
+            err = (out[s].double() - ref).norm(dim=1) / ref.norm(dim=1)
+            assert float(err.max()) < 2 * 2.0 ** -8, (s, t, float(err.max()))
+    assert eng.stats()["len"] == [N + steps]
+    eng.close()
