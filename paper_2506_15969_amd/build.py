@@ -19,12 +19,21 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-I" + INCLUDE,
           # packed-fp32 VALU forms are kept out of all device code
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# the eviction file holds the bit-reproducible binary64 score: no fused multiply-add there
-SOURCES = {"decode_kernels.hip": [], "decode_fused.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=13"], "evict_kernels.hip": ["-ffp-contract=off"],
-           "lazyev_api.hip": [], "prefill_kernels.hip": []}
+# object name -> (source, extra flags)
+FUSED = ["-mllvm", "-amdgpu-kernarg-preload-count=13"]
+SOURCES = {"decode_kernels": ("decode_kernels.hip", []),
+           # the single-launch decode kernel, one object per row type
+           "decode_fused": ("decode_fused.hip", FUSED),
+           "decode_fused_bf16_64": ("decode_fused.hip", FUSED + ["-DLAZYEV_ROWS=1"]),
+           "decode_fused_f32_64": ("decode_fused.hip", FUSED + ["-DLAZYEV_ROWS=2"]),
+           "decode_fused_f32_128": ("decode_fused.hip", FUSED + ["-DLAZYEV_ROWS=3"]),
+           # the eviction file holds the bit-reproducible binary64 score: no fused multiply-add there
+           "evict_kernels": ("evict_kernels.hip", ["-ffp-contract=off"]),
+           "lazyev_api": ("lazyev_api.hip", []),
+           "prefill_kernels": ("prefill_kernels.hip", [])}
 # measuring aids (plain streaming probes): a library of their own, not part of the path
 BENCH_LIB = os.path.join(LIBDIR, "liblazyev_bench.so")
-BENCH_SOURCES = {"probe_kernels.hip": []}
+BENCH_SOURCES = {"probe_kernels": ("probe_kernels.hip", [])}
 # the same library with the fused decode kernel instrumented (per-block time stamps of the last
 # launch; bench.py --timeline reads them): a measuring build, never what the binding loads by default
 TIMELINE_LIB = os.path.join(LIBDIR, "liblazyev_timeline.so")
@@ -32,9 +41,9 @@ TIMELINE_FLAGS = ["-DLAZYEV_TIMELINE"]
 
 
 def _compile(item):
-    name, extra = item
-    obj = os.path.join(LIBDIR, name.replace(".hip", "_timeline.o" if TIMELINE_FLAGS[0] in extra else ".o"))
-    cmd = [HIPCC, *COMMON, *extra, "-c", os.path.join(CSRC, name), "-o", obj]
+    name, (source, extra) = item
+    obj = os.path.join(LIBDIR, name + ".o")
+    cmd = [HIPCC, *COMMON, *extra, "-c", os.path.join(CSRC, source), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s" % (name, r.stderr))
@@ -43,12 +52,12 @@ def _compile(item):
 
 def build_library(verbose: bool = True) -> str:
     os.makedirs(LIBDIR, exist_ok=True)
-    fused = "decode_fused.hip"
-    jobs = list(SOURCES.items()) + list(BENCH_SOURCES.items()) + [(fused, SOURCES[fused] + TIMELINE_FLAGS)]
+    timeline = ("decode_fused_timeline", (SOURCES["decode_fused"][0], FUSED + TIMELINE_FLAGS))
+    jobs = list(SOURCES.items()) + list(BENCH_SOURCES.items()) + [timeline]
     with ThreadPoolExecutor(max_workers=len(jobs)) as ex:
         objs = list(ex.map(_compile, jobs))
     path_objs = objs[:len(SOURCES)]
-    timeline_objs = [objs[-1] if o.endswith("decode_fused.o") else o for o in path_objs]
+    timeline_objs = [objs[-1] if o.endswith("/decode_fused.o") else o for o in path_objs]
     for lib, group in ((LIB, path_objs), (BENCH_LIB, objs[len(SOURCES):-1]), (TIMELINE_LIB, timeline_objs)):
         r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *group, "-o", lib],
                            capture_output=True, text=True)

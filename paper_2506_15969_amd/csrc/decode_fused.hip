@@ -1,4 +1,4 @@
-// Decode step of one layer in ONE launch (bf16, head_dim 128): append, attention (Eq. 4 of the
+// Decode step of one layer in ONE launch: append, attention (Eq. 4 of the
 // paper) and, one call behind, the recurrence tracking of Alg. 1 / Eq. 1.
 //
 // A unit's cache is cut into 16-entry sub-tiles, dealt to the 4 * n_split stream waves of the
@@ -42,7 +42,7 @@
 // per cache entry in the layer's activation log, and track_flush_kernel applies the logged calls
 // in step order before anything reads TS / MRI (TrackArgs::bitlog).
 //
-// Candidate lists (kernel instances <true, ..>, groups of at most 7 heads; every call whose
+// Candidate lists (kernel instances with kCompact; every call whose
 // logits nobody reads as such).  A block knows, once its four stream waves are done, its own
 // share of every head's softmax denominator, which bounds the
 // true denominator from below: an entry whose weight relative to the BLOCK's denominator
@@ -50,15 +50,23 @@
 // entries ("candidates", about a tenth on the benchmark workloads; the appended entry always)
 // as records (7 logits, entry index) into its own region of the logits buffer, and the
 // tracking applies the exact test to the records: the same state bit for bit.  A wave whose run
-// is longer than the sub-tiles it keeps in LDS (instances <true, true, ..>) writes the candidates
+// is longer than the sub-tiles it keeps in LDS (kLong) writes the candidates
 // of every full segment while it streams, with the cut that the block's waves' running sums give
 // at that moment, and only the last segment after the stream.  Where all blocks of the launch
-// fit the chip at once with eight waves each (instances <.., .., true>), four more waves per
+// fit the chip at once with eight waves each (kListWaves), four more waves per
 // block ("list waves") sleep through the stream and build the lists beside the merge.
+//
+// The above is for bf16 rows of 128 elements.  The other row types (Rows) differ in the loads and the
+// two products: bf16 rows of 64 have two sub-tiles on their way and their weights split into three bf16
+// terms, fp32 rows need no LDS on the way to v_mfma_f32_16x16x4_f32.  us per call, these against the split +
+// merge kernels that served them before: bf16 64, 64 units x 1595 entries 37.5 -> 10.8; fp32 128, 32 x
+// 1032 28.3 -> 13.8; fp32 64, 4 x 145 11.5 -> 6.0; 128 units x 6200 entries 203 -> 48.8 (bf16 64), 251 ->
+// 147 (fp32 128, 5.5 TB/s), 160 -> 82 (fp32 64).  Out and weights are as far from 64 bits as before.
 //
 // MFMA operand layouts (lane l, c = l % 16, g = l / 16):
 //   16x16x32: A[row c][k = 8g..8g+7]  B[k = 8g..8g+7][col c]  C[row 4g+i][col c]
 //   16x16x16: A[row c][k = 4g..4g+3]  B[k = 4g..4g+3][col c]  C[row 4g+i][col c]
+//   16x16x4:  A[row c][k = g]  B[k = g][col c]  C[row 4g+i][col c]   (fp32)
 // so a lane that owns head c and entries 4g..4g+3 of a sub-tile after the first product already
 // holds the A operand of the second.
 #include "kernels.h"
@@ -70,8 +78,6 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-constexpr int D = 128;
-constexpr int KC = D / 32;
 constexpr int kFusedSplitMax = 64;      // blocks per unit
 constexpr float kRaise = 8.0f;          // the reference maximum moves when exceeded by this much
 constexpr int kTrackRows = 3;           // entries per thread per tracking batch
@@ -159,11 +165,35 @@ __device__ __forceinline__ float max_over_lane_groups(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// K and V rows of one sub-tile as a wave holds them: 4 + 4 loads of 16 bytes per lane.
-struct SubTile {
-  u32x4_t k[KC];
-  u32x4_t v[4];
+// What the kernel needs to know of a row type: bf16 or fp32, 64 or 128 elements.
+template <typename T, int D>
+struct Rows {
+  static constexpr bool kF32 = sizeof(T) == 4;
+  static constexpr int kBytes = D * static_cast<int>(sizeof(T));
+  static constexpr int kLanes = kBytes / 16;       // lanes of 16 bytes that cover a row
+  static constexpr int kAcc = D / 16;              // accumulators (16 heads x 16 columns) of the output
+  // 16-byte loads per lane and sub-tile: K; V comes in 16-byte pieces, of 64-element bf16 rows in 8-byte ones
+  static constexpr int kK = kBytes / 64;
+  static constexpr int kV = kBytes >= 256 ? kBytes / 64 : 2;
+  // sub-tiles on their way per wave: rows of 128 bytes need two of them for the bytes in flight that
+  // one sub-tile of longer rows has
+  static constexpr int kDepth = kBytes == 128 ? 2 : 1;
+  // fp32 rows of 128 elements take 128 registers for a sub-tile, the accumulators and the queries
+  // alone: two waves per SIMD instead of four, so no list waves
+  static constexpr bool kWide = kBytes == 512;
+  // weights keep their fp32 value in the second product, and exponentials are expf; only the
+  // 128-element bf16 rows round the weights to bf16
+  static constexpr bool kPrecise = !(sizeof(T) == 2 && D == 128);
+  struct SubTile {
+    u32x4_t k[kK];
+    u32x4_t v[kV];
+  };
 };
+template <bool kPrecise>
+__device__ __forceinline__ float exp_of(float x) {
+  if constexpr (kPrecise) return expf(x);
+  else return __expf(x);
+}
 
 // ----------------------------------------------------------------------------- tracking
 // Alg. 1 (first loop) and Eq. 1 for a share of one unit of a finished decode call:
@@ -208,6 +238,7 @@ __device__ __forceinline__ void track_load(const TrackArgs &k, int unit, int par
 
 // The activation test and the TS / MRI update of entry i (Alg. 1, Eq. 1); true if active.
 // log_mask (LDS, or null): the call is logged; an active entry then only sets its bit there.
+template <bool kPrecise>
 __device__ __forceinline__ bool track_one(const TrackArgs &k, int unit, int i, const float (&s)[kHeadPad],
                                           const float (&m)[kHeadPad], const float (&invl)[kHeadPad],
                                           unsigned *log_mask) {
@@ -220,7 +251,7 @@ __device__ __forceinline__ bool track_one(const TrackArgs &k, int unit, int i, c
 #pragma unroll
   for (int h = 0; h < kHeadPad; ++h) {
     if (h < G) {
-      float p = __expf(s[h] - m[h]) * invl[h];
+      float p = exp_of<kPrecise>(s[h] - m[h]) * invl[h];
       const size_t at = (head0 + h) * k.capacity + i;
       if (k.p_out) k.p_out[at] = p;
       if (k.p_override) p = k.p_override[at];
@@ -245,6 +276,7 @@ __device__ __forceinline__ bool track_one(const TrackArgs &k, int unit, int i, c
   return act;
 }
 
+template <bool kPrecise>
 __device__ __forceinline__ unsigned track_apply(const TrackArgs &k, int unit, int part, int n_parts,
                                                 int r0, const TrackBatch &b, const float (&m)[kHeadPad],
                                                 const float (&invl)[kHeadPad], unsigned *log_mask) {
@@ -266,7 +298,7 @@ __device__ __forceinline__ unsigned track_apply(const TrackArgs &k, int unit, in
 #pragma unroll
     for (int h = 0; h < kHeadPad; ++h) {
       if (h < G) {
-        float p = __expf(s[h] - m[h]) * invl[h];
+        float p = exp_of<kPrecise>(s[h] - m[h]) * invl[h];
         const size_t at = (head0 + h) * k.capacity + i;
         if (k.p_out) k.p_out[at] = p;
         if (k.p_override) p = k.p_override[at];
@@ -301,20 +333,27 @@ __host__ __device__ inline int fused_part_cap(int n_old, int n_parts) {
 }
 
 // Tracking from the candidate records of the call's blocks b = part, part + step, ...
+template <bool kPrecise>
 __device__ __forceinline__ unsigned track_records(const TrackArgs &k, int unit, int part, int step,
                                                   const float (&m)[kHeadPad], const float (&invl)[kHeadPad],
                                                   unsigned *log_mask) {
   const int cap = fused_part_cap(k.n_old, k.n_parts);
   unsigned n_act = 0;
   for (int b = part; b < k.n_parts; b += step) {
-    const float *region = k.logits + (static_cast<size_t>(unit) * k.p_stride + static_cast<size_t>(b) * cap) * kHeadPad;
+    const size_t at = static_cast<size_t>(unit) * k.p_stride + static_cast<size_t>(b) * cap;
+    const float *region = k.logits + at * kHeadPad;
     const int n = *reinterpret_cast<const int32_t *>(region);
-    for (int r = threadIdx.x; r < n; r += kBlock) {
+    auto track = [&](int r, auto eight) {          // (groups of eight have the index beside the records)
       const float4 sa = *reinterpret_cast<const float4 *>(region + static_cast<size_t>(1 + r) * kHeadPad);
       const float4 sb = *reinterpret_cast<const float4 *>(region + static_cast<size_t>(1 + r) * kHeadPad + 4);
-      const float s[kHeadPad] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, 0.f};
-      n_act += track_one(k, unit, __float_as_int(sb.w), s, m, invl, log_mask) ? 1u : 0u;
-    }
+      const int i = decltype(eight)::value ? k.cand_index[at + 1 + r] : __float_as_int(sb.w);
+      const float s[kHeadPad] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, decltype(eight)::value ? sb.w : 0.f};
+      n_act += track_one<kPrecise>(k, unit, i, s, m, invl, log_mask) ? 1u : 0u;
+    };
+    if (k.group == kHeadPad)
+      for (int r = threadIdx.x; r < n; r += kBlock) track(r, std::true_type{});
+    else
+      for (int r = threadIdx.x; r < n; r += kBlock) track(r, std::false_type{});
   }
   return n_act;
 }
@@ -354,6 +393,7 @@ __device__ void track_count(const TrackArgs &k, int unit, int part, unsigned n_a
 }
 
 // Tracking alone (lazyev_evict, lazyev_stats, or a caller that wants the weights at once).
+template <bool kPrecise>
 __global__ __launch_bounds__(kBlock) void track_kernel(const TrackArgs k_all, int n_parts) {
   __shared__ unsigned cnt_lds[kWaves];
   const int unit = blockIdx.x / n_parts, part = blockIdx.x % n_parts;
@@ -363,13 +403,13 @@ __global__ __launch_bounds__(kBlock) void track_kernel(const TrackArgs k_all, in
   track_stats(k, unit, m, invl);
   unsigned n_act = 0;
   if (k.compact) {
-    n_act = track_records(k, unit, part, n_parts, m, invl, nullptr);
+    n_act = track_records<kPrecise>(k, unit, part, n_parts, m, invl, nullptr);
   } else {
     const int rounds = track_rounds((k.n_old + 1 + 15) >> 4, n_parts);
     for (int r0 = 0; r0 < rounds; r0 += kTrackRows) {
       TrackBatch b;
       track_load(k, unit, part, n_parts, r0, b);
-      n_act += track_apply(k, unit, part, n_parts, r0, b, m, invl, nullptr);
+      n_act += track_apply<kPrecise>(k, unit, part, n_parts, r0, b, m, invl, nullptr);
     }
   }
   track_count(k, unit, part, n_act, cnt_lds);
@@ -457,6 +497,7 @@ __global__ __launch_bounds__(kBlock) void track_flush_kernel(const FlushArgs f) 
 // Running merge of partials in block order.  Every product and sum is written out with its
 // rounding (no contraction left to the compiler), so that all kernel instances produce the same
 // bits from the same partials.
+template <bool kPrecise>
 struct Merge {
   float m = -INFINITY, l = 0.f;
   float o[4] = {0.f, 0.f, 0.f, 0.f};
@@ -464,8 +505,8 @@ struct Merge {
 #pragma clang fp contract(off)
     const float m_new = fmaxf(m, mj);
     // a block without entries has max = -inf, sum = 0, values = 0: its factor is 0
-    const float fr = m == -INFINITY ? 0.f : __expf(m - m_new);
-    const float fj = mj == -INFINITY ? 0.f : __expf(mj - m_new);
+    const float fr = m == -INFINITY ? 0.f : exp_of<kPrecise>(m - m_new);
+    const float fj = mj == -INFINITY ? 0.f : exp_of<kPrecise>(mj - m_new);
     l = fmaf(l, fr, lj * fj);
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = fmaf(o[i], fr, oj[i] * fj);
@@ -475,18 +516,24 @@ struct Merge {
 
 // The merged row of a unit: thread t writes output elements 4t .. 4t+3 (all of head h) and, as
 // the owner of a head's first elements, the head's softmax statistics for the tracking.
-__device__ __forceinline__ void write_unit_row(const DecodeArgs &a, int unit, const Merge &mg, int e0, int h) {
+template <typename T, int D>
+__device__ __forceinline__ void write_unit_row(const DecodeArgs &a, int unit, const Merge<Rows<T, D>::kPrecise> &mg, int e0, int h) {
   const int G = a.group;
   if (e0 >= G * D) return;
   const int seq = unit / a.n_kv_heads, kvh = unit % a.n_kv_heads;
   const size_t head0 = static_cast<size_t>(seq) * a.n_q_heads + static_cast<size_t>(kvh) * G;
   const float invl = 1.0f / mg.l;
+  T *out = static_cast<T *>(a.out) + head0 * D + e0;
+  if constexpr (Rows<T, D>::kF32) {
+    *reinterpret_cast<f32x4_t *>(out) = f32x4_t{mg.o[0] * invl, mg.o[1] * invl, mg.o[2] * invl, mg.o[3] * invl};
+  } else {
   u32x2_t w;
   w[0] = static_cast<unsigned>(float_to_bf16(mg.o[0] * invl)) |
          (static_cast<unsigned>(float_to_bf16(mg.o[1] * invl)) << 16);
   w[1] = static_cast<unsigned>(float_to_bf16(mg.o[2] * invl)) |
          (static_cast<unsigned>(float_to_bf16(mg.o[3] * invl)) << 16);
-  *reinterpret_cast<u32x2_t *>(static_cast<bf16_t *>(a.out) + head0 * D + e0) = w;
+  *reinterpret_cast<u32x2_t *>(out) = w;
+  }
   if (e0 % D == 0) {
     float *st = a.stat_out + static_cast<size_t>(unit) * (2 * kHeadPad) + 2 * h;
     st[0] = mg.m;
@@ -548,10 +595,10 @@ __device__ __forceinline__ f32x4_t rec_values(const RecPart &r) {
 // until every word carries the launch's number; then the records and (m, l, o) merged in this order.
 // The running merge starts from the first record as it is: folding it into the empty state would
 // reproduce exactly its bits (factors 0 and exp(0) = 1) at the price of a dozen instructions.
-template <int N>
-__device__ __forceinline__ Merge merge_records(const DecodeArgs &a, const unsigned long long *rec, int stride, int n,
+template <int N, bool kPrecise>
+__device__ __forceinline__ Merge<kPrecise> merge_records(const DecodeArgs &a, const unsigned long long *rec, int stride, int n,
                                                int t_own, float m, float l, const f32x4_t &o) {
-  Merge mg;
+  Merge<kPrecise> mg;
   if (n == 0) {                                    // uniform
     mg.m = m; mg.l = l;
 #pragma unroll
@@ -614,10 +661,13 @@ __global__ void clear_records_kernel(unsigned long long *rec, size_t n_words) {
 // second hop, the loads of a variable number of records and the divisions by the split out of it
 // (us per call with an instance of its own / with the one for any split: 32 units x 600 entries, 3 blocks 6.4
 // / 7.7, 4 6.3 / 7.2, 6 6.5 / 7.0).
-template <bool kCompact, bool kLong = false, bool kListWaves = false, int kSplit = 0>
-__global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fused_kernel(
-    const bf16_t *k_cache, const bf16_t *v_cache, const bf16_t *k_new_all, const bf16_t *v_new_all, const int n_old_call, const int n_split_call, const int capacity,
+template <typename T, int D, bool kCompact, bool kLong = false, bool kListWaves = false, int kSplit = 0>
+__global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWide ? 2 : 4)) void decode_fused_kernel(
+    const T *k_cache, const T *v_cache, const T *k_new_all, const T *v_new_all, const int n_old_call, const int n_split_call, const int capacity,
     const int units_call, const int slots_on, const DecodeArgs a) {
+  using R = Rows<T, D>;
+  using SubTile = typename R::SubTile;
+  constexpr bool kPrecise = R::kPrecise;
   const int n_split = kSplit > 0 ? kSplit : n_split_call;   // (a constant where the instance fixes it)
   __shared__ float m_lds[kWaves][16], lsum_lds[kWaves][16];
   // one 16-row K sub-tile per wave while streaming; afterwards the wave's output accumulator
@@ -653,13 +703,13 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
       __syncthreads();
     }
     if (k.compact) {
-      n_act = track_records(k, unit, part, n_track, m, invl, log_mask);
+      n_act = track_records<kPrecise>(k, unit, part, n_track, m, invl, log_mask);
     } else {
       const int rounds = track_rounds((k.n_old + 1 + 15) >> 4, n_track);
       for (int r0 = 0; r0 < rounds; r0 += kTrackRows) {
         TrackBatch b;
         track_load(k, unit, part, n_track, r0, b);
-        n_act += track_apply(k, unit, part, n_track, r0, b, m, invl, log_mask);
+        n_act += track_apply<kPrecise>(k, unit, part, n_track, r0, b, m, invl, log_mask);
       }
     }
     if (k.bitlog) {
@@ -702,13 +752,13 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
 
   // the appended row goes to slot N (the stream waves read it from k_new / v_new, nobody from the slot)
   auto append_row = [&]() {
-    const bf16_t *kn = k_new_all + static_cast<size_t>(unit) * D, *vn = v_new_all + static_cast<size_t>(unit) * D;
-    bf16_t *ku = const_cast<bf16_t *>(k_cache) + static_cast<size_t>(unit) * capacity * D;
-    bf16_t *vu = const_cast<bf16_t *>(v_cache) + static_cast<size_t>(unit) * capacity * D;
-    if (lane < 16)
+    const T *kn = k_new_all + static_cast<size_t>(unit) * D, *vn = v_new_all + static_cast<size_t>(unit) * D;
+    T *ku = const_cast<T *>(k_cache) + static_cast<size_t>(unit) * capacity * D;
+    T *vu = const_cast<T *>(v_cache) + static_cast<size_t>(unit) * capacity * D;
+    if (lane < R::kLanes)
       reinterpret_cast<uint4 *>(ku + static_cast<size_t>(n_old) * D)[lane] = reinterpret_cast<const uint4 *>(kn)[lane];
-    else if (lane < 32)
-      reinterpret_cast<uint4 *>(vu + static_cast<size_t>(n_old) * D)[lane - 16] = reinterpret_cast<const uint4 *>(vn)[lane - 16];
+    else if (lane < 2 * R::kLanes)
+      reinterpret_cast<uint4 *>(vu + static_cast<size_t>(n_old) * D)[lane - R::kLanes] = reinterpret_cast<const uint4 *>(vn)[lane - R::kLanes];
   };
 
   // ---- candidate list of the sub-tiles that stream wave w leaves in LDS (for a long run: the last
@@ -724,6 +774,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
     int entry[kRounds];
     bool always[kRounds], may[kRounds];
     char *region;
+    int32_t *index;                                // of the region's slots (groups of eight)
     int group;
     float alpha98;
   };
@@ -737,6 +788,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
     sp.alpha98 = 0.98f * a.alpha;
     sp.region = reinterpret_cast<char *>(a.logits_out + (static_cast<size_t>(unit) * a.p_stride +
                                                          static_cast<size_t>(split) * fused_part_cap(n_old, n_split)) * kHeadPad);
+    sp.index = a.cand_index_out + static_cast<size_t>(unit) * a.p_stride + static_cast<size_t>(split) * fused_part_cap(n_old, n_split);
     const int e_in = lane & 15;
 #pragma unroll
     for (int rd = 0; rd < kRounds; ++rd) {
@@ -779,9 +831,9 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
     for (int rd = 0; rd < kRounds; ++rd) {
       // s_h >= cut_h in some head  <=>  the largest s_h - cut_h is not negative
       const float d = fmaxf(fmaxf(fmaxf(sa[rd][0] - cut[0], sa[rd][1] - cut[1]), fmaxf(sa[rd][2] - cut[2], sa[rd][3] - cut[3])),
-                            fmaxf(fmaxf(sb[rd][0] - cut[4], sb[rd][1] - cut[5]), sb[rd][2] - cut[6]));
+                            fmaxf(fmaxf(sb[rd][0] - cut[4], sb[rd][1] - cut[5]), fmaxf(sb[rd][2] - cut[6], sb[rd][3] - cut[7])));
       const bool cand = ((d >= 0.f) & sp.may[rd]) | sp.always[rd];
-      sb[rd][3] = __int_as_float(sp.entry[rd]);    // (the 8th place: groups have at most 7 heads here)
+      if (sp.group < kHeadPad) sb[rd][3] = __int_as_float(sp.entry[rd]);   // (the 8th place is free)
       mask[rd] = __builtin_amdgcn_ballot_w64(cand);
       n_rec += static_cast<unsigned>(__popcll(mask[rd]));
     }
@@ -798,6 +850,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
           char *dst = sp.region + at * static_cast<unsigned>(kHeadPad * sizeof(float));   // (a 32-bit offset: under 4 GB)
           *reinterpret_cast<f32x4_t *>(dst) = sa[rd];
           *reinterpret_cast<f32x4_t *>(dst + 16) = sb[rd];
+          if (sp.group == kHeadPad) sp.index[at] = sp.entry[rd];
         }
         base += static_cast<unsigned>(__popcll(mask[rd]));
       }
@@ -823,19 +876,27 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
   const int cnt = wm.cnt;                          // (0 for a wave beyond a short cache)
   auto sub_of = [&](int it) { return wm.first + it * wm.step; };
 
-  const bf16_t *kc = k_cache + static_cast<size_t>(unit) * capacity * D;
-  const bf16_t *vc = v_cache + static_cast<size_t>(unit) * capacity * D;
-  const bf16_t *k_new = k_new_all + static_cast<size_t>(unit) * D;
-  const bf16_t *v_new = v_new_all + static_cast<size_t>(unit) * D;
+  const T *kc = k_cache + static_cast<size_t>(unit) * capacity * D;
+  const T *vc = v_cache + static_cast<size_t>(unit) * capacity * D;
+  const T *k_new = k_new_all + static_cast<size_t>(unit) * D;
+  const T *v_new = v_new_all + static_cast<size_t>(unit) * D;
 
   auto load_k = [&](SubTile &t, int it) {
     const int sub = sub_of(it);
-    // K: whole rows, 16 lanes per row (row 4j+g, 16-byte chunk c); re-laid out through LDS
+    if constexpr (R::kF32) {
+      // fp32: straight into the MFMA operand layout, lane (c, g): row c, columns 16 j + 4 g .. + 3
+      const int row = min(sub * 16 + c, n_old);
+      const T *src = ((row == n_old) ? k_new : kc + static_cast<size_t>(row) * D) + 4 * g;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = min(sub * 16 + 4 * j + g, n_old);
-      const bf16_t *src = (row == n_old) ? k_new : kc + static_cast<size_t>(row) * D;
-      t.k[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + c * 8));
+      for (int j = 0; j < R::kK; ++j) t.k[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + 16 * j));
+    } else {
+      // bf16: whole rows, kLanes lanes per row; re-laid out through LDS
+#pragma unroll
+      for (int j = 0; j < R::kK; ++j) {
+        const int row = min(sub * 16 + j * (64 / R::kLanes) + lane / R::kLanes, n_old);
+        const T *src = (row == n_old) ? k_new : kc + static_cast<size_t>(row) * D;
+        t.k[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + (lane % R::kLanes) * 8));
+      }
     }
   };
   auto load_v = [&](SubTile &t, int it) {
@@ -843,64 +904,105 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = min(sub * 16 + 4 * g + i, n_old);
-      const bf16_t *src = (row == n_old) ? v_new : vc + static_cast<size_t>(row) * D;
-      t.v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + c * 8));
+      const T *src = (row == n_old) ? v_new : vc + static_cast<size_t>(row) * D;
+      if constexpr (R::kF32) {                     // columns 64 h + 4 c .. + 3
+#pragma unroll
+        for (int h = 0; h < D / 64; ++h)
+          t.v[i * (D / 64) + h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + 64 * h + c * 4));
+      } else if constexpr (D == 128) {             // columns 8 c .. + 7
+        t.v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + c * 8));
+      } else {                                     // columns 4 c .. + 3
+        const u32x2_t x = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t *>(src + c * 4));
+        t.v[i / 2][2 * (i % 2)] = x[0];
+        t.v[i / 2][2 * (i % 2) + 1] = x[1];
+      }
     }
   };
   // ---- the stream starts here: the first sub-tile is requested with what the wave was handed
   // in registers, before anything is read from the argument block in memory
-  SubTile buf;
-  if (cnt > 0) { load_k(buf, 0); load_v(buf, 0); }
+  SubTile buf[R::kDepth];
+#pragma unroll
+  for (int x = 0; x < R::kDepth; ++x)
+    if (x < cnt) { load_k(buf[x], x); load_v(buf[x], x); }
 
   const int G = a.group;
   const int seq = unit / a.n_kv_heads, kvh = unit % a.n_kv_heads;
   const int hc = min(c, G - 1);
   const size_t head0 = static_cast<size_t>(seq) * a.n_q_heads + static_cast<size_t>(kvh) * G;
-  const bf16_t *q_row = static_cast<const bf16_t *>(a.q) + (head0 + hc) * D + g * 8;
+  const T *q_row = static_cast<const T *>(a.q) + (head0 + hc) * D + g * (16 / sizeof(T));
   const int run = min(fused_wave_run(n_sub, n_split), kRunMax);
   float *my_logits = logit_lds + static_cast<size_t>(wave) * run * (16 * kHeadPad);
   int seg0 = 0;                                    // first of this wave's sub-tiles whose logits are still in LDS
   float *logits_out = a.logits_out + static_cast<size_t>(unit) * a.p_stride * kHeadPad;
 
   float m_ref = -INFINITY, lsum = 0.f;
-  f32x4_t o[8];
+  f32x4_t o[R::kAcc];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < R::kAcc; ++e) o[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // B operand of the logits: Q^T, head c (zero rows beyond the group)
-  u32x4_t qb[KC];
+  // B operand of the logits: Q^T, head c (zero rows beyond the group); piece kk goes with K's piece kk
+  u32x4_t qb[R::kK];
 #pragma unroll
-  for (int kk = 0; kk < KC; ++kk) {
-    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(q_row + kk * 32);
+  for (int kk = 0; kk < R::kK; ++kk) {
+    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(q_row + kk * (64 / sizeof(T)));
     qb[kk] = c < G ? v : u32x4_t{0, 0, 0, 0};
   }
 
-  // kMore (a std::bool_constant): the wave has a sub-tile after this one and requests it here
+  // kMore (a std::bool_constant): the wave has a sub-tile kDepth after this one and requests it here
   auto compute = [&](SubTile &t, int it, auto more_tag) {
     constexpr bool kMore = decltype(more_tag)::value;
     const int sub = sub_of(it);
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (R::kF32) {
+      // Four terms per instruction; which four of the row's columns go together does not matter as
+      // long as K and Q agree.  Sums of four, then a tree: one chain over the row has the
+      // logit of a strongly matching key (about 45 at 128 columns) off by enough to move its weight by 1e-5.
+      f32x4_t sum[R::kK / 2];
+#pragma unroll
+      for (int y = 0; y < R::kK / 2; ++y) {
+        f32x4_t x[8];
+#pragma unroll
+        for (int z = 0; z < 8; ++z)
+          x[z] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(t.k[2 * y + z / 4][z % 4]), __uint_as_float(qb[2 * y + z / 4][z % 4]),
+                                                      f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        sum[y] = ((x[0] + x[4]) + (x[1] + x[5])) + ((x[2] + x[6]) + (x[3] + x[7]));
+      }
+      acc = sum[0] + sum[1];
+      if constexpr (R::kK == 8) acc += sum[2] + sum[3];
+      if constexpr (kMore) load_k(t, it + R::kDepth);
+    } else {
     // K rows -> MFMA A layout (lane (c, g): row c, chunks 4kk+g).  Chunk x of row r sits at
     // slot x ^ r of the row, so both the row-wise writes and the column-wise reads touch
-    // every LDS bank once.  The staging area is private to the wave: LDS operations of one
+    // every LDS bank once (rows of 8 chunks: at most twice).  The staging area is private to the wave: LDS operations of one
     // wave execute in order, the fences only stop the compiler from reordering them.
-    u32x4_t ka[KC];
+    u32x4_t ka[R::kK];
     {
       u32x4_t *stage = stage_lds[wave];
+      const int ch = lane % R::kLanes, r0 = lane / R::kLanes;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) stage[(4 * j + g) * 16 + (c ^ (4 * j + g))] = t.k[j];
+      for (int j = 0; j < R::kK; ++j) {
+        const int r = j * (64 / R::kLanes) + r0;
+        stage[r * R::kLanes + (ch ^ (r % R::kLanes))] = t.k[j];
+      }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-      for (int kk = 0; kk < KC; ++kk) ka[kk] = stage[c * 16 + ((4 * kk + g) ^ c)];
+      for (int kk = 0; kk < R::kK; ++kk) ka[kk] = stage[c * R::kLanes + ((4 * kk + g) ^ (c % R::kLanes))];
     }
     // the K registers are free again: the next sub-tile's K rows travel during the arithmetic
-    if constexpr (kMore) load_k(t, it + 1);
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (kMore) load_k(t, it + R::kDepth);
+    if constexpr (kPrecise) {                      // (two sums of 32 terms, then their sum)
+      const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[0]), __builtin_bit_cast(bf16x8_t, qb[0]), zero, 0, 0, 0) +
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[1]), __builtin_bit_cast(bf16x8_t, qb[1]), zero, 0, 0, 0);
+    } else {
 #pragma unroll
-    for (int kk = 0; kk < KC; ++kk)
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[kk]),
-                                                    __builtin_bit_cast(bf16x8_t, qb[kk]), acc, 0, 0, 0);
+      for (int kk = 0; kk < R::kK; ++kk)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[kk]),
+                                                      __builtin_bit_cast(bf16x8_t, qb[kk]), acc, 0, 0, 0);
+    }
+    }
     float s[4];
     const int e0 = sub * 16 + 4 * g;
 #pragma unroll
@@ -917,33 +1019,68 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
     tmax = max_over_lane_groups(tmax);
     if (__builtin_amdgcn_ballot_w64(tmax > m_ref + kRaise) != 0) {   // wave-uniform, rare
       const float m_new = fmaxf(m_ref, tmax);
-      const float f = __expf(m_ref - m_new);       // 0 on the first sub-tile (m_ref = -inf)
+      const float f = exp_of<kPrecise>(m_ref - m_new);   // 0 on the first sub-tile (m_ref = -inf)
       lsum *= f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float fh = __shfl(f, 4 * g + i);     // factor of head 4g+i (lane 4g+i owns it)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e][i] *= fh;
+        for (int e = 0; e < R::kAcc; ++e) o[e][i] *= fh;
       }
       m_ref = m_new;
     }
     float p[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) p[i] = __expf(s[i] - m_ref);
+    for (int i = 0; i < 4; ++i) p[i] = exp_of<kPrecise>(s[i] - m_ref);
     lsum += (p[0] + p[1]) + (p[2] + p[3]);
-    u32x2_t pw;
-    pw[0] = static_cast<unsigned>(float_to_bf16(p[0])) | (static_cast<unsigned>(float_to_bf16(p[1])) << 16);
-    pw[1] = static_cast<unsigned>(float_to_bf16(p[2])) | (static_cast<unsigned>(float_to_bf16(p[3])) << 16);
-    const s16x4_t pa = __builtin_bit_cast(s16x4_t, pw);
+    if constexpr (R::kF32) {
+      // lane (c, g) holds the weights of head c for the entries 4g .. 4g+3: the A operand of the
+      // product over entries 4g' + i, g' = 0..3, is p[i].  The sub-tile's 16 terms are summed on their
+      // own and then added: the running sum takes one rounding per sub-tile instead of 16.
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const unsigned sel = (e & 1) ? 0x07060302u : 0x05040100u;
-      u32x2_t vb;
-      vb[0] = __builtin_amdgcn_perm(t.v[1][e >> 1], t.v[0][e >> 1], sel);
-      vb[1] = __builtin_amdgcn_perm(t.v[3][e >> 1], t.v[2][e >> 1], sel);
-      o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, __builtin_bit_cast(s16x4_t, vb), o[e], 0, 0, 0);
+      for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          f32x4_t x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            x = __builtin_amdgcn_mfma_f32_16x16x4f32(p[i], __uint_as_float(t.v[i * (D / 64) + h][e]), x, 0, 0, 0);
+          o[4 * h + e] += x;
+        }
+    } else {
+    // weights as bf16 operands: rounded once, or (kPrecise) as three bf16 terms that add up to the fp32
+    // value exactly (8 bits of the significand each)
+    constexpr int kTerms = kPrecise ? 3 : 1;
+    s16x4_t pa[kTerms];
+#pragma unroll
+    for (int x = 0; x < kTerms; ++x) {
+      bf16_t pb[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        pb[i] = float_to_bf16(p[i]);
+        if (kPrecise) p[i] -= __uint_as_float(static_cast<unsigned>(pb[i]) << 16);
+      }
+      u32x2_t pw;
+      pw[0] = static_cast<unsigned>(pb[0]) | (static_cast<unsigned>(pb[1]) << 16);
+      pw[1] = static_cast<unsigned>(pb[2]) | (static_cast<unsigned>(pb[3]) << 16);
+      pa[x] = __builtin_bit_cast(s16x4_t, pw);
     }
-    if constexpr (kMore) load_v(t, it + 1);
+#pragma unroll
+    for (int e = 0; e < R::kAcc; ++e) {
+      const unsigned sel = (e & 1) ? 0x07060302u : 0x05040100u;
+      auto v_word = [&](int i) {                   // columns (8 c or 4 c) + 2 (e / 2), + 1 of row 4 g + i
+        if constexpr (D == 128) return t.v[i][e >> 1];
+        else return t.v[i / 2][2 * (i % 2) + (e >> 1)];
+      };
+      u32x2_t vb;
+      vb[0] = __builtin_amdgcn_perm(v_word(1), v_word(0), sel);
+      vb[1] = __builtin_amdgcn_perm(v_word(3), v_word(2), sel);
+#pragma unroll
+      for (int x = 0; x < kTerms; ++x)
+        o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa[x], __builtin_bit_cast(s16x4_t, vb), o[e], 0, 0, 0);
+    }
+    }
+    if constexpr (kMore) load_v(t, it + R::kDepth);
   };
 
   // this wave's logits -> workspace, 512 bytes per sub-tile: when the run ends, and for a
@@ -975,7 +1112,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
         sb = *reinterpret_cast<const f32x4_t *>(src + 4);
         entry = sub_of(it) * 16 + e_in;
         cand = sa[0] >= cut[0] || sa[1] >= cut[1] || sa[2] >= cut[2] || sa[3] >= cut[3] ||
-               sb[0] >= cut[4] || sb[1] >= cut[5] || sb[2] >= cut[6];
+               sb[0] >= cut[4] || sb[1] >= cut[5] || sb[2] >= cut[6] || sb[3] >= cut[7];
         cand = (cand && entry < n1) || entry == n_old;
       }
       const unsigned long long mask = __builtin_amdgcn_ballot_w64(cand);
@@ -986,7 +1123,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
         if (cand) {
           const unsigned at = 1 + base + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(mask >> 32),
                                                                   __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(mask), 0u));
-          sb[3] = __int_as_float(entry);
+          if (G < kHeadPad) sb[3] = __int_as_float(entry);
+          else a.cand_index_out[static_cast<size_t>(unit) * a.p_stride + static_cast<size_t>(split) * fused_part_cap(n_old, n_split) + at] = entry;
           *reinterpret_cast<f32x4_t *>(region + static_cast<size_t>(at) * kHeadPad) = sa;
           *reinterpret_cast<f32x4_t *>(region + static_cast<size_t>(at) * kHeadPad + 4) = sb;
         }
@@ -1024,33 +1162,62 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the LDS slots are written again next
     __builtin_amdgcn_wave_barrier();
   };
-  // (the wave's last sub-tile stands outside the loop, so that the loop requests the next
-  // sub-tile unconditionally: no branch between the loads, exact load counts for the waits)
-  for (int it = 0; it + 1 < cnt; ++it) {
-    compute(buf, it, std::true_type{});
-#ifdef LAZYEV_TIMELINE
-    if (it == 0) STAMP(1);
-#endif
-    if (it + 1 - seg0 == kRunMax) {
+  // logits of a long run leave LDS every kRunMax sub-tiles
+  auto segment_end = [&](int it) {
+    if (it + 1 - seg0 == kRunMax && it + 1 < cnt) {
       if constexpr (kLong) segment_candidates(seg0, it + 1);
       else flush(seg0, it + 1);
       seg0 = it + 1;
     }
+  };
+  // (the wave's last sub-tiles stand outside the loop, so that the loop requests the ones to come
+  // unconditionally: no branch between the loads, exact load counts for the waits)
+  if constexpr (R::kDepth == 1) {
+    for (int it = 0; it + 1 < cnt; ++it) {
+      compute(buf[0], it, std::true_type{});
+#ifdef LAZYEV_TIMELINE
+      if (it == 0) STAMP(1);
+#endif
+      segment_end(it);
+    }
+    if (cnt > 0) compute(buf[0], cnt - 1, std::false_type{});
+  } else {
+    int it = 0;
+    for (; it + 3 < cnt; it += 2) {
+      compute(buf[0], it, std::true_type{});
+      segment_end(it);
+      compute(buf[1], it + 1, std::true_type{});
+      segment_end(it + 1);
+    }
+    if (it + 2 < cnt) {
+      compute(buf[0], it, std::true_type{});
+      segment_end(it);
+      compute(buf[1], it + 1, std::false_type{});
+      segment_end(it + 1);
+      compute(buf[0], it + 2, std::false_type{});
+    } else {
+      if (it < cnt) { compute(buf[0], it, std::false_type{}); segment_end(it); }
+      if (it + 1 < cnt) compute(buf[1], it + 1, std::false_type{});
+    }
   }
-  if (cnt > 0) compute(buf, cnt - 1, std::false_type{});
   STAMP(2);
   if (!kCompact) flush(seg0, cnt);
   // ---- the four waves of the block -> one partial
   lsum = sum_over_lane_groups(lsum);
   if (g == 0) { m_lds[wave][c] = m_ref; lsum_lds[wave][c] = lsum; }
-  float *acc_lds = reinterpret_cast<float *>(&stage_lds[0][0]);   // [kWaves][8 * D]
+  constexpr int kAccStride = 16 * 16 * 4;         // (floats of stage_lds[wave])
+  static_assert(8 * D <= kAccStride, "a wave's accumulators fit its staging area");
+  float *acc_lds = reinterpret_cast<float *>(&stage_lds[0][0]);   // a wave's own 4 KB: others may still be streaming
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int head = 4 * g + i;
     if (head < G) {
-      float *d4 = acc_lds + wave * (8 * D) + head * D + 8 * c;
-      *reinterpret_cast<float4 *>(d4) = make_float4(o[0][i], o[1][i], o[2][i], o[3][i]);
-      *reinterpret_cast<float4 *>(d4 + 4) = make_float4(o[4][i], o[5][i], o[6][i], o[7][i]);
+      // accumulators 4 x .. 4 x + 3 hold the columns 8 c + 4 x .. (128-element bf16 rows) or 64 x + 4 c ..
+      float *row = acc_lds + wave * kAccStride + head * D;
+#pragma unroll
+      for (int x = 0; x < R::kAcc / 4; ++x)
+        *reinterpret_cast<float4 *>(row + (!R::kF32 && D == 128 ? 8 * c + 4 * x : 64 * x + 4 * c)) =
+            make_float4(o[4 * x][i], o[4 * x + 1][i], o[4 * x + 2][i], o[4 * x + 3][i]);
     }
   }
   __syncthreads();
@@ -1070,8 +1237,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
     const float mw = m_lds[w][h_own];
-    const float f = mw == -INFINITY ? 0.f : __expf(mw - mb_own);   // a wave without entries: factor 0
-    const f32x4_t x = *reinterpret_cast<const f32x4_t *>(acc_lds + w * (8 * D) + ec);
+    const float f = mw == -INFINITY ? 0.f : exp_of<kPrecise>(mw - mb_own);   // a wave without entries: factor 0
+    const f32x4_t x = *reinterpret_cast<const f32x4_t *>(acc_lds + w * kAccStride + ec);
 #pragma unroll
     for (int i = 0; i < 4; ++i) v_own[i] = fmaf(f, x[i], v_own[i]);
     l_own = fmaf(f, lsum_lds[w][h_own], l_own);
@@ -1094,25 +1261,25 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
   }
   if (leader) {
     constexpr int kIn = kSplit > 1 ? kSplit - 1 : kMergeRadix - 1;   // (instances of a fixed split have one group)
-    // (for six records and more the count is kept from the compiler, which would otherwise hold so
+    // (for five records and more the count is kept from the compiler, which would otherwise hold so
     // many addresses at once that registers spill: 8 blocks per unit of 2048 entries, 14.4 us instead of 8.0)
     int n_in = kSplit > 0 ? kSplit - 1 : split - group0;
-    if (kSplit > 6) __asm__("" : "+s"(n_in));
-    const Merge mg = merge_records<kIn>(a, recs + static_cast<size_t>(group0) * kRecWords, kRecWords, n_in, t_own,
+    if (kSplit > 5) __asm__("" : "+s"(n_in));
+    const Merge<kPrecise> mg = merge_records<kIn, kPrecise>(a, recs + static_cast<size_t>(group0) * kRecWords, kRecWords, n_in, t_own,
                                         mb_own, l_own, v_own);
     const f32x4_t o4 = {mg.o[0], mg.o[1], mg.o[2], mg.o[3]};
     if (kSplit > 0 || n_split <= kMergeRadix) {
       STAMP(4);
-      write_unit_row(a, unit, mg, e0, h_own);
+      write_unit_row<T, D>(a, unit, mg, e0, h_own);
     } else if (!finisher) {
       if (e0 < G * D) rec_store(recs + static_cast<size_t>(split) * kRecWords, tid, o4, mg.m, mg.l, a.seq);
     } else {
       // the other leaders' records (blocks kMergeRadix - 1, 2 kMergeRadix - 1, ...)
-      const Merge all = merge_records<kFusedSplitMax / kMergeRadix - 1>(
+      const Merge<kPrecise> all = merge_records<kFusedSplitMax / kMergeRadix - 1, kPrecise>(
           a, recs + static_cast<size_t>(kMergeRadix - 1) * kRecWords, kMergeRadix * kRecWords, group0 / kMergeRadix, t_own,
           mg.m, mg.l, o4);
       STAMP(4);
-      write_unit_row(a, unit, all, e0, h_own);
+      write_unit_row<T, D>(a, unit, all, e0, h_own);
     }
   }
   if (kCompact) {
@@ -1126,7 +1293,82 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, 4) void decode_fu
   STAMP(5);
 }
 
+// ------------------------------------------------------------------------------- host side
+// Compute units of the current device (asked once).
+int compute_units() {
+  static int n = 0;
+  if (n == 0) {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
+      n = v;
+    else
+      n = 256;
+  }
+  return n;
+}
+
+template <typename T, int D>
+hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) {
+  if (ev) (void)hipEventRecord(ev[0], stream);
+  const int n_sub = (a.n_old + 1 + 15) / 16;
+  int run = fused_wave_run(n_sub, a.n_split);
+  if (run > kRunMax) run = kRunMax;
+  const size_t lds_all = static_cast<size_t>(kWaves) * run * 16 * kHeadPad * sizeof(float);
+  const int units = a.batch * a.n_kv_heads;
+  const int sb = a.n_split * units;
+  const T *kc = static_cast<const T *>(a.k_cache), *vc = static_cast<const T *>(a.v_cache);
+  const T *kn = static_cast<const T *>(a.k_new), *vn = static_cast<const T *>(a.v_new);
+  const int slots_on = a.slots.prompt_len ? 1 : 0;
+  const bool long_run = fused_wave_run(n_sub, a.n_split) > kRunMax;
+  // list waves (blocks of eight waves) where every block of the launch is resident at once: two
+  // such blocks fit a compute unit
+  constexpr bool kList = !Rows<T, D>::kWide;
+  const int n_blocks = sb + (a.track.valid ? a.n_track * units : 0);
+  const bool resident = n_blocks <= 2 * compute_units();
+  const dim3 grid(n_blocks), block(kBlock), block_l(kList ? 2 * kBlock : kBlock);
+#define LAZYEV_LAUNCH(block, ...) \
+  hipLaunchKernelGGL((decode_fused_kernel<T, D, __VA_ARGS__>), grid, block, lds_all, stream, kc, vc, kn, vn, a.n_old, a.n_split, a.capacity, units, slots_on, a)
+#define LAZYEV_SPLIT(n) \
+  case n: \
+    if (long_run) LAZYEV_LAUNCH(block_l, true, true, kList, n); \
+    else LAZYEV_LAUNCH(block_l, true, false, kList, n); \
+    break;
+  if (a.variant == 6 && resident) {
+    switch (a.n_split) {
+      LAZYEV_SPLIT(1)
+      LAZYEV_SPLIT(2)
+      LAZYEV_SPLIT(3)
+      LAZYEV_SPLIT(4)
+      LAZYEV_SPLIT(5)
+      LAZYEV_SPLIT(6)
+      LAZYEV_SPLIT(7)
+      LAZYEV_SPLIT(8)
+      default:
+        if (long_run) LAZYEV_LAUNCH(block_l, true, true, kList, 0);
+        else LAZYEV_LAUNCH(block_l, true, false, kList, 0);
+    }
+  } else if (a.variant == 6 && long_run) LAZYEV_LAUNCH(block, true, true, false, 0);
+  else if (a.variant == 6) LAZYEV_LAUNCH(block, true, false, false, 0);
+  else LAZYEV_LAUNCH(block, false, false, false, 0);
+#undef LAZYEV_SPLIT
+#undef LAZYEV_LAUNCH
+  const hipError_t e = hipGetLastError();
+  if (ev) { (void)hipEventRecord(ev[1], stream); (void)hipEventRecord(ev[2], stream); }
+  return e;
+}
+
 }  // namespace
+
+// This file is compiled once per row type (see build.py): the instances for 128-element bf16 rows with
+// everything that does not depend on the row type, and the other three row types on their own.
+#ifndef LAZYEV_ROWS
+#define LAZYEV_ROWS 0
+#endif
+hipError_t launch_fused_bf16_64(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev);
+hipError_t launch_fused_f32_64(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev);
+hipError_t launch_fused_f32_128(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev);
+#if LAZYEV_ROWS == 0
 
 #ifdef LAZYEV_TIMELINE
 // (host) copies the first n_words words of the stamps of the last launch; waits for the device
@@ -1179,7 +1421,7 @@ hipError_t launch_clear_records(unsigned long long *rec, size_t n_words, hipStre
 }
 
 bool decode_fused_compact_fits(int n_old, int n_split, int p_stride, int group) {
-  if (n_split < 1 || n_split > kFusedSplitMax || group >= kHeadPad) return false;
+  if (n_split < 1 || n_split > kFusedSplitMax || group > kHeadPad) return false;
   const int cap = fused_part_cap(n_old, n_split);
   return static_cast<long long>(cap) * n_split <= p_stride;
 }
@@ -1188,11 +1430,13 @@ hipError_t launch_track(const TrackArgs &k, hipStream_t stream) {
   if (!k.valid || k.units < 1 || k.group > kHeadPad || !k.logits || !k.stat ||
       k.p_stride < (k.n_old + 16) / 16 * 16)
     return hipErrorInvalidValue;
+  if (k.compact && k.group == kHeadPad && !k.cand_index) return hipErrorInvalidValue;
   if (k.compact && !decode_fused_compact_fits(k.n_old, k.n_parts, k.p_stride, k.group)) return hipErrorInvalidValue;
   int n_parts = (k.n_old + 1 + 2 * kBlock - 1) / (2 * kBlock);   // about two entries per thread
   if (n_parts > 64) n_parts = 64;
   if (k.compact) n_parts = k.n_parts;              // one block per block of the call
-  hipLaunchKernelGGL(track_kernel, dim3(k.units * n_parts), dim3(kBlock), 0, stream, k, n_parts);
+  if (k.precise) hipLaunchKernelGGL(track_kernel<true>, dim3(k.units * n_parts), dim3(kBlock), 0, stream, k, n_parts);
+  else hipLaunchKernelGGL(track_kernel<false>, dim3(k.units * n_parts), dim3(kBlock), 0, stream, k, n_parts);
   return hipGetLastError();
 }
 
@@ -1208,23 +1452,9 @@ hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stre
   return hipGetLastError();
 }
 
-// Compute units of the current device (asked once).
-static int compute_units() {
-  static int n = 0;
-  if (n == 0) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      n = v;
-    else
-      n = 256;
-  }
-  return n;
-}
-
 hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) {
   const int units = a.batch * a.n_kv_heads;
-  if (a.dtype != 1 || a.head_dim != D || a.group > kHeadPad || a.n_split < 1 ||
+  if (a.group > kHeadPad || a.n_split < 1 ||
       a.n_split > kFusedSplitMax || a.n_split > a.rec_per_unit || !a.logits_out ||
       !a.ws.part_rec || !a.ws.fault || a.seq == 0 ||
       !a.stat_out || a.p_stride < (a.n_old + 16) / 16 * 16 ||
@@ -1236,52 +1466,23 @@ hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent
        (a.track.log_words < (a.track.capacity + 31) / 32 || a.track.log_words > decode_fused_log_words_max() ||
         a.track.log_unit_stride < a.track.log_words ||
         a.track.slots.prompt_len)) ||
+      (a.track.valid && a.track.compact && a.track.group == kHeadPad && !a.track.cand_index) ||
+      (a.variant == 6 && a.group == kHeadPad && !a.cand_index_out) ||
       (a.variant == 6 && (a.p_out || a.p_override || !decode_fused_compact_fits(a.n_old, a.n_split, a.p_stride, a.group))))
     return hipErrorInvalidValue;
-  if (ev) (void)hipEventRecord(ev[0], stream);
-  const int n_sub = (a.n_old + 1 + 15) / 16;
-  int run = fused_wave_run(n_sub, a.n_split);
-  if (run > kRunMax) run = kRunMax;
-  const size_t lds_all = static_cast<size_t>(kWaves) * run * 16 * kHeadPad * sizeof(float);
-  const int sb = a.n_split * units;
-  const bf16_t *kc = static_cast<const bf16_t *>(a.k_cache), *vc = static_cast<const bf16_t *>(a.v_cache);
-  const bf16_t *kn = static_cast<const bf16_t *>(a.k_new), *vn = static_cast<const bf16_t *>(a.v_new);
-  const int slots_on = a.slots.prompt_len ? 1 : 0;
-  const bool long_run = fused_wave_run(n_sub, a.n_split) > kRunMax;
-  // list waves (blocks of eight waves) where every block of the launch is resident at once: two
-  // such blocks fit a compute unit
-  const int n_blocks = sb + (a.track.valid ? a.n_track * units : 0);
-  const bool list_waves = n_blocks <= 2 * compute_units() ;
-  const dim3 grid(n_blocks), b4(kBlock), b8(2 * kBlock);
-#define LAZYEV_LAUNCH(instance, block) \
-  hipLaunchKernelGGL(instance, grid, block, lds_all, stream, kc, vc, kn, vn, a.n_old, a.n_split, a.capacity, units, slots_on, a)
-#define LAZYEV_SPLIT(n) \
-  case n: \
-    if (long_run) LAZYEV_LAUNCH((decode_fused_kernel<true, true, true, n>), b8); \
-    else LAZYEV_LAUNCH((decode_fused_kernel<true, false, true, n>), b8); \
-    break;
-  if (a.variant == 6 && list_waves) {
-    switch (a.n_split) {
-      LAZYEV_SPLIT(1)
-      LAZYEV_SPLIT(2)
-      LAZYEV_SPLIT(3)
-      LAZYEV_SPLIT(4)
-      LAZYEV_SPLIT(5)
-      LAZYEV_SPLIT(6)
-      LAZYEV_SPLIT(7)
-      LAZYEV_SPLIT(8)
-      default:
-        if (long_run) LAZYEV_LAUNCH((decode_fused_kernel<true, true, true>), b8);
-        else LAZYEV_LAUNCH((decode_fused_kernel<true, false, true>), b8);
-    }
-  } else if (a.variant == 6 && long_run) LAZYEV_LAUNCH((decode_fused_kernel<true, true, false>), b4);
-  else if (a.variant == 6) LAZYEV_LAUNCH((decode_fused_kernel<true, false, false>), b4);
-  else LAZYEV_LAUNCH((decode_fused_kernel<false, false, false>), b4);
-#undef LAZYEV_SPLIT
-#undef LAZYEV_LAUNCH
-  const hipError_t e = hipGetLastError();
-  if (ev) { (void)hipEventRecord(ev[1], stream); (void)hipEventRecord(ev[2], stream); }
-  return e;
+  if (a.dtype == 1 && a.head_dim == 128) return launch_rows<bf16_t, 128>(a, stream, ev);
+  if (a.dtype == 1 && a.head_dim == 64) return launch_fused_bf16_64(a, stream, ev);
+  if (a.dtype == 0 && a.head_dim == 64) return launch_fused_f32_64(a, stream, ev);
+  if (a.dtype == 0 && a.head_dim == 128) return launch_fused_f32_128(a, stream, ev);
+  return hipErrorInvalidValue;
 }
+
+#elif LAZYEV_ROWS == 1
+hipError_t launch_fused_bf16_64(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) { return launch_rows<bf16_t, 64>(a, stream, ev); }
+#elif LAZYEV_ROWS == 2
+hipError_t launch_fused_f32_64(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) { return launch_rows<float, 64>(a, stream, ev); }
+#elif LAZYEV_ROWS == 3
+hipError_t launch_fused_f32_128(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) { return launch_rows<float, 128>(a, stream, ev); }
+#endif
 
 }  // namespace lazyev

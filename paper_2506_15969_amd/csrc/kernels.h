@@ -14,6 +14,7 @@ struct Workspace {
   float    *p_tilde;      // [batch][n_q_heads][p_stride] exp(s - partial max) of every entry
                           // (split + merge kernels); the first logits buffer lies over it
   float    *logits[2];    // [units][p_stride][8]        fused kernel: scaled logits, double-buffered
+  int32_t  *cand_index[2]; // [units][p_stride]          fused kernel, groups of 8: entry indices of the candidate records
   float    *stat[2];      // [units][8][2]               fused kernel: softmax max and 1 / sum per head
   int32_t  *src_index;    // [units][C]                  eviction: source entry of survivor j
   unsigned long long *sel_keys;     // [n_layers][units][C] eviction: score keys of a unit with more candidates
@@ -61,12 +62,15 @@ struct TrackArgs {
   const float *p_override;
   unsigned long long *activation_counter;   // the call's layer
   Slots slots;                      // with slots: n_old is the largest of the sequences', t global
-  // compact != 0 (fused kernel, groups of at most 7 heads): the logits buffer holds, per block
+  int32_t precise;                  // exponentials by expf (see Rows::kPrecise)
+  // compact != 0 (fused kernel): the logits buffer holds, per block
   // of the call (n_parts per unit), only the entries that can reach alpha ("candidates").
   // Block b of a unit owns the slots [b * cap, (b + 1) * cap) of the unit's p_stride slots of 8
   // floats, cap = fused_part_cap(n_old, n_parts): slot 0 holds the number of records (as an
-  // integer), slot 1 + r record r = the entry's 7 logits and, in the 8th place, its index.
+  // integer), slot 1 + r record r = the entry's 7 logits and, in the 8th place, its index.  A group
+  // of 8 heads needs all 8 places: the indices are in cand_index then, at the slots' numbers.
   int32_t compact, n_parts;
+  const int32_t *cand_index;        // [units][p_stride], null for groups of at most 7
   // Activation log (fused kernel, uniform batches).  Not null: the tracking blocks do not touch
   // TS / MRI of the active entries (a 128-byte line read and written for every 4-byte word) but
   // leave ONE BIT per cache entry of the unit, bit i = entry i was active in this call, as
@@ -98,7 +102,7 @@ struct DecodeArgs {
   int32_t n_split_max;    // stride of the partial arrays
   int32_t p_stride;       // row stride of p_tilde (C rounded up to a multiple of 4)
   int32_t variant;        // attention kernel actually launched: 0 vector ALU + merge,
-                          // 4 fused MFMA, 6 fused MFMA leaving candidate lists (see TrackArgs)
+                          // 4 fused, 6 fused leaving candidate lists (see TrackArgs)
   float   alpha, scale;
   int32_t dtype;
   const void *q, *k_new, *v_new;
@@ -115,6 +119,7 @@ struct DecodeArgs {
   uint32_t spin_ticks;                      // fused kernel: longest wait for a record, in 10 ns ticks
   // fused kernel: where this call's logits and statistics go, and the previous call to track
   float *logits_out, *stat_out;
+  int32_t *cand_index_out;                  // see TrackArgs::cand_index
   TrackArgs track;
   Slots slots;                              // with slots: n_old is the largest of the sequences', t global
 };
@@ -173,7 +178,7 @@ hipError_t launch_prefill_track(const PrefillArgs &a, hipStream_t stream);
 // `ev`, when not null, points at three events recorded before the first kernel, between the two
 // kernels and after the second (per-kernel timing for the profiling aid).
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev);
-// One launch per call: split blocks, the last block of a unit merges and tracks (bf16, d 128).
+// One launch per call: split blocks, the last block of a unit merges; tracks the previous call.
 hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev);
 int decode_fused_split_max();
 // Most sub-tiles of 16 entries one wave of a call with n_split blocks per unit takes, and how
@@ -181,7 +186,7 @@ int decode_fused_split_max();
 int decode_fused_wave_run(int n_sub, int n_split);
 int decode_fused_run_max();
 // Can a call with these sizes leave candidate lists (they fit the logits buffer, a wave's logits
-// stay in LDS to the end of its run, and the 8th logit place is free for the entry index)?
+// stay in LDS to the end of its run)?
 bool decode_fused_compact_fits(int n_old, int n_split, int p_stride, int group);
 int decode_fused_head_pad();
 size_t decode_fused_record_bytes();           // one stamped record

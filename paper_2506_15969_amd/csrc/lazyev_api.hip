@@ -110,7 +110,7 @@ int32_t capacity_of(const lazyev_config *c) {
 size_t fused_p_stride(int32_t capacity) { return static_cast<size_t>((capacity + 15) / 16 * 16) + 65 * 64; }
 
 struct Layout {
-  size_t part_acc, part_ml, p_tilde, logits1, stat, prefill_stat, src_index, sel_keys, bitlog, activations, rows_moved, records, fault, hist, slots, total;
+  size_t part_acc, part_ml, p_tilde, logits1, cand_index, stat, prefill_stat, src_index, sel_keys, bitlog, activations, rows_moved, records, fault, hist, slots, total;
   int32_t log_words, log_slots;     // 0: no activation log for this shape
   int32_t n_split_max;
 };
@@ -129,6 +129,9 @@ Layout layout_of(const lazyev_config *c) {
   const size_t logits_bytes = units * fused_p_stride(static_cast<int32_t>(cap)) * 8 * sizeof(float);
   l.p_tilde = off;  off = align_up(off + logits_bytes);
   l.logits1 = off;  off = align_up(off + logits_bytes);
+  // groups of 8 heads: the entry indices of the candidate records (two buffers like the logits)
+  l.cand_index = off;
+  if (g == 8) off = align_up(off + 2 * units * fused_p_stride(static_cast<int32_t>(cap)) * sizeof(int32_t));
   l.stat = off;     off = align_up(off + 2 * units * 16 * sizeof(float));
   // softmax statistics of every (unit, head, prompt position) for the tracking over the prompt
   l.prefill_stat = off;                            // (the longest prompt a slot can hold: capacity - window)
@@ -142,8 +145,7 @@ Layout layout_of(const lazyev_config *c) {
   // many slots as calls lie between two evictions (at most kLogSlotsMax; a full log is applied)
   l.bitlog = off;
   l.log_words = 0; l.log_slots = 0;
-  if (c->dtype == LAZYEV_DTYPE_BF16 && c->head_dim == 128 &&
-      (cap + 31) / 32 <= static_cast<size_t>(lazyev::decode_fused_log_words_max())) {
+  if ((cap + 31) / 32 <= static_cast<size_t>(lazyev::decode_fused_log_words_max())) {
     l.log_words = static_cast<int32_t>((cap + 31) / 32);
     l.log_slots = c->window < lazyev::kLogSlotsMax ? c->window : lazyev::kLogSlotsMax;
     off = align_up(off + static_cast<size_t>(c->n_layers) * l.log_slots * units * l.log_words * sizeof(uint32_t));
@@ -384,6 +386,10 @@ int lazyev_init(const lazyev_config *cfg, lazyev_ctx **out) {
   ctx->ws.p_tilde = reinterpret_cast<float *>(base + l.p_tilde);
   ctx->ws.logits[0] = ctx->ws.p_tilde;
   ctx->ws.logits[1] = reinterpret_cast<float *>(base + l.logits1);
+  for (int i = 0; i < 2; ++i)
+    ctx->ws.cand_index[i] = ctx->group == 8 ? reinterpret_cast<int32_t *>(base + l.cand_index) +
+                                                  i * static_cast<size_t>(ctx->units) * fused_p_stride(ctx->capacity)
+                                            : nullptr;
   ctx->ws.stat[0] = reinterpret_cast<float *>(base + l.stat);
   ctx->ws.stat[1] = ctx->ws.stat[0] + static_cast<size_t>(cfg->batch) * cfg->n_kv_heads * 16;
   std::memset(&ctx->pend, 0, sizeof(ctx->pend));
@@ -485,9 +491,8 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
   a.head_dim = c.head_dim; a.group = ctx->group; a.capacity = ctx->capacity;
   a.n_old = n_old; a.t = t; a.prompt_len = c.prompt_len;
   // which attention kernel: see lazyev_set_variant
-  const bool mfma_shape = c.dtype == LAZYEV_DTYPE_BF16 && c.head_dim == 128;
   // (5 and 6 are 4 with the logits always / never written in full)
-  const int kind = (mfma_shape && ctx->variant != 0) ? 4 : 0;
+  const int kind = ctx->variant != 0 ? 4 : 0;
   bool compact = false;
   if (ctx->slots_on && kind != 4) return LAZYEV_EINVAL;   // only the single-launch kernel knows slots
   a.slots = slots_of(ctx);
@@ -506,6 +511,7 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
     a.chunk = 16;
     a.logits_out = ctx->ws.logits[ctx->cur_buf];
     a.stat_out = ctx->ws.stat[ctx->cur_buf];
+    a.cand_index_out = ctx->ws.cand_index[ctx->cur_buf];
     if (p_out || p_override) {                     // the caller looks at the weights of this call at once:
       const hipError_t ef = flush_tracking(ctx);   // everything older is applied first, in order
       if (ef != hipSuccess) return fail_hip(ctx, ef);
@@ -588,6 +594,8 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
     k.ts = a.ts; k.mri = a.mri; k.pos = a.pos;
     k.logits = a.logits_out; k.stat = a.stat_out;
     k.compact = compact ? 1 : 0; k.n_parts = a.n_split;
+    k.cand_index = a.cand_index_out;
+    k.precise = c.dtype == LAZYEV_DTYPE_BF16 && c.head_dim == 128 ? 0 : 1;
     k.p_out = p_out; k.p_override = p_override;
     k.activation_counter = a.activation_counter;
     k.slots = a.slots;
