@@ -67,40 +67,39 @@ __global__ void score_pairs_kernel(const int32_t *dt, const int32_t *mri, double
   if (i < n) score[i] = mri_centric_score(dt[i], mri[i], flags);
 }
 
-// Counts the first n entries of every unit of a layer by MRI value; values >= n_bins - 1 share
-// the last bin.  Most entries have MRI = 0: those are counted per wave, not per lane.
-__global__ void mri_histogram_kernel(const int32_t *mri, int64_t n_units, int32_t capacity,
-                                     int32_t n, int32_t n_bins, unsigned long long *hist) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const bool in = i < n_units * n;
-  int32_t b = -1;
-  if (in) {
-    const int32_t m = mri[(i / n) * capacity + i % n];
-    b = m < n_bins - 1 ? m : n_bins - 1;
+// Counts the first n entries (seq_len[sequence], when not null) of every unit by MRI value; values >=
+// n_bins - 1 share the last bin.  A block counts kHistSpan entries of one unit in LDS and adds its
+// bins to the result once: with an addition to global memory per entry the few values that most
+// entries have were a queue of some hundred thousand (32 units of 16400 entries in all, 460 -> 5.6 us).  Most entries
+// have MRI = 0: those are counted per wave, not per lane.
+constexpr int kHistBlock = 256;
+constexpr int kHistSpan = 8 * kHistBlock;
+__global__ __launch_bounds__(kHistBlock) void mri_histogram_kernel(const int32_t *mri, int32_t capacity, int32_t n_kv_heads,
+                                                                   const int32_t *seq_len, int32_t n, int32_t spans,
+                                                                   int32_t n_bins, unsigned long long *hist) {
+  extern __shared__ unsigned bins[];
+  const int unit = blockIdx.x / spans, first = blockIdx.x % spans * kHistSpan;
+  const int len = seq_len ? min(seq_len[unit / n_kv_heads], n) : n;
+  if (first >= len) return;
+  const int32_t *m_unit = mri + static_cast<size_t>(unit) * capacity;
+  int32_t m[kHistSpan / kHistBlock];
+#pragma unroll
+  for (int r = 0; r < kHistSpan / kHistBlock; ++r) {
+    const int i = first + r * kHistBlock + static_cast<int>(threadIdx.x);
+    m[r] = i < len ? m_unit[i] : -1;
   }
-  const unsigned long long zeros = __builtin_amdgcn_ballot_w64(b == 0);
-  if (zeros != 0 && (threadIdx.x & 63) == 0)
-    atomicAdd(&hist[0], static_cast<unsigned long long>(__builtin_popcountll(zeros)));
-  if (b > 0) atomicAdd(&hist[b], 1ull);
-}
-
-__global__ void mri_histogram_slots_kernel(const int32_t *mri, int64_t n_units, int32_t capacity,
-                                           int32_t n_kv_heads, const int32_t *seq_len, int32_t n_max,
-                                           int32_t n_bins, unsigned long long *hist) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  int32_t b = -1;
-  if (i < n_units * n_max) {
-    const int64_t unit = i / n_max;
-    const int32_t slot = static_cast<int32_t>(i % n_max);
-    if (slot < seq_len[unit / n_kv_heads]) {
-      const int32_t m = mri[unit * capacity + slot];
-      b = m < n_bins - 1 ? m : n_bins - 1;
-    }
+  for (int b = threadIdx.x; b < n_bins; b += kHistBlock) bins[b] = 0;
+  __syncthreads();
+  unsigned zeros = 0;
+#pragma unroll
+  for (int r = 0; r < kHistSpan / kHistBlock; ++r) {
+    zeros += static_cast<unsigned>(__popcll(__builtin_amdgcn_ballot_w64(m[r] == 0)));
+    if (m[r] > 0) atomicAdd(&bins[min(m[r], n_bins - 1)], 1u);
   }
-  const unsigned long long zeros = __builtin_amdgcn_ballot_w64(b == 0);
-  if (zeros != 0 && (threadIdx.x & 63) == 0)
-    atomicAdd(&hist[0], static_cast<unsigned long long>(__builtin_popcountll(zeros)));
-  if (b > 0) atomicAdd(&hist[b], 1ull);
+  if ((threadIdx.x & 63) == 0 && zeros != 0) atomicAdd(&bins[0], zeros);
+  __syncthreads();
+  for (int b = threadIdx.x; b < n_bins; b += kHistBlock)
+    if (bins[b] != 0) atomicAdd(&hist[b], static_cast<unsigned long long>(bins[b]));
 }
 
 // A sequence starts over in its slot: the state of lazyev_init for its units in every layer,
@@ -466,24 +465,14 @@ hipError_t launch_init_state(int32_t *ts, int32_t *mri, int32_t *pos, int64_t n_
   return hipGetLastError();
 }
 
-hipError_t launch_mri_histogram(const int32_t *mri, int64_t n_units, int32_t capacity, int32_t n,
-                                int32_t n_bins, unsigned long long *hist, hipStream_t stream) {
+hipError_t launch_mri_histogram(const int32_t *mri, int64_t n_units, int32_t capacity, int32_t n_kv_heads,
+                                const int32_t *seq_len, int32_t n, int32_t n_bins, unsigned long long *hist,
+                                hipStream_t stream) {
   if (n_units <= 0 || n <= 0) return hipSuccess;
-  if (n > capacity || n_bins < 2) return hipErrorInvalidValue;
-  const unsigned blocks = static_cast<unsigned>((n_units * n + 255) / 256);
-  hipLaunchKernelGGL(mri_histogram_kernel, dim3(blocks), dim3(256), 0, stream, mri, n_units,
-                     capacity, n, n_bins, hist);
-  return hipGetLastError();
-}
-
-hipError_t launch_mri_histogram_slots(const int32_t *mri, int64_t n_units, int32_t capacity,
-                                      int32_t n_kv_heads, const int32_t *seq_len, int32_t n_max,
-                                      int32_t n_bins, unsigned long long *hist, hipStream_t stream) {
-  if (n_units <= 0 || n_max <= 0) return hipSuccess;
-  if (n_max > capacity || n_bins < 2 || !seq_len || n_kv_heads < 1) return hipErrorInvalidValue;
-  const unsigned blocks = static_cast<unsigned>((n_units * n_max + 255) / 256);
-  hipLaunchKernelGGL(mri_histogram_slots_kernel, dim3(blocks), dim3(256), 0, stream, mri, n_units,
-                     capacity, n_kv_heads, seq_len, n_max, n_bins, hist);
+  const int32_t spans = (n + kHistSpan - 1) / kHistSpan;
+  if (n > capacity || n_bins < 2 || n_kv_heads < 1 || n_units * spans > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(mri_histogram_kernel, dim3(static_cast<unsigned>(n_units * spans)), dim3(kHistBlock),
+                     n_bins * sizeof(unsigned), stream, mri, capacity, n_kv_heads, seq_len, n, spans, n_bins, hist);
   return hipGetLastError();
 }
 

@@ -204,12 +204,10 @@ hipError_t launch_init_state(int32_t *ts, int32_t *mri, int32_t *pos, int64_t n_
 hipError_t launch_init_slot(int32_t *ts, int32_t *mri, int32_t *pos, int32_t n_layers, int32_t batch,
                             int32_t n_kv_heads, int32_t capacity, int32_t seq, int32_t prompt_len,
                             int32_t *dev_prompt_len, int32_t *dev_t0, int32_t t0, hipStream_t stream);
-hipError_t launch_mri_histogram(const int32_t *mri, int64_t n_units, int32_t capacity, int32_t n,
-                                int32_t n_bins, unsigned long long *hist, hipStream_t stream);
-// seq_len (device, [batch]): entries of each sequence, used instead of n when not null
-hipError_t launch_mri_histogram_slots(const int32_t *mri, int64_t n_units, int32_t capacity,
-                                      int32_t n_kv_heads, const int32_t *seq_len, int32_t n_max,
-                                      int32_t n_bins, unsigned long long *hist, hipStream_t stream);
+// seq_len (device, [units / n_kv_heads] or null): entries of each sequence, at most n; null: n entries each
+hipError_t launch_mri_histogram(const int32_t *mri, int64_t n_units, int32_t capacity, int32_t n_kv_heads,
+                                const int32_t *seq_len, int32_t n, int32_t n_bins, unsigned long long *hist,
+                                hipStream_t stream);
 hipError_t launch_score_pairs(const int32_t *dt, const int32_t *mri, double *score, int64_t n,
                               int32_t flags, hipStream_t stream);
 

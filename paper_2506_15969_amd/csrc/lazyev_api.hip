@@ -871,11 +871,14 @@ int lazyev_mri_histogram(lazyev_ctx *ctx, int32_t layer, int32_t n_bins, int64_t
   hipError_t e = flush_tracking(ctx);
   if (e == hipSuccess) e = hipMemsetAsync(ctx->ws.hist, 0, n_bins * sizeof(unsigned long long), ctx->stream);
   const int l0 = layer < 0 ? 0 : layer, l1 = layer < 0 ? ctx->cfg.n_layers : layer + 1;
-  for (int l = l0; l < l1 && e == hipSuccess; ++l) {
+  for (int l = l0; l < l1 && e == hipSuccess;) {
     const int32_t *mri_l = ctx->cfg.mri + static_cast<size_t>(l) * ctx->units * ctx->capacity;
-    if (!ctx->slots_on) {
-      e = lazyev::launch_mri_histogram(mri_l, ctx->units, ctx->capacity, ctx->len[l], n_bins,
-                                       ctx->ws.hist, ctx->stream);
+    if (!ctx->slots_on) {                            // layers of one length (the usual case: all) in one launch
+      int n = 1;
+      while (l + n < l1 && ctx->len[l + n] == ctx->len[l]) ++n;
+      e = lazyev::launch_mri_histogram(mri_l, static_cast<int64_t>(n) * ctx->units, ctx->capacity, ctx->cfg.n_kv_heads,
+                                       nullptr, ctx->len[l], n_bins, ctx->ws.hist, ctx->stream);
+      l += n;
       continue;
     }
     // per-sequence lengths of this layer go to the device first (a rare, synchronous call)
@@ -894,8 +897,9 @@ int lazyev_mri_histogram(lazyev_ctx *ctx, int32_t layer, int32_t n_bins, int64_t
     if (e == hipSuccess)
       e = hipMemcpy(ctx->dev_seq_len, lens.data(), lens.size() * sizeof(int32_t), hipMemcpyHostToDevice);
     if (e == hipSuccess)
-      e = lazyev::launch_mri_histogram_slots(mri_l, ctx->units, ctx->capacity, ctx->cfg.n_kv_heads,
-                                             ctx->dev_seq_len, n_max, n_bins, ctx->ws.hist, ctx->stream);
+      e = lazyev::launch_mri_histogram(mri_l, ctx->units, ctx->capacity, ctx->cfg.n_kv_heads,
+                                       ctx->dev_seq_len, n_max, n_bins, ctx->ws.hist, ctx->stream);
+    ++l;
   }
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e == hipSuccess)
