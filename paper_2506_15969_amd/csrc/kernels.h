@@ -167,8 +167,13 @@ struct PrefillArgs {
   const void *q_prompt;             // [batch][prompt_len][n_q_heads][head_dim], the cache's type
   const void *k_cache;              // the layer's slab
   int32_t *ts, *mri;                // the layer's slab
-  float *stat;                      // [units][group][p16]: -(log-sum-exp of the scaled logits) / scale per
-                                    // (head, position), workspace
+  float *stat;                      // [units][group][p16] per (head, position), workspace: -(log-sum-exp of the
+                                    // scaled logits) / scale; of other rows than 128 x bf16 its larger part in
+                                    // units of log 2, the rest in stat2
+  float *stat2;
+  int4 *seg;                        // [segments][units][prompt_len], workspace: what segments of the queries leave of a key
+  int32_t segments;                 // most segments the area holds; of a launch: its segments ...
+  int32_t seg_tiles, seg_block;     // ... of seg_tiles query tiles of 16 each, and the keys of a block
   float *p_out;                     // [batch][n_q_heads][prompt_len][prompt_len] or null
   const float *p_override;          // same shape or null
   unsigned long long *activation_counter;   // the layer's [units][counter_stride] or null

@@ -135,7 +135,7 @@ Layout layout_of(const lazyev_config *c) {
   l.stat = off;     off = align_up(off + 2 * units * 16 * sizeof(float));
   // softmax statistics of every (unit, head, prompt position) for the tracking over the prompt
   l.prefill_stat = off;                            // (the longest prompt a slot can hold: capacity - window)
-  off = align_up(off + units * 8 * ((cap - c->window + 15) / 16 * 16) * sizeof(float));
+  off = align_up(off + 2 * units * 8 * ((cap - c->window + 15) / 16 * 16) * sizeof(float));
   l.src_index = off; off = align_up(off + static_cast<size_t>(c->n_layers) * units * cap * sizeof(int32_t));   // (all layers may be evicted in one go)
   // score keys of the selection, only if an eviction can have more candidates than LDS holds
   l.sel_keys = off;
@@ -608,6 +608,21 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
   return LAZYEV_OK;
 }
 
+}  // extern "C"
+
+// The workspace areas of a tracking over `units` units' prompts.  The segments' results go where the next
+// decode call leaves its logits: nothing outstanding is read from there.
+static void prefill_areas(const lazyev_ctx *ctx, size_t units, lazyev::PrefillArgs &a) {
+  a.stat = ctx->prefill_stat;
+  a.stat2 = ctx->prefill_stat + units * ctx->group * a.p16;
+  a.seg = reinterpret_cast<int4 *>(ctx->ws.logits[ctx->cur_buf]);
+  const size_t bytes = static_cast<size_t>(ctx->units) * fused_p_stride(ctx->capacity) * 8 * sizeof(float);
+  const size_t n = bytes / (sizeof(int4) * units * static_cast<size_t>(a.prompt_len));
+  a.segments = static_cast<int32_t>(n < 32 ? n : 32);
+}
+
+extern "C" {
+
 int lazyev_prefill_track(lazyev_ctx *ctx, int32_t layer, const void *q_prompt, float *p_out,
                          const float *p_override) {
   if (!ctx || !q_prompt) return LAZYEV_EINVAL;
@@ -629,7 +644,7 @@ int lazyev_prefill_track(lazyev_ctx *ctx, int32_t layer, const void *q_prompt, f
               static_cast<size_t>(layer) * slab * c.head_dim * (c.dtype == LAZYEV_DTYPE_FP32 ? 4 : 2);
   a.ts = c.ts + static_cast<size_t>(layer) * slab;
   a.mri = c.mri + static_cast<size_t>(layer) * slab;
-  a.stat = ctx->prefill_stat;
+  prefill_areas(ctx, ctx->units, a);
   a.p_out = p_out; a.p_override = p_override;
   a.activation_counter = ctx->ws.activations + static_cast<size_t>(layer) * ctx->units * lazyev::decode_slice_max();
   const hipError_t e = lazyev::launch_prefill_track(a, ctx->stream);
@@ -660,7 +675,7 @@ int lazyev_prefill_track_seq(lazyev_ctx *ctx, int32_t layer, int32_t seq, const 
   a.k_cache = static_cast<char *>(c.k_cache) + (static_cast<size_t>(layer) * slab + first * ctx->capacity) * c.head_dim * 2;
   a.ts = c.ts + static_cast<size_t>(layer) * slab + first * ctx->capacity;
   a.mri = c.mri + static_cast<size_t>(layer) * slab + first * ctx->capacity;
-  a.stat = ctx->prefill_stat;
+  prefill_areas(ctx, c.n_kv_heads, a);
   a.p_out = p_out; a.p_override = p_override;
   a.activation_counter = ctx->ws.activations +
                          (static_cast<size_t>(layer) * ctx->units + first) * lazyev::decode_slice_max();

@@ -1,322 +1,589 @@
-// Recurrence tracking over the prompt (MFMA kernels for bf16 with head_dim 128, plain vector-ALU
-// kernels at the end of the file for fp32 rows or head_dim 64): the first loop of Alg. 1 and Eq. 1 of
-// the paper applied to the prompt's own causal attention, so that prompt entries enter the
+// Recurrence tracking over the prompt: the first loop of Alg. 1 and Eq. 1 of the
+// paper applied to the prompt's own causal attention, so that prompt entries enter the
 // decode phase with a TS / MRI history instead of TS = 0, MRI = 0.  Prompt position i (0-based,
 // P positions) acts as the query of step tau_i = i + 1 - P over the keys 0..i; entry i is born
 // with TS = tau_i, MRI = 0; decoding continues at step 1.
 //
-// Two kernels, both built on S^T = K Q^T tiles of v_mfma_f32_16x16x32_bf16 (16 keys x 16
-// queries of ONE head); MFMA layouts
-//   A[row c][k = 8g..8g+7]  B[k = 8g..8g+7][col c]  C[row 4g+i][col c]     (lane l, c = l % 16, g = l / 16):
-//   stats  the four waves of a block keep 64 queries each of one head in registers (four B
-//          operands per wave, loaded straight into the layout) and walk the key tiles 0..their
-//          own together, keeping the running softmax maximum and sum of every query; leaves
-//          b = -(log-sum-exp of the query's scaled logits) / scale per (unit, head, position)
-//          in the workspace
-//   track  the four waves of a block keep 64 keys each in registers (four A operands) and walk
+// Two kernels, both built on S^T = K Q^T tiles of 16 keys x 16 queries of ONE head
+// (v_mfma_f32_16x16x32_bf16, or v_mfma_f32_16x16x4_f32 for fp32 rows); MFMA layouts (lane l, c = l % 16, g = l / 16)
+//   16x16x32: A[row c][k = 8g..8g+7]  B[k = 8g..8g+7][col c]  C[row 4g+i][col c]
+//   16x16x4:  A[row c][k = g]         B[k = g][col c]         C[row 4g+i][col c]
+//   stats  the four waves of a block keep NB tiles of 16 queries each of one head in registers and walk the
+//          key tiles 0..their own together, keeping every query's softmax sum relative to a
+//          reference that is raised only when a weight would leave the range of fp32; leaves the
+//          log-sum-exp of every (unit, head, position) in the workspace
+//   track  the four waves of a block keep NB tiles of 16 keys each in registers and walk
 //          the (query tile, head) pairs from the block's own position upwards together.  The
-//          weight of key j for query i in head h is p = exp(scale (q.k + b)), so the product is
-//          started from b instead of 0 (accumulator input of the first MFMA) and the largest
-//          q.k + b over the heads of the group decides (exp and the scaling are monotone): one
-//          maximum per weight and head, one exponential and one compare with alpha per weight
+//          largest logarithm of the key's weight over the heads of the group decides (exp is monotone): one
+//          maximum per logit and head, one exponential and one compare with alpha per weight
 //          after the group's last head.  The activations of each key are then applied in order
 //          of the query position (one key per lane).
-// The streamed tile (keys in the first kernel, queries in the second) is fetched once per block
-// and shared through LDS, one barrier per tile: fetched per wave, the second kernel read 7 GB
-// per call past the L2 for a 2048-token prompt of the benchmark's third workload.  Four
-// products per streamed tile and wave (one: the matrix cores wait for operands; eight: the
-// registers allow only two waves per SIMD).  Blocks start in index order, so the heaviest tiles
-// get the lowest indices.  No wave waits for another block.
+// The streamed tiles (keys in the first kernel, queries in the second) are fetched once per block,
+// a stage of 4 KB (8 KB for fp32 rows of 128) at a time, and shared through LDS, one barrier per stage: fetched
+// per wave, the second kernel read 7 GB per call past the L2 for 128 units x 2048 positions.  Four
+// products per streamed tile and wave where that fills the chip (two: 1312 instead of 1190 us there, the operand
+// reads from LDS are twice as many); short prompts and few units take one
+// tile per wave.  The second kernel also cuts the queries into segments whose
+// results (first and last activation, largest gap between) a third kernel joins, where its blocks are few.
+// Blocks start in index order, so the heaviest tiles get the lowest indices.  No wave waits for another block.
+//
+// What bounds it: the vector work beside the products (a multiply-add, an exponential and an addition per weight
+// in the first kernel, a maximum in the second; the matrix cores are busy 35% of the time).  Measured, us for both
+// kernels, before (a running maximum with two exponentials per weight, an exponential and a comparison per
+// weight in the second kernel, rows of 64 and fp32 rows on a kernel without matrix instructions) and now:
+//   32 sequences, 28 / 4 heads of 128, bf16   600 positions 292 -> 170, 2048 positions 1370 -> 1190
+//   16 sequences, 40 / 8 heads of 128, bf16  4096 positions 3520 -> 2900
+//    8 sequences, 28 / 4 heads of 128, bf16  1024 positions 350 -> 112
+//    1 sequence,  28 / 4 heads of 128, bf16    33 positions 22.9 -> 13.5,  400 positions 141 -> 24
+//    4 sequences, 32 / 8 heads of  64, bf16   499 positions 5470 -> 32
+//    2 sequences, 28 / 4 heads of 128, fp32   300 positions 10880 -> 50
 #include "kernels.h"
+
+#include <cfloat>
+#include <climits>
+#include <type_traits>
 
 namespace lazyev {
 namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-constexpr int D = 128;
-constexpr int KC = D / 32;
 constexpr int kHeadMax = 8;
-
+// stages on their way from memory (one: 1250 instead of 1190 us for 128 units x 2048 positions; four: 1190)
+constexpr int kAhead = 2;
 typedef unsigned short bf16_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
 
-// 16 rows x 128 columns of bf16 at `rows` (row stride `stride` elements), rows clamped to
-// `last`, as an MFMA A or B operand: lane (c, g) takes row c, columns 32 kk + 8 g .. + 7.
-__device__ __forceinline__ void load_operand(u32x4_t (&x)[KC], const bf16_t *rows, int first, int last,
-                                             size_t stride, int c, int g) {
-  const int r = min(first + c, last);
-  const bf16_t *p = rows + static_cast<size_t>(r) * stride + g * 8;
-#pragma unroll
-  for (int kk = 0; kk < KC; ++kk) x[kk] = *reinterpret_cast<const u32x4_t *>(p + kk * 32);
-}
-
-__device__ __forceinline__ f32x4_t logits_tile(const u32x4_t (&ka)[KC], const u32x4_t (&qb)[KC],
-                                               f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f}) {
-#pragma unroll
-  for (int kk = 0; kk < KC; ++kk)
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[kk]),
-                                                  __builtin_bit_cast(bf16x8_t, qb[kk]), acc, 0, 0, 0);
-  return acc;
-}
-
-// The streamed tile (16 rows x 256 bytes) is fetched ONCE per block: thread t brings the 16-byte
-// chunk t % 16 of row t / 16 (whole 256-byte rows per 16 lanes), the block keeps it in LDS, and
-// every wave reads its MFMA operand from there.  Chunk x of row r sits at slot x ^ r of the row,
-// so that the row-wise writes and the column-wise operand reads both touch every bank once.
-struct SharedTile {
-  u32x4_t slot[2][16 * 16];                        // double-buffered
+template <typename T, int D>
+struct Rows {
+  static constexpr bool kF32 = sizeof(T) == 4;
+  static constexpr int kChunks = D * static_cast<int>(sizeof(T)) / 16;   // 16-byte chunks of a row
+  static constexpr int kK = kChunks / 4;           // operand registers of 16 bytes per lane and tile
+  static constexpr int kStage = kChunks == 8 ? 2 : 1;   // tiles per stage (4 KB; 8 KB for fp32 rows of 128)
+  static constexpr int kSlots = kStage * 16 * kChunks;                   // 16-byte chunks of a stage
+  static constexpr int kFetch = kSlots / kBlock;   // of them per thread
+  // The weight of a key: exp2((q.k) c2 - m - log2 l) with m and log2 l kept apart, so that nothing is
+  // rounded at the magnitude of the log-sum-exp; 128-element bf16 rows fold both into one number that
+  // the product starts from, b = -(m + log2 l) / c2 (c2 = scale log2 e).
+  static constexpr bool kApart = !(sizeof(T) == 2 && D == 128);
+  static constexpr int kTiles = kK == 8 ? 2 : 4;   // tiles a wave keeps in registers where there is work for all
+  static constexpr int waves(int nb) { return nb == 1 ? 4 : kF32 ? 2 : 3; }   // waves per SIMD the registers are held to
 };
 
-__device__ __forceinline__ u32x4_t tile_fetch(const bf16_t *rows, int first, int last, size_t stride) {
-  const int r = min(first + (static_cast<int>(threadIdx.x) >> 4), last);
-  return *reinterpret_cast<const u32x4_t *>(rows + static_cast<size_t>(r) * stride + (threadIdx.x & 15) * 8);
-}
-
-__device__ __forceinline__ void tile_put(SharedTile &t, int buf, u32x4_t v) {
-  const int r = static_cast<int>(threadIdx.x) >> 4, x = threadIdx.x & 15;
-  t.slot[buf][r * 16 + (x ^ r)] = v;
-}
-
-__device__ __forceinline__ void tile_operand(const SharedTile &t, int buf, u32x4_t (&x)[KC], int c, int g) {
+// 16 rows at `rows` (row stride `stride` elements), rows clamped to `last`, as an MFMA A or B
+// operand: lane (c, g) takes the 16-byte chunks 4 kk + g of row c.
+template <typename T, int D>
+__device__ __forceinline__ void load_operand(const T *rows, int first, int last, size_t stride, int c, int g,
+                                             u32x4_t (&x)[Rows<T, D>::kK]) {
+  const int r = min(first + c, last);
+  const T *p = rows + static_cast<size_t>(r) * stride + g * (16 / sizeof(T));
 #pragma unroll
-  for (int kk = 0; kk < KC; ++kk) x[kk] = t.slot[buf][c * 16 + ((4 * kk + g) ^ c)];
+  for (int kk = 0; kk < Rows<T, D>::kK; ++kk) x[kk] = *reinterpret_cast<const u32x4_t *>(p + kk * (64 / sizeof(T)));
 }
 
-constexpr int NB = 4;                              // tiles a wave keeps in registers
-constexpr int kSpan = 16 * NB;                     // queries (stats) or keys (track) per wave
+// acc[n] += a tile x tile n for N tiles of which either the keys (kKeys) or the queries are the N and the
+// other operand is one tile.  The N chains of dependent products go side by side.  (fp32 rows: four
+// products per operand register; which columns of the row go together does not matter as long as both
+// operands agree; two chains each, added at the end.)
+template <typename T, int D, int N, bool kKeys>
+__device__ __forceinline__ void logits_tiles(const u32x4_t (&many)[N][Rows<T, D>::kK], const u32x4_t (&one)[Rows<T, D>::kK],
+                                             f32x4_t (&acc)[N]) {
+  if constexpr (Rows<T, D>::kF32) {
+    f32x4_t odd[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) odd[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < Rows<T, D>::kK; ++kk)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+          const float x = __uint_as_float(kKeys ? many[n][kk][e] : one[kk][e]), y = __uint_as_float(kKeys ? one[kk][e] : many[n][kk][e]);
+          f32x4_t &to = e % 2 ? odd[n] : acc[n];
+          to = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, to, 0, 0, 0);
+        }
+#pragma unroll
+    for (int n = 0; n < N; ++n) acc[n] += odd[n];
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < Rows<T, D>::kK; ++kk)
+#pragma unroll
+      for (int n = 0; n < N; ++n)
+        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kKeys ? many[n][kk] : one[kk]),
+                                                         __builtin_bit_cast(bf16x8_t, kKeys ? one[kk] : many[n][kk]), acc[n], 0, 0, 0);
+  }
+}
+
+// The streamed rows of a stage: thread t brings the 16-byte chunks t, t + 256, ... in row order (whole
+// rows), the block keeps them in LDS, and every wave reads its MFMA operands from there.  Chunk x
+// of row r sits at slot x ^ r of the row, so that the row-wise writes and the column-wise operand
+// reads both spread over the banks.
+template <typename T, int D>
+struct SharedTile {
+  u32x4_t slot[2][Rows<T, D>::kSlots];             // double-buffered
+};
+template <typename T, int D>
+__device__ __forceinline__ void stage_put(SharedTile<T, D> &t, int buf, const u32x4_t (&v)[Rows<T, D>::kFetch]) {
+  constexpr int C = Rows<T, D>::kChunks;
+#pragma unroll
+  for (int u = 0; u < Rows<T, D>::kFetch; ++u) {
+    const int at = static_cast<int>(threadIdx.x) + u * kBlock, r = at / C, x = at % C;
+    t.slot[buf][r * C + (x ^ (r % C))] = v[u];
+  }
+}
+template <typename T, int D>
+__device__ __forceinline__ void tile_operand(const SharedTile<T, D> &t, int buf, int j, u32x4_t (&x)[Rows<T, D>::kK], int c, int g) {
+  constexpr int C = Rows<T, D>::kChunks;
+#pragma unroll
+  for (int kk = 0; kk < Rows<T, D>::kK; ++kk) x[kk] = t.slot[buf][(16 * j + c) * C + ((4 * kk + g) ^ ((16 * j + c) % C))];
+}
+
+// The operands a wave keeps have arrived before the loop starts.  The waits in the loop are then for its own
+// stages alone, in the order of their requests: a load from before the loop, or a path through it that
+// leaves stages out, would have every wait in it count to (nearly) zero, i.e. each stage wait for its
+// own request.
+template <int N, int K>
+__device__ __forceinline__ void settle(u32x4_t (&x)[N][K]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int k = 0; k < K; ++k) __asm__ volatile("" : "+v"(x[n][k]));
+}
 
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kFar = 0x1p64f;                    // a sum of four weights beyond this raises the reference
 
-// max(a, b) of two numbers as ONE instruction (the median of a, b and +inf); fmaxf spends two
-// more on making signalling NaNs quiet, and there are no NaNs here.
-__device__ __forceinline__ float max_f32(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, INFINITY); }
+// (this file is compiled with -fno-honor-nans, so that a maximum is one instruction and not three that
+// first make signalling NaNs quiet)
+__device__ __forceinline__ float max_f32(float a, float b) { return __builtin_fmaxf(a, b); }
 
-// One key tile against one query tile in the statistics kernel.  Logits are kept in units of
-// log 2 (scaled by scale * log2(e)), so an exponential is one v_exp_f32.  Every lane keeps the
-// running maximum and sum of ITS four key rows of every tile (the four lanes of a query column
-// are merged once, at the end): no cross-lane traffic inside the loop.  kMask: the tile may
-// hold keys newer than a query or positions beyond the prompt.
-template <bool kMask>
-__device__ __forceinline__ void stats_tile(const u32x4_t (&ka)[KC], const u32x4_t (&qb)[KC], float c2, int key0,
-                                           int query, int P, float &m, float &l) {
-  const f32x4_t acc = logits_tile(ka, qb);
-  float s[4];
+// One key tile against the wave's NB query tiles in the statistics kernel.  Logits are kept in units of
+// log 2 (scaled by c2 = scale * log2(e)), so a weight is one multiply-add and one v_exp_f32.  Every lane sums
+// ITS four key rows of every tile (the four lanes of a query column are merged once, at the end): no
+// cross-lane traffic inside the loop.  The reference m of a query need not be its maximum: a
+// floating-point sum is as exact relative to any reference within the range of the exponent, so there is no
+// running maximum, only a look whether the weights leave the range (first: there is no reference
+// yet).  kMask: the tile may hold keys newer than a query or positions beyond the prompt.
+template <typename T, int D, int NB, bool kMask, bool kFirst>
+__device__ __forceinline__ void stats_tiles(const u32x4_t (&ka)[Rows<T, D>::kK], const u32x4_t (&qb)[NB][Rows<T, D>::kK],
+                                            float c2, int key0, int query0, int P, float (&m)[NB], float (&l)[NB]) {
+  f32x4_t acc[NB];
+  float ps[NB], far = 0.f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    s[i] = acc[i] * c2;
-    if (kMask) s[i] = (key0 + i <= query && key0 + i < P) ? s[i] : -INFINITY;
+  for (int n = 0; n < NB; ++n) acc[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  logits_tiles<T, D, NB, false>(qb, ka, acc);
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    if (kMask) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc[n][i] = (key0 + i <= query0 + 16 * n && key0 + i < P) ? acc[n][i] : -INFINITY;
+    }
+    if (kFirst) {                                  // (key 0 is visible to every query, but to one of the column's four lanes only)
+      float top = max_f32(max_f32(acc[n][0], acc[n][1]), max_f32(acc[n][2], acc[n][3])) * c2;
+      top = max_f32(top, __shfl_xor(top, 16));
+      m[n] = max_f32(top, __shfl_xor(top, 32));
+    }
+    auto weight = [&](int i) { return __builtin_amdgcn_exp2f(fmaf(acc[n][i], c2, -m[n])); };
+    ps[n] = (weight(0) + weight(1)) + (weight(2) + weight(3));
+    far = n == 0 ? ps[n] : max_f32(far, ps[n]);
   }
-  const float m_new = max_f32(max_f32(max_f32(s[0], s[1]), max_f32(s[2], s[3])), m);
-  if (kMask && m_new == -INFINITY) return;         // this lane has seen no key of the query yet
-  const float ps = (__builtin_amdgcn_exp2f(s[0] - m_new) + __builtin_amdgcn_exp2f(s[1] - m_new)) +
-                   (__builtin_amdgcn_exp2f(s[2] - m_new) + __builtin_amdgcn_exp2f(s[3] - m_new));
-  l = l * __builtin_amdgcn_exp2f(m - m_new) + ps;  // first tile: l = 0 * 2^(-inf) + ps
-  m = m_new;
+  if (!kFirst && __builtin_expect(__builtin_amdgcn_ballot_w64(far > kFar) != 0, 0)) {   // (wave-uniform)
+    __asm__ volatile("");                          // (stays a branch: not worked out beforehand)
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const float top = max_f32(max_f32(acc[n][0], acc[n][1]), max_f32(acc[n][2], acc[n][3])) * c2;
+      const float up = max_f32(m[n], top);
+      l[n] *= __builtin_amdgcn_exp2f(m[n] - up);
+      m[n] = up;
+      auto weight = [&](int i) { return __builtin_amdgcn_exp2f(fmaf(acc[n][i], c2, -m[n])); };
+      ps[n] = (weight(0) + weight(1)) + (weight(2) + weight(3));
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < NB; ++n) l[n] += ps[n];
 }
 
 // Softmax statistics of every (head, prompt position) of a unit:
-// blocks = units * G * ceil(P / (4 * kSpan)); the four waves of a block hold consecutive query
+// blocks = units * G * ceil(P / (64 NB)); the four waves of a block hold consecutive query
 // spans of one head and walk the key tiles together.
-__global__ __launch_bounds__(kBlock) void prefill_stats_kernel(const PrefillArgs a) {
-  __shared__ SharedTile tile;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <typename T, int D, int NB>
+__global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats_kernel(const PrefillArgs a) {
+  using R = Rows<T, D>;
+  constexpr int kSpan = 16 * NB;
+  __shared__ SharedTile<T, D> tile;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int P = a.prompt_len, G = a.group;
   const int n_qt = (P + kWaves * kSpan - 1) / (kWaves * kSpan);
   // Blocks start in index order and late query tiles carry more work than early ones: the
   // heaviest tiles get the lowest block indices (they start first, the light ones fill the
   // end), and consecutive blocks, which go to different XCDs, hold the same tile position of
-  // different (unit, head) pairs, so every XCD gets every tile position equally often.
-  const int n_uh = static_cast<int>(gridDim.x) / n_qt;            // units * G
+  // different (unit, head) pairs, so every XCD gets every tile position equally often.  (All blocks of a unit on
+  // one XCD, for its L2: 580 instead of 566 us for 128 units x 2048 positions.)
+  const int n_uh = a.batch * a.n_kv_heads * G;
   const int qt = n_qt - 1 - static_cast<int>(blockIdx.x) / n_uh;
-  const int b = static_cast<int>(blockIdx.x) % n_uh;
-  const int h = b % G;
-  const int unit = b / G;
+  const int uh = static_cast<int>(blockIdx.x) % n_uh;
+  const int unit = uh / G, h = uh % G;
   const int i0 = (qt * kWaves + wave) * kSpan;     // this wave's queries: i0 .. i0 + kSpan - 1
   const bool have = i0 < P;                        // (a wave without queries still fetches and waits with the block)
   const int seq = unit / a.n_kv_heads, kvh = unit % a.n_kv_heads;
-  const bf16_t *q = static_cast<const bf16_t *>(a.q_prompt) +
-                    (static_cast<size_t>(seq) * P * a.n_q_heads + kvh * G + h) * D;
-  const bf16_t *kc = static_cast<const bf16_t *>(a.k_cache) + static_cast<size_t>(unit) * a.capacity * D;
+  const T *q = static_cast<const T *>(a.q_prompt) + (static_cast<size_t>(seq) * P * a.n_q_heads + kvh * G + h) * D;
+  const T *kc = static_cast<const T *>(a.k_cache) + static_cast<size_t>(unit) * a.capacity * D;
   const float c2 = a.scale * kLog2e;
-  u32x4_t qb[NB][KC];
+  u32x4_t qb[NB][R::kK];
 #pragma unroll
   for (int n = 0; n < NB; ++n)
-    load_operand(qb[n], q, i0 + 16 * n, P - 1, static_cast<size_t>(a.n_q_heads) * D, c, g);
+    load_operand<T, D>(q, i0 + 16 * n, P - 1, static_cast<size_t>(a.n_q_heads) * D, c, g, qb[n]);
 
   float m[NB], l[NB];                              // of query i0 + 16 n + c, over this lane's key rows
 #pragma unroll
-  for (int n = 0; n < NB; ++n) { m[n] = -INFINITY; l[n] = 0.f; }
+  for (int n = 0; n < NB; ++n) { m[n] = 0.f; l[n] = 0.f; }
   const int my_last = have ? min(i0 + kSpan - 1, P - 1) >> 4 : -1;
   const int block_last = min(qt * kWaves * kSpan + kWaves * kSpan - 1, P - 1) >> 4;
-  tile_put(tile, 0, tile_fetch(kc, 0, P - 1, D));
+  const int n_stages = block_last / R::kStage + 1;
+  // the rows of a stage follow one another in the cache: thread t's chunks lie 16 t (+ 4096 u) bytes in
+  auto fetch = [&](int st, u32x4_t (&v)[R::kFetch]) {
+    const int left = P - 1 - st * (16 * R::kStage);  // last row of the stage that exists
+    const T *base = kc + static_cast<size_t>(st) * (16 * R::kStage) * D;
+#pragma unroll
+    for (int u = 0; u < R::kFetch; ++u) {
+      const int at = static_cast<int>(threadIdx.x) + u * kBlock;
+      const unsigned off = static_cast<unsigned>(min(at / R::kChunks, left)) * R::kChunks + at % R::kChunks;
+      v[u] = reinterpret_cast<const u32x4_t *>(base)[off];
+    }
+  };
+  u32x4_t next[kAhead][R::kFetch];                 // stage s in next[s % kAhead]
+  fetch(0, next[0]);
+  stage_put<T, D>(tile, 0, next[0]);
+#pragma unroll
+  for (int x = 1; x <= kAhead; ++x) {
+    fetch(min(x, n_stages - 1), next[x % kAhead]);
+    __builtin_amdgcn_sched_barrier(0);             // (in this order: the waits in the loop count on it)
+  }
   __syncthreads();
-  for (int jt = 0; jt <= block_last; ++jt) {
-    // the next key tile travels during the arithmetic
-    const u32x4_t next = tile_fetch(kc, min(jt + 1, block_last) * 16, P - 1, D);
-    if (jt <= my_last) {
-      u32x4_t ka[KC];
-      tile_operand(tile, jt & 1, ka, c, g);
-      // all four products, no branches inside; only the wave's last four key tiles can hold
-      // keys newer than a query (or positions beyond the prompt)
-      if (jt * 16 + 15 <= i0 && jt * 16 + 15 < P) {
+  auto stage = [&](int st, auto tag) {             // (st % kAhead is known to the code)
+    constexpr int buf = decltype(tag)::value % 2, reg = (decltype(tag)::value + 1) % kAhead;
 #pragma unroll
-        for (int n = 0; n < NB; ++n) stats_tile<false>(ka, qb[n], c2, jt * 16 + 4 * g, i0 + 16 * n + c, P, m[n], l[n]);
-      } else {
-#pragma unroll
-        for (int n = 0; n < NB; ++n) stats_tile<true>(ka, qb[n], c2, jt * 16 + 4 * g, i0 + 16 * n + c, P, m[n], l[n]);
+    for (int j = 0; j < R::kStage; ++j) {
+      const int jt = st * R::kStage + j;
+      if (jt <= my_last) {                         // (wave-uniform)
+        u32x4_t ka[R::kK];
+        tile_operand<T, D>(tile, buf, j, ka, c, g);
+        // only the wave's last NB key tiles can hold keys newer than a query (or positions beyond the prompt)
+        if (decltype(tag)::value == 0 && j == 0 && jt == 0)
+          stats_tiles<T, D, NB, true, true>(ka, qb, c2, 4 * g, i0 + c, P, m, l);
+        else if (jt * 16 + 15 <= i0 && jt * 16 + 15 < P)
+          stats_tiles<T, D, NB, false, false>(ka, qb, c2, jt * 16 + 4 * g, i0 + c, P, m, l);
+        else
+          stats_tiles<T, D, NB, true, false>(ka, qb, c2, jt * 16 + 4 * g, i0 + c, P, m, l);
       }
     }
-    tile_put(tile, (jt + 1) & 1, next);
-    __syncthreads();                               // tile jt + 1 is complete, tile jt no longer read
+    stage_put<T, D>(tile, buf ^ 1, next[reg]);
+    fetch(min(st + 1 + kAhead, n_stages - 1), next[reg]);
+    __syncthreads();                               // stage st + 1 is complete, stage st no longer read
+  };
+  settle(qb);
+  for (int st = 0;; st += kAhead) {                // (left from its middle: see settle)
+    stage(st, std::integral_constant<int, 0>{});
+    if (st + 1 >= n_stages) break;
+    stage(st + 1, std::integral_constant<int, 1>{});
+    if (st + 2 >= n_stages) break;
   }
   if (!have) return;
-  // the four lanes of a query column (g = 0..3) -> the column's maximum and sum; a lane that
-  // saw no key of the query (possible in the first tiles of a wave) holds (-inf, 0)
+  // the four lanes of a query column (g = 0..3) -> the column's reference and sum
 #pragma unroll
   for (int n = 0; n < NB; ++n) {
 #pragma unroll
     for (int o = 16; o <= 32; o <<= 1) {
       const float mo = __shfl_xor(m[n], o), lo = __shfl_xor(l[n], o);
       const float mx = fmaxf(m[n], mo);
-      const float fa = m[n] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[n] - mx);
-      const float fb = mo == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mo - mx);
-      l[n] = l[n] * fa + lo * fb;
+      l[n] = l[n] * __builtin_amdgcn_exp2f(m[n] - mx) + lo * __builtin_amdgcn_exp2f(mo - mx);
       m[n] = mx;
     }
   }
-  if (g == 0) {                                    // b = -(m + log2 l) / (scale log2 e): see the tracking kernel
+  if (g == 0) {
     float *st = a.stat + (static_cast<size_t>(unit) * G + h) * a.p16;
 #pragma unroll
-    for (int n = 0; n < NB; ++n)
-      if (i0 + 16 * n + c < P) st[i0 + 16 * n + c] = -(m[n] + __builtin_amdgcn_logf(l[n])) / c2;
+    for (int n = 0; n < NB; ++n) {
+      const int i = i0 + 16 * n + c;
+      if (i >= P) continue;
+      if constexpr (R::kApart) {
+        // the reference moved next to the log-sum-exp (the difference of the two references is exact)
+        const float near = m[n] + floorf(__builtin_amdgcn_logf(l[n]));
+        st[i] = near;
+        a.stat2[(static_cast<size_t>(unit) * G + h) * a.p16 + i] =
+            __builtin_amdgcn_logf(l[n] * __builtin_amdgcn_exp2f(m[n] - near));
+      } else {                                     // b: see Rows
+        st[i] = -(m[n] + __builtin_amdgcn_logf(l[n])) / c2;
+      }
+    }
   }
 }
 
-// Tracking: blocks = units * ceil(P / (4 * kSpan)); a wave owns the keys j0 .. j0 + kSpan - 1.
-// kIO: the weights are exported and / or replaced (a checker's route).
-template <bool kIO>
-__global__ __launch_bounds__(kBlock) void prefill_track_kernel(const PrefillArgs a) {
-  __shared__ SharedTile tile;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Transposes the 16 x 16 bits of 16 lanes: bit x of lane c (of each group of 16) -> bit c of lane x.  The 16 bits
+// are kept twice in the register, so that a rotation by s serves the lower and (by 32 - s) the upper half;
+// lane ^ 1, 2, 4 (= 7 ^ 3) and 8 are data-parallel moves within the vector ALU.
+__device__ __forceinline__ unsigned transpose16(unsigned bits, int c) {
+  unsigned m = bits | (bits << 16);
+  auto step = [&](unsigned other, int s, unsigned keep) {
+    const bool up = c & s;
+    const unsigned turned = __builtin_amdgcn_alignbit(other, other, up ? s : 32 - s);   // rotated right
+    const unsigned k = up ? ~keep : keep;
+    m = (m & k) | (turned & ~k);
+  };
+  auto move = [](unsigned x, auto ctrl) { return static_cast<unsigned>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), decltype(ctrl)::value, 0xF, 0xF, true)); };
+  step(move(m, std::integral_constant<int, 0x128>{}), 8, 0x00FF00FFu);       // row_ror:8
+  step(move(move(m, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{}), 4, 0x0F0F0F0Fu);   // row_half_mirror, quad_perm 3 2 1 0
+  step(move(m, std::integral_constant<int, 0x4E>{}), 2, 0x33333333u);        // quad_perm 2 3 0 1
+  step(move(m, std::integral_constant<int, 0xB1>{}), 1, 0x55555555u);        // quad_perm 1 0 3 2
+  return m & 0xFFFFu;
+}
+
+// Length of the longest run of ones among the lowest 16 bits of z (at most 15): x2, x4, x8 mark where 2, 4, 8 ones in a row start.
+__device__ __forceinline__ int longest_run(unsigned z) {
+  const unsigned x2 = z & (z >> 1), x4 = x2 & (x2 >> 2), x8 = x4 & (x4 >> 4);
+  int r = x8 ? 8 : 0;
+  unsigned at = x8 ? x8 : ~0u;                     // starts of runs of at least r ones
+  unsigned t = at & (x4 >> r);
+  if (t) { r += 4; at = t; }
+  t = at & (x2 >> r);
+  if (t) { r += 2; at = t; }
+  return (at & (z >> r)) ? r + 1 : r;
+}
+
+// Tracking: blocks = units * ceil(P / (64 NB)) * segments; a wave owns the keys j0 .. j0 + 16 NB - 1.
+// kIO: the weights are exported and / or replaced (a checker's route).  kSeg: the block walks its segment of
+// the queries only and leaves, of every key, its first (INT_MAX: none) and last activation there, the largest gap
+// between two of them and their number, instead of TS / MRI.
+template <typename T, int D, int NB, bool kIO, bool kSeg>
+__global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track_kernel(const PrefillArgs a) {
+  using R = Rows<T, D>;
+  constexpr int kSpan = 16 * NB;
+  __shared__ SharedTile<T, D> tile;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int P = a.prompt_len, G = a.group;
   const int n_kt = (P + kWaves * kSpan - 1) / (kWaves * kSpan);
   // early keys carry more work: heaviest first, as in the first kernel
-  const int n_units = static_cast<int>(gridDim.x) / n_kt;
-  const int kt = static_cast<int>(blockIdx.x) / n_units, unit = static_cast<int>(blockIdx.x) % n_units;
+  const int units = a.batch * a.n_kv_heads;
+  const int unit = static_cast<int>(blockIdx.x) % units, kz = static_cast<int>(blockIdx.x) / units;
+  const int kt = kSeg ? kz / a.segments : kz, z = kSeg ? kz % a.segments : 0;
   const int j0 = (kt * kWaves + wave) * kSpan;
   const bool have = j0 < P;                        // (a wave without keys still fetches and waits with the block)
   const int seq = unit / a.n_kv_heads, kvh = unit % a.n_kv_heads;
-  const bf16_t *q = static_cast<const bf16_t *>(a.q_prompt) +
-                    (static_cast<size_t>(seq) * P * a.n_q_heads + kvh * G) * D;
-  const bf16_t *kc = static_cast<const bf16_t *>(a.k_cache) + static_cast<size_t>(unit) * a.capacity * D;
+  const T *q = static_cast<const T *>(a.q_prompt) + (static_cast<size_t>(seq) * P * a.n_q_heads + kvh * G) * D;
+  const T *kc = static_cast<const T *>(a.k_cache) + static_cast<size_t>(unit) * a.capacity * D;
   const float *stat = a.stat + static_cast<size_t>(unit) * G * a.p16;
+  const float *stat2 = R::kApart ? a.stat2 + static_cast<size_t>(unit) * G * a.p16 : nullptr;
   const float c2 = a.scale * kLog2e;
-  u32x4_t ka[NB][KC];
+  u32x4_t ka[NB][R::kK];
 #pragma unroll
-  for (int n = 0; n < NB; ++n) load_operand(ka[n], kc, j0 + 16 * n, P - 1, D, c, g);
+  for (int n = 0; n < NB; ++n) load_operand<T, D>(kc, j0 + 16 * n, P - 1, D, c, g, ka[n]);
 
-  // lane (c, g) carries the state of key row 4 g + (c & 3) of key tile c >> 2
+  // lane (c, g), c < 4 NB, carries the state of key row 4 g + (c & 3) of key tile c >> 2
   const int my_key = j0 + 16 * (c >> 2) + 4 * g + (c & 3);
-  int32_t ts = my_key + 1 - P, mri = 0;
+  int32_t ts = kSeg ? INT_MIN : my_key + 1 - P, mri = 0, first = INT_MAX;
   unsigned n_act = 0;
-  // (query tile, head) pairs in order, the same for the four waves of the block (a wave skips
-  // the query tiles before its own keys); the query tile of a pair is fetched once per block,
-  // the next pair's travels during the arithmetic of the current one
-  const size_t q_stride = static_cast<size_t>(a.n_q_heads) * D;
-  int it = (kt * kWaves * kSpan) >> 4, h = 0;      // the block's oldest key tile
+  // this block's query tiles, and in them the (query tile, head) pairs in order, the same for the four waves of the
+  // block (a wave skips the query tiles before its own keys); the query tiles of a stage are fetched
+  // once per block, the next stage's travel during the arithmetic of the current one
+  const int n_it = (P + 15) >> 4, it_first = (kt * kWaves * kSpan) >> 4;      // (the block's oldest key tile)
+  const int it_begin = kSeg ? max(it_first, z * a.seg_tiles) : it_first;
+  const int it_end = kSeg ? min(n_it, (z + 1) * a.seg_tiles) : n_it;
+  if (kSeg && it_begin >= it_end) return;          // (no query of the segment sees these keys; nobody reads a record of it)
   const int my_first = j0 >> 4;
-  tile_put(tile, 0, tile_fetch(q, it * 16, P - 1, q_stride));
-  float bq = stat[min(it * 16 + c, P - 1)];
-  __syncthreads();
-  int buf = 0;
-  // amax[4 n + i]: largest q.k + b over the heads seen so far of the current query tile, for key
+  const int plain_first = (j0 + kSpan - 1 + 15) >> 4, plain_end = j0 + kSpan - 1 < P ? P >> 4 : 0;
+  const size_t q_stride = static_cast<size_t>(a.n_q_heads) * D;
+  // A place in the sequence of pairs: 16 queries from it * 16 on of head h, the first of their rows, and where
+  // their statistics lie.  It stays on the block's last pair.
+  struct Place { int it, h; const T *rows; int stat_at; };
+  const int stat_wrap = 16 - (G - 1) * a.p16;
+  const ptrdiff_t rows_wrap = static_cast<ptrdiff_t>(16 * q_stride) - (G - 1) * D;
+  auto next_pair = [&](Place &x) {
+    const bool wrap = x.h + 1 == G, last = wrap && x.it + 1 >= it_end;
+    x.rows += last ? 0 : wrap ? rows_wrap : D;
+    x.stat_at += last ? 0 : wrap ? stat_wrap : a.p16;
+    x.it = wrap && !last ? x.it + 1 : x.it;
+    x.h = last ? x.h : wrap ? 0 : x.h + 1;
+  };
+  // this thread's chunks of a tile's rows as byte offsets (16 rows of all heads are under 4 GB): rows beyond the
+  // prompt, in its last tile, are replaced by the last one
+  const int t_row = static_cast<int>(threadIdx.x) & (R::kStage == 2 ? kBlock / 2 - 1 : kBlock - 1);
+  unsigned row_off[R::kFetch], row_off_end[R::kFetch];
+#pragma unroll
+  for (int u = 0; u < R::kFetch; ++u) {
+    const int at = t_row + u * kBlock, r = at / R::kChunks;
+    row_off[u] = static_cast<unsigned>(r * q_stride * sizeof(T)) + at % R::kChunks * 16;
+    row_off_end[u] = static_cast<unsigned>(min(r, (P - 1) & 15) * q_stride * sizeof(T)) + at % R::kChunks * 16;
+  }
+  // rows of the stage whose first pair is at x
+  auto fetch_rows = [&](Place x, u32x4_t (&v)[R::kFetch]) {
+    if (R::kStage == 2) {                          // (two tiles per load: waves 2 and 3 bring the second)
+      Place y = x;
+      next_pair(y);
+      x.it = wave >= kWaves / 2 ? y.it : x.it;
+      x.rows = wave >= kWaves / 2 ? y.rows : x.rows;
+    }
+    const bool end = x.it == n_it - 1;
+#pragma unroll
+    for (int u = 0; u < R::kFetch; ++u)
+      v[u] = *reinterpret_cast<const u32x4_t *>(reinterpret_cast<const char *>(x.rows) + (end ? row_off_end[u] : row_off[u]));
+  };
+  // ... and the statistics of this lane's queries in it (p16 covers the last tile)
+  struct Stats { float b[R::kStage], ll[R::kStage]; };
+  auto fetch_stats = [&](Place x, Stats &s) {
+#pragma unroll
+    for (int j = 0; j < R::kStage; ++j) {
+      s.b[j] = stat[x.stat_at + c];
+      s.ll[j] = R::kApart ? stat2[x.stat_at + c] : 0.f;
+      next_pair(x);
+    }
+  };
+  auto advance = [&](int &it, int &h) {
+    if (++h == G) { h = 0; ++it; }
+  };
+  auto weight = [&](float lw) { return __builtin_amdgcn_exp2f(R::kApart ? lw : lw * c2); };
+  // The logarithms from which on the weight is >= alpha, so that the test is one comparison and no exponential:
+  // the first float x with weight(x) >= alpha, found by stepping from the logarithm of alpha (which is
+  // off by a few floats at most; alphas below the normal range count as the smallest normal number, like
+  // the weights there).
+  // alpha = 0: every key that is no newer (amax is -inf where none was seen).
+  float reach = -FLT_MAX;
+  if (a.alpha > 0.f) {
+    const float alpha = max_f32(a.alpha, 0x1p-126f);
+    auto step = [](float x, int up) {              // the next float above (up = 1) or below (-1)
+      const int i = __float_as_int(x);
+      return x == 0.f ? __int_as_float(up > 0 ? 1 : static_cast<int>(0x80000001u)) : __int_as_float(i + ((i >= 0) == (up > 0) ? 1 : -1));
+    };
+    reach = __builtin_amdgcn_logf(alpha) / (R::kApart ? 1.f : c2);
+    for (int n = 0; n < 64 && weight(reach) >= alpha; ++n) reach = step(reach, -1);
+    for (int n = 0; n < 128 && !(weight(reach) >= alpha); ++n) reach = step(reach, 1);
+  }
+  // amax[4 n + i]: largest logarithm of a weight over the heads seen so far of the current query tile, for key
   // row 4 g + i of key tile n and query column c (-inf: the key is newer than the query)
   float amax[4 * NB];
 #pragma unroll
   for (int x = 0; x < 4 * NB; ++x) amax[x] = -INFINITY;
   unsigned over = 0;                               // kIO with injected weights: bit 4 n + i = some head's weight >= alpha
-  while (it * 16 < P) {
-    int h2 = h + 1, it2 = it;
-    if (h2 == G) { h2 = 0; ++it2; }
-    const int itn = it2 * 16 < P ? it2 : it, hn = it2 * 16 < P ? h2 : h;   // (the last pair is fetched twice)
-    const u32x4_t next = tile_fetch(q + static_cast<size_t>(hn) * D, itn * 16, P - 1, q_stride);
-    const float bn = stat[static_cast<size_t>(hn) * a.p16 + min(itn * 16 + c, P - 1)];
-    const int qi = it * 16 + c;                    // this lane's query column
-    const f32x4_t b4 = {bq, bq, bq, bq};
-    if (have && it >= my_first) {
-    u32x4_t qb[KC];
-    tile_operand(tile, buf, qb, c, g);
-    // every key of the wave exists and is no newer than any query of the tile, and every
-    // query of the tile exists: nothing to mask (all but the wave's first four query tiles,
-    // the prompt's last tile and its last wave)
-    const bool plain = !kIO && j0 + kSpan - 1 <= it * 16 && j0 + kSpan - 1 < P && it * 16 + 15 < P;
-    if (plain) {
+  {
+    int it = it_begin, h = 0;                      // the pair worked on
+    // the block's stage s: rows in next[s % kAhead] until they are in LDS, statistics in bs[s % kAhead] until used
+    u32x4_t next[kAhead][R::kFetch];
+    Stats bs[kAhead];
+    Place to_come = {it_begin, 0, q + static_cast<size_t>(it_begin) * 16 * q_stride, it_begin * 16};   // first pair of the next stage to request
+    Place before = to_come;                        // ... and of the one before it, whose statistics are requested now
+    auto more_rows = [&](u32x4_t (&to)[R::kFetch]) {
+      fetch_rows(to_come, to);
+      before = to_come;
 #pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        const f32x4_t acc = logits_tile(ka[n], qb, b4);
+      for (int j = 0; j < R::kStage; ++j) next_pair(to_come);
+    };
+    auto more_stats = [&](Stats &to) { fetch_stats(before, to); };
+    more_rows(next[0]);
+    stage_put<T, D>(tile, 0, next[0]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) amax[4 * n + i] = max_f32(amax[4 * n + i], acc[i]);
-      }
-    } else {
+    for (int x = 0; x < kAhead; ++x) {             // (in this order: the waits in the loop count on it)
+      more_stats(bs[x]);
+      more_rows(next[(x + 1) % kAhead]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+    auto stage = [&](auto tag) {                   // (its number modulo kAhead is known to the code)
+      constexpr int buf = decltype(tag)::value % 2, reg = (decltype(tag)::value + 1) % kAhead;
 #pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        const f32x4_t acc = logits_tile(ka[n], qb, b4);
+      for (int j = 0; j < R::kStage; ++j) {
+        if (it < it_end && have && it >= my_first) {
+          const int qi = it * 16 + c;              // this lane's query column
+          const float b = bs[decltype(tag)::value].b[j], ll = bs[decltype(tag)::value].ll[j];
+          u32x4_t qb[R::kK];
+          tile_operand<T, D>(tile, buf, j, qb, c, g);
+          const float start = R::kApart ? 0.f : b;
+          f32x4_t acc[NB];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int key = j0 + 16 * n + 4 * g + i;
-          const bool seen = key <= qi && qi < P;   // (key <= qi < P implies key < P)
-          if (seen) amax[4 * n + i] = max_f32(amax[4 * n + i], acc[i]);
-          if (kIO) {
-            if (seen) {
-              const size_t at = ((static_cast<size_t>(seq) * a.n_q_heads + kvh * G + h) * P + qi) * P + key;
-              if (a.p_out) a.p_out[at] = __builtin_amdgcn_exp2f(acc[i] * c2);
-              if (a.p_override && a.p_override[at] >= a.alpha) over |= 1u << (4 * n + i);
+          for (int n = 0; n < NB; ++n) acc[n] = f32x4_t{start, start, start, start};
+          logits_tiles<T, D, NB, true>(ka, qb, acc);
+          // the logarithm of the weight, in units of log 2 (over c2 where b is folded in)
+          auto log_weight = [&](float x) { return R::kApart ? fmaf(x, c2, -b) - ll : x; };
+          // every key of the wave exists and is no newer than any query of the tile, and every
+          // query of the tile exists: nothing to mask (all but the wave's first NB query tiles,
+          // the prompt's last tile and its last wave)
+          const bool plain = !kIO && it >= plain_first && it < plain_end;
+          if (plain) {
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) amax[4 * n + i] = max_f32(amax[4 * n + i], log_weight(acc[n][i]));
+          } else {
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const int key = j0 + 16 * n + 4 * g + i;
+                const bool seen = key <= qi && qi < P;   // (key <= qi < P implies key < P)
+                const float lw = log_weight(acc[n][i]);
+                if (seen) amax[4 * n + i] = max_f32(amax[4 * n + i], lw);
+                if (kIO) {
+                  if (seen) {
+                    const size_t at = ((static_cast<size_t>(seq) * a.n_q_heads + kvh * G + h) * P + qi) * P + key;
+                    if (a.p_out) a.p_out[at] = weight(lw);
+                    if (a.p_override && a.p_override[at] >= a.alpha) over |= 1u << (4 * n + i);
+                  }
+                }
+              }
+            }
+          }
+          if (h == G - 1) {                        // the tile's last head: apply its activations
+            // bit 4 n + i of this lane: key row 4 g + i of key tile n and query column c; after the transposition
+            // bit q of lane (c, g): the key row and tile with 4 n + i = c, query q
+            unsigned bits = 0;
+#pragma unroll
+            for (int x = 4 * NB - 1; x >= 0; --x) {
+              const bool on = (kIO && a.p_override) ? (over >> x) & 1u : amax[x] >= reach;   // weight(amax[x]) >= alpha
+              bits = bits + bits + (on ? 1u : 0u);
+              amax[x] = -INFINITY;
+            }
+            over = 0;
+            if (__builtin_amdgcn_ballot_w64(bits != 0) != 0) {   // (wave-uniform)
+              const unsigned mask = transpose16(bits, c);
+              n_act += __popc(mask);
+              if (mask != 0) {                     // in order of the query position (Alg. 1, Eq. 1)
+                const int lo = __builtin_ctz(mask), hi = 31 - __builtin_clz(mask);
+                const int32_t tau = it * 16 + 1 - P;
+                if (kSeg && ts == INT_MIN) first = tau + lo;
+                else mri = max(mri, tau + lo - ts);
+                if (hi > lo) mri = max(mri, 1 + longest_run(~mask & ((1u << hi) - (1u << lo))));
+                ts = tau + hi;
+              }
             }
           }
         }
+        advance(it, h);
       }
+      stage_put<T, D>(tile, buf ^ 1, next[reg]);
+      more_stats(bs[decltype(tag)::value]);
+      more_rows(next[reg]);
+      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();                             // the next stage is complete, this one no longer read
+    };
+    settle(ka);
+    for (;;) {                                     // (left from its middle: see settle)
+      stage(std::integral_constant<int, 0>{});
+      if (it >= it_end) break;
+      stage(std::integral_constant<int, 1>{});
+      if (it >= it_end) break;
     }
-    if (h2 == 0) {                                 // the tile's last head: apply its activations
-      // key row 4 g' + i of key tile n over the tile's 16 queries: bits 16 g' .. 16 g' + 15 of
-      // the ballot of entry 4 n + i; lane (c, g) wants the one with 4 n + i = c
-      unsigned long long mine = 0, any = 0;
-#pragma unroll
-      for (int x = 0; x < 4 * NB; ++x) {
-        bool on = __builtin_amdgcn_exp2f(amax[x] * c2) >= a.alpha;       // exp2(-inf) = 0
-        if (kIO && a.p_override) on = (over >> x) & 1u;
-        const unsigned long long bal = __builtin_amdgcn_ballot_w64(on);
-        if (c == x) mine = bal;
-        any |= bal;
-        amax[x] = -INFINITY;
-      }
-      over = 0;
-      if (any != 0) {                              // (wave-uniform)
-        unsigned mask = static_cast<unsigned>(mine >> (16 * g)) & 0xFFFFu;
-        n_act += __popc(mask);
-        while (mask) {                             // in order of the query position (Alg. 1, Eq. 1)
-          const int32_t tau = it * 16 + __builtin_ctz(mask) + 1 - P;
-          mask &= mask - 1;
-          const int32_t gap = tau - ts;
-          if (gap > mri) mri = gap;
-          ts = tau;
-        }
-      }
-    }
-    }
-    tile_put(tile, buf ^ 1, next);
-    __syncthreads();                               // the next pair's tile is complete, this pair's no longer read
-    buf ^= 1;
-    bq = bn;
-    it = it2;
-    h = h2;
   }
   if (!have) return;
-  if (my_key < P) {
+  const bool owner = c < 4 * NB && my_key < P;
+  if constexpr (kSeg) {
+    if (owner)
+      a.seg[(static_cast<size_t>(z) * units + unit) * P + my_key] = make_int4(first, ts, mri, static_cast<int32_t>(n_act));
+    return;
+  }
+  if (owner) {
     a.ts[static_cast<size_t>(unit) * a.capacity + my_key] = ts;
     a.mri[static_cast<size_t>(unit) * a.capacity + my_key] = mri;
   }
@@ -326,99 +593,80 @@ __global__ __launch_bounds__(kBlock) void prefill_track_kernel(const PrefillArgs
   }
 }
 
-// ---- any other shape (fp32 rows, head_dim 64): the same two steps on the vector ALU, one
-// thread per (unit, head, query position) and one per (unit, key).  A dot product adds its
-// terms in index order in both kernels, so both see the same logit.
-template <int DH, typename T>
-__device__ inline void row_to_float(const T *src, float (&dst)[DH]) {
-#pragma unroll
-  for (int e = 0; e < DH; ++e) {
-    if constexpr (sizeof(T) == 4) dst[e] = src[e];
-    else dst[e] = __uint_as_float(static_cast<unsigned>(src[e]) << 16);
-  }
-}
-template <int DH, typename T>
-__device__ inline float dot_row(const float (&reg)[DH], const T *mem, bool reg_is_q) {
-  float s = 0.f;
-#pragma unroll 8
-  for (int e = 0; e < DH; ++e) {
-    float m;
-    if constexpr (sizeof(T) == 4) m = mem[e];
-    else m = __uint_as_float(static_cast<unsigned>(mem[e]) << 16);
-    s = reg_is_q ? fmaf(reg[e], m, s) : fmaf(m, reg[e], s);
-  }
-  return s;
-}
-
-// stat[(unit * G + h) * p16 + i] = log-sum-exp of the scaled logits of query i of head h
-template <int DH, typename T>
-__global__ __launch_bounds__(256) void prefill_stats_simple_kernel(const PrefillArgs a) {
-  const int P = a.prompt_len, G = a.group;
-  const long long idx = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= static_cast<long long>(a.batch) * a.n_kv_heads * G * P) return;
-  const int i = static_cast<int>(idx % P), h = static_cast<int>((idx / P) % G);
-  const int unit = static_cast<int>(idx / (static_cast<long long>(P) * G));
-  const int seq = unit / a.n_kv_heads, kvh = unit % a.n_kv_heads;
-  const T *q = static_cast<const T *>(a.q_prompt) +
-               ((static_cast<size_t>(seq) * P + i) * a.n_q_heads + kvh * G + h) * DH;
-  const T *k = static_cast<const T *>(a.k_cache) + static_cast<size_t>(unit) * a.capacity * DH;
-  float qr[DH];
-  row_to_float<DH>(q, qr);
-  float m = -INFINITY, l = 0.f;
-  for (int j = 0; j <= i; ++j) {
-    const float sc = a.scale * dot_row<DH>(qr, k + static_cast<size_t>(j) * DH, true);
-    if (sc > m) { l = l * __expf(m - sc) + 1.f; m = sc; }      // (exp(-inf) = 0 on the first key)
-    else l += __expf(sc - m);
-  }
-  a.stat[(static_cast<size_t>(unit) * G + h) * a.p16 + i] = m + __logf(l);
-}
-
-template <int DH, typename T>
-__global__ __launch_bounds__(256) void prefill_track_simple_kernel(const PrefillArgs a) {
-  const int P = a.prompt_len, G = a.group;
-  const long long idx = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const bool live = idx < static_cast<long long>(a.batch) * a.n_kv_heads * P;
-  const int j = live ? static_cast<int>(idx % P) : 0;
-  const int unit = live ? static_cast<int>(idx / P) : 0;
-  const int seq = unit / a.n_kv_heads, kvh = unit % a.n_kv_heads;
+// The segments of every key joined in order (Eq. 1): between two segments lies the gap from the last activation
+// before to the first one in it.
+__global__ __launch_bounds__(kBlock) void prefill_join_kernel(const PrefillArgs a) {
+  const int units = a.batch * a.n_kv_heads, P = a.prompt_len;
+  const int spans = (P + kBlock - 1) / kBlock;
+  const int unit = static_cast<int>(blockIdx.x) / spans, key = static_cast<int>(blockIdx.x) % spans * kBlock + threadIdx.x;
   unsigned n_act = 0;
-  if (live) {
-    float kr[DH];
-    row_to_float<DH>(static_cast<const T *>(a.k_cache) + (static_cast<size_t>(unit) * a.capacity + j) * DH, kr);
-    int32_t ts = j + 1 - P, mri = 0;                 // born at its own step
-    for (int i = j; i < P; ++i) {                    // in order of the query position (Alg. 1, Eq. 1)
-      bool on = false;
-      for (int h = 0; h < G; ++h) {
-        const int head = kvh * G + h;
-        const size_t at = ((static_cast<size_t>(seq) * a.n_q_heads + head) * P + i) * P + j;
-        const T *q = static_cast<const T *>(a.q_prompt) + ((static_cast<size_t>(seq) * P + i) * a.n_q_heads + head) * DH;
-        float pw = __expf(a.scale * dot_row<DH>(kr, q, false) - a.stat[(static_cast<size_t>(unit) * G + h) * a.p16 + i]);
-        if (a.p_out) a.p_out[at] = pw;
-        if (a.p_override) pw = a.p_override[at];
-        on = on || pw >= a.alpha;
-      }
-      if (on) {
-        const int32_t tau = i + 1 - P, gap = tau - ts;
-        if (gap > mri) mri = gap;
-        ts = tau;
-        n_act += 1;
-      }
+  if (key < P) {
+    int32_t ts = key + 1 - P, mri = 0;             // born at its own step
+    // (the first segment that a block of its wave's keys worked on)
+    for (int z = key / a.seg_block * (a.seg_block / 16) / a.seg_tiles; z < a.segments; ++z) {
+      const int4 s = a.seg[(static_cast<size_t>(z) * units + unit) * P + key];
+      if (s.x == INT_MAX) continue;
+      mri = max(mri, max(s.x - ts, s.z));
+      ts = s.y;
+      n_act += static_cast<unsigned>(s.w);
     }
-    a.ts[static_cast<size_t>(unit) * a.capacity + j] = ts;
-    a.mri[static_cast<size_t>(unit) * a.capacity + j] = mri;
+    a.ts[static_cast<size_t>(unit) * a.capacity + key] = ts;
+    a.mri[static_cast<size_t>(unit) * a.capacity + key] = mri;
   }
-  if (a.activation_counter && n_act) atomicAdd(a.activation_counter + static_cast<size_t>(unit) * a.counter_stride, static_cast<unsigned long long>(n_act));
+  if (a.activation_counter) {
+    for (int o = 32; o > 0; o >>= 1) n_act += __shfl_xor(n_act, o);
+    if ((threadIdx.x & 63) == 0 && n_act) atomicAdd(a.activation_counter + unit * a.counter_stride, static_cast<unsigned long long>(n_act));
+  }
 }
 
-template <int DH, typename T>
-hipError_t launch_prefill_simple(const PrefillArgs &a, hipStream_t stream) {
+template <typename T, int D>
+hipError_t launch_rows(PrefillArgs a, hipStream_t stream) {
+  constexpr int NB = Rows<T, D>::kTiles;
   const long long units = static_cast<long long>(a.batch) * a.n_kv_heads;
-  const long long n1 = (units * a.group * a.prompt_len + 255) / 256, n2 = (units * a.prompt_len + 255) / 256;
-  if (n1 > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((prefill_stats_simple_kernel<DH, T>), dim3(static_cast<unsigned>(n1)), dim3(256), 0, stream, a);
-  const hipError_t e = hipGetLastError();
+  const long long wide = (a.prompt_len + kWaves * 16 * NB - 1) / (kWaves * 16 * NB), narrow = (a.prompt_len + kWaves * 16 - 1) / (kWaves * 16);
+  if (units * a.group * narrow > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+  if (units * a.group * wide >= 512)
+    hipLaunchKernelGGL((prefill_stats_kernel<T, D, NB>), dim3(static_cast<unsigned>(units * a.group * wide)), dim3(kBlock), 0, stream, a);
+  else
+    hipLaunchKernelGGL((prefill_stats_kernel<T, D, 1>), dim3(static_cast<unsigned>(units * a.group * narrow)), dim3(kBlock), 0, stream, a);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((prefill_track_simple_kernel<DH, T>), dim3(static_cast<unsigned>(n2)), dim3(256), 0, stream, a);
+  if (a.p_out || a.p_override) {
+    hipLaunchKernelGGL((prefill_track_kernel<T, D, 1, true, false>), dim3(static_cast<unsigned>(units * narrow)), dim3(kBlock), 0, stream, a);
+    return hipGetLastError();
+  }
+  // Blocks of four waves with NB key tiles each, or with one each where that does not fill the chip.  The
+  // queries are cut into segments where the blocks are fewer than eight per compute unit (wide) or two (narrow):
+  // early keys have all queries to walk, one after the other, and with one block for that the chip ends
+  // on the few blocks of the earliest keys.  One segment / cut, us for both kernels: 32 units x 1024 positions
+  // 267 / 112, 8 units x 8192 2129 / 1146, 128 units x 600 230 / 169; from 2048 blocks on nothing is gained
+  // (128 units x 4096, 4096 blocks asked for instead: 2966 / 2900).  A segment is two query tiles at
+  // least (wide: four).
+  const long long n_it = (a.prompt_len + 15) / 16;
+  const long long most = n_it / 4 < a.segments ? n_it / 4 : a.segments;        // (what the workspace holds records for)
+  const bool use_wide = units * wide * (most < 1 ? 1 : most) >= 512;
+  const long long per_unit = use_wide ? wide : narrow, want = use_wide ? 2048 : 512;
+  long long z = (want + units * per_unit - 1) / (units * per_unit);
+  if (z > (use_wide ? n_it / 4 : n_it / 2)) z = use_wide ? n_it / 4 : n_it / 2;
+  if (z > a.segments) z = a.segments;
+  if (z <= 1) {
+    const dim3 grid(static_cast<unsigned>(units * per_unit));
+    if (use_wide) hipLaunchKernelGGL((prefill_track_kernel<T, D, NB, false, false>), grid, dim3(kBlock), 0, stream, a);
+    else hipLaunchKernelGGL((prefill_track_kernel<T, D, 1, false, false>), grid, dim3(kBlock), 0, stream, a);
+    return hipGetLastError();
+  }
+  a.seg_tiles = static_cast<int32_t>((n_it + z - 1) / z);
+  z = (n_it + a.seg_tiles - 1) / a.seg_tiles;
+  a.seg_block = kWaves * 16 * (use_wide ? NB : 1);
+  a.segments = static_cast<int32_t>(z);
+  if (units * per_unit * z > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(units * per_unit * z));
+  if (use_wide) hipLaunchKernelGGL((prefill_track_kernel<T, D, NB, false, true>), grid, dim3(kBlock), 0, stream, a);
+  else hipLaunchKernelGGL((prefill_track_kernel<T, D, 1, false, true>), grid, dim3(kBlock), 0, stream, a);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const long long spans = (a.prompt_len + kBlock - 1) / kBlock;
+  hipLaunchKernelGGL(prefill_join_kernel, dim3(static_cast<unsigned>(units * spans)), dim3(kBlock), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -427,24 +675,14 @@ hipError_t launch_prefill_simple(const PrefillArgs &a, hipStream_t stream) {
 hipError_t launch_prefill_track(const PrefillArgs &a, hipStream_t stream) {
   if (a.prompt_len < 1 || a.prompt_len > a.capacity || a.group < 1 || a.group > kHeadMax ||
       a.n_q_heads != a.n_kv_heads * a.group || a.batch < 1 || a.p16 < (a.prompt_len + 15) / 16 * 16 ||
-      !a.q_prompt || !a.k_cache || !a.ts || !a.mri || !a.stat || a.counter_stride < 1)
+      !a.q_prompt || !a.k_cache || !a.ts || !a.mri || !a.stat || !a.stat2 || a.counter_stride < 1 ||
+      (a.segments > 1 && !a.seg))
     return hipErrorInvalidValue;
-  if (a.dtype == 0 && a.head_dim == 64) return launch_prefill_simple<64, float>(a, stream);
-  if (a.dtype == 0 && a.head_dim == 128) return launch_prefill_simple<128, float>(a, stream);
-  if (a.dtype == 1 && a.head_dim == 64) return launch_prefill_simple<64, bf16_t>(a, stream);
-  if (a.dtype != 1 || a.head_dim != D) return hipErrorInvalidValue;
-  const long long units = static_cast<long long>(a.batch) * a.n_kv_heads;
-  const long long n_t = (a.prompt_len + kWaves * kSpan - 1) / (kWaves * kSpan);
-  if (units * a.group * n_t > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(prefill_stats_kernel, dim3(static_cast<unsigned>(units * a.group * n_t)), dim3(kBlock), 0,
-                     stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.p_out || a.p_override)
-    hipLaunchKernelGGL(prefill_track_kernel<true>, dim3(static_cast<unsigned>(units * n_t)), dim3(kBlock), 0, stream, a);
-  else
-    hipLaunchKernelGGL(prefill_track_kernel<false>, dim3(static_cast<unsigned>(units * n_t)), dim3(kBlock), 0, stream, a);
-  return hipGetLastError();
+  if (a.dtype == 0 && a.head_dim == 64) return launch_rows<float, 64>(a, stream);
+  if (a.dtype == 0 && a.head_dim == 128) return launch_rows<float, 128>(a, stream);
+  if (a.dtype == 1 && a.head_dim == 64) return launch_rows<bf16_t, 64>(a, stream);
+  if (a.dtype == 1 && a.head_dim == 128) return launch_rows<bf16_t, 128>(a, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace lazyev
