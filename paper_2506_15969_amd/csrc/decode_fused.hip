@@ -69,6 +69,7 @@
 //   16x16x4:  A[row c][k = g]  B[k = g][col c]  C[row 4g+i][col c]   (fp32)
 // so a lane that owns head c and entries 4g..4g+3 of a sub-tile after the first product already
 // holds the A operand of the second.
+#include "bits.h"
 #include "kernels.h"
 
 #include <type_traits>
@@ -415,81 +416,79 @@ __global__ __launch_bounds__(kBlock) void track_kernel(const TrackArgs k_all, in
   track_count(k, unit, part, n_act, cnt_lds);
 }
 
-// The logged calls of a layer applied to TS / MRI: one thread per cache entry, the calls in step
-// order.  An entry's bit in the words of a call says that it was active there (TrackArgs::bitlog).
-// Block b works on the kFlushSpan entries from kFlushSpan * (b % spans) on of unit (b / spans) % units
-// of layer b / spans / units, spans = blocks per unit.  The span's 32 words of every logged call
-// go to LDS first (all requested together: one memory round trip), then every thread walks the
-// calls for its four entries.
-constexpr int kFlushSpan = 4 * kBlock;
+// The logged calls of a layer applied to TS / MRI.  An entry's bit in the words of a call says that it
+// was active there (TrackArgs::bitlog).  Block b works on the kFlushSpan entries from kFlushSpan * (b % spans)
+// on of unit (b / spans) % units of layer b / spans / units, spans = blocks per unit; a wave on 128
+// of them: lane (half, j) brings the words 2 half and 2 half + 1 of call s + j, and after a transposition across the 32
+// lanes holds the 32 calls of entries 64 half + j and 64 half + 32 + j.  A logged
+// call's step is the one before it plus one, so the largest gap between activations is a run of zeros and no call is
+// looked at by itself.  (Walking the set bits, the steps from LDS, took as long as the wave's most active
+// entry: 256 units of 1152 entries x 127 calls, in two launches as the layers differed by a call, 72 us, now 8.)
+constexpr int kFlushWords = 2;                     // per lane and call
+constexpr int kFlushSpan = kWaves * 64 * kFlushWords;
 __global__ __launch_bounds__(kBlock) void track_flush_kernel(const FlushArgs f) {
-  __shared__ uint32_t lw[kLogSlotsMax * (kFlushSpan / 32)];
-  __shared__ int32_t lt[kLogSlotsMax];             // the calls' steps (an indexed read of the argument block costs a scalar load each time)
-  __shared__ int32_t lo[kLogSlotsMax];             // the entries the calls appended
-  constexpr int kSpanWords = kFlushSpan / 32;
   const int spans = (f.capacity + kFlushSpan - 1) / kFlushSpan;
   const int span = blockIdx.x % spans, lu = blockIdx.x / spans;
   const int layer = lu / f.units, unit = lu % f.units;
+  const FlushArgs::Layer of = f.layer[layer];
+  if (of.n_calls == 0) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, j = lane & 31;
   const size_t slab = (static_cast<size_t>(layer) * f.units + unit) * f.capacity;
-  const uint32_t *log = f.bitlog + (static_cast<size_t>(layer) * f.units + unit) * f.log_slots * f.log_words +
-                        span * kSpanWords;           // (a unit's slots lie together: a stream of n_calls * log_words words)
-  const size_t slot_stride = static_cast<size_t>(f.log_words);
-  const int n_words = min(kSpanWords, f.log_words - span * kSpanWords);
-  for (int x = threadIdx.x; x < f.n_calls * kSpanWords; x += kBlock) {
-    const int s = x / kSpanWords, j = x % kSpanWords;
-    lw[x] = j < n_words ? log[s * slot_stride + j] : 0u;
-  }
-  for (int s = threadIdx.x; s < f.n_calls; s += kBlock) { lt[s] = f.t[s]; lo[s] = f.n_old[s]; }
-  int32_t ts[4], mri[4];
+  const uint32_t *log = f.bitlog + (static_cast<size_t>(layer) * f.units + unit) * f.log_slots * f.log_words;   // (a unit's slots lie together)
+  const int word = span * (kFlushSpan / 32) + (wave * 2 + half) * kFlushWords;
+  constexpr int kBatch = 4;                        // sets of 32 calls requested together
+  unsigned w[kBatch][kFlushWords];
+  auto fetch = [&](int s0) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {                    // (requested while the words travel)
-    const int i = span * kFlushSpan + e * kBlock + static_cast<int>(threadIdx.x);
-    ts[e] = mri[e] = 0;
-    if (i < f.capacity) { ts[e] = f.ts[slab + i]; mri[e] = f.mri[slab + i]; }
-  }
-  __syncthreads();
+    for (int b = 0; b < kBatch; ++b) {
+      const uint32_t *row = log + static_cast<size_t>(min(s0 + 32 * b + j, of.n_calls - 1)) * f.log_words;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int il = e * kBlock + static_cast<int>(threadIdx.x), i = span * kFlushSpan + il;
-    if (i >= f.capacity) continue;
-    const uint32_t *w = lw + (il >> 5);
-    bool touched = false;
-    const int sh = il & 31;
-    // An entry that one of the calls appended starts there (Sec. 4): no earlier call has a bit for
-    // it, so it is started before the bits are walked.  (Calls of consecutive steps append
-    // consecutive entries: the first guess is right unless steps were left out.)
-    {
-      int s_new = i - lo[0];
-      if (s_new < 0 || s_new >= f.n_calls || lo[s_new] != i) {
-        s_new = -1;
-        if (i >= lo[0] && i <= lo[f.n_calls - 1])
-          for (int s = 0; s < f.n_calls; ++s) s_new = lo[s] == i ? s : s_new;
-      }
-      if (s_new >= 0) {
-        ts[e] = lt[s_new];
-        mri[e] = 0;
-        f.pos[slab + i] = f.prompt_len + lt[s_new] - 1;
-        touched = true;
+      for (int x = 0; x < kFlushWords; ++x) w[b][x] = row[min(word + x, f.log_words - 1)];
+    }
+  };
+  fetch(0);
+  int32_t ts[kFlushWords], mri[kFlushWords];
+  bool touched[kFlushWords];
+#pragma unroll
+  for (int x = 0; x < kFlushWords; ++x) {          // (requested while the words travel)
+    const int i = (word + x) * 32 + j;
+    ts[x] = mri[x] = 0;
+    if (i < f.capacity) { ts[x] = f.ts[slab + i]; mri[x] = f.mri[slab + i]; }
+  }
+#pragma unroll
+  for (int x = 0; x < kFlushWords; ++x) {
+    // An entry that one of the calls appended starts there (Sec. 4): no earlier call has a bit for it
+    const int i = (word + x) * 32 + j, s_new = i - of.n_old;
+    touched[x] = i < f.capacity && s_new >= 0 && s_new < of.n_calls;
+    if (touched[x]) {
+      ts[x] = of.t + s_new;
+      mri[x] = 0;
+      f.pos[slab + i] = f.prompt_len + ts[x] - 1;
+    }
+  }
+  for (int s0 = 0; s0 < of.n_calls; s0 += 32 * kBatch) {
+    if (s0 > 0) fetch(s0);
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      const int s = s0 + 32 * b;
+      if (s >= of.n_calls) break;                  // (uniform)
+#pragma unroll
+      for (int x = 0; x < kFlushWords; ++x) {
+        const unsigned calls = transpose_bits<32>(s + j < of.n_calls ? w[b][x] : 0u, j);
+        if (calls == 0) continue;
+        const int lo = __builtin_ctz(calls), hi = 31 - __builtin_clz(calls);
+        mri[x] = max(mri[x], of.t + s + lo - ts[x]);                       // Eq. 1
+        if (hi > lo) mri[x] = max(mri[x], longest_gap<32>(calls, lo, hi));
+        ts[x] = of.t + s + hi;                                             // Alg. 1
+        touched[x] = true;
       }
     }
-    for (int s0 = 0; s0 < f.n_calls; s0 += 32) {   // 32 calls at a time: in which of them was the entry active?
-      unsigned calls = 0;
-      const int n32 = min(32, f.n_calls - s0);
+  }
 #pragma unroll
-      for (int d = 0; d < 32; ++d)                 // (no branch in here: the LDS reads overlap; reads beyond the
-        calls |= ((w[min(s0 + d, f.n_calls - 1) * kSpanWords] >> sh) & 1u) << d;   // last call repeat it and are masked)
-      calls &= n32 == 32 ? ~0u : (1u << n32) - 1u;
-      while (calls) {                              // ... and those, in step order
-        const int s = s0 + __builtin_ctz(calls);
-        calls &= calls - 1;
-        const int32_t t_s = lt[s];
-        const int32_t gap = t_s - ts[e];
-        if (gap > mri[e]) mri[e] = gap;            // Eq. 1
-        ts[e] = t_s;                               // Alg. 1
-        touched = true;
-      }
-    }
-    if (touched) { f.ts[slab + i] = ts[e]; f.mri[slab + i] = mri[e]; }
+  for (int x = 0; x < kFlushWords; ++x) {
+    const int i = (word + x) * 32 + j;
+    if (touched[x] && i < f.capacity) { f.ts[slab + i] = ts[x]; f.mri[slab + i] = mri[x]; }
   }
 }
 
@@ -1443,10 +1442,15 @@ hipError_t launch_track(const TrackArgs &k, hipStream_t stream) {
 int decode_fused_log_words_max() { return static_cast<int>(sizeof(u32x4_t) * kWaves * 256 / sizeof(unsigned)); }
 
 hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stream) {
-  if (!f.ts || !f.mri || !f.pos || !f.bitlog || f.units < 1 || n_layers < 1 || f.capacity < 1 ||
-      f.log_words < (f.capacity + 31) / 32 || f.n_calls < 0 || f.n_calls > f.log_slots || f.log_slots > kLogSlotsMax)
+  if (!f.ts || !f.mri || !f.pos || !f.bitlog || f.units < 1 || n_layers < 1 || n_layers > kFlushLayers ||
+      f.capacity < 1 || f.log_words < (f.capacity + 31) / 32 || f.log_slots > kLogSlotsMax)
     return hipErrorInvalidValue;
-  if (f.n_calls == 0) return hipSuccess;
+  bool any = false;
+  for (int l = 0; l < n_layers; ++l) {
+    if (f.layer[l].n_calls < 0 || f.layer[l].n_calls > f.log_slots) return hipErrorInvalidValue;
+    any = any || f.layer[l].n_calls > 0;
+  }
+  if (!any) return hipSuccess;
   const unsigned spans = static_cast<unsigned>((f.capacity + kFlushSpan - 1) / kFlushSpan);
   hipLaunchKernelGGL(track_flush_kernel, dim3(static_cast<unsigned>(n_layers) * f.units * spans), dim3(kBlock), 0, stream, f);
   return hipGetLastError();

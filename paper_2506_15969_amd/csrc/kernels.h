@@ -83,14 +83,17 @@ struct TrackArgs {
 // The logged calls of one or several layers applied to TS / MRI (Alg. 1 first loop, Eq. 1, in the
 // order of the calls).  Block b works on layer b / units, unit b % units.
 constexpr int kLogSlotsMax = 256;
+constexpr int kFlushLayers = 64;    // layers of a launch
 struct FlushArgs {
   int32_t *ts, *mri, *pos;          // first layer's slab; the other layers' follow
   int32_t prompt_len;
   const uint32_t *bitlog;           // [layer][units][log_slots][log_words], first layer of the launch
   int32_t units, capacity, log_words, log_slots;
-  int32_t n_calls;                  // logged calls to apply: slots 0 .. n_calls - 1
-  int32_t t[kLogSlotsMax];          // step of the call in slot s (what TS becomes)
-  int32_t n_old[kLogSlotsMax];      // the entry that call appended (it starts with TS = t, MRI = 0, pos = P + t - 1)
+  struct Layer {                    // the logged calls to apply: slots 0 .. n_calls - 1, of consecutive steps
+    int32_t n_calls;
+    int32_t t;                      // step of the first (TS becomes t + slot)
+    int32_t n_old;                  // the entry it appended (call s appended n_old + s: TS = t + s, MRI = 0, pos = P + t + s - 1)
+  } layer[kFlushLayers];
 };
 
 struct DecodeArgs {

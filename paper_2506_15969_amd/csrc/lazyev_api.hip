@@ -49,9 +49,9 @@ struct lazyev_ctx {
   // one bit per cache entry and not yet applied to TS / MRI; null when the shape has no log
   uint32_t *bitlog;
   int32_t log_words, log_slots;
-  std::vector<int32_t> log_n;       // per layer: logged calls
-  std::vector<int32_t> log_t;       // [layer][log_slots]: their steps
-  std::vector<int32_t> log_n_old;   // [layer][log_slots]: the entries they appended
+  std::vector<int32_t> log_n;       // per layer: logged calls (of consecutive steps) ...
+  std::vector<int32_t> log_t;       // ... the step of the first ...
+  std::vector<int32_t> log_n_old;   // ... and the entry it appended
   // the last decode call, if the fused kernel ran it: its logits and statistics are still in
   // the workspace (what an eviction that ranks by that step's weights reads)
   int32_t last_layer;
@@ -268,10 +268,8 @@ void fill_due(const lazyev_ctx *ctx, int32_t t, lazyev::EvictArgs &a) {
   }
 }
 
-// Applies the logged calls of layers l0 .. l1 - 1, which all hold the same calls, to TS / MRI.
+// Applies the logged calls of layers l0 .. l1 - 1 (at most kFlushLayers) to TS / MRI in one launch.
 hipError_t flush_log_range(lazyev_ctx *ctx, int l0, int l1) {
-  const int n = ctx->log_n[l0];
-  if (n == 0) return hipSuccess;
   lazyev::FlushArgs f;
   std::memset(&f, 0, sizeof(f));
   const size_t slab = static_cast<size_t>(ctx->units) * ctx->capacity;
@@ -282,10 +280,10 @@ hipError_t flush_log_range(lazyev_ctx *ctx, int l0, int l1) {
   f.bitlog = ctx->bitlog + static_cast<size_t>(l0) * ctx->log_slots * ctx->units * ctx->log_words;
   f.units = ctx->units; f.capacity = ctx->capacity;
   f.log_words = ctx->log_words; f.log_slots = ctx->log_slots;
-  f.n_calls = n;
-  for (int s = 0; s < n; ++s) {
-    f.t[s] = ctx->log_t[static_cast<size_t>(l0) * ctx->log_slots + s];
-    f.n_old[s] = ctx->log_n_old[static_cast<size_t>(l0) * ctx->log_slots + s];
+  for (int l = l0; l < l1; ++l) {
+    f.layer[l - l0].n_calls = ctx->log_n[l];
+    f.layer[l - l0].t = ctx->log_t[l];
+    f.layer[l - l0].n_old = ctx->log_n_old[l];
   }
   const hipError_t e = lazyev::launch_track_flush(f, l1 - l0, ctx->stream);
   if (e == hipSuccess)
@@ -293,26 +291,16 @@ hipError_t flush_log_range(lazyev_ctx *ctx, int l0, int l1) {
   return e;
 }
 
-// Applies every layer's logged calls: consecutive layers that hold the same calls (the usual
-// case: all of them) in one launch.
+// Applies every layer's logged calls, also where one layer holds more of them than another (the last call is
+// not in the log yet): 64 layers per launch.
 hipError_t flush_logs(lazyev_ctx *ctx) {
   if (!ctx->bitlog) return hipSuccess;
   const int L = ctx->cfg.n_layers;
-  for (int l0 = 0; l0 < L;) {
-    int l1 = l0 + 1;
-    const int n = ctx->log_n[l0];
-    while (l1 < L && ctx->log_n[l1] == n &&
-           std::equal(ctx->log_t.begin() + static_cast<size_t>(l0) * ctx->log_slots,
-                      ctx->log_t.begin() + static_cast<size_t>(l0) * ctx->log_slots + n,
-                      ctx->log_t.begin() + static_cast<size_t>(l1) * ctx->log_slots) &&
-           std::equal(ctx->log_n_old.begin() + static_cast<size_t>(l0) * ctx->log_slots,
-                      ctx->log_n_old.begin() + static_cast<size_t>(l0) * ctx->log_slots + n,
-                      ctx->log_n_old.begin() + static_cast<size_t>(l1) * ctx->log_slots) &&
-           static_cast<long long>(l1 + 1 - l0) * ctx->units <= 65535)
-      ++l1;
-    const hipError_t e = flush_log_range(ctx, l0, l1);
+  int step = 65535 / ctx->units;                   // (bounds the launch's blocks)
+  step = step < 1 ? 1 : step > lazyev::kFlushLayers ? lazyev::kFlushLayers : step;
+  for (int l0 = 0; l0 < L; l0 += step) {
+    const hipError_t e = flush_log_range(ctx, l0, l0 + step < L ? l0 + step : L);
     if (e != hipSuccess) return e;
-    l0 = l1;
   }
   return hipSuccess;
 }
@@ -361,8 +349,8 @@ int lazyev_init(const lazyev_config *cfg, lazyev_ctx **out) {
     ctx->n_evict_events.assign(cfg->n_layers, 0);
     ctx->n_evicted.assign(cfg->n_layers, 0);
     ctx->log_n.assign(cfg->n_layers, 0);
-    ctx->log_t.assign(static_cast<size_t>(cfg->n_layers) * (l.log_slots > 0 ? l.log_slots : 1), 0);
-    ctx->log_n_old.assign(ctx->log_t.size(), 0);
+    ctx->log_t.assign(cfg->n_layers, 0);
+    ctx->log_n_old.assign(cfg->n_layers, 0);
   } catch (const std::bad_alloc &) {
     delete ctx;
     return LAZYEV_ENOMEM;
@@ -521,7 +509,9 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
       // ... as one bit per cache entry in the next free slot of its layer's log (a full log is
       // applied first)
       const int ly = ctx->pend_layer;
-      if (ctx->log_n[ly] == ctx->log_slots) {
+      if (ctx->log_n[ly] == ctx->log_slots ||
+          (ctx->log_n[ly] > 0 && (a.track.t != ctx->log_t[ly] + ctx->log_n[ly] ||      // (a log holds consecutive calls)
+                                  a.track.n_old != ctx->log_n_old[ly] + ctx->log_n[ly]))) {
         const hipError_t ef = flush_log_range(ctx, ly, ly + 1);
         if (ef != hipSuccess) return fail_hip(ctx, ef);
       }
@@ -529,8 +519,7 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
       a.track.bitlog = ctx->bitlog + (static_cast<size_t>(ly) * ctx->units * ctx->log_slots + slot) * ctx->log_words;
       a.track.log_words = ctx->log_words;
       a.track.log_unit_stride = ctx->log_slots * ctx->log_words;
-      ctx->log_t[static_cast<size_t>(ly) * ctx->log_slots + slot] = a.track.t;
-      ctx->log_n_old[static_cast<size_t>(ly) * ctx->log_slots + slot] = a.track.n_old;
+      if (slot == 0) { ctx->log_t[ly] = a.track.t; ctx->log_n_old[ly] = a.track.n_old; }
     }
     a.p_stride = static_cast<int32_t>(fused_p_stride(ctx->capacity));
     // candidate lists instead of every logit, unless somebody reads the logits as such (the
@@ -1020,7 +1009,7 @@ int lazyev_log_peek(lazyev_ctx *ctx, int32_t layer, int32_t back, int32_t unit, 
                   ctx->bitlog + ((static_cast<size_t>(layer) * ctx->units + unit) * ctx->log_slots + slot) * ctx->log_words,
                   ctx->log_words * sizeof(uint32_t), hipMemcpyDeviceToHost);
   if (e != hipSuccess) return fail_hip(ctx, e);
-  if (t) *t = ctx->log_t[static_cast<size_t>(layer) * ctx->log_slots + slot];
+  if (t) *t = ctx->log_t[layer] + slot;
   return LAZYEV_OK;
 }
 

@@ -37,6 +37,7 @@
 //    1 sequence,  28 / 4 heads of 128, bf16    33 positions 22.9 -> 13.5,  400 positions 141 -> 24
 //    4 sequences, 32 / 8 heads of  64, bf16   499 positions 5470 -> 32
 //    2 sequences, 28 / 4 heads of 128, fp32   300 positions 10880 -> 50
+#include "bits.h"
 #include "kernels.h"
 
 #include <cfloat>
@@ -323,37 +324,6 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats
   }
 }
 
-// Transposes the 16 x 16 bits of 16 lanes: bit x of lane c (of each group of 16) -> bit c of lane x.  The 16 bits
-// are kept twice in the register, so that a rotation by s serves the lower and (by 32 - s) the upper half;
-// lane ^ 1, 2, 4 (= 7 ^ 3) and 8 are data-parallel moves within the vector ALU.
-__device__ __forceinline__ unsigned transpose16(unsigned bits, int c) {
-  unsigned m = bits | (bits << 16);
-  auto step = [&](unsigned other, int s, unsigned keep) {
-    const bool up = c & s;
-    const unsigned turned = __builtin_amdgcn_alignbit(other, other, up ? s : 32 - s);   // rotated right
-    const unsigned k = up ? ~keep : keep;
-    m = (m & k) | (turned & ~k);
-  };
-  auto move = [](unsigned x, auto ctrl) { return static_cast<unsigned>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), decltype(ctrl)::value, 0xF, 0xF, true)); };
-  step(move(m, std::integral_constant<int, 0x128>{}), 8, 0x00FF00FFu);       // row_ror:8
-  step(move(move(m, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{}), 4, 0x0F0F0F0Fu);   // row_half_mirror, quad_perm 3 2 1 0
-  step(move(m, std::integral_constant<int, 0x4E>{}), 2, 0x33333333u);        // quad_perm 2 3 0 1
-  step(move(m, std::integral_constant<int, 0xB1>{}), 1, 0x55555555u);        // quad_perm 1 0 3 2
-  return m & 0xFFFFu;
-}
-
-// Length of the longest run of ones among the lowest 16 bits of z (at most 15): x2, x4, x8 mark where 2, 4, 8 ones in a row start.
-__device__ __forceinline__ int longest_run(unsigned z) {
-  const unsigned x2 = z & (z >> 1), x4 = x2 & (x2 >> 2), x8 = x4 & (x4 >> 4);
-  int r = x8 ? 8 : 0;
-  unsigned at = x8 ? x8 : ~0u;                     // starts of runs of at least r ones
-  unsigned t = at & (x4 >> r);
-  if (t) { r += 4; at = t; }
-  t = at & (x2 >> r);
-  if (t) { r += 2; at = t; }
-  return (at & (z >> r)) ? r + 1 : r;
-}
-
 // Tracking: blocks = units * ceil(P / (64 NB)) * segments; a wave owns the keys j0 .. j0 + 16 NB - 1.
 // kIO: the weights are exported and / or replaced (a checker's route).  kSeg: the block walks its segment of
 // the queries only and leaves, of every key, its first (INT_MAX: none) and last activation there, the largest gap
@@ -547,14 +517,14 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
             }
             over = 0;
             if (__builtin_amdgcn_ballot_w64(bits != 0) != 0) {   // (wave-uniform)
-              const unsigned mask = transpose16(bits, c);
+              const unsigned mask = transpose_bits<16>(bits, c);
               n_act += __popc(mask);
               if (mask != 0) {                     // in order of the query position (Alg. 1, Eq. 1)
                 const int lo = __builtin_ctz(mask), hi = 31 - __builtin_clz(mask);
                 const int32_t tau = it * 16 + 1 - P;
                 if (kSeg && ts == INT_MIN) first = tau + lo;
                 else mri = max(mri, tau + lo - ts);
-                if (hi > lo) mri = max(mri, 1 + longest_run(~mask & ((1u << hi) - (1u << lo))));
+                if (hi > lo) mri = max(mri, longest_gap<16>(mask, lo, hi));
                 ts = tau + hi;
               }
             }
