@@ -25,7 +25,7 @@
 // groups' last blocks hand theirs to the unit's last block, which finishes the unit (see
 // "hand-over" below): no acknowledgement is waited for, nothing is signalled, one memory round trip
 // a hop.  (Until this replaced a ticket counter for more than four blocks, whose holder loaded four
-// partials per round trip: 8 units x 2112 entries 14.8 -> 8.6 us per call, 32 x 1056 9.4 -> 7.9.)
+// partials per round trip: 8 units x 2112 entries 14.8 -> 8.6 us per call, 32 x 1056 9.1 -> 6.9, with block_place.)
 // The partials are merged in an order that depends on the split alone, and the finishing block
 // leaves the unit's softmax statistics (max, 1 / sum per head) for the tracking.
 //
@@ -89,7 +89,7 @@ constexpr int kRunMax = 20;             // sub-tiles whose logits a wave keeps i
 // ..., so the waves of a unit read one moving window of the cache together (measured against a
 // region of consecutive sub-tiles per block: 28.6 against 29.2 us per call on the 2048-entry
 // workload).  The unit's LAST block comes first in that order: when the sub-tiles do not divide
-// evenly its waves take the longer runs, and it is the block that finishes a unit of 2..4 blocks,
+// evenly its waves take the longer runs, and it is the block that finishes the unit,
 // so the other blocks' partials are on their way while it still streams.
 struct WaveMap { int first, step, cnt; };
 __host__ __device__ inline WaveMap fused_wave_map(int n_sub, int n_split, int split, int wave) {
@@ -104,16 +104,27 @@ __host__ __device__ inline int fused_wave_run(int n_sub, int n_split) {
   return (n_sub + kWaves * n_split - 1) / (kWaves * n_split);
 }
 
-// Unit and place in the unit of stream block b.  The units' last blocks, which finish them, come
-// after all others: a block then waits for blocks of lower indices only, and the finishing blocks,
-// which read what all the others hand over, are dealt to the eight XCDs in turn (blocks go to the
-// XCDs round robin; with the blocks of a unit side by side and 8 per unit every finishing block sat
-// on the same XCD: 10.5 instead of 8.5 us per call at 32 units and 1024 entries).
+// Unit and place in the unit of stream block b: the first blocks of all units, the second ones, and so
+// on.  A block then waits for blocks of lower indices only, and, as blocks go to the eight XCDs round
+// robin, the blocks of a unit share an XCD where the units are a multiple of eight (or two XCDs where they are one of four),
+// which makes the hand-over shorter, while the finishing blocks are dealt to all XCDs.  us per call, with
+// the blocks of a unit side by side but its finishing block / like this: 32 units x 1040 entries 7.6
+// / 6.9, 48 x 1040 9.5 / 8.7, 8 x 2080 9.0 / 8.6, 4 x 9000 12.2 / 11.1; with the finishing block beside the others, 8
+// blocks a unit, every finishing block sat on one XCD (2 us more).
+// kSplit > 0: the units have kSplit blocks, and no division is needed.
 struct BlockPlace { int unit, split; };
+template <int kSplit>
 __device__ __forceinline__ BlockPlace block_place(int b, int n_split, int units) {
-  const int others = (n_split - 1) * units;
-  if (n_split == 1 || b >= others) return {b - others, n_split - 1};
-  return {b / (n_split - 1), b % (n_split - 1)};
+  if constexpr (kSplit > 0) {
+    int split = 0, first = 0;
+#pragma unroll
+    for (int s = 1; s < kSplit; ++s) {
+      if (b >= s * units) { split = s; first = s * units; }
+    }
+    return {b - first, split};
+  }
+  if (n_split == 1) return {b, 0};
+  return {b % units, b / units};
 }
 
 #ifdef LAZYEV_TIMELINE
@@ -686,7 +697,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     if (kListWaves && threadIdx.x >= kBlock) return;  // (the tracking has no use for list waves)
     const int tb = blockIdx.x - n_split * units_call;
     const int n_track = a.n_track;
-    const BlockPlace at = block_place(tb, n_track, units_call);
+    const BlockPlace at = block_place<kSplit>(tb, n_track, units_call);
     const int unit = at.unit, part = at.split;
     TrackArgs k;
     if (!track_for_unit(a.track, unit, k)) return;
@@ -737,7 +748,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     __syncthreads();
   }
   const int c = lane & 15, g = lane >> 4;
-  const BlockPlace place = block_place(blockIdx.x, n_split, units_call);
+  const BlockPlace place = block_place<kSplit>(blockIdx.x, n_split, units_call);
   const int unit = place.unit, split = place.split;
   int n_old = n_old_call;
   if (slots_on) {                                  // per-sequence timing: this unit's own length
@@ -1260,10 +1271,10 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   }
   if (leader) {
     constexpr int kIn = kSplit > 1 ? kSplit - 1 : kMergeRadix - 1;   // (instances of a fixed split have one group)
-    // (for five records and more the count is kept from the compiler, which would otherwise hold so
+    // (for four records and more the count is kept from the compiler, which would otherwise hold so
     // many addresses at once that registers spill: 8 blocks per unit of 2048 entries, 14.4 us instead of 8.0)
     int n_in = kSplit > 0 ? kSplit - 1 : split - group0;
-    if (kSplit > 5) __asm__("" : "+s"(n_in));
+    if (kSplit > 4) __asm__("" : "+s"(n_in));
     const Merge<kPrecise> mg = merge_records<kIn, kPrecise>(a, recs + static_cast<size_t>(group0) * kRecWords, kRecWords, n_in, t_own,
                                         mb_own, l_own, v_own);
     const f32x4_t o4 = {mg.o[0], mg.o[1], mg.o[2], mg.o[3]};
