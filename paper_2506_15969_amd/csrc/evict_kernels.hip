@@ -2,7 +2,8 @@
 // paper), as two kernels:
 //   select  one block per unit: scores every candidate entry (all but the last W) in binary64,
 //           finds the (B-W)-th largest score with an 8-bit radix select over the score bit
-//           patterns held in LDS (beyond 8192 candidates: in the workspace), breaks ties in favour of the more recent entry, prefix-scans
+//           patterns held in registers (beyond 8192 entries in LDS, beyond 8192 candidates in the
+//           workspace), breaks ties in favour of the more recent entry, prefix-scans
 //           the keep flags into destination slots, compacts TS / MRI / pos in place and leaves
 //           the gather list (source entry of every survivor) in the workspace.
 //   move    blocks per (unit, K|V, 128-byte column part): walk the gather list in order and
@@ -11,6 +12,8 @@
 // This file is compiled with floating-point contraction off: the score is a fixed sequence of
 // individually rounded binary64 operations so that it can be reproduced bit for bit elsewhere.
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace lazyev {
 namespace {
@@ -153,6 +156,260 @@ __device__ unsigned block_exclusive_scan(unsigned v, unsigned *wave_tot, unsigne
   return base + incl - v;
 }
 
+// Entries of the unit and its step, if its eviction is due (with per-sequence timing a launch also holds units that
+// have none).
+__device__ __forceinline__ bool unit_due(const EvictArgs &a, int unit, int &n, int &t) {
+  n = a.n;
+  t = a.t;
+  if (!a.slots.prompt_len) return true;
+  const int seq = (unit % a.units_per_layer) / a.n_kv_heads;
+  const int32_t P = a.slots.prompt_len[seq], tau = a.t - a.slots.t0[seq];
+  if (P < 0 || tau < 1 || tau % a.window != 0) return false;
+  n = slot_n_old(P, tau, a.budget, a.window) + 1;
+  t = tau;
+  return n > a.budget;
+}
+
+// Score = the weight each candidate received at this step, largest over the query group: the same
+// fp32 expression the tracking uses, widened exactly.
+__device__ __forceinline__ void weight_keys(const EvictArgs &a, int unit, int n_cand, unsigned long long *keys) {
+  const float *lg = a.logits + static_cast<size_t>(unit) * a.p_stride * 8;
+  const float *st = a.stat + static_cast<size_t>(unit) * 16;
+  for (int i = threadIdx.x; i < n_cand; i += kSelBlock) {
+    const float4 sa = *reinterpret_cast<const float4 *>(lg + static_cast<size_t>(i) * 8);
+    const float4 sb = *reinterpret_cast<const float4 *>(lg + static_cast<size_t>(i) * 8 + 4);
+    const float sv[8] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
+    float best = 0.f;
+#pragma unroll
+    for (int h = 0; h < 8; ++h)
+      if (h < a.group) best = fmaxf(best, __expf(sv[h] - st[2 * h]) * st[2 * h + 1]);
+    keys[i] = static_cast<unsigned long long>(__double_as_longlong(static_cast<double>(best)));
+  }
+}
+
+// Inclusive sums over the lanes of a wave, by moves within the vector ALU: inside the rows of 16, then the last
+// lane of a row (of the lower half) into the next row (the upper half).
+__device__ __forceinline__ unsigned wave_scan(unsigned v) {
+  auto add = [&](auto ctrl, auto rows) {
+    v += static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), decltype(ctrl)::value, decltype(rows)::value, 0xF, false));
+  };
+  constexpr std::integral_constant<int, 0xF> all{};
+  add(std::integral_constant<int, 0x111>{}, all);  // row_shr:1
+  add(std::integral_constant<int, 0x112>{}, all);
+  add(std::integral_constant<int, 0x114>{}, all);
+  add(std::integral_constant<int, 0x118>{}, all);  // row_shr:8
+  add(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});   // row_bcast:15 into rows 1 and 3
+  add(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// The selection for units of at most R * kSelBlock entries.  One block per unit, so what bounds it is the chain of its
+// steps (and the scores, at 4096 entries): memory is read once, at the start (TS, MRI and pos stay in registers, R
+// entries per thread), the keys lie in registers, every wave finds the threshold's digit for itself, and the
+// destinations of all entries come from one exchange of counts.  us, before (keys in LDS, shuffles of 16 waves
+// queueing up at it for ANDs, ORs and scans, a pass over TS / MRI / pos per 1024 entries at the end, as
+// evict_select_kernel still has it) and now: 144 entries 9.2 -> 5.3, 1056 15.6 -> 7.2, 2112 17.5 -> 10.0, 256 units of 4160
+// 29.6 -> 17.1.
+// The first digit is 0 for the score 0 (the usual threshold: the entries that were never re-activated) and the
+// score in steps of 1 / 126 from 1 on (scores lie in 0 .. 2, weights in 0 .. 1), which tells keys apart better than their
+// leading byte: mostly one pass ends at the zeros or leaves at most kSmallSet keys.  The following digits are the
+// bytes, the highest first, of the keys still in play.
+template <int R>
+__global__ __launch_bounds__(kSelBlock) void evict_select_held_kernel(const EvictArgs a) {
+  extern __shared__ unsigned long long keys_lds[];      // score bit pattern of each candidate
+  __shared__ unsigned hist[3][256];                // of passes p, p + 1, p + 2: a barrier lies between the last reading
+  __shared__ unsigned long long wave_key[2][kSelWaves];   // of one, its clearing and its next use
+  __shared__ unsigned wave_kind[2][kSelWaves];     // keys of the wave in play: 0 none, 1 all wave_key, 2 several values
+  __shared__ unsigned long long small_keys[kSmallSet];
+  __shared__ unsigned small_n, moved, sel_rem, sel_cnt;
+  __shared__ unsigned long long small_thr;
+  __shared__ unsigned count[128];                  // [R][waves] ties << 16 | certain survivors
+  static_assert(R * kSelWaves <= 128 && R * kSelBlock < 65536, "counts of a unit");
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int unit = evict_unit_of(a, blockIdx.x);
+  int n, t;
+  if (!unit_due(a, unit, n, t)) return;
+  const int n_cand = n - a.window, k_keep = a.budget - a.window;
+  int32_t *ts = a.ts + static_cast<size_t>(unit) * a.capacity;
+  int32_t *mri = a.mri + static_cast<size_t>(unit) * a.capacity;
+  int32_t *pos = a.pos + static_cast<size_t>(unit) * a.capacity;
+  int32_t *src_index = a.ws.src_index + static_cast<size_t>(unit) * a.capacity;
+  int32_t v_ts[R], v_mri[R], v_pos[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int slot = r * kSelBlock + tid;
+    v_ts[r] = v_mri[r] = v_pos[r] = 0;
+    if (slot < n) { v_ts[r] = ts[slot]; v_mri[r] = mri[slot]; v_pos[r] = pos[slot]; }
+  }
+  if (tid < 256) hist[0][tid] = hist[1][tid] = hist[2][tid] = 0;
+  if (tid == 0) { small_n = 0; moved = 0; }
+
+  // scores (non-negative doubles order like their bit patterns); the slots of a thread are its own, and its
+  // loop over them stays a loop: the code of R scores in a row would have to be fetched by every launch
+  if (a.score_flags & 32) {
+    weight_keys(a, unit, n_cand, keys_lds);
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int slot = r * kSelBlock + tid;
+      if (slot < n_cand)
+        keys_lds[slot] = (static_cast<unsigned long long>(static_cast<unsigned>(t - v_ts[r])) << 32) | static_cast<unsigned>(v_mri[r]);
+    }
+#pragma unroll 1
+    for (int i = tid; i < n_cand; i += kSelBlock) {
+      const unsigned long long x = keys_lds[i];
+      keys_lds[i] = static_cast<unsigned long long>(__double_as_longlong(
+          mri_centric_score(static_cast<int32_t>(x >> 32), static_cast<int32_t>(x), a.score_flags)));
+    }
+  }
+  unsigned long long key[R];
+  unsigned alive = 0;                              // bit r: key[r] is still in play
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int slot = r * kSelBlock + tid;
+    key[r] = slot < n_cand ? keys_lds[slot] : 0ull;
+    alive |= (slot < n_cand ? 1u : 0u) << r;
+  }
+  __syncthreads();                                 // the counters are cleared
+
+  unsigned long long thr = 0;
+  unsigned k_rem = static_cast<unsigned>(k_keep);  // kept among the keys still in play ...
+  unsigned ties_total = static_cast<unsigned>(n_cand);   // ... of which there are this many
+  for (int pass = 0, pb = 0;; ++pass, pb = pb == 2 ? 0 : pb + 1) {
+    auto digit_of = [&](unsigned long long k) -> unsigned {
+      if (pass == 0) return k == 0ull ? 0u : 1u + min(static_cast<unsigned>(__longlong_as_double(static_cast<long long>(k)) * 126.0), 254u);
+      return static_cast<unsigned>(k >> (64 - 8 * min(pass, 8))) & 255u;
+    };
+    // this wave's keys in play: are they one value?  (No shuffles: those of 16 waves queue up at the LDS.)
+    unsigned long long some = 0;
+#pragma unroll
+    for (int r = R - 1; r >= 0; --r) some = (alive >> r) & 1u ? key[r] : some;
+    const unsigned long long any = __builtin_amdgcn_ballot_w64(alive != 0);
+    const int first = any ? __ffsll(static_cast<long long>(any)) - 1 : 0;
+    const unsigned long long ref =
+        (static_cast<unsigned long long>(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(some >> 32), first))) << 32) |
+        static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(some), first));
+    bool other = false;
+    unsigned zeros = 0;                            // (a third of the keys or so are 0: counted per wave)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const bool in = (alive >> r) & 1u;
+      zeros += static_cast<unsigned>(__popcll(__builtin_amdgcn_ballot_w64(in && key[r] == 0ull)));
+      other = other || (in && key[r] != ref);
+      if (in && key[r] != 0ull) atomicAdd(&hist[pb][digit_of(key[r])], 1u);
+    }
+    const bool mixed = __builtin_amdgcn_ballot_w64(other) != 0;
+    if (lane == 0) {
+      if (zeros) atomicAdd(&hist[pb][0], zeros);
+      wave_key[pass & 1][wave] = ref;
+      wave_kind[pass & 1][wave] = any == 0 ? 0u : mixed ? 2u : 1u;
+    }
+    __syncthreads();
+    {
+      const unsigned kind = lane < kSelWaves ? wave_kind[pass & 1][lane] : 0u;
+      const unsigned long long k = lane < kSelWaves ? wave_key[pass & 1][lane] : 0ull;
+      const unsigned long long single = __builtin_amdgcn_ballot_w64(kind == 1u);
+      const int at = single ? __ffsll(static_cast<long long>(single)) - 1 : 0;
+      thr = (static_cast<unsigned long long>(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(k >> 32), at))) << 32) |
+            static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(k), at));
+      // all keys in play are one value (at the latest after the last byte)
+      if (__builtin_amdgcn_ballot_w64(kind == 2u || (kind == 1u && k != thr)) == 0 || pass == 9) break;
+    }
+    // lane l of every wave takes the digits 255 - 4 l .. 252 - 4 l, the largest first
+    const uint4 h = *reinterpret_cast<const uint4 *>(&hist[pb][252 - 4 * lane]);
+    const unsigned sum = h.x + h.y + h.z + h.w;
+    unsigned above = wave_scan(sum) - sum;
+    const unsigned in_lane[4] = {h.w, h.z, h.y, h.x};
+    unsigned found = 0, rem = 0, cnt = 0;          // found: digit + 1
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      if (above < k_rem && k_rem <= above + in_lane[x]) { found = 256u - 4 * lane - x; rem = k_rem - above; cnt = in_lane[x]; }
+      above += in_lane[x];
+    }
+    const int at = __ffsll(static_cast<long long>(__builtin_amdgcn_ballot_w64(found != 0))) - 1;   // (one lane has it)
+    const unsigned digit = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(found), at)) - 1u;
+    k_rem = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(rem), at));
+    ties_total = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(cnt), at));
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (digit_of(key[r]) != digit) alive &= ~(1u << r);
+    if (pass == 0 && digit == 0u) {                // the threshold falls among the zeros
+      thr = 0;
+      break;
+    }
+    const int clear = pb == 0 ? 2 : pb - 1;        // (of the pass before: nobody reads it any more)
+    if (tid < 256) hist[clear][tid] = 0;
+    if (ties_total <= static_cast<unsigned>(kSmallSet)) {
+      // few keys left: listed, and each (four threads) counts the listed keys above it and equal to it
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if ((alive >> r) & 1u) small_keys[atomicAdd(&small_n, 1u)] = key[r];
+      __syncthreads();
+      const unsigned mine = static_cast<unsigned>(tid) >> 2;
+      const unsigned long long k = small_keys[mine < ties_total ? mine : 0];
+      unsigned gt = 0, eq = 0;
+      for (unsigned j = tid & 3; j < ties_total; j += 4) {
+        const unsigned long long other = small_keys[j];
+        gt += other > k ? 1u : 0u;
+        eq += other == k ? 1u : 0u;
+      }
+      gt += __shfl_xor(gt, 1); eq += __shfl_xor(eq, 1);
+      gt += __shfl_xor(gt, 2); eq += __shfl_xor(eq, 2);
+      if (mine < ties_total && gt < k_rem && k_rem <= gt + eq) {   // (every holder of that value writes the same)
+        small_thr = k;
+        sel_rem = k_rem - gt;
+        sel_cnt = eq;
+      }
+      __syncthreads();
+      thr = small_thr;
+      k_rem = sel_rem;
+      ties_total = sel_cnt;
+      break;
+    }
+  }
+  // thr is the threshold key; k_rem of the ties_total entries equal to it are kept, the most
+  // recent ones (largest slots) first.
+  const unsigned drop_ties = ties_total - k_rem;
+  unsigned long long definite[R], tie[R];          // of the wave's lanes
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int slot = r * kSelBlock + tid;
+    definite[r] = __builtin_amdgcn_ballot_w64(slot < n && (slot >= n_cand || key[r] > thr));
+    tie[r] = __builtin_amdgcn_ballot_w64(slot < n_cand && key[r] == thr);
+    if (lane == 0)
+      count[r * kSelWaves + wave] = (static_cast<unsigned>(__popcll(tie[r])) << 16) | static_cast<unsigned>(__popcll(definite[r]));
+    // every read precedes the writes: the loads have returned (touching the values makes the compiler wait for
+    // them; the barrier alone only drains the LDS counter), in every thread
+    __asm__ volatile("" : "+v"(v_ts[r]), "+v"(v_mri[r]), "+v"(v_pos[r]));
+  }
+  __syncthreads();
+  const unsigned c0 = 2 * lane < R * kSelWaves ? count[2 * lane] : 0u, c1 = 2 * lane < R * kSelWaves ? count[2 * lane + 1] : 0u;
+  const unsigned before = wave_scan(c0 + c1) - (c0 + c1);
+  unsigned n_moved = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int slot = r * kSelBlock + tid, e = r * kSelWaves + wave;
+    unsigned ex = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(before), e >> 1));
+    if (e & 1) ex += static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(c0), e >> 1));
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const unsigned def_before = (ex & 0xFFFFu) + static_cast<unsigned>(__popcll(definite[r] & below));
+    const unsigned tie_rank = (ex >> 16) + static_cast<unsigned>(__popcll(tie[r] & below));
+    const bool keep = ((definite[r] >> lane) & 1ull) || (((tie[r] >> lane) & 1ull) && tie_rank >= drop_ties);
+    const unsigned dst = def_before + (tie_rank > drop_ties ? tie_rank - drop_ties : 0u);
+    if (keep) {
+      ts[dst] = v_ts[r]; mri[dst] = v_mri[r]; pos[dst] = v_pos[r];
+      src_index[dst] = slot;
+    }
+    n_moved += static_cast<unsigned>(__popcll(__builtin_amdgcn_ballot_w64(keep && dst != static_cast<unsigned>(slot))));
+  }
+  // how many survivors change slot (what the row move has to copy); one writer per unit
+  if (lane == 0 && n_moved) atomicAdd(&moved, n_moved);
+  __syncthreads();
+  if (tid == 0) a.rows_moved[unit] += moved;
+}
+
+// The selection for more entries than a block holds in registers.
 // kKeysInLds: the candidates' keys fit the dynamic LDS of the launch (the usual case); otherwise
 // they go through the unit's part of the workspace (same passes over global memory, slower).
 template <bool kKeysInLds>
@@ -168,15 +425,8 @@ __global__ __launch_bounds__(kSelBlock) void evict_select_kernel(const EvictArgs
 
   const int tid = threadIdx.x;
   const int unit = evict_unit_of(a, blockIdx.x);
-  int n = a.n, t = a.t;
-  if (a.slots.prompt_len) {                        // per-sequence timing: is this unit's eviction due?
-    const int seq = (unit % a.units_per_layer) / a.n_kv_heads;
-    const int32_t P = a.slots.prompt_len[seq], tau = a.t - a.slots.t0[seq];
-    if (P < 0 || tau < 1 || tau % a.window != 0) return;
-    n = slot_n_old(P, tau, a.budget, a.window) + 1;
-    if (n <= a.budget) return;
-    t = tau;
-  }
+  int n, t;
+  if (!unit_due(a, unit, n, t)) return;
   const int n_cand = n - a.window, k_keep = a.budget - a.window;
   int32_t *ts = a.ts + static_cast<size_t>(unit) * a.capacity;
   int32_t *mri = a.mri + static_cast<size_t>(unit) * a.capacity;
@@ -187,20 +437,7 @@ __global__ __launch_bounds__(kSelBlock) void evict_select_kernel(const EvictArgs
 
   // scores (non-negative doubles order like their bit patterns)
   if (a.score_flags & 32) {
-    // the weight each candidate received at this step, largest over the query group: the same
-    // fp32 expression the tracking uses, widened exactly
-    const float *lg = a.logits + static_cast<size_t>(unit) * a.p_stride * 8;
-    const float *st = a.stat + static_cast<size_t>(unit) * 16;
-    for (int i = tid; i < n_cand; i += kSelBlock) {
-      const float4 sa = *reinterpret_cast<const float4 *>(lg + static_cast<size_t>(i) * 8);
-      const float4 sb = *reinterpret_cast<const float4 *>(lg + static_cast<size_t>(i) * 8 + 4);
-      const float sv[8] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
-      float best = 0.f;
-#pragma unroll
-      for (int h = 0; h < 8; ++h)
-        if (h < a.group) best = fmaxf(best, __expf(sv[h] - st[2 * h]) * st[2 * h + 1]);
-      keys[i] = static_cast<unsigned long long>(__double_as_longlong(static_cast<double>(best)));
-    }
+    weight_keys(a, unit, n_cand, keys);
   } else {
     for (int i = tid; i < n_cand; i += kSelBlock)
       keys[i] = static_cast<unsigned long long>(
@@ -436,7 +673,17 @@ hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) 
     n_blocks = a.units / a.units_per_layer * a.n_due * a.n_kv_heads;
   }
   if (ev) (void)hipEventRecord(ev[0], stream);
-  if (n_cand <= kLdsCandidates)
+  // as few entries per thread as hold the unit (an instance of 8 for all: 1056 entries 12.4 instead of 7.2 us, 2112 13.0 instead of 10.0); beyond 8 and
+  // its 64 KB of keys the passes go over memory
+  if (a.n <= 2 * kSelBlock)
+    hipLaunchKernelGGL(evict_select_held_kernel<2>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
+  else if (a.n <= 3 * kSelBlock)
+    hipLaunchKernelGGL(evict_select_held_kernel<3>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
+  else if (a.n <= 5 * kSelBlock)
+    hipLaunchKernelGGL(evict_select_held_kernel<5>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
+  else if (a.n <= kLdsCandidates)
+    hipLaunchKernelGGL(evict_select_held_kernel<8>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
+  else if (n_cand <= kLdsCandidates)
     hipLaunchKernelGGL(evict_select_kernel<true>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
   else
     hipLaunchKernelGGL(evict_select_kernel<false>, dim3(n_blocks), dim3(kSelBlock), 0, stream, a);
