@@ -178,7 +178,7 @@ def timeline_mode(args):
     prompt = budget, so the cache is at its budget) on the instrumented build of the library
     (liblazyev_timeline.so: every block of the fused decode kernel leaves time stamps of the
     100 MHz counter) and prints, over the blocks of the sampled launches, when the stream, the
-    ticket and the block end fall, counted from the start of the launch's first block."""
+    arrival of the other blocks' partials and the block end fall, counted from the start of the launch's first block."""
     os.environ["LAZYEV_LIBRARY"] = "liblazyev_timeline.so"
     import numpy as np
     import torch
@@ -223,7 +223,7 @@ def timeline_mode(args):
         eng.evict_all(t)                              # (fires where the schedule says so)
     n1 = eng.stats()["len"][0]
     names = ["block start", "first sub-tile multiplied", "end of wave 0's stream", "all four waves done",
-             "ticket taken", "block end"]
+             "partials complete (finishing blocks)", "block end"]
 
     def q(x):
         return {"min": round(float(np.min(x)), 2), "p50": round(float(np.median(x)), 2),
@@ -248,14 +248,15 @@ def timeline_mode(args):
     end = np.concatenate([s[0][:, 2] for s in samples])
     xcd = np.concatenate([s[3] for s in samples])
     blk = np.concatenate([s[4] for s in samples])
-    n_split = max(1, int(samples[0][0].shape[0]) // (cfg.batch * cfg.n_kv_heads))
+    n_units = cfg.batch * cfg.n_kv_heads            # (the first blocks of all units, then the second ones, ...)
+    n_split = max(1, int(samples[0][0].shape[0]) // n_units)
     res["stream_end_by_xcd"] = {str(int(x)): {"blocks_per_launch": round(float((xcd == x).sum()) / len(samples), 1),
                                               "mean": round(float(end[xcd == x].mean()), 2)}
                                 for x in np.unique(xcd)}
-    res["stream_end_by_block_of_the_unit"] = {str(j): round(float(end[blk % n_split == j].mean()), 2)
+    res["stream_end_by_block_of_the_unit"] = {str(j): round(float(end[blk // n_units == j].mean()), 2)
                                               for j in range(n_split)}
     res["xcd_of_block_index_mod_8"] = {str(j): sorted(int(x) for x in np.unique(xcd[blk % 8 == j])) for j in range(8)}
-    per_unit = [s[0][:, 2].reshape(-1, n_split) for s in samples]
+    per_unit = [s[0][:, 2].reshape(n_split, -1).T for s in samples]
     res["spread_of_a_unit's_blocks (latest - earliest stream end)"] = q(
         np.concatenate([u.max(axis=1) - u.min(axis=1) for u in per_unit]))
     fin = np.concatenate([s[1] == 1 for s in samples])

@@ -102,7 +102,7 @@ typedef struct {
 int32_t lazyev_capacity(const lazyev_config *cfg /*host*/);
 
 /* Bytes of workspace the configuration needs (split partials, two buffers of per-entry logits,
- * gather lists, counters, tickets).  0 if cfg is invalid. */
+ * gather lists, counters, records of partials).  0 if cfg is invalid. */
 size_t lazyev_workspace_size(const lazyev_config *cfg /*host*/);
 
 /* Creates a context.  The caller has already written the prompt's K/V rows to entries

@@ -1399,9 +1399,9 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //     two on all of them the bytes in flight only widen the spread of the blocks' ends (128 units x
 //     4144 entries: 44.5 with one, 46.4 with two).
 //   * only a long cache pays for the second hop that more than kMergeRadix blocks need (8 units x 2200
-//     entries: 8 blocks 8.0, 16 9.6, 32 9.7; x 6200 entries: 14.6, 12.8, 11.9).
+//     entries: 8 blocks 8.9, 16 9.7, 32 9.8; x 6200 entries: 14.8, 13.0, 11.8).
 //   * seven or eight blocks only where they do not fill the chip to the last compute unit (32 units x
-//     1200 / 2200 / 6200 entries: 6 blocks 7.9 / 10.6 / 21.4, 8 8.6 / 11.1 / 22.0; 24 units x 6200: 6 19.0, 8 18.0).
+//     1040 / 2200 / 6200 entries: 6 blocks 7.0 / 10.2 / 20.9, 8 7.6 / 10.3 / 21.4; 24 units x 6200: 6 19.0, 8 18.0).
 //   * two sub-tiles or more per wave (8 units x 600 entries: 4 blocks 6.0, 5 6.0; x 350: 2 5.3, 4 5.5),
 //     but two blocks from a unit's fifth sub-tile on.
 //   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to
