@@ -201,6 +201,11 @@ struct Rows {
     u32x4_t v[kV];
   };
 };
+// Two bf16 numbers with infinities and NaNs replaced by zero.
+__device__ __forceinline__ unsigned finite_bf16(unsigned w) {
+  const unsigned top = ((w & 0x7FFF7FFFu) + 0x00800080u) & 0x80008000u;   // of the halves whose exponent is all ones
+  return w & ~((top >> 15) * 0xFFFFu);
+}
 template <bool kPrecise>
 __device__ __forceinline__ float exp_of(float x) {
   if constexpr (kPrecise) return expf(x);
@@ -958,9 +963,10 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     qb[kk] = c < G ? v : u32x4_t{0, 0, 0, 0};
   }
 
-  // kMore (a std::bool_constant): the wave has a sub-tile kDepth after this one and requests it here
-  auto compute = [&](SubTile &t, int it, auto more_tag) {
-    constexpr bool kMore = decltype(more_tag)::value;
+  // kMore (a std::bool_constant): the wave has a sub-tile kDepth after this one and requests it here.
+  // kAgain: the wave goes over its run once more because an accumulator became NaN (see below)
+  auto compute = [&](SubTile &t, int it, auto more_tag, auto again_tag) {
+    constexpr bool kMore = decltype(more_tag)::value, kAgain = decltype(again_tag)::value;
     const int sub = sub_of(it);
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     if constexpr (R::kF32) {
@@ -1020,7 +1026,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     // logits of the sub-tile -> [entry][head] in LDS -> 512 contiguous bytes of the workspace
     // logits of the sub-tile -> [entry][head] in LDS; written out when the wave's run ends (a
     // store among the loads would hold up the in-order load counter)
-    if (c < kHeadPad) {
+    if (!kAgain && c < kHeadPad) {
       float *dst = my_logits + (it - seg0) * (16 * kHeadPad);
 #pragma unroll
       for (int i = 0; i < 4; ++i) dst[(4 * g + i) * kHeadPad + c] = s[i];
@@ -1043,6 +1049,22 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[i] = exp_of<kPrecise>(s[i] - m_ref);
     lsum += (p[0] + p[1]) + (p[2] + p[3]);
+    if constexpr (kPrecise && !kMore) {
+      // The unit's last sub-tile: rows beyond the cache are copies of the appended one with a weight of zero, and
+      // zero times an infinite element is NaN
+      if (sub == n_sub - 1) {                      // wave-uniform
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (e0 + i < n1) continue;
+          if constexpr (R::kF32) {
+#pragma unroll
+            for (int h = 0; h < D / 64; ++h) t.v[i * (D / 64) + h] = u32x4_t{0, 0, 0, 0};
+          } else {
+            t.v[i / 2][2 * (i % 2)] = t.v[i / 2][2 * (i % 2) + 1] = 0;
+          }
+        }
+      }
+    }
     if constexpr (R::kF32) {
       // lane (c, g) holds the weights of head c for the entries 4g .. 4g+3: the A operand of the
       // product over entries 4g' + i, g' = 0..3, is p[i].  The sub-tile's 16 terms are summed on their
@@ -1086,8 +1108,10 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
       vb[0] = __builtin_amdgcn_perm(v_word(1), v_word(0), sel);
       vb[1] = __builtin_amdgcn_perm(v_word(3), v_word(2), sel);
 #pragma unroll
-      for (int x = 0; x < kTerms; ++x)
+      for (int x = 0; x < kTerms; ++x) {
         o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa[x], __builtin_bit_cast(s16x4_t, vb), o[e], 0, 0, 0);
+        if (kAgain && x == 0) { vb[0] = finite_bf16(vb[0]); vb[1] = finite_bf16(vb[1]); }
+      }
     }
     }
     if constexpr (kMore) load_v(t, it + R::kDepth);
@@ -1184,30 +1208,49 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   // unconditionally: no branch between the loads, exact load counts for the waits)
   if constexpr (R::kDepth == 1) {
     for (int it = 0; it + 1 < cnt; ++it) {
-      compute(buf[0], it, std::true_type{});
+      compute(buf[0], it, std::true_type{}, std::false_type{});
 #ifdef LAZYEV_TIMELINE
       if (it == 0) STAMP(1);
 #endif
       segment_end(it);
     }
-    if (cnt > 0) compute(buf[0], cnt - 1, std::false_type{});
+    if (cnt > 0) compute(buf[0], cnt - 1, std::false_type{}, std::false_type{});
   } else {
     int it = 0;
     for (; it + 3 < cnt; it += 2) {
-      compute(buf[0], it, std::true_type{});
+      compute(buf[0], it, std::true_type{}, std::false_type{});
       segment_end(it);
-      compute(buf[1], it + 1, std::true_type{});
+      compute(buf[1], it + 1, std::true_type{}, std::false_type{});
       segment_end(it + 1);
     }
     if (it + 2 < cnt) {
-      compute(buf[0], it, std::true_type{});
+      compute(buf[0], it, std::true_type{}, std::false_type{});
       segment_end(it);
-      compute(buf[1], it + 1, std::false_type{});
+      compute(buf[1], it + 1, std::false_type{}, std::false_type{});
       segment_end(it + 1);
-      compute(buf[0], it + 2, std::false_type{});
+      compute(buf[0], it + 2, std::false_type{}, std::false_type{});
     } else {
-      if (it < cnt) { compute(buf[0], it, std::false_type{}); segment_end(it); }
-      if (it + 1 < cnt) compute(buf[1], it + 1, std::false_type{});
+      if (it < cnt) { compute(buf[0], it, std::false_type{}, std::false_type{}); segment_end(it); }
+      if (it + 1 < cnt) compute(buf[1], it + 1, std::false_type{}, std::false_type{});
+    }
+  }
+  if constexpr (kPrecise && !R::kF32) {
+    // The second and third bf16 terms of a weight may be negative or zero, so an infinite element of V, which
+    // the weight itself would leave infinite, becomes NaN.  Such a wave goes over its run once more, these products
+    // left out of it (one look at the accumulators per run; a look at the V words would be on the way of every sub-tile).
+    float any = 0.f;
+#pragma unroll
+    for (int e = 0; e < R::kAcc; ++e) any += (o[e][0] + o[e][1]) + (o[e][2] + o[e][3]);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(any != any) != 0, 0)) {   // wave-uniform
+      m_ref = -INFINITY;
+      lsum = 0.f;
+#pragma unroll
+      for (int e = 0; e < R::kAcc; ++e) o[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int it = 0; it < cnt; ++it) {
+        load_k(buf[0], it);
+        load_v(buf[0], it);
+        compute(buf[0], it, std::false_type{}, std::true_type{});
+      }
     }
   }
   STAMP(2);

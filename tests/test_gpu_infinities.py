@@ -1,0 +1,57 @@
+"""Infinite and NaN elements in the caches and in the appended rows: the single-launch kernel against the split +
+merge kernels (variant 0), which multiply every weight in fp32.  The same elements of the output are +inf, -inf, NaN
+and finite; finite ones agree."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+ROWS = [("fp32", 64), ("fp32", 128), ("bf16", 64)]
+
+
+def _run(lazyev_lib, variant, dtype, d, place, value, N, H=2, G=4, S=2, steps=2):
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    eng = lazyev_lib.LazyEviction(1, S, H * G, H, d, N + 40, 8, N, 0.01, dtype=dtype)
+    eng.k_cache[:, :, :, :N].normal_(generator=gen)
+    eng.v_cache[:, :, :, :N].normal_(generator=gen)
+    cols = torch.arange(0, d, 5, device="cuda")    # columns in every register of a row
+    sign = torch.where(cols % 2 == 0, value, -value).to(dtype)
+    q, kn, vn = (torch.empty((steps, S, h, d), device="cuda").normal_(generator=gen).to(dtype) for h in (H * G, H, H))
+    if place == "cached V":
+        eng.v_cache[0, 0, :, N // 2, cols] = sign
+    elif place == "first V":
+        eng.v_cache[0, :, :, 0, cols] = sign
+    elif place == "appended V":
+        vn[0, :, 0, cols] = sign
+    elif place == "cached K":
+        eng.k_cache[0, 0, 0, N // 3, 3] = value
+    elif place == "query":
+        q[0, 1, 2, 7] = value
+    eng.init()
+    eng.set_variant(variant)
+    if N > 2000:                                   # one block per unit: runs whose logits leave LDS in segments
+        eng.set_target_blocks(S * H)
+    out = torch.zeros((steps, S, H * G, d), dtype=dtype, device="cuda")
+    for t in range(1, steps + 1):
+        eng.decode_step(0, t, q[t - 1], kn[t - 1], vn[t - 1], out[t - 1])
+    act = eng.stats()["n_activations"]
+    state = [x[:, :, :, :N + steps].clone() for x in (eng.ts, eng.mri)]
+    eng.close()
+    return out.double(), state, act
+
+
+@pytest.mark.parametrize("dtype,d", ROWS)
+@pytest.mark.parametrize("place", ["cached V", "first V", "appended V", "cached K", "query"])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("N", [3, 15, 64, 333, 2600])
+def test_infinite_elements(lazyev_lib, dtype, d, place, value, N):
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    (want, state0, act0), (got, state1, act1) = (_run(lazyev_lib, v, dt, d, place, value, N) for v in (0, 1))
+    assert torch.equal(got.isnan(), want.isnan())
+    assert torch.equal(got.isposinf(), want.isposinf()) and torch.equal(got.isneginf(), want.isneginf())
+    assert (want.isposinf().any() and want.isneginf().any()) if place.endswith("V") and value == float("inf") else want.isnan().any()
+    ok = want.isfinite()
+    # two orders of fp32 sums of N + 2 terms, of unit size together; bf16: one rounding of each of two results
+    tol = (N + 2) * 2.0 ** -23 if dt == torch.float32 else 2.0 ** -7
+    assert float((got - want)[ok].abs().max()) < tol * max(1.0, float(want[ok].abs().max()))
+    assert act0 == act1 and all(torch.equal(x, y) for x, y in zip(state0, state1))
