@@ -15,7 +15,7 @@
 //   track  the four waves of a block keep NB tiles of 16 keys each in registers and walk
 //          the (query tile, head) pairs from the block's own position upwards together.  The
 //          largest logarithm of the key's weight over the heads of the group decides (exp is monotone): one
-//          maximum per logit and head, one exponential and one compare with alpha per weight
+//          maximum per logit and head, one compare with the logarithm of alpha per weight
 //          after the group's last head.  The activations of each key are then applied in order
 //          of the query position (one key per lane).
 // The streamed tiles (keys in the first kernel, queries in the second) are fetched once per block,
@@ -416,21 +416,38 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
     if (++h == G) { h = 0; ++it; }
   };
   auto weight = [&](float lw) { return __builtin_amdgcn_exp2f(R::kApart ? lw : lw * c2); };
-  // The logarithms from which on the weight is >= alpha, so that the test is one comparison and no exponential:
-  // the first float x with weight(x) >= alpha, found by stepping from the logarithm of alpha (which is
-  // off by a few floats at most; alphas below the normal range count as the smallest normal number, like
-  // the weights there).
+  // The logarithm from which on the weight is >= alpha, so that the test is one comparison and no exponential:
+  // the first float x with weight(x) >= alpha (alphas below the normal range count as the smallest normal number, like
+  // the weights there).  It lies within a few floats of the logarithm of alpha, but for alphas close to 1: there
+  // hundreds of floats x have one weight, at 1 some hundred million.  64 floats around the logarithm are tried
+  // at once; if it is not among them, all floats are searched in their order, u = 0 .. 2^32 - 1, 64 places at a time
+  // (weight never falls from a float to the next: v_exp_f32 tried on all of them).
   // alpha = 0: every key that is no newer (amax is -inf where none was seen).
   float reach = -FLT_MAX;
   if (a.alpha > 0.f) {
     const float alpha = max_f32(a.alpha, 0x1p-126f);
-    auto step = [](float x, int up) {              // the next float above (up = 1) or below (-1)
-      const int i = __float_as_int(x);
-      return x == 0.f ? __int_as_float(up > 0 ? 1 : static_cast<int>(0x80000001u)) : __int_as_float(i + ((i >= 0) == (up > 0) ? 1 : -1));
+    auto float_at = [](unsigned u) {             // (from -FLT_MAX to +inf, the ends repeated)
+      u = min(max(u, 0x00800000u), 0xFF800000u);
+      return __uint_as_float((u >> 31) ? u ^ 0x80000000u : ~u);
     };
-    reach = __builtin_amdgcn_logf(alpha) / (R::kApart ? 1.f : c2);
-    for (int n = 0; n < 64 && weight(reach) >= alpha; ++n) reach = step(reach, -1);
-    for (int n = 0; n < 128 && !(weight(reach) >= alpha); ++n) reach = step(reach, 1);
+    auto under = [&](unsigned u, int shift) {    // the lanes whose place has a weight < alpha
+      return __builtin_amdgcn_ballot_w64(weight(float_at(u + (static_cast<unsigned>(lane) << shift))) < alpha);
+    };
+    const unsigned guess = __float_as_uint(__builtin_amdgcn_logf(alpha) / (R::kApart ? 1.f : c2));
+    unsigned below = ((guess >> 31) ? ~guess : guess ^ 0x80000000u) - 32u;
+    unsigned long long m = under(below, 0);
+    if ((m & 1) == 0 || (m >> 63) != 0) {        // (wave-uniform)
+      below = 0;
+      m = 1;
+#pragma unroll 1
+      for (int s = 26; s >= -4; s -= 6) {
+        const int shift = max(s, 0);
+        m = under(below, shift);
+        below += static_cast<unsigned>(__popcll(m) - 1) << shift;
+      }
+      m = 1;
+    }
+    reach = float_at(below + static_cast<unsigned>(__popcll(m)));
   }
   // amax[4 n + i]: largest logarithm of a weight over the heads seen so far of the current query tile, for key
   // row 4 g + i of key tile n and query column c (-inf: the key is newer than the query)
