@@ -155,6 +155,9 @@ int lazyev_prefill_track_seq(lazyev_ctx *ctx, int32_t layer, int32_t seq, const 
  * p_out or p_override is given.  A caller that reads ts / mri / pos itself calls lazyev_stats
  * first.
  * t must be the layer's previous step + 1 (first step is 1).
+ * A call on a stream that is being captured into a HIP graph is recorded with the step, entry and
+ * pointers it was made with, and the context goes on from there; every replay computes `out` and
+ * the appended rows from what the pointers hold then.
  * p_out (device, nullable): receives the fp32 probabilities the threshold test used, entries
  *   [0, N+1) of each row.
  * p_override (device, nullable): probabilities to threshold INSTEAD of the computed ones (the

@@ -565,6 +565,9 @@ __device__ __forceinline__ void write_unit_row(const DecodeArgs &a, int unit, co
 // started in index order and a block waits for blocks of lower indices only, so every wait ends;
 // it is bounded all the same (spin_ticks of the 100 MHz counter), after which the block raises the
 // workspace's fault word and goes on.
+// The number is an argument, so a captured call has the same one in every replay and would find the records
+// of the replay before complete: a call that is being captured has its records cleared by a launch
+// before it (see lazyev_decode_step).
 // A unit's blocks form groups of kMergeRadix; the last block of a group (its leader) merges the
 // group, and the unit's last block, a leader itself, merges what the other leaders hand over: one
 // hop for up to kMergeRadix blocks, two for up to kFusedSplitMax.  A hop is one memory round trip
@@ -649,10 +652,10 @@ __device__ __forceinline__ Merge<kPrecise> merge_records(const DecodeArgs &a, co
   return mg;
 }
 
-__global__ void clear_records_kernel(unsigned long long *rec, size_t n_words) {
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n_words;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x)
-    rec[i] = 0;
+// The first n_records records of every unit (block b: unit b) as before any launch.
+__global__ __launch_bounds__(kBlock) void clear_records_kernel(unsigned long long *rec, int rec_per_unit, int n_records) {
+  unsigned long long *mine = rec + static_cast<size_t>(blockIdx.x) * rec_per_unit * kRecWords;
+  for (int i = threadIdx.x; i < n_records * kRecWords; i += kBlock) mine[i] = 0;
 }
 
 // ------------------------------------------------------------------------------- the kernel
@@ -1468,8 +1471,10 @@ int decode_fused_records_per_unit(int units) {
   return r < kMergeRadix ? kMergeRadix : r > kFusedSplitMax ? kFusedSplitMax : r;
 }
 
-hipError_t launch_clear_records(unsigned long long *rec, size_t n_words, hipStream_t stream) {
-  hipLaunchKernelGGL(clear_records_kernel, dim3(256), dim3(256), 0, stream, rec, n_words);
+hipError_t launch_clear_records(unsigned long long *rec, int units, int rec_per_unit, int n_records, hipStream_t stream) {
+  if (!rec || units < 1 || n_records < 0 || n_records > rec_per_unit) return hipErrorInvalidValue;
+  if (n_records == 0) return hipSuccess;
+  hipLaunchKernelGGL(clear_records_kernel, dim3(units), dim3(kBlock), 0, stream, rec, rec_per_unit, n_records);
   return hipGetLastError();
 }
 

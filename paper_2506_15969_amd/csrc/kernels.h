@@ -200,7 +200,7 @@ int decode_fused_head_pad();
 size_t decode_fused_record_bytes();           // one stamped record
 int decode_fused_records_per_unit(int units);
 int decode_fused_split(int units, int n_sub);   // blocks per unit of a call over n_sub sub-tiles of 16 entries
-hipError_t launch_clear_records(unsigned long long *rec, size_t n_words, hipStream_t stream);
+hipError_t launch_clear_records(unsigned long long *rec, int units, int rec_per_unit, int n_records, hipStream_t stream);
 hipError_t launch_track(const TrackArgs &k, hipStream_t stream);
 hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stream);
 int decode_fused_log_words_max();                // cache entries / 32 up to which the fused kernel can log

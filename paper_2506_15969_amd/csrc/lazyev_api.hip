@@ -548,12 +548,20 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
   a.ws = ctx->ws;
   if (kind == 4) {
     // the number of this launch stamps the partials its blocks hand over; 0 is what the records
-    // hold before any launch, so after a wrap-around they are cleared and the count restarts
-    if (++ctx->launch_seq == 0) {
-      const hipError_t ec = lazyev::launch_clear_records(
-          ctx->ws.part_rec, static_cast<size_t>(ctx->units) * a.rec_per_unit * lazyev::decode_fused_record_bytes() / 8, ctx->stream);
+    // hold before any launch, so after a wrap-around they are cleared and the count restarts.  A
+    // call that is being captured will be launched with one number again and again: the records it
+    // hands over go back to 0 before each time (the default stream cannot be captured)
+    const bool wrapped = ++ctx->launch_seq == 0;
+    if (wrapped) ctx->launch_seq = 1;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (ctx->stream && a.n_split > 1) {
+      const hipError_t ec = hipStreamIsCapturing(ctx->stream, &capture);
       if (ec != hipSuccess) return fail_hip(ctx, ec);
-      ctx->launch_seq = 1;
+    }
+    if (wrapped || capture != hipStreamCaptureStatusNone) {
+      const hipError_t ec = lazyev::launch_clear_records(ctx->ws.part_rec, ctx->units, a.rec_per_unit,
+                                                         wrapped ? a.rec_per_unit : a.n_split, ctx->stream);
+      if (ec != hipSuccess) return fail_hip(ctx, ec);
     }
     a.seq = ctx->launch_seq;
     a.spin_ticks = ctx->spin_ticks;
