@@ -997,7 +997,9 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     u32x4_t ka[R::kK];
     {
       u32x4_t *stage = stage_lds[wave];
-      const int ch = lane % R::kLanes, r0 = lane / R::kLanes;
+      int here = lane;
+      if constexpr (kLong && !kMore) __asm__ volatile("" : "+v"(here));   // (addresses of its own: see segment_candidates)
+      const int ch = here % R::kLanes, r0 = here / R::kLanes, c = here & 15, g = here >> 4;
 #pragma unroll
       for (int j = 0; j < R::kK; ++j) {
         const int r = j * (64 / R::kLanes) + r0;
@@ -1134,7 +1136,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   };
   // candidates among this wave's sub-tiles it_a .. it_b - 1 (their logits are in LDS from slot 0
   // on) under the cuts of the eight heads -> records in the block's region
-  auto emit_candidates = [&](int it_a, int it_b, const float (&cut)[kHeadPad]) {
+  auto emit_candidates = [&](int it_a, int it_b, int lane, const float (&cut)[kHeadPad]) {
     float *region = a.logits_out + (static_cast<size_t>(unit) * a.p_stride +
                                     static_cast<size_t>(split) * fused_part_cap(n_old, n_split)) * kHeadPad;
     const int e_in = lane & 15;
@@ -1173,6 +1175,12 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   // so far: the sums only grow, so p <= exp(s - lse) holds with the log-sum-exp of any subset of
   // the entries at any earlier time.
   auto segment_candidates = [&](int it_a, int it_b) {
+    // (the lane's number is worked out again, hidden from the compiler, which would otherwise keep addresses that
+    // depend on it in registers through the stream and spill one: 64 units x 6200 entries 41.3 us a call, 40.7 without
+    // scratch; 24 units x 16400 44.2 / 43.6)
+    int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    __asm__ volatile("" : "+v"(lane));
+    const int c = lane & 15, g = lane >> 4;
     float ls = lsum;
     ls = sum_over_lane_groups(ls);
     if (g == 0 && c < kHeadPad) run_lse[wave][c] = ls > 0.f ? m_ref + __logf(ls) : -INFINITY;
@@ -1195,7 +1203,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
 #pragma unroll
     for (int h = 0; h < kHeadPad; ++h)
       cut[h] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cut_h), h));
-    emit_candidates(it_a, it_b, cut);
+    emit_candidates(it_a, it_b, lane, cut);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the LDS slots are written again next
     __builtin_amdgcn_wave_barrier();
   };
