@@ -23,8 +23,9 @@ extern "C" {
  *     64..256; default 128).
  *   lazyev_set_target_blocks: stream blocks per layer call the single-launch attention kernel
  *     aims for, taken literally: each unit gets round(n_blocks / units) blocks, at least one
- *     and at most 64 (8 from 64 units on, ceil(512 / units) between: as many as the workspace holds
- *     records for).  Until this is called the library sizes the split from the number of units
+ *     and at most 64, and no more than the workspace has records for: one per block but the last,
+ *     12 KB each, in the area of the vector-ALU kernel's partials (20 blocks for units of 2112
+ *     entries, 7 query heads of 128; never fewer than the library's own choice).  Until this is called the library sizes the split from the number of units
  *     and the cache length (about one block per compute unit).
  * Errors: EINVAL. */
 int lazyev_set_chunk(lazyev_ctx *ctx, int32_t chunk);

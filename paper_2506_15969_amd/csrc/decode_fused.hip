@@ -1473,10 +1473,18 @@ int decode_fused_split(int units, int n_sub) {
   return n < by_work ? n : by_work;
 }
 
-int decode_fused_records_per_unit(int units) {
-  // as many as a unit can have blocks, as long as that keeps the records of all units within a few MB
-  const int r = (2 * 256 + units - 1) / units;
-  return r < kMergeRadix ? kMergeRadix : r > kFusedSplitMax ? kFusedSplitMax : r;
+// A unit of n blocks hands over n - 1 records.  decode_fused_split has at most 512 blocks for all units together (6 MB
+// of records); lazyev_set_target_blocks may ask for more, as far as the area that is there anyway holds them.
+int decode_fused_records_needed(int units, int capacity) {
+  const int by_length = ((capacity + 15) / 16 + 3) / 4, by_units = (2 * 256 + units - 1) / units;
+  const int n = by_length < by_units ? by_length : by_units;
+  return (n < kFusedSplitMax ? n : kFusedSplitMax) - 1;
+}
+int decode_fused_records_held(int units, int capacity, size_t bytes) {
+  const int by_length = ((capacity + 15) / 16 + 3) / 4;
+  const int most = (by_length < kFusedSplitMax ? by_length : kFusedSplitMax) - 1;
+  const size_t n = bytes / (decode_fused_record_bytes() * units);
+  return n < static_cast<size_t>(most) ? static_cast<int>(n) : most;
 }
 
 hipError_t launch_clear_records(unsigned long long *rec, int units, int rec_per_unit, int n_records, hipStream_t stream) {
@@ -1526,7 +1534,7 @@ hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stre
 hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) {
   const int units = a.batch * a.n_kv_heads;
   if (a.group > kHeadPad || a.n_split < 1 ||
-      a.n_split > kFusedSplitMax || a.n_split > a.rec_per_unit || !a.logits_out ||
+      a.n_split > kFusedSplitMax || a.n_split > a.rec_per_unit + 1 || !a.logits_out ||
       !a.ws.part_rec || !a.ws.fault || a.seq == 0 ||
       !a.stat_out || a.p_stride < (a.n_old + 16) / 16 * 16 ||
       (a.track.valid && (a.track.units != units || !a.track.logits || !a.track.stat ||

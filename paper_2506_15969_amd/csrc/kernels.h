@@ -13,6 +13,7 @@ struct Workspace {
   float    *part_ml;      // [units][n_split_max][2][G]  partial row max, partial row sum
   float    *p_tilde;      // [batch][n_q_heads][p_stride] exp(s - partial max) of every entry
                           // (split + merge kernels); the first logits buffer lies over it
+                          // (a call uses the three arrays above or the records, logits and lists below)
   float    *logits[2];    // [units][p_stride][8]        fused kernel: scaled logits, double-buffered
   int32_t  *cand_index[2]; // [units][p_stride]          fused kernel, groups of 8: entry indices of the candidate records
   float    *stat[2];      // [units][8][2]               fused kernel: softmax max and 1 / sum per head
@@ -22,7 +23,7 @@ struct Workspace {
   unsigned long long *activations;  // [n_layers][units][slice_max]  running activation counts
   unsigned long long *rows_moved;   // [n_layers][units]             entries an eviction moved to a new slot
   unsigned long long *part_rec;     // [units][rec_per_unit][fused record]  fused kernel: the partials that
-                                    // blocks hand over as stamped records
+                                    // blocks hand over as stamped records; lies over part_acc and part_ml
   int32_t  *fault;        // [1]                         set when a block gave up waiting for a record
   unsigned long long *hist;         // [LAZYEV_MAX_HIST_BINS]  MRI histogram under construction
 };
@@ -116,7 +117,7 @@ struct DecodeArgs {
   const float *p_override;
   Workspace ws;
   unsigned long long *activation_counter;   // this layer's [units][slice_max] counters
-  int32_t rec_per_unit;                     // fused kernel: records per unit in ws.part_rec (the most blocks a unit can have)
+  int32_t rec_per_unit;                     // fused kernel: records per unit in ws.part_rec (a unit can have one block more)
   int32_t n_track;                          // fused kernel: tracking blocks per unit (when a call is tracked)
   uint32_t seq;                             // fused kernel: number of this launch (never 0), the stamp of its records
   uint32_t spin_ticks;                      // fused kernel: longest wait for a record, in 10 ns ticks
@@ -173,7 +174,7 @@ struct PrefillArgs {
   float *stat;                      // [units][group][p16] per (head, position), workspace: -(log-sum-exp of the
                                     // scaled logits) / scale; of other rows than 128 x bf16 its larger part in
                                     // units of log 2, the rest in stat2
-  float *stat2;
+  float *stat2;                     // (null for rows of 128 x bf16)
   int4 *seg;                        // [segments][units][prompt_len], workspace: what segments of the queries leave of a key
   int32_t segments;                 // most segments the area holds; of a launch: its segments ...
   int32_t seg_tiles, seg_block;     // ... of seg_tiles query tiles of 16 each, and the keys of a block
@@ -198,7 +199,8 @@ int decode_fused_run_max();
 bool decode_fused_compact_fits(int n_old, int n_split, int p_stride, int group);
 int decode_fused_head_pad();
 size_t decode_fused_record_bytes();           // one stamped record
-int decode_fused_records_per_unit(int units);
+int decode_fused_records_needed(int units, int capacity);   // most records per unit that decode_fused_split asks for
+int decode_fused_records_held(int units, int capacity, size_t bytes);   // most records per unit of use that `bytes` hold for all units
 int decode_fused_split(int units, int n_sub);   // blocks per unit of a call over n_sub sub-tiles of 16 entries
 hipError_t launch_clear_records(unsigned long long *rec, int units, int rec_per_unit, int n_records, hipStream_t stream);
 hipError_t launch_track(const TrackArgs &k, hipStream_t stream);

@@ -4,6 +4,7 @@
 #include "lazyev.h"
 #include "lazyev_bench.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -40,6 +41,8 @@ struct lazyev_ctx {
   int device;                       // the device that was current at lazyev_init
   int32_t *static_scratch;          // that device's copy of `scratch` (see static_scratch_of)
   uint32_t launch_seq;              // fused kernel: launches so far (the stamp of handed-over partials)
+  int32_t rec_per_unit;             // records of handed-over partials per unit ...
+  int32_t rec_clean;                // ... of which the first ones hold nothing but what launches of earlier numbers left
   uint32_t spin_ticks;              // fused kernel: longest wait for such a partial, 10 ns ticks
   // fused kernel: the call whose tracking has not been applied yet, and the buffer pair in turn
   lazyev::TrackArgs pend;
@@ -110,9 +113,9 @@ int32_t capacity_of(const lazyev_config *c) {
 size_t fused_p_stride(int32_t capacity) { return static_cast<size_t>((capacity + 15) / 16 * 16) + 65 * 64; }
 
 struct Layout {
-  size_t part_acc, part_ml, p_tilde, logits1, cand_index, stat, prefill_stat, src_index, sel_keys, bitlog, activations, rows_moved, records, fault, hist, slots, total;
+  size_t part_acc, part_ml, p_tilde, logits1, cand_index, stat, prefill_stat, src_index, sel_keys, bitlog, activations, rows_moved, fault, hist, slots, total;
   int32_t log_words, log_slots;     // 0: no activation log for this shape
-  int32_t n_split_max;
+  int32_t n_split_max, rec_per_unit;
 };
 
 Layout layout_of(const lazyev_config *c) {
@@ -124,6 +127,10 @@ Layout layout_of(const lazyev_config *c) {
   size_t off = 0;
   l.part_acc = off; off = align_up(off + units * l.n_split_max * g * c->head_dim * sizeof(float));
   l.part_ml = off;  off = align_up(off + units * l.n_split_max * 2 * g * sizeof(float));
+  // the stamped records of partials of the single-launch kernel lie over these two (a call needs one or the other)
+  const int rec_needed = lazyev::decode_fused_records_needed(static_cast<int>(units), static_cast<int>(cap));
+  off = std::max(off, align_up(units * rec_needed * lazyev::decode_fused_record_bytes()));
+  l.rec_per_unit = lazyev::decode_fused_records_held(static_cast<int>(units), static_cast<int>(cap), off);
   // two logits buffers of [units][fused_p_stride][8] floats; the split + merge kernels use the
   // first as [batch][n_q_heads][C16]
   const size_t logits_bytes = units * fused_p_stride(static_cast<int32_t>(cap)) * 8 * sizeof(float);
@@ -133,9 +140,11 @@ Layout layout_of(const lazyev_config *c) {
   l.cand_index = off;
   if (g == 8) off = align_up(off + 2 * units * fused_p_stride(static_cast<int32_t>(cap)) * sizeof(int32_t));
   l.stat = off;     off = align_up(off + 2 * units * 16 * sizeof(float));
-  // softmax statistics of every (unit, head, prompt position) for the tracking over the prompt
+  // softmax statistics of every (unit, head, prompt position) for the tracking over the prompt, of other rows than
+  // 128 x bf16 in two parts
   l.prefill_stat = off;                            // (the longest prompt a slot can hold: capacity - window)
-  off = align_up(off + 2 * units * 8 * ((cap - c->window + 15) / 16 * 16) * sizeof(float));
+  const size_t stat_parts = c->dtype == LAZYEV_DTYPE_BF16 && c->head_dim == 128 ? 1 : 2;
+  off = align_up(off + stat_parts * units * 8 * ((cap - c->window + 15) / 16 * 16) * sizeof(float));
   l.src_index = off; off = align_up(off + static_cast<size_t>(c->n_layers) * units * cap * sizeof(int32_t));   // (all layers may be evicted in one go)
   // score keys of the selection, only if an eviction can have more candidates than LDS holds
   l.sel_keys = off;
@@ -152,10 +161,7 @@ Layout layout_of(const lazyev_config *c) {
   }
   l.activations = off; off = align_up(off + static_cast<size_t>(c->n_layers) * units * lazyev::decode_slice_max() * sizeof(unsigned long long));
   l.rows_moved = off; off = align_up(off + static_cast<size_t>(c->n_layers) * units * sizeof(unsigned long long));
-  // fused kernel: stamped records of the partials that a unit's blocks hand over (zero at first:
-  // no launch has the number 0), and the word a block raises when it gives up waiting for one
-  l.records = off;
-  off = align_up(off + units * lazyev::decode_fused_records_per_unit(static_cast<int>(units)) * lazyev::decode_fused_record_bytes());
+  // fused kernel: the word a block raises when it gives up waiting for a record
   l.fault = off; off = align_up(off + sizeof(int32_t));
   l.hist = off; off = align_up(off + LAZYEV_MAX_HIST_BINS * sizeof(unsigned long long));
   l.slots = off; off = align_up(off + 3 * static_cast<size_t>(c->batch) * sizeof(int32_t));
@@ -394,7 +400,9 @@ int lazyev_init(const lazyev_config *cfg, lazyev_ctx **out) {
   ctx->pend_layer = -1;
   ctx->ws.activations = reinterpret_cast<unsigned long long *>(base + l.activations);
   ctx->ws.rows_moved = reinterpret_cast<unsigned long long *>(base + l.rows_moved);
-  ctx->ws.part_rec = reinterpret_cast<unsigned long long *>(base + l.records);
+  ctx->ws.part_rec = reinterpret_cast<unsigned long long *>(base + l.part_acc);
+  ctx->rec_per_unit = l.rec_per_unit;
+  ctx->rec_clean = std::min(l.rec_per_unit, lazyev::decode_fused_records_needed(ctx->units, ctx->capacity));
   ctx->ws.fault = reinterpret_cast<int32_t *>(base + l.fault);
   ctx->launch_seq = 0;
   ctx->spin_ticks = 2000000;           // 20 ms of the 100 MHz counter
@@ -408,8 +416,10 @@ int lazyev_init(const lazyev_config *cfg, lazyev_ctx **out) {
   if (ctx->chunk > lazyev::decode_chunk_max()) { delete ctx; return LAZYEV_EINVAL; }
   if (static_scratch_of(&ctx->device, &ctx->static_scratch) != hipSuccess) { delete ctx; return LAZYEV_EHIP; }
 
-  // activation counters, moved-row counters, records and the fault word lie next to each other
+  // activation counters, moved-row counters and the fault word lie next to each other
   hipError_t e = hipMemsetAsync(ctx->ws.activations, 0, l.total - l.activations, ctx->stream);
+  if (e == hipSuccess)                             // (0: no launch has that number)
+    e = lazyev::launch_clear_records(ctx->ws.part_rec, ctx->units, ctx->rec_per_unit, ctx->rec_clean, ctx->stream);
   if (e == hipSuccess)
     e = lazyev::launch_init_state(cfg->ts, cfg->mri, cfg->pos,
                                   static_cast<int64_t>(cfg->n_layers) * ctx->units, ctx->capacity,
@@ -491,8 +501,8 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
     if (!ctx->target_blocks_set) n_split = lazyev::decode_fused_split(ctx->units, n_sub);
     if (n_split > (n_sub + 3) / 4) n_split = (n_sub + 3) / 4;
     if (n_split > lazyev::decode_fused_split_max()) n_split = lazyev::decode_fused_split_max();
-    a.rec_per_unit = lazyev::decode_fused_records_per_unit(ctx->units);
-    if (n_split > a.rec_per_unit) n_split = a.rec_per_unit;
+    a.rec_per_unit = ctx->rec_per_unit;
+    if (n_split > a.rec_per_unit + 1) n_split = a.rec_per_unit + 1;
     if (n_split < 1) n_split = 1;
     a.n_split = n_split;
     a.n_track = n_split;
@@ -547,21 +557,26 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
   a.p_out = p_out; a.p_override = p_override;
   a.ws = ctx->ws;
   if (kind == 4) {
-    // the number of this launch stamps the partials its blocks hand over; 0 is what the records
-    // hold before any launch, so after a wrap-around they are cleared and the count restarts.  A
-    // call that is being captured will be launched with one number again and again: the records it
-    // hands over go back to 0 before each time (the default stream cannot be captured)
-    const bool wrapped = ++ctx->launch_seq == 0;
-    if (wrapped) ctx->launch_seq = 1;
+    // The number of this launch stamps the partials its blocks hand over; 0 is what a cleared record
+    // holds.  Records are cleared before their first use (what lazyev_init did not clear, because only
+    // lazyev_set_target_blocks asks for it; what the split + merge kernels wrote over), and
+    // after the number has wrapped around.  A call that is being captured will be launched with one
+    // number again and again: its records go back to 0 before each time (the default stream cannot
+    // be captured).
+    if (++ctx->launch_seq == 0) {
+      ctx->launch_seq = 1;
+      ctx->rec_clean = 0;
+    }
+    const int32_t n_rec = a.n_split - 1;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (ctx->stream && a.n_split > 1) {
+    if (ctx->stream && n_rec > 0) {
       const hipError_t ec = hipStreamIsCapturing(ctx->stream, &capture);
       if (ec != hipSuccess) return fail_hip(ctx, ec);
     }
-    if (wrapped || capture != hipStreamCaptureStatusNone) {
-      const hipError_t ec = lazyev::launch_clear_records(ctx->ws.part_rec, ctx->units, a.rec_per_unit,
-                                                         wrapped ? a.rec_per_unit : a.n_split, ctx->stream);
+    if (n_rec > ctx->rec_clean || (n_rec > 0 && capture != hipStreamCaptureStatusNone)) {
+      const hipError_t ec = lazyev::launch_clear_records(ctx->ws.part_rec, ctx->units, a.rec_per_unit, n_rec, ctx->stream);
       if (ec != hipSuccess) return fail_hip(ctx, ec);
+      if (capture == hipStreamCaptureStatusNone) ctx->rec_clean = n_rec;   // (a captured launch has not run yet)
     }
     a.seq = ctx->launch_seq;
     a.spin_ticks = ctx->spin_ticks;
@@ -571,6 +586,7 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
   if (kind != 4) {                                 // the other kernels track in the same call
     const hipError_t ef = flush_tracking(ctx);
     if (ef != hipSuccess) return fail_hip(ctx, ef);
+    ctx->rec_clean = 0;                            // (their partials lie over the records)
   }
   const hipError_t e = lazyev::launch_decode(a, ctx->stream, arm_events(ctx, 0));
   if (e != hipSuccess) return fail_hip(ctx, e);
@@ -611,7 +627,8 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
 // decode call leaves its logits: nothing outstanding is read from there.
 static void prefill_areas(const lazyev_ctx *ctx, size_t units, lazyev::PrefillArgs &a) {
   a.stat = ctx->prefill_stat;
-  a.stat2 = ctx->prefill_stat + units * ctx->group * a.p16;
+  const bool one_part = ctx->cfg.dtype == LAZYEV_DTYPE_BF16 && ctx->cfg.head_dim == 128;
+  a.stat2 = one_part ? nullptr : ctx->prefill_stat + units * ctx->group * a.p16;
   a.seg = reinterpret_cast<int4 *>(ctx->ws.logits[ctx->cur_buf]);
   const size_t bytes = static_cast<size_t>(ctx->units) * fused_p_stride(ctx->capacity) * 8 * sizeof(float);
   const size_t n = bytes / (sizeof(int4) * units * static_cast<size_t>(a.prompt_len));

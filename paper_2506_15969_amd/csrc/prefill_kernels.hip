@@ -662,7 +662,8 @@ hipError_t launch_rows(PrefillArgs a, hipStream_t stream) {
 hipError_t launch_prefill_track(const PrefillArgs &a, hipStream_t stream) {
   if (a.prompt_len < 1 || a.prompt_len > a.capacity || a.group < 1 || a.group > kHeadMax ||
       a.n_q_heads != a.n_kv_heads * a.group || a.batch < 1 || a.p16 < (a.prompt_len + 15) / 16 * 16 ||
-      !a.q_prompt || !a.k_cache || !a.ts || !a.mri || !a.stat || !a.stat2 || a.counter_stride < 1 ||
+      !a.q_prompt || !a.k_cache || !a.ts || !a.mri || !a.stat || (!a.stat2 && !(a.dtype == 1 && a.head_dim == 128)) ||
+      a.counter_stride < 1 ||
       (a.segments > 1 && !a.seg))
     return hipErrorInvalidValue;
   if (a.dtype == 0 && a.head_dim == 64) return launch_rows<float, 64>(a, stream);
