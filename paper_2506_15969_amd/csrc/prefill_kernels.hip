@@ -65,9 +65,10 @@ struct Rows {
   static constexpr int kStage = kChunks == 8 ? 2 : 1;   // tiles per stage (4 KB; 8 KB for fp32 rows of 128)
   static constexpr int kSlots = kStage * 16 * kChunks;                   // 16-byte chunks of a stage
   static constexpr int kFetch = kSlots / kBlock;   // of them per thread
-  // The weight of a key: exp2((q.k) c2 - m - log2 l) with m and log2 l kept apart, so that nothing is
-  // rounded at the magnitude of the log-sum-exp; 128-element bf16 rows fold both into one number that
-  // the product starts from, b = -(m + log2 l) / c2 (c2 = scale log2 e).
+  // The weight of a key: exp2((q.k - r) c2 - ll) with a reference product r next to the log-sum-exp and what the
+  // sum of the weights relative to it leaves, ll, kept apart, so that nothing is rounded at the magnitude of the
+  // log-sum-exp; 128-element bf16 rows fold both into one number that the product starts
+  // from, b = -(m + log2 l) / c2 (c2 = scale log2 e, m = r c2).
   static constexpr bool kApart = !(sizeof(T) == 2 && D == 128);
   static constexpr int kTiles = kK == 8 ? 2 : 4;   // tiles a wave keeps in registers where there is work for all
   static constexpr int waves(int nb) { return nb == 1 ? 4 : kF32 ? 2 : 3; }   // waves per SIMD the registers are held to
@@ -155,6 +156,15 @@ __device__ __forceinline__ void settle(u32x4_t (&x)[N][K]) {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kFar = 0x1p64f;                    // a sum of four weights beyond this raises the reference
+// A reference is a rounded product, so up to a magnitude of 2^24 the exact product (a fused multiply-add) is within 1
+// of it, and within the rounding of the logits at any.  Beyond, the difference could leave the range of exp2: then
+// the product is rounded first, as the reference was.
+constexpr float kHuge = 0x1p24f;
+__device__ __forceinline__ float rounded_product(float x, float c2) {
+  float s = x * c2;
+  __asm__("" : "+v"(s));                           // (not fused with what follows)
+  return s;
+}
 
 // (this file is compiled with -fno-honor-nans, so that a maximum is one instruction and not three that
 // first make signalling NaNs quiet)
@@ -166,10 +176,12 @@ __device__ __forceinline__ float max_f32(float a, float b) { return __builtin_fm
 // cross-lane traffic inside the loop.  The reference m of a query need not be its maximum: a
 // floating-point sum is as exact relative to any reference within the range of the exponent, so there is no
 // running maximum, only a look whether the weights leave the range (first: there is no reference
-// yet).  kMask: the tile may hold keys newer than a query or positions beyond the prompt.
+// yet; where all logits of the first tile are -inf it is the lowest finite number, and the first other logit
+// raises it).  limit: kFar, or, once some reference of the wave is beyond kHuge, a number that every sum exceeds.  kMask: the tile may hold keys newer than a query or
+// positions beyond the prompt.
 template <typename T, int D, int NB, bool kMask, bool kFirst>
 __device__ __forceinline__ void stats_tiles(const u32x4_t (&ka)[Rows<T, D>::kK], const u32x4_t (&qb)[NB][Rows<T, D>::kK],
-                                            float c2, int key0, int query0, int P, float (&m)[NB], float (&l)[NB]) {
+                                            float c2, int key0, int query0, int P, float (&r)[NB], float (&m)[NB], float (&l)[NB], float &limit) {
   f32x4_t acc[NB];
   float ps[NB], far = 0.f;
 #pragma unroll
@@ -183,23 +195,38 @@ __device__ __forceinline__ void stats_tiles(const u32x4_t (&ka)[Rows<T, D>::kK],
         acc[n][i] = (key0 + i <= query0 + 16 * n && key0 + i < P) ? acc[n][i] : -INFINITY;
     }
     if (kFirst) {                                  // (key 0 is visible to every query, but to one of the column's four lanes only)
-      float top = max_f32(max_f32(acc[n][0], acc[n][1]), max_f32(acc[n][2], acc[n][3])) * c2;
+      float top = max_f32(max_f32(acc[n][0], acc[n][1]), max_f32(acc[n][2], acc[n][3]));
       top = max_f32(top, __shfl_xor(top, 16));
-      m[n] = max_f32(top, __shfl_xor(top, 32));
+      top = max_f32(max_f32(top, __shfl_xor(top, 32)), -FLT_MAX);
+      if (Rows<T, D>::kApart) r[n] = top;
+      m[n] = max_f32(top * c2, -FLT_MAX);
     }
     auto weight = [&](int i) { return __builtin_amdgcn_exp2f(fmaf(acc[n][i], c2, -m[n])); };
     ps[n] = (weight(0) + weight(1)) + (weight(2) + weight(3));
     far = n == 0 ? ps[n] : max_f32(far, ps[n]);
   }
-  if (!kFirst && __builtin_expect(__builtin_amdgcn_ballot_w64(far > kFar) != 0, 0)) {   // (wave-uniform)
+  if (kFirst || __builtin_expect(__builtin_amdgcn_ballot_w64(far > limit) != 0, 0)) {   // (wave-uniform)
     __asm__ volatile("");                          // (stays a branch: not worked out beforehand)
+    float largest = 0.f;
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-      const float top = max_f32(max_f32(acc[n][0], acc[n][1]), max_f32(acc[n][2], acc[n][3])) * c2;
-      const float up = max_f32(m[n], top);
-      l[n] *= __builtin_amdgcn_exp2f(m[n] - up);
-      m[n] = up;
-      auto weight = [&](int i) { return __builtin_amdgcn_exp2f(fmaf(acc[n][i], c2, -m[n])); };
+      if (!kFirst) {
+        const float top = max_f32(max_f32(acc[n][0], acc[n][1]), max_f32(acc[n][2], acc[n][3]));
+        if (Rows<T, D>::kApart) r[n] = max_f32(r[n], top);
+        const float up = max_f32(m[n], top * c2);
+        l[n] *= __builtin_amdgcn_exp2f(m[n] - up);
+        m[n] = up;
+      }
+      largest = max_f32(largest, fabsf(m[n]));
+    }
+    const bool huge = __builtin_amdgcn_ballot_w64(largest > kHuge) != 0;
+    limit = huge ? -1.f : kFar;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      if (kFirst && !huge) continue;               // (as worked out above)
+      auto weight = [&](int i) {
+        return __builtin_amdgcn_exp2f(huge ? rounded_product(acc[n][i], c2) - m[n] : fmaf(acc[n][i], c2, -m[n]));
+      };
       ps[n] = (weight(0) + weight(1)) + (weight(2) + weight(3));
     }
   }
@@ -239,9 +266,10 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats
   for (int n = 0; n < NB; ++n)
     load_operand<T, D>(q, i0 + 16 * n, P - 1, static_cast<size_t>(a.n_q_heads) * D, c, g, qb[n]);
 
-  float m[NB], l[NB];                              // of query i0 + 16 n + c, over this lane's key rows
+  float r[NB], m[NB], l[NB];                       // of query i0 + 16 n + c, over this lane's key rows; m = r c2
 #pragma unroll
-  for (int n = 0; n < NB; ++n) { m[n] = 0.f; l[n] = 0.f; }
+  for (int n = 0; n < NB; ++n) { r[n] = 0.f; m[n] = 0.f; l[n] = 0.f; }
+  float limit = kFar;
   const int my_last = have ? min(i0 + kSpan - 1, P - 1) >> 4 : -1;
   const int block_last = min(qt * kWaves * kSpan + kWaves * kSpan - 1, P - 1) >> 4;
   const int n_stages = block_last / R::kStage + 1;
@@ -275,11 +303,11 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats
         tile_operand<T, D>(tile, buf, j, ka, c, g);
         // only the wave's last NB key tiles can hold keys newer than a query (or positions beyond the prompt)
         if (decltype(tag)::value == 0 && j == 0 && jt == 0)
-          stats_tiles<T, D, NB, true, true>(ka, qb, c2, 4 * g, i0 + c, P, m, l);
+          stats_tiles<T, D, NB, true, true>(ka, qb, c2, 4 * g, i0 + c, P, r, m, l, limit);
         else if (jt * 16 + 15 <= i0 && jt * 16 + 15 < P)
-          stats_tiles<T, D, NB, false, false>(ka, qb, c2, jt * 16 + 4 * g, i0 + c, P, m, l);
+          stats_tiles<T, D, NB, false, false>(ka, qb, c2, jt * 16 + 4 * g, i0 + c, P, r, m, l, limit);
         else
-          stats_tiles<T, D, NB, true, false>(ka, qb, c2, jt * 16 + 4 * g, i0 + c, P, m, l);
+          stats_tiles<T, D, NB, true, false>(ka, qb, c2, jt * 16 + 4 * g, i0 + c, P, r, m, l, limit);
       }
     }
     stage_put<T, D>(tile, buf ^ 1, next[reg]);
@@ -299,9 +327,10 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats
   for (int n = 0; n < NB; ++n) {
 #pragma unroll
     for (int o = 16; o <= 32; o <<= 1) {
-      const float mo = __shfl_xor(m[n], o), lo = __shfl_xor(l[n], o);
+      const float ro = __shfl_xor(r[n], o), mo = __shfl_xor(m[n], o), lo = __shfl_xor(l[n], o);
       const float mx = fmaxf(m[n], mo);
       l[n] = l[n] * __builtin_amdgcn_exp2f(m[n] - mx) + lo * __builtin_amdgcn_exp2f(mo - mx);
+      r[n] = max_f32(r[n], ro);
       m[n] = mx;
     }
   }
@@ -312,11 +341,15 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats
       const int i = i0 + 16 * n + c;
       if (i >= P) continue;
       if constexpr (R::kApart) {
-        // the reference moved next to the log-sum-exp (the difference of the two references is exact)
-        const float near = m[n] + floorf(__builtin_amdgcn_logf(l[n]));
+        // The reference moved next to the log-sum-exp, by the whole part of log2 l: near = r + step - lost, exactly
+        // (the error of a sum, Knuth).  What m and step lost when they were rounded goes into ll (huge references: m was
+        // that of rounded products).
+        const float whole = floorf(__builtin_amdgcn_logf(l[n])), step = whole / c2, near = r[n] + step, part = near - r[n];
+        const float lost = (r[n] - (near - part)) + (step - part);
+        const float off = (limit < 0.f ? 0.f : fmaf(r[n], c2, -m[n])) + fmaf(step, c2, -whole) - lost * c2;
         st[i] = near;
         a.stat2[(static_cast<size_t>(unit) * G + h) * a.p16 + i] =
-            __builtin_amdgcn_logf(l[n] * __builtin_amdgcn_exp2f(m[n] - near));
+            __builtin_amdgcn_logf(l[n] * __builtin_amdgcn_exp2f(-whole)) - off;
       } else {                                     // b: see Rows
         st[i] = -(m[n] + __builtin_amdgcn_logf(l[n])) / c2;
       }
@@ -493,7 +526,7 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
           for (int n = 0; n < NB; ++n) acc[n] = f32x4_t{start, start, start, start};
           logits_tiles<T, D, NB, true>(ka, qb, acc);
           // the logarithm of the weight, in units of log 2 (over c2 where b is folded in)
-          auto log_weight = [&](float x) { return R::kApart ? fmaf(x, c2, -b) - ll : x; };
+          auto log_weight = [&](float x) { return R::kApart ? fmaf(x - b, c2, -ll) : x; };
           // every key of the wave exists and is no newer than any query of the tile, and every
           // query of the tile exists: nothing to mask (all but the wave's first NB query tiles,
           // the prompt's last tile and its last wave)
