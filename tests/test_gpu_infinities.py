@@ -27,6 +27,8 @@ def _run(lazyev_lib, variant, dtype, d, place, value, N, H=2, G=4, S=2, steps=2)
         eng.k_cache[0, 0, 0, N // 3, 3] = value
     elif place == "query":
         q[0, 1, 2, 7] = value
+    elif place == "large K":
+        eng.k_cache[0, 0, 0, N // 3] *= value
     eng.init()
     eng.set_variant(variant)
     if N > 2000:                                   # one block per unit: runs whose logits leave LDS in segments
@@ -54,4 +56,17 @@ def test_infinite_elements(lazyev_lib, dtype, d, place, value, N):
     # two orders of fp32 sums of N + 2 terms, of unit size together; bf16: one rounding of each of two results
     tol = (N + 2) * 2.0 ** -23 if dt == torch.float32 else 2.0 ** -7
     assert float((got - want)[ok].abs().max()) < tol * max(1.0, float(want[ok].abs().max()))
+    assert act0 == act1 and all(torch.equal(x, y) for x, y in zip(state0, state1))
+
+
+@pytest.mark.parametrize("dtype,d", ROWS + [("bf16", 128)])
+@pytest.mark.parametrize("value", [1e8, 1e12, 1e25])
+@pytest.mark.parametrize("N", [3, 64, 333, 2600])
+def test_large_logits(lazyev_lib, dtype, d, value, N):
+    """A key with logits so large that their rounding exceeds the range of an exponential."""
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    (want, state0, act0), (got, state1, act1) = (_run(lazyev_lib, v, dt, d, "large K", value, N) for v in (0, 1))
+    assert bool(want.isfinite().all()) and bool(got.isfinite().all())
+    tol = (N + 2) * 2.0 ** -23 if dt == torch.float32 else 2.0 ** -6
+    assert float((got - want).abs().max()) < tol * max(1.0, float(want.abs().max()))
     assert act0 == act1 and all(torch.equal(x, y) for x, y in zip(state0, state1))
