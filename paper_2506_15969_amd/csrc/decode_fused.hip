@@ -297,13 +297,7 @@ template <bool kPrecise>
 __device__ __forceinline__ unsigned track_apply(const TrackArgs &k, int unit, int part, int n_parts,
                                                 int r0, const TrackBatch &b, const float (&m)[kHeadPad],
                                                 const float (&invl)[kHeadPad], unsigned *log_mask) {
-  const int seq = unit / k.n_kv_heads, kvh = unit % k.n_kv_heads;
-  const int G = k.group;
-  const int n_old = k.n_old, n1 = k.n_old + 1;
-  const int n_sub = (n1 + 15) >> 4;
-  const size_t head0 = static_cast<size_t>(seq) * k.n_q_heads + static_cast<size_t>(kvh) * G;
-  int32_t *ts = k.ts + static_cast<size_t>(unit) * k.capacity;
-  int32_t *mri = k.mri + static_cast<size_t>(unit) * k.capacity;
+  const int n1 = k.n_old + 1, n_sub = (n1 + 15) >> 4;
   unsigned n_act = 0;
 #pragma unroll
   for (int r = 0; r < kTrackRows; ++r) {
@@ -311,33 +305,7 @@ __device__ __forceinline__ unsigned track_apply(const TrackArgs &k, int unit, in
     if (i >= n1) continue;
     const float s[kHeadPad] = {b.sa[r].x, b.sa[r].y, b.sa[r].z, b.sa[r].w,
                                b.sb[r].x, b.sb[r].y, b.sb[r].z, b.sb[r].w};
-    bool act = false;
-#pragma unroll
-    for (int h = 0; h < kHeadPad; ++h) {
-      if (h < G) {
-        float p = exp_of<kPrecise>(s[h] - m[h]) * invl[h];
-        const size_t at = (head0 + h) * k.capacity + i;
-        if (k.p_out) k.p_out[at] = p;
-        if (k.p_override) p = k.p_override[at];
-        act = act || (p >= k.alpha);
-      }
-    }
-    if (i == n_old) {                              // the appended entry starts here (Sec. 4)
-      if (!log_mask) {                             // (of a logged call: when the log is applied)
-        ts[i] = k.t;
-        mri[i] = 0;
-        k.pos[static_cast<size_t>(unit) * k.capacity + i] = k.prompt_len + k.t - 1;
-      }
-    } else if (act) {                              // few entries are active: TS / MRI are read only here
-      if (log_mask) {
-        atomicOr(log_mask + (i >> 5), 1u << (i & 31));
-      } else {
-        const int32_t gap = k.t - ts[i];
-        if (gap > mri[i]) mri[i] = gap;            // Eq. 1
-        ts[i] = k.t;                               // Alg. 1
-      }
-    }
-    n_act += act ? 1u : 0u;
+    n_act += track_one<kPrecise>(k, unit, i, s, m, invl, log_mask) ? 1u : 0u;
   }
   return n_act;
 }
@@ -672,8 +640,9 @@ __global__ __launch_bounds__(kBlock) void clear_records_kernel(unsigned long lon
 // logits in LDS while the first four merge, exchange and finish the unit; that phase is serial
 // code of one wave per SIMD, so a second wave per SIMD takes the lists off its path.  Used when
 // all blocks of the launch are resident at once with eight waves each (a stream block and a
-// tracking block per compute unit: every instance keeps to 128 registers per lane); a launch of
-// more blocks runs four-wave blocks whose stream waves build their own lists.
+// tracking block per compute unit: these instances keep to 128 registers per lane); a launch of
+// more blocks, and fp32 rows of 128 elements (up to 230 registers), run four-wave blocks whose
+// stream waves build their own lists.
 // kSplit > 0: the instance is for units of exactly kSplit blocks (1 .. 8, with list waves).  What
 // precedes and follows the stream is serial code of single waves, and a split known at compile time takes the
 // second hop, the loads of a variable number of records and the divisions by the split out of it
@@ -1028,7 +997,6 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     const int e0 = sub * 16 + 4 * g;
 #pragma unroll
     for (int i = 0; i < 4; ++i) s[i] = (e0 + i < n1) ? acc[i] * a.scale : -INFINITY;
-    // logits of the sub-tile -> [entry][head] in LDS -> 512 contiguous bytes of the workspace
     // logits of the sub-tile -> [entry][head] in LDS; written out when the wave's run ends (a
     // store among the loads would hold up the in-order load counter)
     if (!kAgain && c < kHeadPad) {
@@ -1442,12 +1410,9 @@ extern "C" int lazyev_timeline_read(unsigned long long *out, int n_words) {
 }
 #endif
 int decode_fused_split_max() { return kFusedSplitMax; }
-int decode_fused_wave_run(int n_sub, int n_split) { return fused_wave_run(n_sub, n_split); }
-int decode_fused_run_max() { return kRunMax; }
-int decode_fused_head_pad() { return kHeadPad; }
 size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * sizeof(unsigned long long); }
 
-// Blocks per unit.  Measured on 28 query / 4 KV heads, us per call:
+// Blocks per unit.  Measured on 28 query / 4 KV heads of 128 x bf16, us per call; the other row types take the same rule:
 //   * no more blocks than compute units: a second stream block on some of them holds up the whole
 //     launch (80 units x 2200 entries: 3 blocks per unit 17.4, 4 22.1; 48 units: 5 12.6, 6 16.6), and with
 //     two on all of them the bytes in flight only widen the spread of the blocks' ends (128 units x
@@ -1461,8 +1426,12 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to
 //     two per compute unit (96 units x 6200 entries: 2 blocks per unit 61.8, 5 58.1; 144 units: 1 98.9, 3 88.5;
 //     with 2200 entries still 20.1 against 23.6 and 33.1 against 31.1: from 32 sub-tiles per wave on).
+//     From 171 units on that would be two blocks, and one is the better at every length (1 / 2 blocks, 172 units
+//     x 600 12.6 / 14.8, x 2200 38.5 / 40.5, x 6200 115 / 119; 192 units 12.7 / 15.3, 39.9 / 42.1, 123 / 130; 240 units
+//     14.6 / 17.5, 48.7 / 50.7, 143 / 152), as it is for fp32 rows (192 units x 2200, 64 46.5 / 47.9, 128 84.2 / 89.1);
+//     bf16 rows of 64 would gain from two between about 1000 entries and 220 units (192 x 2200 31.0 / 26.6).
 int decode_fused_split(int units, int n_sub) {
-  constexpr int kUnitsOfChip = 256;
+  constexpr int kUnitsOfChip = 256;                // compute units of the chip that the figures above are from
   int n = kUnitsOfChip / units;
   if (n < 1) n = 1;
   if (n > kMergeRadix && n_sub <= kWaves * kMergeRadix * 8) n = kMergeRadix;

@@ -82,7 +82,7 @@ struct TrackArgs {
 };
 
 // The logged calls of one or several layers applied to TS / MRI (Alg. 1 first loop, Eq. 1, in the
-// order of the calls).  Block b works on layer b / units, unit b % units.
+// order of the calls).  Blocks: [layer][unit][span of entries], see track_flush_kernel.
 constexpr int kLogSlotsMax = 256;
 constexpr int kFlushLayers = 64;    // layers of a launch
 struct FlushArgs {
@@ -190,14 +190,9 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev
 // One launch per call: split blocks, the last block of a unit merges; tracks the previous call.
 hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev);
 int decode_fused_split_max();
-// Most sub-tiles of 16 entries one wave of a call with n_split blocks per unit takes, and how
-// many of them a wave keeps in LDS at a time.
-int decode_fused_wave_run(int n_sub, int n_split);
-int decode_fused_run_max();
 // Can a call with these sizes leave candidate lists (they fit the logits buffer, a wave's logits
 // stay in LDS to the end of its run)?
 bool decode_fused_compact_fits(int n_old, int n_split, int p_stride, int group);
-int decode_fused_head_pad();
 size_t decode_fused_record_bytes();           // one stamped record
 int decode_fused_records_needed(int units, int capacity);   // most records per unit that decode_fused_split asks for
 int decode_fused_records_held(int units, int capacity, size_t bytes);   // most records per unit of use that `bytes` hold for all units
