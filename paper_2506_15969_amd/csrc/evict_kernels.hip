@@ -123,9 +123,15 @@ __global__ void init_slot_kernel(int32_t *ts, int32_t *mri, int32_t *pos, int32_
   pos[at] = slot < prompt_len ? slot : -1;
 }
 
+// The state of every entry, and the first rec_words of the rec_stride words that each of rec_units units has for its
+// records of partials (here, because a launch of their own added 4 us to lazyev_init).
 __global__ void init_state_kernel(int32_t *ts, int32_t *mri, int32_t *pos, int64_t total,
-                                  int32_t capacity, int32_t prompt_len) {
+                                  int32_t capacity, int32_t prompt_len, unsigned long long *rec, int32_t rec_units,
+                                  int32_t rec_stride, int32_t rec_words) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t words = static_cast<int64_t>(rec_units) * rec_words;
+  for (int64_t j = i; j < words; j += static_cast<int64_t>(gridDim.x) * blockDim.x)
+    rec[j / rec_words * rec_stride + j % rec_words] = 0;
   if (i >= total) return;
   const int32_t slot = static_cast<int32_t>(i % capacity);
   ts[i] = 0;
@@ -704,11 +710,13 @@ hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) 
 }
 
 hipError_t launch_init_state(int32_t *ts, int32_t *mri, int32_t *pos, int64_t n_units,
-                             int32_t capacity, int32_t prompt_len, hipStream_t stream) {
-  const int64_t total = n_units * capacity;
-  const unsigned blocks = static_cast<unsigned>((total + 255) / 256);
+                             int32_t capacity, int32_t prompt_len, unsigned long long *rec, int32_t rec_units,
+                             int32_t rec_stride, int32_t rec_words, hipStream_t stream) {
+  if (rec_words > rec_stride || (rec_words > 0 && !rec)) return hipErrorInvalidValue;
+  const int64_t total = n_units * capacity, words = static_cast<int64_t>(rec_units) * rec_words;
+  const unsigned blocks = static_cast<unsigned>(((total > words ? total : words) + 255) / 256);
   hipLaunchKernelGGL(init_state_kernel, dim3(blocks), dim3(256), 0, stream, ts, mri, pos, total,
-                     capacity, prompt_len);
+                     capacity, prompt_len, rec, rec_units, rec_stride, rec_words);
   return hipGetLastError();
 }
 

@@ -204,7 +204,8 @@ int decode_fused_log_words_max();                // cache entries / 32 up to whi
 hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev);
 int evict_lds_candidates();   // candidates per unit whose keys the selection keeps in LDS
 hipError_t launch_init_state(int32_t *ts, int32_t *mri, int32_t *pos, int64_t n_units,
-                             int32_t capacity, int32_t prompt_len, hipStream_t stream);
+                             int32_t capacity, int32_t prompt_len, unsigned long long *rec, int32_t rec_units,
+                             int32_t rec_stride, int32_t rec_words, hipStream_t stream);
 // One sequence starts over: TS = 0, MRI = 0, pos = i for its first prompt_len entries in every layer.
 hipError_t launch_init_slot(int32_t *ts, int32_t *mri, int32_t *pos, int32_t n_layers, int32_t batch,
                             int32_t n_kv_heads, int32_t capacity, int32_t seq, int32_t prompt_len,

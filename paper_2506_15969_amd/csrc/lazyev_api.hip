@@ -417,13 +417,13 @@ int lazyev_init(const lazyev_config *cfg, lazyev_ctx **out) {
   if (static_scratch_of(&ctx->device, &ctx->static_scratch) != hipSuccess) { delete ctx; return LAZYEV_EHIP; }
 
   // activation counters, moved-row counters and the fault word lie next to each other
+  const int32_t rec_words = static_cast<int32_t>(lazyev::decode_fused_record_bytes() / sizeof(unsigned long long));
   hipError_t e = hipMemsetAsync(ctx->ws.activations, 0, l.total - l.activations, ctx->stream);
-  if (e == hipSuccess)                             // (0: no launch has that number)
-    e = lazyev::launch_clear_records(ctx->ws.part_rec, ctx->units, ctx->rec_per_unit, ctx->rec_clean, ctx->stream);
   if (e == hipSuccess)
     e = lazyev::launch_init_state(cfg->ts, cfg->mri, cfg->pos,
                                   static_cast<int64_t>(cfg->n_layers) * ctx->units, ctx->capacity,
-                                  cfg->prompt_len, ctx->stream);
+                                  cfg->prompt_len, ctx->ws.part_rec, ctx->units, ctx->rec_per_unit * rec_words,
+                                  ctx->rec_clean * rec_words, ctx->stream);   // (a cleared record: no launch has the number 0)
   if (e != hipSuccess) { delete ctx; return LAZYEV_EHIP; }
   *out = ctx;
   return LAZYEV_OK;

@@ -38,10 +38,10 @@ def test_kernels_in_turn(lazyev_lib, dtype, d, plan):
     assert st_w == st_g and all(torch.equal(x, y) for x, y in zip(state_w, state_g))
 
 
-@pytest.mark.parametrize("units", [128, 192, 600])
-def test_more_blocks_than_the_library_would_take(lazyev_lib, units):
+@pytest.mark.parametrize("units,N", [(128, 700), (172, 700), (192, 700), (192, 6200), (240, 2200), (600, 700)])
+def test_more_blocks_than_the_library_would_take(lazyev_lib, units, N):
     """lazyev_set_target_blocks far beyond the chip: as many blocks per unit as the workspace has records for."""
-    H, G, d, N = 4, 7, 128, 700
+    H, G, d = 4, 7, 128
     outs = []
     for blocks in (0, 100):
         gen = torch.Generator(device="cuda").manual_seed(3)
@@ -59,5 +59,5 @@ def test_more_blocks_than_the_library_would_take(lazyev_lib, units):
         outs.append((out.double(), eng.stats()["n_activations"]))
         eng.close()
     (a, n_a), (b, n_b) = outs
-    # (a weight within rounding of alpha may fall on either side of it: about one in 1e7, of up to 9e6 here)
-    assert abs(n_a[0] - n_b[0]) <= 5 and float(((a - b).norm(dim=-1) / a.norm(dim=-1)).max()) < 2 * 2.0 ** -8
+    # (a weight within rounding of alpha may fall on either side of it: about one in 1e7, of up to 3e7 here)
+    assert abs(n_a[0] - n_b[0]) <= 20 and float(((a - b).norm(dim=-1) / a.norm(dim=-1)).max()) < 2 * 2.0 ** -8
