@@ -72,6 +72,7 @@
 #include "bits.h"
 #include "kernels.h"
 
+#include <cfloat>
 #include <type_traits>
 
 namespace lazyev {
@@ -482,14 +483,13 @@ __global__ __launch_bounds__(kBlock) void track_flush_kernel(const FlushArgs f) 
 // bits from the same partials.
 template <bool kPrecise>
 struct Merge {
-  float m = -INFINITY, l = 0.f;
+  float m = -FLT_MAX, l = 0.f;
   float o[4] = {0.f, 0.f, 0.f, 0.f};
   __device__ __forceinline__ void fold(float mj, float lj, const f32x4_t &oj) {
 #pragma clang fp contract(off)
     const float m_new = fmaxf(m, mj);
-    // a block without entries has max = -inf, sum = 0, values = 0: its factor is 0
-    const float fr = m == -INFINITY ? 0.f : exp_of<kPrecise>(m - m_new);
-    const float fj = mj == -INFINITY ? 0.f : exp_of<kPrecise>(mj - m_new);
+    // (a block without entries has the lowest maximum, sum = 0, values = 0)
+    const float fr = exp_of<kPrecise>(m - m_new), fj = exp_of<kPrecise>(mj - m_new);
     l = fmaf(l, fr, lj * fj);
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = fmaf(o[i], fr, oj[i] * fj);
@@ -797,8 +797,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     float lbh = 0.f;
 #pragma unroll
     for (int w2 = 0; w2 < kWaves; ++w2) {
-      const float mw = m_lds[w2][hh];
-      lbh = fmaf(mw == -INFINITY ? 0.f : __expf(mw - mbh), lsum_lds[w2][hh], lbh);
+      lbh = fmaf(__expf(m_lds[w2][hh] - mbh), lsum_lds[w2][hh], lbh);
     }
     // the logits of all rounds are read first ...
     f32x4_t sa[kRounds], sb[kRounds];
@@ -922,7 +921,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   int seg0 = 0;                                    // first of this wave's sub-tiles whose logits are still in LDS
   float *logits_out = a.logits_out + static_cast<size_t>(unit) * a.p_stride * kHeadPad;
 
-  float m_ref = -INFINITY, lsum = 0.f;
+  // (no reference yet: the lowest number, below which no logit but -inf lies and from which that has the weight 0)
+  float m_ref = -FLT_MAX, lsum = 0.f;
   f32x4_t o[R::kAcc];
 #pragma unroll
   for (int e = 0; e < R::kAcc; ++e) o[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -1008,7 +1008,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     tmax = max_over_lane_groups(tmax);
     if (__builtin_amdgcn_ballot_w64(tmax > m_ref + kRaise) != 0) {   // wave-uniform, rare
       const float m_new = fmaxf(m_ref, tmax);
-      const float f = exp_of<kPrecise>(m_ref - m_new);   // 0 on the first sub-tile (m_ref = -inf)
+      const float f = exp_of<kPrecise>(m_ref - m_new);   // 0 on the first sub-tile
       lsum *= f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -1221,7 +1221,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
 #pragma unroll
     for (int e = 0; e < R::kAcc; ++e) any += (o[e][0] + o[e][1]) + (o[e][2] + o[e][3]);
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(any != any) != 0, 0)) {   // wave-uniform
-      m_ref = -INFINITY;
+      m_ref = -FLT_MAX;
       lsum = 0.f;
 #pragma unroll
       for (int e = 0; e < R::kAcc; ++e) o[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -1268,8 +1268,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   // serial code, every instruction counts)
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
-    const float mw = m_lds[w][h_own];
-    const float f = mw == -INFINITY ? 0.f : exp_of<kPrecise>(mw - mb_own);   // a wave without entries: factor 0
+    const float f = exp_of<kPrecise>(m_lds[w][h_own] - mb_own);   // (a wave without entries: sum and values 0)
     const f32x4_t x = *reinterpret_cast<const f32x4_t *>(acc_lds + w * kAccStride + ec);
 #pragma unroll
     for (int i = 0; i < 4; ++i) v_own[i] = fmaf(f, x[i], v_own[i]);

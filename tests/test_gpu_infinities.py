@@ -70,3 +70,36 @@ def test_large_logits(lazyev_lib, dtype, d, value, N):
     tol = (N + 2) * 2.0 ** -23 if dt == torch.float32 else 2.0 ** -6
     assert float((got - want).abs().max()) < tol * max(1.0, float(want.abs().max()))
     assert act0 == act1 and all(torch.equal(x, y) for x, y in zip(state0, state1))
+
+
+@pytest.mark.parametrize("dtype,d", ROWS + [("bf16", 128)])
+@pytest.mark.parametrize("N,blocks", [(40, 0), (333, 0), (333, 1), (700, 3), (2600, 1)])
+def test_entries_without_weight(lazyev_lib, dtype, d, N, blocks):
+    """Runs of entries whose logits are -inf in every head, long enough to fill whole sub-tiles, a wave's first ones among
+    them: softmax in 64 bits over the others, and no activation of theirs."""
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    H, G, S, steps = 2, 4, 2, 2
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    eng = lazyev_lib.LazyEviction(1, S, H * G, H, d, N + 40, 8, N, 0.001, dtype=dt)
+    eng.k_cache[:, :, :, :N].normal_(generator=gen)
+    eng.v_cache[:, :, :, :N].normal_(generator=gen)
+    gone = torch.zeros(N, dtype=torch.bool, device="cuda")
+    gone[:35] = gone[N // 2:N // 2 + 70] = True
+    gone[N - 1] = False
+    eng.k_cache[0, :, :, :N][:, :, gone, 5] = -float("inf")
+    eng.init()
+    if blocks:
+        eng.set_target_blocks(blocks * S * H)
+    out = torch.zeros((S, H * G, d), dtype=dt, device="cuda")
+    for t in range(1, steps + 1):
+        q, kn, vn = (torch.empty((S, h, d), device="cuda").normal_(generator=gen).to(dt) for h in (H * G, H, H))
+        q[..., 5] = q[..., 5].abs() + 0.125
+        eng.decode_step(0, t, q, kn, vn, out)
+        k, v = eng.k_cache[0, :, :, :N + t].double(), eng.v_cache[0, :, :, :N + t].double()
+        p = torch.softmax(torch.matmul(q.double().view(S, H, G, d), k.transpose(2, 3).contiguous()) * d ** -0.5, dim=-1)
+        want = torch.matmul(p, v).view(S, H * G, d)
+        err = float(((out.double() - want).norm(dim=-1) / want.norm(dim=-1)).max())
+        assert err < (1e-5 if dt == torch.float32 else 2 * 2.0 ** -8), (t, err)
+    eng.stats()
+    assert bool((eng.ts[0, :, :, :N][:, :, gone] == 0).all()) and bool((eng.ts[0, :, :, :N][:, :, ~gone] > 0).any())
+    eng.close()
