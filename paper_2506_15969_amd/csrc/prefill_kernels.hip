@@ -344,7 +344,8 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats
         // The reference moved next to the log-sum-exp, by the whole part of log2 l: near = r + step - lost, exactly
         // (the error of a sum, Knuth).  What m and step lost when they were rounded goes into ll (huge references: m was
         // that of rounded products).
-        const float whole = floorf(__builtin_amdgcn_logf(l[n])), step = whole / c2, near = r[n] + step, part = near - r[n];
+        const float whole = floorf(__builtin_amdgcn_logf(l[n]));
+        const float step = c2 > 1e-30f ? whole / c2 : 0.f, near = r[n] + step, part = near - r[n];   // (a finite step)
         const float lost = (r[n] - (near - part)) + (step - part);
         const float off = (limit < 0.f ? 0.f : fmaf(r[n], c2, -m[n])) + fmaf(step, c2, -whole) - lost * c2;
         st[i] = near;
