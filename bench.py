@@ -43,9 +43,9 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 # counters are scaled by what they read for the plain copy kernel of --calibrate-copy-mb):
 # (mean entries per unit after the append in that profile, bytes).  Printed as roofline.traffic
 # only when the timed steps of this run have the same mean cache length.
-PROFILED_TRAFFIC = {"cfg3": (2080.5, 2 * 68000 * 1024 + 2325 * 1024),      # 136.9 MB algorithmic
-                    "cfg4": (1088.5, 2 * 36080 * 1024 + 1987 * 1024),      # 71.9 MB
-                    "cfg5": (4128.5, 2 * 134300 * 1024 + 3988 * 1024)}     # 271.0 MB
+PROFILED_TRAFFIC = {"cfg3": (2080.5, 2 * 68180 * 1024 + 2719 * 1024),      # 136.9 MB algorithmic
+                    "cfg4": (1088.5, 2 * 36260 * 1024 + 2395 * 1024),      # 71.9 MB
+                    "cfg5": (4128.5, 2 * 134700 * 1024 + 4787 * 1024)}     # 271.0 MB
 
 
 def algorithmic_bytes_decode(cfg, n1: int) -> int:
@@ -228,13 +228,16 @@ def timeline_mode(args):
     def q(x):
         return {"min": round(float(np.min(x)), 2), "p50": round(float(np.median(x)), 2),
                 "p90": round(float(np.percentile(x, 90)), 2), "max": round(float(np.max(x)), 2)}
+
+    def at(sample, i):                             # (only finishing blocks leave stamp 4)
+        return sample[0][:, i][sample[1] == 1] if i == 4 else sample[0][:, i]
     res = {"what": "in-kernel timeline of decode_fused_kernel, microseconds from the start of the launch's "
                    "first block, over the stream blocks of %d launches" % len(samples),
            "config": {"workload": "%s-prompt%d" % (base.name, P), "layers": L, "entries_per_unit_at_the_end": n1,
                       "stream_blocks_per_launch": int(samples[0][0].shape[0])},
-           "stamps": {n: dict(q(np.concatenate([s[0][:, i] for s in samples])),
-                              mean_of_per_launch_max=round(float(np.mean([s[0][:, i].max() for s in samples])), 2),
-                              mean_of_per_launch_min=round(float(np.mean([s[0][:, i].min() for s in samples])), 2))
+           "stamps": {n: dict(q(np.concatenate([at(s, i) for s in samples])),
+                              mean_of_per_launch_max=round(float(np.mean([at(s, i).max() for s in samples])), 2),
+                              mean_of_per_launch_min=round(float(np.mean([at(s, i).min() for s in samples])), 2))
                       for i, n in enumerate(names)},
            "finisher_tail_us (block end - end of its stream)":
                q(np.concatenate([(s[0][:, 5] - s[0][:, 2])[s[1] == 1] for s in samples])),
