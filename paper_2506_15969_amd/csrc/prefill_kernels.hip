@@ -30,13 +30,14 @@
 // What bounds it: the vector work beside the products (a multiply-add, an exponential and an addition per weight
 // in the first kernel, a maximum in the second; the matrix cores are busy 35% of the time).  Measured, us for both
 // kernels, before (a running maximum with two exponentials per weight, an exponential and a comparison per
-// weight in the second kernel, rows of 64 and fp32 rows on a kernel without matrix instructions) and now:
-//   32 sequences, 28 / 4 heads of 128, bf16   600 positions 292 -> 170, 2048 positions 1370 -> 1190
+// weight in the second kernel, rows of 64 and fp32 rows on a kernel without matrix instructions) and now, calls back to
+// back (3 % from box to box; the other figures in this file are against 1190 - 1223 us for 2048 positions in their own runs):
+//   32 sequences, 28 / 4 heads of 128, bf16   600 positions 292 -> 178, 2048 positions 1370 -> 1150
 //   16 sequences, 40 / 8 heads of 128, bf16  4096 positions 3520 -> 2900
-//    8 sequences, 28 / 4 heads of 128, bf16  1024 positions 350 -> 112
-//    1 sequence,  28 / 4 heads of 128, bf16    33 positions 22.9 -> 13.5,  400 positions 141 -> 24
-//    4 sequences, 32 / 8 heads of  64, bf16   499 positions 5470 -> 32
-//    2 sequences, 28 / 4 heads of 128, fp32   300 positions 10880 -> 50
+//    8 sequences, 28 / 4 heads of 128, bf16  1024 positions 350 -> 110
+//    1 sequence,  28 / 4 heads of 128, bf16    33 positions 22.9 -> 13.0,  400 positions 141 -> 23.6
+//    4 sequences, 32 / 8 heads of  64, bf16   499 positions 5470 -> 30
+//    2 sequences, 28 / 4 heads of 128, fp32   300 positions 10880 -> 48
 #include "bits.h"
 #include "kernels.h"
 
