@@ -69,3 +69,22 @@ def test_extreme_logits(lazyev_lib, dtype, d, S, H, G, P, place):
         want[:, :, j] = got[:, :, j] = 0.0
     # (logits of ordinary keys: fp32 sums of d products, about 10 in magnitude together)
     assert float((got - want).abs().max()) <= 2 * d * 2.0 ** -24 * 10
+
+
+@pytest.mark.parametrize("dtype,d", ROWS[1:])
+@pytest.mark.parametrize("scale", [1e-38, 1e-31, 1e-20, 1e-6])
+def test_smallest_softmax_scales(lazyev_lib, dtype, d, scale):
+    """Every key has the same weight."""
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    S, H, G, P = 1, 2, 2, 90
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    eng = lazyev_lib.LazyEviction(1, S, H * G, H, d, P + 40, 8, P, 0.02, dtype=dt, softmax_scale=scale)
+    eng.k_cache[0, :, :, :P].normal_(generator=gen)
+    eng.init()
+    q = torch.empty((S, P, H * G, d), device="cuda").normal_(generator=gen).to(dt)
+    p = torch.zeros((S, H * G, P, P), device="cuda")
+    eng.prefill_track(0, q, p_out=p)
+    want = 1.0 / torch.arange(1, P + 1, device="cuda", dtype=torch.float64).view(P, 1).expand(P, P).tril()
+    rel = ((p.double() - want) / want).tril()[..., torch.ones((P, P), dtype=torch.bool, device="cuda").tril()]
+    assert float(rel.abs().max()) < 1e-4               # (logits of up to 40 scale, and a few roundings of 2^-24)
+    eng.close()
