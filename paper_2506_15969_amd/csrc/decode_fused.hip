@@ -73,6 +73,7 @@
 #include "kernels.h"
 
 #include <cfloat>
+#include <cstddef>
 #include <type_traits>
 
 namespace lazyev {
@@ -499,14 +500,11 @@ struct Merge {
 
 // The merged row of a unit: thread t writes output elements 4t .. 4t+3 (all of head h) and, as
 // the owner of a head's first elements, the head's softmax statistics for the tracking.
-template <typename T, int D>
-__device__ __forceinline__ void write_unit_row(const DecodeArgs &a, int unit, const Merge<Rows<T, D>::kPrecise> &mg, int e0, int h) {
-  const int G = a.group;
+template <typename T, int D, typename Args>
+__device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, const Merge<Rows<T, D>::kPrecise> &mg, int e0, int h) {
   if (e0 >= G * D) return;
-  const int seq = unit / a.n_kv_heads, kvh = unit % a.n_kv_heads;
-  const size_t head0 = static_cast<size_t>(seq) * a.n_q_heads + static_cast<size_t>(kvh) * G;
   const float invl = 1.0f / mg.l;
-  T *out = static_cast<T *>(a.out) + head0 * D + e0;
+  T *out = a.out + static_cast<size_t>(unit) * G * D + e0;   // (a unit's query heads follow one another, unit after unit)
   if constexpr (Rows<T, D>::kF32) {
     *reinterpret_cast<f32x4_t *>(out) = f32x4_t{mg.o[0] * invl, mg.o[1] * invl, mg.o[2] * invl, mg.o[3] * invl};
   } else {
@@ -581,8 +579,8 @@ __device__ __forceinline__ f32x4_t rec_values(const RecPart &r) {
 // until every word carries the launch's number; then the records and (m, l, o) merged in this order.
 // The running merge starts from the first record as it is: folding it into the empty state would
 // reproduce exactly its bits (factors 0 and exp(0) = 1) at the price of a dozen instructions.
-template <int N, bool kPrecise>
-__device__ __forceinline__ Merge<kPrecise> merge_records(const DecodeArgs &a, const unsigned long long *rec, int stride, int n,
+template <int N, bool kPrecise, typename Args>
+__device__ __forceinline__ Merge<kPrecise> merge_records(const Args &a, const unsigned long long *rec, int stride, int n,
                                                int t_own, float m, float l, const f32x4_t &o) {
   Merge<kPrecise> mg;
   if (n == 0) {                                    // uniform
@@ -605,7 +603,7 @@ __device__ __forceinline__ Merge<kPrecise> merge_records(const DecodeArgs &a, co
     const unsigned long long now = wall_clock64();
     if (t_first == 0) t_first = now;
     if (now - t_first >= a.spin_ticks) {           // (a limit of 0: no second look)
-      atomicOr(a.ws.fault, 1);                     // (cannot happen otherwise, see above; the row is then wrong)
+      atomicOr(a.fault, 1);                     // (cannot happen otherwise, see above; the row is then wrong)
       break;
     }
   }
@@ -627,8 +625,68 @@ __global__ __launch_bounds__(kBlock) void clear_records_kernel(unsigned long lon
 }
 
 // ------------------------------------------------------------------------------- the kernel
+// The kernel's arguments as they lie in memory.  The argument block `a` is read through args_from_here only: left to itself the
+// compiler fetches words of it at the top of the kernel for whichever path needs them, and a stream wave, whose first
+// loads need none of them, waited there for such a fetch (its registers were used again), 0.5 us in every call; the queries took
+// another round trip behind it.  us per pass, before and now (queries from the leading arguments, the block read
+// behind the first loads): 64 units x 1563 entries of 64 x bf16 1283 -> 1188, 8 units x 2081 2385 -> 2218, 128 x 2081 3128 -> 3066.
+template <typename T>
+struct Kernarg {
+  const T *k_cache, *v_cache, *k_new, *v_new, *q;
+  int n_old, capacity;
+  unsigned shape;
+  DecodeArgs a;
+};
+typedef const __attribute__((address_space(4))) DecodeArgs *const_args_t;
+template <typename T>
+__device__ __forceinline__ const DecodeArgs &args_from_here() {
+  uintptr_t p = reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()) + offsetof(Kernarg<T>, a);
+  __asm__ volatile("" : "+s"(p));                  // (nothing of it is read before this place)
+  return *(const DecodeArgs *)reinterpret_cast<const_args_t>(p);
+}
+// What a wave needs of the argument block: read in one go while its first loads travel and kept (a word that
+// is read where it is used, behind the stream, is a round trip on the way of the whole launch).
+template <typename T>
+struct CallArgs {
+  float scale, alpha;
+  int p_stride, rec_per_unit;
+  uint32_t seq, spin_ticks;
+  float *logits_out, *stat_out;
+  int32_t *cand_index_out, *fault;
+  T *out;
+  unsigned long long *part_rec;
+  __device__ __forceinline__ void read() {
+    const DecodeArgs &a = args_from_here<T>();
+    scale = a.scale; alpha = a.alpha;
+    p_stride = a.p_stride; rec_per_unit = a.rec_per_unit;
+    seq = a.seq; spin_ticks = a.spin_ticks;
+    logits_out = a.logits_out; stat_out = a.stat_out;
+    cand_index_out = a.cand_index_out; fault = a.ws.fault;
+    out = static_cast<T *>(a.out);
+    part_rec = a.ws.part_rec;
+    __asm__ volatile("" : "+s"(scale), "+s"(alpha), "+s"(p_stride), "+s"(rec_per_unit), "+s"(seq), "+s"(spin_ticks));
+    keep(logits_out); keep(stat_out); keep(cand_index_out); keep(fault); keep(out); keep(part_rec);
+  }
+  template <typename P>
+  static __device__ __forceinline__ void keep(P *&p) {   // (known as an address of global memory: flat stores would have every load wait for all)
+    auto g = (__attribute__((address_space(1))) P *)p;
+    __asm__ volatile("" : "+s"(g));
+    p = (P *)g;
+  }
+};
+// Units, blocks per unit, query heads per unit and whether sequences have their own timing, in one scalar argument
+// (what a wave is handed in registers at its start is limited to a few words).
+static_assert(kFusedSplitMax < 128, "seven bits");
+inline unsigned pack_shape(int units, int n_split, int group, bool slots) {
+  return static_cast<unsigned>(units) | (static_cast<unsigned>(n_split) << 16) | (static_cast<unsigned>(group - 1) << 23) |
+         (slots ? 1u << 26 : 0u);
+}
+__device__ __forceinline__ int shape_units(unsigned s) { return static_cast<int>(s & 0xFFFFu); }
+__device__ __forceinline__ int shape_split(unsigned s) { return static_cast<int>((s >> 16) & 127u); }
+__device__ __forceinline__ int shape_group(unsigned s) { return static_cast<int>((s >> 23) & 7u) + 1; }
+__device__ __forceinline__ bool shape_slots(unsigned s) { return (s >> 26) & 1u; }
 // kCompact: this call leaves candidate lists instead of every logit.
-// The leading scalar arguments repeat what a stream wave needs to request its first sub-tile
+// The leading scalar arguments repeat what a stream wave needs to request its queries and first sub-tile
 // (the same values are in `a`): scalar kernel arguments are handed to a wave in registers at its
 // start (kernel-argument preload, see build.py), a struct has to be fetched from memory first.
 // kLong (with kCompact): a wave's run is longer than the kRunMax sub-tiles whose logits it keeps
@@ -650,12 +708,14 @@ __global__ __launch_bounds__(kBlock) void clear_records_kernel(unsigned long lon
 // / 7.7, 4 6.3 / 7.2, 6 6.5 / 7.0).
 template <typename T, int D, bool kCompact, bool kLong = false, bool kListWaves = false, int kSplit = 0>
 __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWide ? 2 : 4)) void decode_fused_kernel(
-    const T *k_cache, const T *v_cache, const T *k_new_all, const T *v_new_all, const int n_old_call, const int n_split_call, const int capacity,
-    const int units_call, const int slots_on, const DecodeArgs a) {
+    const T *k_cache, const T *v_cache, const T *k_new_all, const T *v_new_all, const T *q_all, const int n_old_call, const int capacity,
+    const unsigned shape, const DecodeArgs) {
   using R = Rows<T, D>;
   using SubTile = typename R::SubTile;
   constexpr bool kPrecise = R::kPrecise;
-  const int n_split = kSplit > 0 ? kSplit : n_split_call;   // (a constant where the instance fixes it)
+  const int units_call = shape_units(shape), G = shape_group(shape);
+  const bool slots_on = shape_slots(shape);
+  const int n_split = kSplit > 0 ? kSplit : shape_split(shape);   // (a constant where the instance fixes it)
   __shared__ float m_lds[kWaves][16], lsum_lds[kWaves][16];
   // one 16-row K sub-tile per wave while streaming; afterwards the wave's output accumulator
   __shared__ u32x4_t stage_lds[kWaves][16 * 16];
@@ -672,6 +732,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     // tracking of the previous call: n_split blocks per unit, spread over the compute units
     // like the stream blocks
     if (kListWaves && threadIdx.x >= kBlock) return;  // (the tracking has no use for list waves)
+    const DecodeArgs &a = args_from_here<T>();
     const int tb = blockIdx.x - n_split * units_call;
     const int n_track = a.n_track;
     const BlockPlace at = block_place<kSplit>(tb, n_track, units_call);
@@ -729,6 +790,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   const int unit = place.unit, split = place.split;
   int n_old = n_old_call;
   if (slots_on) {                                  // per-sequence timing: this unit's own length
+    const DecodeArgs &a = args_from_here<T>();
     const int seq_s = unit / a.n_kv_heads;
     const int32_t P = a.slots.prompt_len[seq_s], tau = a.t - a.slots.t0[seq_s];
     if (P < 0 || tau < 1) return;                  // the whole unit sits this call out
@@ -737,6 +799,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   const int n1 = n_old + 1;
   const int n_sub = (n1 + 15) >> 4;
 
+  CallArgs<T> a;                                   // (read where a wave has nothing better to do)
   // the appended row goes to slot N (the stream waves read it from k_new / v_new, nobody from the slot)
   auto append_row = [&]() {
     const T *kn = k_new_all + static_cast<size_t>(unit) * D, *vn = v_new_all + static_cast<size_t>(unit) * D;
@@ -771,7 +834,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     const int s0 = (kLong && cnt_w > 0) ? (cnt_w - 1) / kRunMax * kRunMax : 0;
     const int run_w = min(fused_wave_run(n_sub, n_split), kRunMax);
     const float *logits = logit_lds + static_cast<size_t>(w) * run_w * (16 * kHeadPad);
-    sp.group = a.group;
+    sp.group = G;
     sp.alpha98 = 0.98f * a.alpha;
     sp.region = reinterpret_cast<char *>(a.logits_out + (static_cast<size_t>(unit) * a.p_stride +
                                                          static_cast<size_t>(split) * fused_part_cap(n_old, n_split)) * kHeadPad);
@@ -847,10 +910,10 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     // ---- list wave kWaves + w: appends the new row (one of them), plans, sleeps at the barrier
     // that ends the stream, builds stream wave w's list
     const int w = wave - kWaves;
+    a.read();
     if (split == 0 && w == 1) append_row();
     ScanPlan sp;
     plan_scan(sp, w);
-    __asm__ volatile("" ::"s"(sp.group), "s"(sp.alpha98), "s"(sp.region));   // (fetched before the barrier, not after)
     __syncthreads();                               // the stream has ended, the waves' statistics are in LDS
     run_scan(sp);
     __syncthreads();                               // cand_total is complete
@@ -904,18 +967,22 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
       }
     }
   };
-  // ---- the stream starts here: the first sub-tile is requested with what the wave was handed
+  // ---- the stream starts here: the queries and the first sub-tile are requested with what the wave was handed
   // in registers, before anything is read from the argument block in memory
+  // B operand of the logits: Q^T, head c (zero rows beyond the group); piece kk goes with K's piece kk
+  const int hc = min(c, G - 1);
+  const T *q_row = q_all + (static_cast<size_t>(unit) * G + hc) * D + g * (16 / sizeof(T));
+  u32x4_t qb[R::kK];
+#pragma unroll
+  for (int kk = 0; kk < R::kK; ++kk) qb[kk] = *reinterpret_cast<const u32x4_t *>(q_row + kk * (64 / sizeof(T)));
   SubTile buf[R::kDepth];
 #pragma unroll
-  for (int x = 0; x < R::kDepth; ++x)
-    if (x < cnt) { load_k(buf[x], x); load_v(buf[x], x); }
-
-  const int G = a.group;
-  const int seq = unit / a.n_kv_heads, kvh = unit % a.n_kv_heads;
-  const int hc = min(c, G - 1);
-  const size_t head0 = static_cast<size_t>(seq) * a.n_q_heads + static_cast<size_t>(kvh) * G;
-  const T *q_row = static_cast<const T *>(a.q) + (head0 + hc) * D + g * (16 / sizeof(T));
+  for (int x = 0; x < R::kDepth; ++x) {            // (unconditionally, for exact load counts: beyond a short cache, copies of the appended row)
+    load_k(buf[x], x);
+    load_v(buf[x], x);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  a.read();
   const int run = min(fused_wave_run(n_sub, n_split), kRunMax);
   float *my_logits = logit_lds + static_cast<size_t>(wave) * run * (16 * kHeadPad);
   int seg0 = 0;                                    // first of this wave's sub-tiles whose logits are still in LDS
@@ -927,13 +994,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
 #pragma unroll
   for (int e = 0; e < R::kAcc; ++e) o[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // B operand of the logits: Q^T, head c (zero rows beyond the group); piece kk goes with K's piece kk
-  u32x4_t qb[R::kK];
 #pragma unroll
-  for (int kk = 0; kk < R::kK; ++kk) {
-    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(q_row + kk * (64 / sizeof(T)));
-    qb[kk] = c < G ? v : u32x4_t{0, 0, 0, 0};
-  }
+  for (int kk = 0; kk < R::kK; ++kk) qb[kk] = c < G ? qb[kk] : u32x4_t{0, 0, 0, 0};
 
   // kMore (a std::bool_constant): the wave has a sub-tile kDepth after this one and requests it here.
   // kAgain: the wave goes over its run once more because an accumulator became NaN (see below)
@@ -1177,6 +1239,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   };
   // logits of a long run leave LDS every kRunMax sub-tiles
   auto segment_end = [&](int it) {
+    if constexpr (kCompact && !kLong) return;      // (its runs are no longer than that)
     if (it + 1 - seg0 == kRunMax && it + 1 < cnt) {
       if constexpr (kLong) segment_candidates(seg0, it + 1);
       else flush(seg0, it + 1);
@@ -1278,7 +1341,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   const int group0 = split / kMergeRadix * kMergeRadix;   // the blocks group0 .. of this block's group
   const bool leader = finisher || split - group0 == kMergeRadix - 1;
   const int t_own = ec >> 2;                       // (threads beyond the group's rows read a valid place)
-  unsigned long long *recs = a.ws.part_rec + static_cast<size_t>(unit) * a.rec_per_unit * kRecWords;
+  unsigned long long *recs = a.part_rec + static_cast<size_t>(unit) * a.rec_per_unit * kRecWords;
   if (!leader && e0 < G * D) rec_store(recs + static_cast<size_t>(split) * kRecWords, tid, v_own, mb_own, l_own, a.seq);
   // what only the NEXT launch needs, while the partial travels: the appended row and this wave's
   // candidate list (list waves, where the block has them, do both meanwhile)
@@ -1301,7 +1364,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     const f32x4_t o4 = {mg.o[0], mg.o[1], mg.o[2], mg.o[3]};
     if (kSplit > 0 || n_split <= kMergeRadix) {
       STAMP(4);
-      write_unit_row<T, D>(a, unit, mg, e0, h_own);
+      write_unit_row<T, D>(a, unit, G, mg, e0, h_own);
     } else if (!finisher) {
       if (e0 < G * D) rec_store(recs + static_cast<size_t>(split) * kRecWords, tid, o4, mg.m, mg.l, a.seq);
     } else {
@@ -1310,7 +1373,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
           a, recs + static_cast<size_t>(kMergeRadix - 1) * kRecWords, kMergeRadix * kRecWords, group0 / kMergeRadix, t_own,
           mg.m, mg.l, o4);
       STAMP(4);
-      write_unit_row<T, D>(a, unit, all, e0, h_own);
+      write_unit_row<T, D>(a, unit, G, all, e0, h_own);
     }
   }
   if (kCompact) {
@@ -1350,7 +1413,8 @@ hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) 
   const int sb = a.n_split * units;
   const T *kc = static_cast<const T *>(a.k_cache), *vc = static_cast<const T *>(a.v_cache);
   const T *kn = static_cast<const T *>(a.k_new), *vn = static_cast<const T *>(a.v_new);
-  const int slots_on = a.slots.prompt_len ? 1 : 0;
+  const T *q = static_cast<const T *>(a.q);
+  const unsigned shape = pack_shape(units, a.n_split, a.group, a.slots.prompt_len != nullptr);
   const bool long_run = fused_wave_run(n_sub, a.n_split) > kRunMax;
   // list waves (blocks of eight waves) where every block of the launch is resident at once: two
   // such blocks fit a compute unit
@@ -1359,7 +1423,7 @@ hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) 
   const bool resident = n_blocks <= 2 * compute_units();
   const dim3 grid(n_blocks), block(kBlock), block_l(kList ? 2 * kBlock : kBlock);
 #define LAZYEV_LAUNCH(block, ...) \
-  hipLaunchKernelGGL((decode_fused_kernel<T, D, __VA_ARGS__>), grid, block, lds_all, stream, kc, vc, kn, vn, a.n_old, a.n_split, a.capacity, units, slots_on, a)
+  hipLaunchKernelGGL((decode_fused_kernel<T, D, __VA_ARGS__>), grid, block, lds_all, stream, kc, vc, kn, vn, q, a.n_old, a.capacity, shape, a)
 #define LAZYEV_SPLIT(n) \
   case n: \
     if (long_run) LAZYEV_LAUNCH(block_l, true, true, kList, n); \
