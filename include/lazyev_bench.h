@@ -24,7 +24,7 @@ extern "C" {
  *   lazyev_set_target_blocks: stream blocks per layer call the single-launch attention kernel
  *     aims for, taken literally: each unit gets round(n_blocks / units) blocks, at least one
  *     and at most 64, and no more than the workspace has records for: one per block but the last,
- *     12 KB each, in the area of the vector-ALU kernel's partials (20 blocks for units of 2112
+ *     8 KB each, in the area of the vector-ALU kernel's partials (30 blocks for units of 2112
  *     entries, 7 query heads of 128; never fewer than the library's own choice).  Until this is called the library sizes the split from the number of units
  *     and the cache length (about one block per compute unit).
  * Errors: EINVAL. */

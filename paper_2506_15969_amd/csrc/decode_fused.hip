@@ -479,22 +479,29 @@ __global__ __launch_bounds__(kBlock) void track_flush_kernel(const FlushArgs f) 
 }
 
 // ------------------------------------------------------------- merging the partials of a unit
-// Running merge of partials in block order.  Every product and sum is written out with its
-// rounding (no contraction left to the compiler), so that all kernel instances produce the same
-// bits from the same partials.
+// A merged partial: maximum, sum and this thread's four output values of n partials, in block order, each scaled to the
+// largest of the maxima: that is found first, so that the exponentials do not wait for one another and every
+// partial takes one.  Every product and sum is written out with its rounding (no contraction left to the
+// compiler), so that all kernel instances produce the same bits from the same partials.
 template <bool kPrecise>
 struct Merge {
-  float m = -FLT_MAX, l = 0.f;
-  float o[4] = {0.f, 0.f, 0.f, 0.f};
-  __device__ __forceinline__ void fold(float mj, float lj, const f32x4_t &oj) {
+  float m, l;
+  float o[4];
+  // (a block without entries has the lowest maximum, sum = 0, values = 0)
+  __device__ __forceinline__ void start(float m_all, float mj, float lj, const f32x4_t &oj) {
 #pragma clang fp contract(off)
-    const float m_new = fmaxf(m, mj);
-    // (a block without entries has the lowest maximum, sum = 0, values = 0)
-    const float fr = exp_of<kPrecise>(m - m_new), fj = exp_of<kPrecise>(mj - m_new);
-    l = fmaf(l, fr, lj * fj);
+    m = m_all;
+    const float f = exp_of<kPrecise>(mj - m);
+    l = lj * f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = fmaf(o[i], fr, oj[i] * fj);
-    m = m_new;
+    for (int i = 0; i < 4; ++i) o[i] = oj[i] * f;
+  }
+  __device__ __forceinline__ void add(float mj, float lj, const f32x4_t &oj) {
+#pragma clang fp contract(off)
+    const float f = exp_of<kPrecise>(mj - m);
+    l = fmaf(lj, f, l);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = fmaf(oj[i], f, o[i]);
   }
 };
 
@@ -524,8 +531,8 @@ __device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, c
 
 // ------------------------------------------------------------------- hand-over of partials
 // A block hands its partial over to a block of a higher index as a record of 64-bit words, each =
-// (number of the launch << 32) | value bits, written and read with 64-bit device-scope atomics.  A
-// word that shows this launch's number holds this launch's value, whatever else is still on its way,
+// 16 bits of the launch's number, 16 bits of the maximum or the sum, 32 bits of an output value, written and read with 64-bit
+// device-scope atomics.  A word that shows this launch's number holds this launch's values, whatever else is still on its way,
 // so the writer neither waits for its stores nor signals, and the reader needs no second round
 // trip after a flag: it reads the words it needs until all of them carry the number.  Blocks are
 // started in index order and a block waits for blocks of lower indices only, so every wait ends;
@@ -538,47 +545,60 @@ __device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, c
 // group, and the unit's last block, a leader itself, merges what the other leaders hand over: one
 // hop for up to kMergeRadix blocks, two for up to kFusedSplitMax.  A hop is one memory round trip
 // whatever the number of records, because all of them are requested together.
-// Record of a block: for each of the four waves six rows of 64 words; rows 0..3 hold the output
-// elements (element 4 t + i of thread t in row i: one store instruction of a wave writes 512
-// contiguous bytes), rows 4 and 5 the maximum and the sum of thread t's head (each thread its own
-// copy: what the reader needs of a head then never waits for another wave's store).  A thread's six
-// words lie within the reach of a load's constant offset.
-constexpr int kRecWords = 6 * kBlock;
-__device__ __forceinline__ unsigned rec_at(int t) { return static_cast<unsigned>(t >> 6) * (6 * 64) + (t & 63); }
+// The numbers run from 1 to 65535; before they start over the records are cleared (lazyev_decode_step).
+// Record of a block: for each of the four waves four rows of 64 words; row i holds the output
+// element 4 t + i of thread t (one store instruction of a wave writes 512
+// contiguous bytes), and the 16 bits beside it are a half of the maximum (rows 0 and 1) or the sum of thread t's head (each thread its own
+// copy: what the reader needs of a head then never waits for another wave's store).  What a merge costs is the
+// instructions of single waves: with a word of its own, half of it the number, for each of the six values, a merge of seven
+// records was 42 loads and 42 comparisons, now 28 and 14, and with one exponential per record instead of two that wait for
+// those before (see Merge) 8 units x 2081 entries take 2074 us for 256 calls instead of 2218, 32 x 1040 241 for 32 instead of 256.
+constexpr int kRecWords = 4 * kBlock;
+// thread t's first word, as a byte offset
+__device__ __forceinline__ unsigned rec_at(int t) { return (static_cast<unsigned>(t >> 6) * (4 * 64) + (t & 63)) * 8u; }
 constexpr int kMergeRadix = 8;
+constexpr uint32_t kSeqMax = 0xFFFF;
 
-__device__ __forceinline__ void rec_word_store(unsigned long long *p, float v, unsigned seq) {
-  __hip_atomic_store(p, (static_cast<unsigned long long>(seq) << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
+__device__ __forceinline__ void rec_word_store(unsigned long long *p, float v, unsigned top) {
+  __hip_atomic_store(p, (static_cast<unsigned long long>(top) << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void rec_store(unsigned long long *rec, int t_own, const f32x4_t &o, float m, float l, unsigned seq) {
+  const unsigned mu = __float_as_uint(m), lu = __float_as_uint(l), number = seq << 16;
+  const unsigned top[4] = {number | (mu >> 16), number | (mu & 0xFFFFu), number | (lu >> 16), number | (lu & 0xFFFFu)};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) rec_word_store(rec + rec_at(t_own) + i * 64, o[i], seq);
-  rec_word_store(rec + rec_at(t_own) + 4 * 64, m, seq);
-  rec_word_store(rec + rec_at(t_own) + 5 * 64, l, seq);
+  for (int i = 0; i < 4; ++i)
+    rec_word_store(reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(rec) + rec_at(t_own)) + i * 64, o[i], top[i]);
 }
 // What one thread reads of another block's record: its four output elements, its head's max and sum.
-struct RecPart { unsigned long long w[6]; };
+struct RecPart { unsigned long long w[4]; };
+// (rec, the same for the whole wave, is kept a scalar: with the four addresses of every record in vector registers seven records spill)
 __device__ __forceinline__ void rec_load(RecPart &r, const unsigned long long *rec, unsigned at) {
+  auto base = (const __attribute__((address_space(1))) char *)rec;
+  __asm__ volatile("" : "+s"(base));
 #pragma unroll
-  for (int i = 0; i < 6; ++i)
-    r.w[i] = __hip_atomic_load(rec + at + i * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int i = 0; i < 4; ++i)
+    r.w[i] = __hip_atomic_load((const __attribute__((address_space(1))) unsigned long long *)(base + at) + i * 64, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned rec_top(const RecPart &r, int i) { return static_cast<unsigned>(r.w[i] >> 32); }
+// the upper halves of words i and i + 1 (upper) or the lower ones
+__device__ __forceinline__ unsigned rec_halves(const RecPart &r, int i, bool upper) {
+  return __builtin_amdgcn_perm(rec_top(r, i), rec_top(r, i + 1), upper ? 0x07060302u : 0x05040100u);
 }
 __device__ __forceinline__ bool rec_valid(const RecPart &r, unsigned seq) {
-  bool ok = true;
-#pragma unroll
-  for (int i = 0; i < 6; ++i) ok = ok & (static_cast<unsigned>(r.w[i] >> 32) == seq);
-  return ok;
+  const unsigned twice = seq | (seq << 16);
+  return ((rec_halves(r, 0, true) ^ twice) | (rec_halves(r, 2, true) ^ twice)) == 0;
 }
-__device__ __forceinline__ float rec_value(unsigned long long w) { return __uint_as_float(static_cast<unsigned>(w)); }
+__device__ __forceinline__ float rec_max(const RecPart &r) { return __uint_as_float(rec_halves(r, 0, false)); }
+__device__ __forceinline__ float rec_sum(const RecPart &r) { return __uint_as_float(rec_halves(r, 2, false)); }
 __device__ __forceinline__ f32x4_t rec_values(const RecPart &r) {
-  return f32x4_t{rec_value(r.w[0]), rec_value(r.w[1]), rec_value(r.w[2]), rec_value(r.w[3])};
+  auto value = [&](int i) { return __uint_as_float(static_cast<unsigned>(r.w[i])); };
+  return f32x4_t{value(0), value(1), value(2), value(3)};
 }
 
 // What one thread needs of n <= N records at rec, rec + stride, ..., all requested together, again
 // until every word carries the launch's number; then the records and (m, l, o) merged in this order.
-// The running merge starts from the first record as it is: folding it into the empty state would
-// reproduce exactly its bits (factors 0 and exp(0) = 1) at the price of a dozen instructions.
 template <int N, bool kPrecise, typename Args>
 __device__ __forceinline__ Merge<kPrecise> merge_records(const Args &a, const unsigned long long *rec, int stride, int n,
                                                int t_own, float m, float l, const f32x4_t &o) {
@@ -603,18 +623,18 @@ __device__ __forceinline__ Merge<kPrecise> merge_records(const Args &a, const un
     const unsigned long long now = wall_clock64();
     if (t_first == 0) t_first = now;
     if (now - t_first >= a.spin_ticks) {           // (a limit of 0: no second look)
-      atomicOr(a.fault, 1);                     // (cannot happen otherwise, see above; the row is then wrong)
+      atomicOr(a.fault, 1);                        // (cannot happen otherwise, see above; the row is then wrong)
       break;
     }
   }
-  mg.m = rec_value(r[0].w[4]);
-  mg.l = rec_value(r[0].w[5]);
+  float m_all = m;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) mg.o[i] = rec_value(r[0].w[i]);
+  for (int j = 0; j < N; ++j) m_all = fmaxf(m_all, rec_max(r[j]));
+  mg.start(m_all, rec_max(r[0]), rec_sum(r[0]), rec_values(r[0]));
 #pragma unroll
   for (int j = 1; j < N; ++j)
-    if (j < n) mg.fold(rec_value(r[j].w[4]), rec_value(r[j].w[5]), rec_values(r[j]));
-  mg.fold(m, l, o);
+    if (j < n) mg.add(rec_max(r[j]), rec_sum(r[j]), rec_values(r[j]));
+  mg.add(m, l, o);
   return mg;
 }
 
@@ -1355,10 +1375,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   }
   if (leader) {
     constexpr int kIn = kSplit > 1 ? kSplit - 1 : kMergeRadix - 1;   // (instances of a fixed split have one group)
-    // (for four records and more the count is kept from the compiler, which would otherwise hold so
-    // many addresses at once that registers spill: 8 blocks per unit of 2048 entries, 14.4 us instead of 8.0)
-    int n_in = kSplit > 0 ? kSplit - 1 : split - group0;
-    if (kSplit > 4) __asm__("" : "+s"(n_in));
+    const int n_in = kSplit > 0 ? kSplit - 1 : split - group0;
     const Merge<kPrecise> mg = merge_records<kIn, kPrecise>(a, recs + static_cast<size_t>(group0) * kRecWords, kRecWords, n_in, t_own,
                                         mb_own, l_own, v_own);
     const f32x4_t o4 = {mg.o[0], mg.o[1], mg.o[2], mg.o[3]};
@@ -1478,6 +1495,7 @@ extern "C" int lazyev_timeline_read(unsigned long long *out, int n_words) {
 }
 #endif
 int decode_fused_split_max() { return kFusedSplitMax; }
+uint32_t decode_fused_seq_max() { return kSeqMax; }
 size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * sizeof(unsigned long long); }
 
 // Blocks per unit.  Measured on 28 query / 4 KV heads of 128 x bf16, us per call; the other row types take the same rule:
@@ -1510,7 +1528,7 @@ int decode_fused_split(int units, int n_sub) {
   return n < by_work ? n : by_work;
 }
 
-// A unit of n blocks hands over n - 1 records.  decode_fused_split has at most 512 blocks for all units together (6 MB
+// A unit of n blocks hands over n - 1 records.  decode_fused_split has at most 512 blocks for all units together (4 MB
 // of records); lazyev_set_target_blocks may ask for more, as far as the area that is there anyway holds them.
 int decode_fused_records_needed(int units, int capacity) {
   const int by_length = ((capacity + 15) / 16 + 3) / 4, by_units = (2 * 256 + units - 1) / units;
@@ -1572,7 +1590,7 @@ hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent
   const int units = a.batch * a.n_kv_heads;
   if (a.group > kHeadPad || a.n_split < 1 ||
       a.n_split > kFusedSplitMax || a.n_split > a.rec_per_unit + 1 || !a.logits_out ||
-      !a.ws.part_rec || !a.ws.fault || a.seq == 0 ||
+      !a.ws.part_rec || !a.ws.fault || a.seq == 0 || a.seq > kSeqMax ||
       !a.stat_out || a.p_stride < (a.n_old + 16) / 16 * 16 ||
       (a.track.valid && (a.track.units != units || !a.track.logits || !a.track.stat ||
                          a.track.logits == a.logits_out || a.track.stat == a.stat_out)) ||

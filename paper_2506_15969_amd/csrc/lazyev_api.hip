@@ -560,10 +560,10 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
     // The number of this launch stamps the partials its blocks hand over; 0 is what a cleared record
     // holds.  Records are cleared before their first use (what lazyev_init did not clear, because only
     // lazyev_set_target_blocks asks for it; what the split + merge kernels wrote over), and
-    // after the number has wrapped around.  A call that is being captured will be launched with one
+    // when the numbers start over (every 65535 launches).  A call that is being captured will be launched with one
     // number again and again: its records go back to 0 before each time (the default stream cannot
     // be captured).
-    if (++ctx->launch_seq == 0) {
+    if (++ctx->launch_seq > lazyev::decode_fused_seq_max()) {
       ctx->launch_seq = 1;
       ctx->rec_clean = 0;
     }

@@ -75,3 +75,33 @@ def test_more_units_than_blocks_fit_evenly(lazyev_lib, batch, N):
             assert float(err.max()) < 2 * 2.0 ** -8, (s, t, float(err.max()))
     assert eng.stats()["len"] == [N + steps]
     eng.close()
+
+
+def test_launch_numbers_start_over(lazyev_lib):
+    """The stamp of a record has 16 bits: 67 layers x 980 steps are more launches than that.  Outputs of the steps
+    around the 65536th launch against fp64 softmax attention, and no block gave up waiting."""
+    L, H, group, B, W, steps = 67, 2, 7, 130, 60, 980
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    eng = lazyev_lib.LazyEviction(L, 1, group * H, H, 128, B, W, B, 0.05)
+    eng.k_cache[:, :, :, :B].normal_(generator=gen)
+    eng.v_cache[:, :, :, :B].normal_(generator=gen)
+    eng.init()
+    q, kn, vn = (torch.empty((4, 1, h, 128), device="cuda").normal_(generator=gen).to(torch.bfloat16) for h in (group * H, H, H))
+    out = torch.zeros((L, 1, group * H, 128), dtype=torch.bfloat16, device="cuda")
+    n = B
+    for t in range(1, steps + 1):
+        x = t % 4
+        for layer in range(L):
+            eng.decode_step(layer, t, q[x], kn[x], vn[x], out[layer])
+        n += 1
+        if 976 <= t <= 979:                            # launches 65326 .. 65593
+            ref_q = q[x, 0].double().view(H, group, 128)
+            k, v = eng.k_cache[:, 0, :, :n].double(), eng.v_cache[:, 0, :, :n].double()
+            p = torch.softmax(torch.matmul(ref_q, k.transpose(2, 3).contiguous()) / np.sqrt(128.0), dim=-1)
+            ref = torch.matmul(p, v).view(L, group * H, 128)
+            err = (out[:, 0].double() - ref).norm(dim=2) / ref.norm(dim=2)
+            assert float(err.max()) < 2 * 2.0 ** -8, (t, float(err.max()))   # (two roundings to bf16, as above)
+        if eng.evict_all(t):
+            n = B
+    assert eng.stats()["last_step"] == [steps] * L
+    eng.close()
