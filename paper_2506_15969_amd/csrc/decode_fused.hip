@@ -155,10 +155,11 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2_t;
 
-__device__ __forceinline__ bf16_t float_to_bf16(float f) {   // round to nearest even
-  unsigned u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return static_cast<bf16_t>(u >> 16);
+// two floats as bf16, rounded to nearest even (one instruction), the first in the lower half
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+__device__ __forceinline__ unsigned pair_to_bf16(float lo, float hi) {
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
 }
 
 // x + (x of lane ^ 16) + (the same of lane ^ 32), and the maximum likewise: the sum / maximum over
@@ -516,10 +517,8 @@ __device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, c
     *reinterpret_cast<f32x4_t *>(out) = f32x4_t{mg.o[0] * invl, mg.o[1] * invl, mg.o[2] * invl, mg.o[3] * invl};
   } else {
   u32x2_t w;
-  w[0] = static_cast<unsigned>(float_to_bf16(mg.o[0] * invl)) |
-         (static_cast<unsigned>(float_to_bf16(mg.o[1] * invl)) << 16);
-  w[1] = static_cast<unsigned>(float_to_bf16(mg.o[2] * invl)) |
-         (static_cast<unsigned>(float_to_bf16(mg.o[3] * invl)) << 16);
+  w[0] = pair_to_bf16(mg.o[0] * invl, mg.o[1] * invl);
+  w[1] = pair_to_bf16(mg.o[2] * invl, mg.o[3] * invl);
   *reinterpret_cast<u32x2_t *>(out) = w;
   }
   if (e0 % D == 0) {
@@ -739,6 +738,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   __shared__ float m_lds[kWaves][16], lsum_lds[kWaves][16];
   // one 16-row K sub-tile per wave while streaming; afterwards the wave's output accumulator
   __shared__ u32x4_t stage_lds[kWaves][16 * 16];
+  __shared__ u32x4_t new_lds[kWaves][2 * Rows<T, D>::kLanes];   // the appended rows of K and V, a copy per wave
   extern __shared__ float logit_lds[];             // [kWaves][min(run, kRunMax)][16 entries][8 heads]
   __shared__ unsigned cnt_lds[kWaves];
   __shared__ unsigned cand_total;                  // candidate records of this block so far
@@ -950,40 +950,92 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   const T *k_new = k_new_all + static_cast<size_t>(unit) * D;
   const T *v_new = v_new_all + static_cast<size_t>(unit) * D;
 
+  // Two ways to a sub-tile's rows.  kFlat: they lie one after the other in the cache, so a scalar address and one 32-bit offset
+  // per lane and load reach them, rows beyond the cache taken as its last one; the row to be appended is not there yet,
+  // and patch_k and patch_v put it in place when the unit's last sub-tile, which alone has it, is worked on.  Otherwise every load
+  // chooses the source of its row, 64 of the 230 vector instructions of a sub-tile.  Where the bytes set the time those cost
+  // nothing, and the patch at the end of the run does: us per pass, chosen / flat, 128 units x 2081 3009 / 3029, x 4129 of 80 (2 blocks a unit) 5766 / 5816;
+  // with three blocks a unit or more, and for rows of 128 bytes, the latency of a sub-tile does: 8 units x 2081 1999 / 1950,
+  // 48 units x 1000 1273 / 1254, 64 units x 1563 of 64 x bf16 1160 / 1090.  (fp32 rows: the products are longer than either, 840 / 842.)
+  constexpr bool kFlat = !R::kF32 && (kSplit >= 3 || R::kBytes == 128);
   auto load_k = [&](SubTile &t, int it) {
-    const int sub = sub_of(it);
-    if constexpr (R::kF32) {
-      // fp32: straight into the MFMA operand layout, lane (c, g): row c, columns 16 j + 4 g .. + 3
-      const int row = min(sub * 16 + c, n_old);
-      const T *src = ((row == n_old) ? k_new : kc + static_cast<size_t>(row) * D) + 4 * g;
+    if constexpr (!kFlat) {
+      const int sub = sub_of(it);
+      if constexpr (R::kF32) {
+        // fp32: straight into the MFMA operand layout, lane (c, g): row c, columns 16 j + 4 g .. + 3
+        const int row = min(sub * 16 + c, n_old);
+        const T *src = ((row == n_old) ? k_new : kc + static_cast<size_t>(row) * D) + 4 * g;
 #pragma unroll
-      for (int j = 0; j < R::kK; ++j) t.k[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + 16 * j));
-    } else {
-      // bf16: whole rows, kLanes lanes per row; re-laid out through LDS
+        for (int j = 0; j < R::kK; ++j) t.k[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + 16 * j));
+      } else {
+        // bf16: whole rows, kLanes lanes per row; re-laid out through LDS
 #pragma unroll
-      for (int j = 0; j < R::kK; ++j) {
-        const int row = min(sub * 16 + j * (64 / R::kLanes) + lane / R::kLanes, n_old);
-        const T *src = (row == n_old) ? k_new : kc + static_cast<size_t>(row) * D;
-        t.k[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + (lane % R::kLanes) * 8));
+        for (int j = 0; j < R::kK; ++j) {
+          const int row = min(sub * 16 + j * (64 / R::kLanes) + lane / R::kLanes, n_old);
+          const T *src = (row == n_old) ? k_new : kc + static_cast<size_t>(row) * D;
+          t.k[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + (lane % R::kLanes) * 8));
+        }
+      }
+      return;
+    }
+    const int sub = min(sub_of(it), n_sub - 1), left = n_old - sub * 16;
+    const char *rows = reinterpret_cast<const char *>(kc) + static_cast<size_t>(sub) * (16 * R::kBytes);
+    const unsigned last = static_cast<unsigned>(min(left, 16) * R::kBytes + (lane % R::kLanes) * 16);
+#pragma unroll
+    for (int j = 0; j < R::kK; ++j)
+      t.k[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(rows + min(static_cast<unsigned>(lane * 16 + j * 1024), last)));
+  };
+  auto load_v = [&](SubTile &t, int it) {
+    if constexpr (!kFlat) {
+      const int sub = sub_of(it);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = min(sub * 16 + 4 * g + i, n_old);
+        const T *src = (row == n_old) ? v_new : vc + static_cast<size_t>(row) * D;
+        if constexpr (R::kF32) {                     // columns 64 h + 4 c .. + 3
+#pragma unroll
+          for (int h = 0; h < D / 64; ++h)
+            t.v[i * (D / 64) + h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + 64 * h + c * 4));
+        } else if constexpr (D == 128) {             // columns 8 c .. + 7
+          t.v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + c * 8));
+        } else {                                     // columns 4 c .. + 3
+          const u32x2_t x = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t *>(src + c * 4));
+          t.v[i / 2][2 * (i % 2)] = x[0];
+          t.v[i / 2][2 * (i % 2) + 1] = x[1];
+        }
+      }
+      return;
+    }
+    const int sub = min(sub_of(it), n_sub - 1), left = n_old - sub * 16;
+    const char *rows = reinterpret_cast<const char *>(vc) + static_cast<size_t>(sub) * (16 * R::kBytes);
+    const unsigned last = static_cast<unsigned>(min(left, 16) * R::kBytes + c * (D / 8));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {                  // rows 4 g .. 4 g + 3; columns 8 c .. + 7 or 4 c .. + 3
+      const unsigned at = min(static_cast<unsigned>((4 * g + i) * R::kBytes + c * (D / 8)), last);
+      if constexpr (D == 128) {
+        t.v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(rows + at));
+      } else {
+        const u32x2_t x = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t *>(rows + at));
+        t.v[i / 2][2 * (i % 2)] = x[0];
+        t.v[i / 2][2 * (i % 2) + 1] = x[1];
       }
     }
   };
-  auto load_v = [&](SubTile &t, int it) {
-    const int sub = sub_of(it);
+  // kFlat, the unit's last sub-tile: the lanes whose row is the appended one, or beyond it, get V from where the wave
+  // has kept it in LDS since its start (K: see compute).  kPrecise: rows beyond count as zero: zero times an infinite element is NaN.
+  auto patch_v = [&](SubTile &t, int left) {
+    const char *row = reinterpret_cast<const char *>(new_lds[wave]) + R::kBytes;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int row = min(sub * 16 + 4 * g + i, n_old);
-      const T *src = (row == n_old) ? v_new : vc + static_cast<size_t>(row) * D;
-      if constexpr (R::kF32) {                     // columns 64 h + 4 c .. + 3
-#pragma unroll
-        for (int h = 0; h < D / 64; ++h)
-          t.v[i * (D / 64) + h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + 64 * h + c * 4));
-      } else if constexpr (D == 128) {             // columns 8 c .. + 7
-        t.v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + c * 8));
-      } else {                                     // columns 4 c .. + 3
-        const u32x2_t x = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t *>(src + c * 4));
-        t.v[i / 2][2 * (i % 2)] = x[0];
-        t.v[i / 2][2 * (i % 2) + 1] = x[1];
+      const bool here = 4 * g + i >= left, beyond = kPrecise && 4 * g + i > left;
+      if constexpr (D == 128) {
+        const u32x4_t x = *reinterpret_cast<const u32x4_t *>(row + c * 16);
+        t.v[i] = here ? x : t.v[i];
+      } else {
+        u32x2_t x = *reinterpret_cast<const u32x2_t *>(row + c * 8);
+        x = beyond ? u32x2_t{0, 0} : x;
+        t.v[i / 2][2 * (i % 2)] = here ? x[0] : t.v[i / 2][2 * (i % 2)];
+        t.v[i / 2][2 * (i % 2) + 1] = here ? x[1] : t.v[i / 2][2 * (i % 2) + 1];
       }
     }
   };
@@ -995,14 +1047,22 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   u32x4_t qb[R::kK];
 #pragma unroll
   for (int kk = 0; kk < R::kK; ++kk) qb[kk] = *reinterpret_cast<const u32x4_t *>(q_row + kk * (64 / sizeof(T)));
+  u32x4_t new_piece = {0, 0, 0, 0};
+  if (kFlat) new_piece = reinterpret_cast<const u32x4_t *>(lane & R::kLanes ? v_new : k_new)[lane % R::kLanes];
   SubTile buf[R::kDepth];
 #pragma unroll
-  for (int x = 0; x < R::kDepth; ++x) {            // (unconditionally, for exact load counts: beyond a short cache, copies of the appended row)
+  for (int x = 0; x < R::kDepth; ++x) {            // (unconditionally, for exact load counts: beyond a short cache, copies of its end)
     load_k(buf[x], x);
     load_v(buf[x], x);
   }
   __builtin_amdgcn_sched_barrier(0);
   a.read();
+  if constexpr (kFlat) {
+    new_lds[wave][lane % (2 * R::kLanes)] = new_piece;   // (where fewer lanes cover it, several write the same)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
   const int run = min(fused_wave_run(n_sub, n_split), kRunMax);
   float *my_logits = logit_lds + static_cast<size_t>(wave) * run * (16 * kHeadPad);
   int seg0 = 0;                                    // first of this wave's sub-tiles whose logits are still in LDS
@@ -1022,6 +1082,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   auto compute = [&](SubTile &t, int it, auto more_tag, auto again_tag) {
     constexpr bool kMore = decltype(more_tag)::value, kAgain = decltype(again_tag)::value;
     const int sub = sub_of(it);
+    const bool last_sub = !kMore && sub == n_sub - 1;   // (wave-uniform)
+    const int left = n_old - sub * 16;
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     if constexpr (R::kF32) {
       // Four terms per instruction; which four of the row's columns go together does not matter as
@@ -1056,14 +1118,18 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
         const int r = j * (64 / R::kLanes) + r0;
         stage[r * R::kLanes + (ch ^ (r % R::kLanes))] = t.k[j];
       }
+      if (kFlat && last_sub && lane < R::kLanes) stage[left * R::kLanes + (lane ^ (left % R::kLanes))] = new_lds[wave][lane];
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      // the K registers are free again: the next sub-tile's K rows travel during the arithmetic
+      if constexpr (kMore) {
+        load_k(t, it + R::kDepth);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int kk = 0; kk < R::kK; ++kk) ka[kk] = stage[c * R::kLanes + ((4 * kk + g) ^ (c % R::kLanes))];
     }
-    // the K registers are free again: the next sub-tile's K rows travel during the arithmetic
-    if constexpr (kMore) load_k(t, it + R::kDepth);
     if constexpr (kPrecise) {                      // (two sums of 32 terms, then their sum)
       const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[0]), __builtin_bit_cast(bf16x8_t, qb[0]), zero, 0, 0, 0) +
@@ -1078,7 +1144,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     float s[4];
     const int e0 = sub * 16 + 4 * g;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s[i] = (e0 + i < n1) ? acc[i] * a.scale : -INFINITY;
+    for (int i = 0; i < 4; ++i) s[i] = kMore || e0 + i < n1 ? acc[i] * a.scale : -INFINITY;   // (a wave's earlier sub-tiles are full)
     // logits of the sub-tile -> [entry][head] in LDS; written out when the wave's run ends (a
     // store among the loads would hold up the in-order load counter)
     if (!kAgain && c < kHeadPad) {
@@ -1104,7 +1170,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[i] = exp_of<kPrecise>(s[i] - m_ref);
     lsum += (p[0] + p[1]) + (p[2] + p[3]);
-    if constexpr (kPrecise && !kMore) {
+    if (kFlat && last_sub) patch_v(t, left);
+    if constexpr (kPrecise && !kFlat && !kMore) {
       // The unit's last sub-tile: rows beyond the cache are copies of the appended one with a weight of zero, and
       // zero times an infinite element is NaN
       if (sub == n_sub - 1) {                      // wave-uniform
@@ -1141,15 +1208,15 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     s16x4_t pa[kTerms];
 #pragma unroll
     for (int x = 0; x < kTerms; ++x) {
-      bf16_t pb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        pb[i] = float_to_bf16(p[i]);
-        if (kPrecise) p[i] -= __uint_as_float(static_cast<unsigned>(pb[i]) << 16);
-      }
       u32x2_t pw;
-      pw[0] = static_cast<unsigned>(pb[0]) | (static_cast<unsigned>(pb[1]) << 16);
-      pw[1] = static_cast<unsigned>(pb[2]) | (static_cast<unsigned>(pb[3]) << 16);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        pw[i] = pair_to_bf16(p[2 * i], p[2 * i + 1]);
+        if (kPrecise) {
+          p[2 * i] -= __uint_as_float(pw[i] << 16);
+          p[2 * i + 1] -= __uint_as_float(pw[i] & 0xFFFF0000u);
+        }
+      }
       pa[x] = __builtin_bit_cast(s16x4_t, pw);
     }
 #pragma unroll
