@@ -28,16 +28,19 @@
 // Blocks start in index order, so the heaviest tiles get the lowest indices.  No wave waits for another block.
 //
 // What bounds it: the vector work beside the products (a multiply-add, an exponential and an addition per weight
-// in the first kernel, a maximum in the second; the matrix cores are busy 35% of the time).  Measured, us for both
+// in the first kernel, a maximum in the second; the matrix cores are busy 45 % of the time).  Measured, us for both
 // kernels, before (a running maximum with two exponentials per weight, an exponential and a comparison per
 // weight in the second kernel, rows of 64 and fp32 rows on a kernel without matrix instructions) and now, calls back to
 // back (3 % from box to box; the other figures in this file are against 1190 - 1223 us for 2048 positions in their own runs):
-//   32 sequences, 28 / 4 heads of 128, bf16   600 positions 292 -> 178, 2048 positions 1370 -> 1150
-//   16 sequences, 40 / 8 heads of 128, bf16  4096 positions 3520 -> 2900
+//   32 sequences, 28 / 4 heads of 128, bf16   600 positions 292 -> 166, 2048 positions 1370 -> 1050
+//   16 sequences, 40 / 8 heads of 128, bf16  4096 positions 3520 -> 2760
 //    8 sequences, 28 / 4 heads of 128, bf16  1024 positions 350 -> 110
 //    1 sequence,  28 / 4 heads of 128, bf16    33 positions 22.9 -> 13.0,  400 positions 141 -> 23.6
 //    4 sequences, 32 / 8 heads of  64, bf16   499 positions 5470 -> 30
 //    2 sequences, 28 / 4 heads of 128, fp32   300 positions 10880 -> 48
+// (Of the first two 1158 -> 1050 and 2960 -> 2760 by loops without a way out of their middle, whose stages therefore waited for their own
+// request, by masks and maxima in place instead of copies of 16 registers a stage, and by four waves per SIMD in the first kernel.
+// The clock falls as the matrix cores get busier, 1.98 -> 1.87 GHz under the profiler: 16 % fewer cycles were 12 % of the time.)
 #include "bits.h"
 #include "kernels.h"
 
@@ -72,7 +75,10 @@ struct Rows {
   // from, b = -(m + log2 l) / c2 (c2 = scale log2 e, m = r c2).
   static constexpr bool kApart = !(sizeof(T) == 2 && D == 128);
   static constexpr int kTiles = kK == 8 ? 2 : 4;   // tiles a wave keeps in registers where there is work for all
-  static constexpr int waves(int nb) { return nb == 1 ? 4 : kF32 ? 2 : 3; }   // waves per SIMD the registers are held to
+  // waves per SIMD the registers are held to: in the second kernel, and in the first (128 x bf16: 128 registers just suffice for
+  // four; three 1086, four 1070 us for both kernels, 128 units x 2048 positions)
+  static constexpr int waves(int nb) { return nb == 1 ? 4 : kF32 ? 2 : 3; }
+  static constexpr int stats_waves(int nb) { return nb == 1 || !kF32 ? 4 : 2; }
 };
 
 // 16 rows at `rows` (row stride `stride` elements), rows clamped to `last`, as an MFMA A or B
@@ -144,9 +150,9 @@ __device__ __forceinline__ void tile_operand(const SharedTile<T, D> &t, int buf,
 }
 
 // The operands a wave keeps have arrived before the loop starts.  The waits in the loop are then for its own
-// stages alone, in the order of their requests: a load from before the loop, or a path through it that
-// leaves stages out, would have every wait in it count to (nearly) zero, i.e. each stage wait for its
-// own request.
+// stages alone, in the order of their requests: a load from before the loop, a path through it that
+// leaves stages out, or a way out of its middle (from where the compiler sees a way to its top) would have the waits in it
+// count to (nearly) zero, i.e. a stage wait for its own request.
 template <int N, int K>
 __device__ __forceinline__ void settle(u32x4_t (&x)[N][K]) {
 #pragma unroll
@@ -178,23 +184,25 @@ __device__ __forceinline__ float max_f32(float a, float b) { return __builtin_fm
 // floating-point sum is as exact relative to any reference within the range of the exponent, so there is no
 // running maximum, only a look whether the weights leave the range (first: there is no reference
 // yet; where all logits of the first tile are -inf it is the lowest finite number, and the first other logit
-// raises it).  limit: kFar, or, once some reference of the wave is beyond kHuge, a number that every sum exceeds.  kMask: the tile may hold keys newer than a query or
+// raises it).  limit: kFar, or, once some reference of the wave is beyond kHuge, a number that every sum exceeds.  mask: the tile may hold keys newer than a query or
 // positions beyond the prompt.
-template <typename T, int D, int NB, bool kMask, bool kFirst>
-__device__ __forceinline__ void stats_tiles(const u32x4_t (&ka)[Rows<T, D>::kK], const u32x4_t (&qb)[NB][Rows<T, D>::kK],
+template <typename T, int D, int NB, bool kFirst>
+__device__ __forceinline__ void stats_tiles(bool mask, const u32x4_t (&ka)[Rows<T, D>::kK], const u32x4_t (&qb)[NB][Rows<T, D>::kK],
                                             float c2, int key0, int query0, int P, float (&r)[NB], float (&m)[NB], float (&l)[NB], float &limit) {
   f32x4_t acc[NB];
   float ps[NB], far = 0.f;
 #pragma unroll
   for (int n = 0; n < NB; ++n) acc[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   logits_tiles<T, D, NB, false>(qb, ka, acc);
+  if (mask) {                                      // (wave-uniform)
 #pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    if (kMask) {
+    for (int n = 0; n < NB; ++n)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         acc[n][i] = (key0 + i <= query0 + 16 * n && key0 + i < P) ? acc[n][i] : -INFINITY;
-    }
+  }
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
     if (kFirst) {                                  // (key 0 is visible to every query, but to one of the column's four lanes only)
       float top = max_f32(max_f32(acc[n][0], acc[n][1]), max_f32(acc[n][2], acc[n][3]));
       top = max_f32(top, __shfl_xor(top, 16));
@@ -239,7 +247,7 @@ __device__ __forceinline__ void stats_tiles(const u32x4_t (&ka)[Rows<T, D>::kK],
 // blocks = units * G * ceil(P / (64 NB)); the four waves of a block hold consecutive query
 // spans of one head and walk the key tiles together.
 template <typename T, int D, int NB>
-__global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats_kernel(const PrefillArgs a) {
+__global__ __launch_bounds__(kBlock, (Rows<T, D>::stats_waves(NB))) void prefill_stats_kernel(const PrefillArgs a) {
   using R = Rows<T, D>;
   constexpr int kSpan = 16 * NB;
   __shared__ SharedTile<T, D> tile;
@@ -294,7 +302,8 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats
     __builtin_amdgcn_sched_barrier(0);             // (in this order: the waits in the loop count on it)
   }
   __syncthreads();
-  auto stage = [&](int st, auto tag) {             // (st % kAhead is known to the code)
+  // kFirst: stage 0.  The stage's number modulo kAhead is known to the code.
+  auto stage = [&](int st, auto tag, auto first) {
     constexpr int buf = decltype(tag)::value % 2, reg = (decltype(tag)::value + 1) % kAhead;
 #pragma unroll
     for (int j = 0; j < R::kStage; ++j) {
@@ -303,25 +312,26 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_stats
         u32x4_t ka[R::kK];
         tile_operand<T, D>(tile, buf, j, ka, c, g);
         // only the wave's last NB key tiles can hold keys newer than a query (or positions beyond the prompt)
-        if (decltype(tag)::value == 0 && j == 0 && jt == 0)
-          stats_tiles<T, D, NB, true, true>(ka, qb, c2, 4 * g, i0 + c, P, r, m, l, limit);
-        else if (jt * 16 + 15 <= i0 && jt * 16 + 15 < P)
-          stats_tiles<T, D, NB, false, false>(ka, qb, c2, jt * 16 + 4 * g, i0 + c, P, r, m, l, limit);
+        const bool mask = jt * 16 + 15 > i0 || jt * 16 + 15 >= P;
+        if (decltype(first)::value && j == 0)
+          stats_tiles<T, D, NB, true>(true, ka, qb, c2, 4 * g, i0 + c, P, r, m, l, limit);
         else
-          stats_tiles<T, D, NB, true, false>(ka, qb, c2, jt * 16 + 4 * g, i0 + c, P, r, m, l, limit);
+          stats_tiles<T, D, NB, false>(mask, ka, qb, c2, jt * 16 + 4 * g, i0 + c, P, r, m, l, limit);
       }
     }
     stage_put<T, D>(tile, buf ^ 1, next[reg]);
     fetch(min(st + 1 + kAhead, n_stages - 1), next[reg]);
+    __builtin_amdgcn_sched_barrier(0);
     __syncthreads();                               // stage st + 1 is complete, stage st no longer read
   };
   settle(qb);
-  for (int st = 0;; st += kAhead) {                // (left from its middle: see settle)
-    stage(st, std::integral_constant<int, 0>{});
-    if (st + 1 >= n_stages) break;
-    stage(st + 1, std::integral_constant<int, 1>{});
-    if (st + 2 >= n_stages) break;
+  stage(0, std::integral_constant<int, 0>{}, std::true_type{});
+  int st = 1;
+  for (; st + 1 < n_stages; st += kAhead) {        // (whole rounds: see settle)
+    stage(st, std::integral_constant<int, 1>{}, std::false_type{});
+    stage(st + 1, std::integral_constant<int, 0>{}, std::false_type{});
   }
+  if (st < n_stages) stage(st, std::integral_constant<int, 1>{}, std::false_type{});
   if (!have) return;
   // the four lanes of a query column (g = 0..3) -> the column's reference and sum
 #pragma unroll
@@ -402,17 +412,19 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
   const int my_first = j0 >> 4;
   const int plain_first = (j0 + kSpan - 1 + 15) >> 4, plain_end = j0 + kSpan - 1 < P ? P >> 4 : 0;
   const size_t q_stride = static_cast<size_t>(a.n_q_heads) * D;
-  // A place in the sequence of pairs: 16 queries from it * 16 on of head h, the first of their rows, and where
-  // their statistics lie.  It stays on the block's last pair.
-  struct Place { int it, h; const T *rows; int stat_at; };
+  // A place in the sequence of pairs: 16 queries from it * 16 on of head h, the first of their rows, where
+  // their statistics lie, and the pairs behind it.  It stays on the block's last pair.
+  struct Place { int it, h; const T *rows; int stat_at, left; };
   const int stat_wrap = 16 - (G - 1) * a.p16;
   const ptrdiff_t rows_wrap = static_cast<ptrdiff_t>(16 * q_stride) - (G - 1) * D;
   auto next_pair = [&](Place &x) {
-    const bool wrap = x.h + 1 == G, last = wrap && x.it + 1 >= it_end;
-    x.rows += last ? 0 : wrap ? rows_wrap : D;
-    x.stat_at += last ? 0 : wrap ? stat_wrap : a.p16;
-    x.it = wrap && !last ? x.it + 1 : x.it;
-    x.h = last ? x.h : wrap ? 0 : x.h + 1;
+    if (x.left == 0) return;                       // (uniform)
+    const bool wrap = x.h + 1 == G;
+    x.left -= 1;
+    x.rows += wrap ? rows_wrap : D;
+    x.stat_at += wrap ? stat_wrap : a.p16;
+    x.it += wrap ? 1 : 0;
+    x.h = wrap ? 0 : x.h + 1;
   };
   // this thread's chunks of a tile's rows as byte offsets (16 rows of all heads are under 4 GB): rows beyond the
   // prompt, in its last tile, are replaced by the last one
@@ -442,8 +454,9 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
   auto fetch_stats = [&](Place x, Stats &s) {
 #pragma unroll
     for (int j = 0; j < R::kStage; ++j) {
-      s.b[j] = stat[x.stat_at + c];
-      s.ll[j] = R::kApart ? stat2[x.stat_at + c] : 0.f;
+      auto of_lane = [&](const float *p) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p + x.stat_at) + 4u * c); };
+      s.b[j] = of_lane(stat);
+      s.ll[j] = R::kApart ? of_lane(stat2) : 0.f;
       next_pair(x);
     }
   };
@@ -495,7 +508,7 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
     // the block's stage s: rows in next[s % kAhead] until they are in LDS, statistics in bs[s % kAhead] until used
     u32x4_t next[kAhead][R::kFetch];
     Stats bs[kAhead];
-    Place to_come = {it_begin, 0, q + static_cast<size_t>(it_begin) * 16 * q_stride, it_begin * 16};   // first pair of the next stage to request
+    Place to_come = {it_begin, 0, q + static_cast<size_t>(it_begin) * 16 * q_stride, it_begin * 16, (it_end - it_begin) * G - 1};   // first pair of the next stage to request
     Place before = to_come;                        // ... and of the one before it, whose statistics are requested now
     auto more_rows = [&](u32x4_t (&to)[R::kFetch]) {
       fetch_rows(to_come, to);
@@ -533,29 +546,59 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
           // query of the tile exists: nothing to mask (all but the wave's first NB query tiles,
           // the prompt's last tile and its last wave)
           const bool plain = !kIO && it >= plain_first && it < plain_end;
-          if (plain) {
+          if constexpr (R::kApart) {
+            if (plain) {
 #pragma unroll
-            for (int n = 0; n < NB; ++n)
+              for (int n = 0; n < NB; ++n)
 #pragma unroll
-              for (int i = 0; i < 4; ++i) amax[4 * n + i] = max_f32(amax[4 * n + i], log_weight(acc[n][i]));
-          } else {
+                for (int i = 0; i < 4; ++i) amax[4 * n + i] = max_f32(amax[4 * n + i], log_weight(acc[n][i]));
+            } else {
 #pragma unroll
-            for (int n = 0; n < NB; ++n) {
+              for (int n = 0; n < NB; ++n) {
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const int key = j0 + 16 * n + 4 * g + i;
-                const bool seen = key <= qi && qi < P;   // (key <= qi < P implies key < P)
-                const float lw = log_weight(acc[n][i]);
-                if (seen) amax[4 * n + i] = max_f32(amax[4 * n + i], lw);
-                if (kIO) {
-                  if (seen) {
-                    const size_t at = ((static_cast<size_t>(seq) * a.n_q_heads + kvh * G + h) * P + qi) * P + key;
-                    if (a.p_out) a.p_out[at] = weight(lw);
-                    if (a.p_override && a.p_override[at] >= a.alpha) over |= 1u << (4 * n + i);
+                for (int i = 0; i < 4; ++i) {
+                  const int key = j0 + 16 * n + 4 * g + i;
+                  const bool seen = key <= qi && qi < P;   // (key <= qi < P implies key < P)
+                  const float lw = log_weight(acc[n][i]);
+                  if (seen) amax[4 * n + i] = max_f32(amax[4 * n + i], lw);
+                  if (kIO) {
+                    if (seen) {
+                      const size_t at = ((static_cast<size_t>(seq) * a.n_q_heads + kvh * G + h) * P + qi) * P + key;
+                      if (a.p_out) a.p_out[at] = weight(lw);
+                      if (a.p_override && a.p_override[at] >= a.alpha) over |= 1u << (4 * n + i);
+                    }
                   }
                 }
               }
             }
+          } else {
+            // (masked in place and then one maximum for both: with a maximum on either way the 16 of them are copied around every
+            // stage, 1105 instead of 1040 us for 128 units x 2048 positions; with the products' differences above it is the other way, 31.8 / 30.6)
+            float lw[4 * NB];
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) lw[4 * n + i] = log_weight(acc[n][i]);
+            if (!plain) {
+#pragma unroll
+              for (int n = 0; n < NB; ++n) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                  const int key = j0 + 16 * n + 4 * g + i;
+                  const bool seen = key <= qi && qi < P;   // (key <= qi < P implies key < P)
+                  if (kIO) {
+                    if (seen) {
+                      const size_t at = ((static_cast<size_t>(seq) * a.n_q_heads + kvh * G + h) * P + qi) * P + key;
+                      if (a.p_out) a.p_out[at] = weight(lw[4 * n + i]);
+                      if (a.p_override && a.p_override[at] >= a.alpha) over |= 1u << (4 * n + i);
+                    }
+                  }
+                  lw[4 * n + i] = seen ? lw[4 * n + i] : -INFINITY;
+                }
+              }
+            }
+#pragma unroll
+            for (int x = 0; x < 4 * NB; ++x) amax[x] = max_f32(amax[x], lw[x]);
           }
           if (h == G - 1) {                        // the tile's last head: apply its activations
             // bit 4 n + i of this lane: key row 4 g + i of key tile n and query column c; after the transposition
@@ -591,12 +634,10 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
       __syncthreads();                             // the next stage is complete, this one no longer read
     };
     settle(ka);
-    for (;;) {                                     // (left from its middle: see settle)
+    do {                                           // (whole rounds: see settle; a stage too many works on nothing)
       stage(std::integral_constant<int, 0>{});
-      if (it >= it_end) break;
       stage(std::integral_constant<int, 1>{});
-      if (it >= it_end) break;
-    }
+    } while (it < it_end);
   }
   if (!have) return;
   const bool owner = c < 4 * NB && my_key < P;
