@@ -1565,15 +1565,21 @@ int decode_fused_split_max() { return kFusedSplitMax; }
 uint32_t decode_fused_seq_max() { return kSeqMax; }
 size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * sizeof(unsigned long long); }
 
-// Blocks per unit.  Measured on 28 query / 4 KV heads of 128 x bf16, us per call; the other row types take the same rule:
+// Blocks per unit.  Measured on 28 query / 4 KV heads of 128 x bf16, us per call, unless it says otherwise:
 //   * no more blocks than compute units: a second stream block on some of them holds up the whole
 //     launch (80 units x 2200 entries: 3 blocks per unit 17.4, 4 22.1; 48 units: 5 12.6, 6 16.6), and with
 //     two on all of them the bytes in flight only widen the spread of the blocks' ends (128 units x
 //     4144 entries: 44.5 with one, 46.4 with two).
 //   * only a long cache pays for the second hop that more than kMergeRadix blocks need (8 units x 2200
-//     entries: 8 blocks 8.9, 16 9.7, 32 9.8; x 6200 entries: 14.8, 13.0, 11.8).
-//   * seven or eight blocks only where they do not fill the chip to the last compute unit (32 units x
-//     1040 / 2200 / 6200 entries: 6 blocks 7.0 / 10.2 / 20.9, 8 7.6 / 10.3 / 21.4; 24 units x 6200: 6 19.0, 8 18.0).
+//     entries: 8 blocks 8.9, 16 9.7, 32 9.8; x 6200 entries: 13.3, 11.6, 10.3), and then in whole groups, the leaders' merges
+//     being what it waits for (12 units x 8200: 8 blocks 17.1, 16 14.6, 21 16.0; 28 x 8200: 8 23.6, 9 27.5; 24 x 8200: 8 20.3,
+//     10 21.8), but for caches so long that idle compute units cost more (20 units x 16400: 8 38.8, 12 36.5; 24: 8 44.1, 10 43.1).
+//   * seven or eight blocks where they leave some compute units to the tracking (28 units x 1040 / 2060 / 4200
+//     entries: 6 blocks 7.25 / 9.52 / 14.6, 8 7.22 / 9.47 / 13.9); where they fill the chip to the last one, six up to some thousand
+//     entries (32 units x 1040 / 4100 / 6200: 6 blocks 7.1 / 15.0 / 20.1, 8 7.4 / 15.4 / 20.6; x 8200 / 12000 27.3 / 42.9, 8
+//     26.2 / 39.0; 36 units x 6200 / 12000: 6 22.9 / 47.0, 7 25.1 / 44.8). The other row types have more to do per byte, or fewer bytes per entry:
+//     eight from about 1800 entries on (32 units x 2060 / 4100, 6 / 8: 64 x bf16 8.43 / 8.24, 11.6 / 10.9; 64 x fp32
+//     11.6 / 11.1, 18.0 / 16.6; 128 x fp32 19.2 / 18.7, 30.4 / 29.3; x 1016 12.6 / 13.3).
 //   * two sub-tiles or more per wave (8 units x 600 entries: 4 blocks 6.0, 5 6.0; x 350: 2 5.3, 4 5.5),
 //     but two blocks from a unit's fifth sub-tile on.
 //   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to
@@ -1582,17 +1588,19 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //     From 171 units on that would be two blocks, and one is the better at every length (1 / 2 blocks, 172 units
 //     x 600 12.6 / 14.8, x 2200 38.5 / 40.5, x 6200 115 / 119; 192 units 12.7 / 15.3, 39.9 / 42.1, 123 / 130; 240 units
 //     14.6 / 17.5, 48.7 / 50.7, 143 / 152), as it is for fp32 rows (192 units x 2200, 64 46.5 / 47.9, 128 84.2 / 89.1);
-//     bf16 rows of 64 would gain from two between about 1000 entries and 220 units (192 x 2200 31.0 / 26.6).
-int decode_fused_split(int units, int n_sub) {
+//     so it is for bf16 rows of 64 (176 units x 2200 25.4 / 25.3).
+int decode_fused_split(int units, int n_sub, bool bf16_128) {
   constexpr int kUnitsOfChip = 256;                // compute units of the chip that the figures above are from
   int n = kUnitsOfChip / units;
   if (n < 1) n = 1;
   if (n > kMergeRadix && n_sub <= kWaves * kMergeRadix * 8) n = kMergeRadix;
-  if (n > 6 && n <= kMergeRadix && n * units > 216) n = 6;
-  const int n2 = 2 * kUnitsOfChip / units;
-  if (units < kUnitsOfChip && n_sub >= 32 * kWaves * n && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2;
+  if (n > 6 && n <= kMergeRadix && n * units > 240 && n_sub < (n < kMergeRadix ? 512 : bf16_128 ? 480 : 112)) n = 6;
   const int by_work = n_sub <= kWaves ? 1 : n_sub < 4 * kWaves ? 2 : (n_sub + kWaves) / (2 * kWaves);
-  return n < by_work ? n : by_work;
+  if (n > by_work) n = by_work;
+  if (n > kMergeRadix && (n >= 2 * kMergeRadix || n == kMergeRadix + 1 || n_sub < 768)) n = n / kMergeRadix * kMergeRadix;
+  const int n2 = 2 * kUnitsOfChip / units;
+  if (units < kUnitsOfChip && n <= kMergeRadix && n_sub >= 32 * kWaves * n && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2 < by_work ? n2 : by_work;
+  return n;
 }
 
 // A unit of n blocks hands over n - 1 records.  decode_fused_split has at most 512 blocks for all units together (4 MB

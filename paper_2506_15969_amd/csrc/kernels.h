@@ -197,7 +197,7 @@ size_t decode_fused_record_bytes();           // one stamped record
 uint32_t decode_fused_seq_max();              // largest number of a launch (the stamp has 16 bits)
 int decode_fused_records_needed(int units, int capacity);   // most records per unit that decode_fused_split asks for
 int decode_fused_records_held(int units, int capacity, size_t bytes);   // most records per unit of use that `bytes` hold for all units
-int decode_fused_split(int units, int n_sub);   // blocks per unit of a call over n_sub sub-tiles of 16 entries
+int decode_fused_split(int units, int n_sub, bool bf16_128);   // blocks per unit of a call over n_sub sub-tiles of 16 entries (rows of 128 x bf16, or others)
 hipError_t launch_clear_records(unsigned long long *rec, int units, int rec_per_unit, int n_records, hipStream_t stream);
 hipError_t launch_track(const TrackArgs &k, hipStream_t stream);
 hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stream);
