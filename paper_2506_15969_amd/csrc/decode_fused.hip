@@ -808,16 +808,32 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   const int c = lane & 15, g = lane >> 4;
   const BlockPlace place = block_place<kSplit>(blockIdx.x, n_split, units_call);
   const int unit = place.unit, split = place.split;
-  int n_old = n_old_call;
-  if (slots_on) {                                  // per-sequence timing: this unit's own length
+  int n_old = n_old_call, n1 = n_old + 1, n_sub = (n1 + 15) >> 4;
+  // Per-sequence timing: this unit's own length, at the end of two round trips.  False: the whole unit sits this call out.
+  auto own_length = [&]() -> bool {
+    typedef const __attribute__((address_space(4))) int32_t *scalar_t;   // (written by earlier launches only)
     const DecodeArgs &a = args_from_here<T>();
     const int seq_s = unit / a.n_kv_heads;
-    const int32_t P = a.slots.prompt_len[seq_s], tau = a.t - a.slots.t0[seq_s];
-    if (P < 0 || tau < 1) return;                  // the whole unit sits this call out
+    const int32_t P = ((scalar_t)a.slots.prompt_len)[seq_s], tau = a.t - ((scalar_t)a.slots.t0)[seq_s];
     n_old = slot_n_old(P, tau, a.slots.budget, a.slots.window);
-  }
-  const int n1 = n_old + 1;
-  const int n_sub = (n1 + 15) >> 4;
+    n1 = n_old + 1;
+    n_sub = (n1 + 15) >> 4;
+    return P >= 0 && tau >= 1;
+  };
+
+  // Two ways to a sub-tile's rows.  kFlat: they lie one after the other in the cache, so a scalar address and one 32-bit offset
+  // per lane and load reach them, rows beyond the cache taken as its last one; the row to be appended is not there yet,
+  // and patch_k and patch_v put it in place when the unit's last sub-tile, which alone has it, is worked on.  Otherwise every load
+  // chooses the source of its row, 64 of the 230 vector instructions of a sub-tile.  Where the bytes set the time those cost
+  // nothing, and the patch at the end of the run does: us per pass, chosen / flat, 128 units x 2081 3009 / 3029, x 4129 of 80 (2 blocks a unit) 5766 / 5816;
+  // with three blocks a unit or more, and for rows of 128 bytes, the latency of a sub-tile does: 8 units x 2081 1999 / 1950,
+  // 48 units x 1000 1273 / 1254, 64 units x 1563 of 64 x bf16 1160 / 1090.  (fp32 rows: the products are longer than either, 840 / 842.)
+  constexpr bool kFlat = !R::kF32 && (kSplit >= 3 || R::kBytes == 128);
+  // ... Such a wave's first sub-tile does not depend on the unit's length but for the clamp of its rows, so with per-sequence timing the
+  // length is worked out while that travels (its rows clamped to the unit's capacity): 48 units x 1000, a pass of
+  // continuous_batch's shapes, 1240 -> 1225 us.
+  if (slots_on && !(kFlat && wave < kWaves))
+    if (!own_length()) return;
 
   CallArgs<T> a;                                   // (read where a wave has nothing better to do)
   // the appended row goes to slot N (the stream waves read it from k_new / v_new, nobody from the slot)
@@ -941,8 +957,9 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   }
 
   // this wave's sub-tiles (fused_wave_map)
-  const WaveMap wm = fused_wave_map(n_sub, n_split, split, wave);
-  const int cnt = wm.cnt;                          // (0 for a wave beyond a short cache)
+  WaveMap wm = fused_wave_map(n_sub, n_split, split, wave);
+  int cnt = wm.cnt;                                // (0 for a wave beyond a short cache)
+  int row_last = kFlat && slots_on ? capacity - 1 : n_old;   // kFlat: rows beyond are read as this one
   auto sub_of = [&](int it) { return wm.first + it * wm.step; };
 
   const T *kc = k_cache + static_cast<size_t>(unit) * capacity * D;
@@ -950,14 +967,6 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   const T *k_new = k_new_all + static_cast<size_t>(unit) * D;
   const T *v_new = v_new_all + static_cast<size_t>(unit) * D;
 
-  // Two ways to a sub-tile's rows.  kFlat: they lie one after the other in the cache, so a scalar address and one 32-bit offset
-  // per lane and load reach them, rows beyond the cache taken as its last one; the row to be appended is not there yet,
-  // and patch_k and patch_v put it in place when the unit's last sub-tile, which alone has it, is worked on.  Otherwise every load
-  // chooses the source of its row, 64 of the 230 vector instructions of a sub-tile.  Where the bytes set the time those cost
-  // nothing, and the patch at the end of the run does: us per pass, chosen / flat, 128 units x 2081 3009 / 3029, x 4129 of 80 (2 blocks a unit) 5766 / 5816;
-  // with three blocks a unit or more, and for rows of 128 bytes, the latency of a sub-tile does: 8 units x 2081 1999 / 1950,
-  // 48 units x 1000 1273 / 1254, 64 units x 1563 of 64 x bf16 1160 / 1090.  (fp32 rows: the products are longer than either, 840 / 842.)
-  constexpr bool kFlat = !R::kF32 && (kSplit >= 3 || R::kBytes == 128);
   auto load_k = [&](SubTile &t, int it) {
     if constexpr (!kFlat) {
       const int sub = sub_of(it);
@@ -978,7 +987,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
       }
       return;
     }
-    const int sub = min(sub_of(it), n_sub - 1), left = n_old - sub * 16;
+    const int sub = min(sub_of(it), row_last >> 4), left = row_last - sub * 16;
     const char *rows = reinterpret_cast<const char *>(kc) + static_cast<size_t>(sub) * (16 * R::kBytes);
     const unsigned last = static_cast<unsigned>(min(left, 16) * R::kBytes + (lane % R::kLanes) * 16);
 #pragma unroll
@@ -1006,7 +1015,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
       }
       return;
     }
-    const int sub = min(sub_of(it), n_sub - 1), left = n_old - sub * 16;
+    const int sub = min(sub_of(it), row_last >> 4), left = row_last - sub * 16;
     const char *rows = reinterpret_cast<const char *>(vc) + static_cast<size_t>(sub) * (16 * R::kBytes);
     const unsigned last = static_cast<unsigned>(min(left, 16) * R::kBytes + c * (D / 8));
 #pragma unroll
@@ -1056,6 +1065,12 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     load_v(buf[x], x);
   }
   __builtin_amdgcn_sched_barrier(0);
+  if (kFlat && slots_on) {
+    if (!own_length()) return;
+    wm = fused_wave_map(n_sub, n_split, split, wave);
+    cnt = wm.cnt;
+    row_last = n_old;
+  }
   a.read();
   if constexpr (kFlat) {
     new_lds[wave][lane % (2 * R::kLanes)] = new_piece;   // (where fewer lanes cover it, several write the same)
