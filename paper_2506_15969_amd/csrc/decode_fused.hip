@@ -71,6 +71,7 @@
 // holds the A operand of the second.
 #include "bits.h"
 #include "kernels.h"
+#include "track.h"
 
 #include <cfloat>
 #include <cstddef>
@@ -80,32 +81,11 @@ namespace lazyev {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kWaves = kBlock / 64;
+static_assert(kWaves == kBlock / 64, "");
 constexpr int kFusedSplitMax = 64;      // blocks per unit
 constexpr float kRaise = 8.0f;          // the reference maximum moves when exceeded by this much
 constexpr int kTrackRows = 3;           // entries per thread per tracking batch
-constexpr int kHeadPad = 8;             // logits and statistics are stored for 8 heads per unit
 constexpr int kRunMax = 20;             // sub-tiles whose logits a wave keeps in LDS (10 KB) before it writes them out
-// How a unit's n_sub sub-tiles of 16 entries are dealt to the kWaves * n_split waves of its
-// n_split blocks: wave wv (= kWaves * (n_split - 1 - split) + wave) takes wv, wv + kWaves * n_split,
-// ..., so the waves of a unit read one moving window of the cache together (measured against a
-// region of consecutive sub-tiles per block: 28.6 against 29.2 us per call on the 2048-entry
-// workload).  The unit's LAST block comes first in that order: when the sub-tiles do not divide
-// evenly its waves take the longer runs, and it is the block that finishes the unit,
-// so the other blocks' partials are on their way while it still streams.
-struct WaveMap { int first, step, cnt; };
-__host__ __device__ inline WaveMap fused_wave_map(int n_sub, int n_split, int split, int wave) {
-  WaveMap m;
-  m.first = (n_split - 1 - split) * kWaves + wave;
-  m.step = kWaves * n_split;
-  m.cnt = m.first < n_sub ? (n_sub - m.first + m.step - 1) / m.step : 0;
-  return m;
-}
-// Most sub-tiles one wave takes.
-__host__ __device__ inline int fused_wave_run(int n_sub, int n_split) {
-  return (n_sub + kWaves * n_split - 1) / (kWaves * n_split);
-}
-
 // Unit and place in the unit of stream block b: the first blocks of all units, the second ones, and so
 // on.  A block then waits for blocks of lower indices only, and, as blocks go to the eight XCDs round
 // robin, the blocks of a unit share an XCD where the units are a multiple of eight (or two XCDs where they are one of four),
@@ -209,12 +189,6 @@ __device__ __forceinline__ unsigned finite_bf16(unsigned w) {
   const unsigned top = ((w & 0x7FFF7FFFu) + 0x00800080u) & 0x80008000u;   // of the halves whose exponent is all ones
   return w & ~((top >> 15) * 0xFFFFu);
 }
-template <bool kPrecise>
-__device__ __forceinline__ float exp_of(float x) {
-  if constexpr (kPrecise) return expf(x);
-  else return __expf(x);
-}
-
 // ----------------------------------------------------------------------------- tracking
 // Alg. 1 (first loop) and Eq. 1 for a share of one unit of a finished decode call:
 // probabilities from the stored logits and statistics, >= alpha over the query group, TS / MRI
@@ -271,7 +245,7 @@ __device__ __forceinline__ bool track_one(const TrackArgs &k, int unit, int i, c
 #pragma unroll
   for (int h = 0; h < kHeadPad; ++h) {
     if (h < G) {
-      float p = exp_of<kPrecise>(s[h] - m[h]) * invl[h];
+      float p = weight_of<kPrecise>(s[h], m[h], invl[h]);
       const size_t at = (head0 + h) * k.capacity + i;
       if (k.p_out) k.p_out[at] = p;
       if (k.p_override) p = k.p_override[at];
@@ -311,13 +285,6 @@ __device__ __forceinline__ unsigned track_apply(const TrackArgs &k, int unit, in
     n_act += track_one<kPrecise>(k, unit, i, s, m, invl, log_mask) ? 1u : 0u;
   }
   return n_act;
-}
-
-// Slots of a block's region of candidate records in a call with n_parts blocks per unit: one
-// for the count and one for each entry the block can own.
-__host__ __device__ inline int fused_part_cap(int n_old, int n_parts) {
-  const int n_sub = (n_old + 1 + 15) >> 4;
-  return fused_wave_run(n_sub, n_parts) * (kWaves * 16) + 1;
 }
 
 // Tracking from the candidate records of the call's blocks b = part, part + step, ...

@@ -1,6 +1,7 @@
 // Lagged eviction of one layer (Sec. 4 "MRI-Centric Eviction", Eq. 3, Eq. 6, Alg. 1 of the
 // paper), as two kernels:
-//   select  one block per unit: scores every candidate entry (all but the last W) in binary64,
+//   select  one block per unit: applies the tracking that is outstanding (units whose entries fit its
+//           registers), scores every candidate entry (all but the last W) in binary64,
 //           finds the (B-W)-th largest score with an 8-bit radix select over the score bit
 //           patterns held in registers (beyond 8192 entries in LDS, beyond 8192 candidates in the
 //           workspace), breaks ties in favour of the more recent entry, prefix-scans
@@ -11,7 +12,9 @@
 //
 // This file is compiled with floating-point contraction off: the score is a fixed sequence of
 // individually rounded binary64 operations so that it can be reproduced bit for bit elsewhere.
+#include "bits.h"
 #include "kernels.h"
+#include "track.h"
 
 #include <type_traits>
 
@@ -209,6 +212,115 @@ __device__ __forceinline__ unsigned wave_scan(unsigned v) {
   return v;
 }
 
+// The records of the last call before the eviction (Alg. 1, first loop): bits of the active entries.  Wave w takes the regions
+// w, w + 16, ... of the unit.
+template <bool kPrecise>
+__device__ __forceinline__ unsigned last_call_bits(const TrackArgs &k, int unit, unsigned *active) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cap = fused_part_cap(k.n_old, k.n_parts);
+  float m[kHeadPad], invl[kHeadPad];
+#pragma unroll
+  for (int h = 0; h < kHeadPad; ++h) {
+    m[h] = k.stat[static_cast<size_t>(unit) * (2 * kHeadPad) + 2 * h];
+    invl[h] = k.stat[static_cast<size_t>(unit) * (2 * kHeadPad) + 2 * h + 1];
+  }
+  unsigned n_act = 0;
+  for (int b = wave; b < k.n_parts; b += kSelWaves) {
+    const size_t at = static_cast<size_t>(unit) * k.p_stride + static_cast<size_t>(b) * cap;
+    const float *region = k.logits + at * kHeadPad;
+    const int n = *reinterpret_cast<const int32_t *>(region);
+    for (int r = lane; r < n; r += 64) {
+      const float4 sa = *reinterpret_cast<const float4 *>(region + static_cast<size_t>(1 + r) * kHeadPad);
+      const float4 sb = *reinterpret_cast<const float4 *>(region + static_cast<size_t>(1 + r) * kHeadPad + 4);
+      const bool eight = k.group == kHeadPad;      // (groups of eight have the index beside the records)
+      const int i = eight ? k.cand_index[at + 1 + r] : __float_as_int(sb.w);
+      const float s[kHeadPad] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
+      bool act = false;
+#pragma unroll
+      for (int h = 0; h < kHeadPad; ++h)
+        if (h < k.group) act = act || weight_of<kPrecise>(s[h], m[h], invl[h]) >= k.alpha;
+      if (act) {
+        n_act += 1;
+        if (i != k.n_old) atomicOr(&active[i >> 5], 1u << (i & 31));   // (the appended entry starts at its own step)
+      }
+    }
+  }
+  return n_act;
+}
+
+// Applies what is outstanding to the entries in registers, entry r * kSelBlock + tid in place r (the same
+// updates as track_flush_kernel's and track_kernel's, which are the comments' place; launches of their own took 8 - 13 us
+// before every eviction).  A wave has 64 entries in a row, two words of a call: lane (half, j) brings word `half` of call
+// s + j, and after a transposition across the 32 lanes holds the 32 calls of entry 32 half + j.
+template <int R>
+__device__ __forceinline__ void apply_outstanding(const EvictArgs &a, int unit, int32_t (&v_ts)[R], int32_t (&v_mri)[R], int32_t (&v_pos)[R],
+                                                  unsigned *active, unsigned *n_active) {
+  const OutstandingArgs &o = a.todo;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int layer = unit / a.units_per_layer, unit_l = unit % a.units_per_layer;
+  const FlushArgs::Layer of = o.layer[layer];
+  const bool last = layer == o.last_layer;
+  if (last) {
+    for (int i = tid; i < R * kSelBlock / 32; i += kSelBlock) active[i] = 0;
+    if (tid == 0) *n_active = 0;
+    __syncthreads();
+    unsigned n = o.last.precise ? last_call_bits<true>(o.last, unit_l, active) : last_call_bits<false>(o.last, unit_l, active);
+    for (int x = 32; x > 0; x >>= 1) n += __shfl_xor(n, x);
+    if (lane == 0 && n) atomicAdd(n_active, n);
+  }
+  const int half = lane >> 5, j = lane & 31;
+  const uint32_t *log = o.bitlog + static_cast<size_t>(unit) * o.log_slots * o.log_words;   // (a unit's slots lie together)
+#pragma unroll
+  for (int r = 0; r < R; ++r) {                    // entries that the logged calls appended start there
+    const int s_new = r * kSelBlock + tid - of.n_old;
+    if (s_new >= 0 && s_new < of.n_calls) {
+      v_ts[r] = of.t + s_new;
+      v_mri[r] = 0;
+      v_pos[r] = o.prompt_len + v_ts[r] - 1;
+    }
+  }
+  constexpr int kBatch = R <= 3 ? 4 : 2;           // sets of 32 calls requested together
+  for (int s0 = 0; s0 < of.n_calls; s0 += 32 * kBatch) {
+    unsigned w[kBatch][R];
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      const uint32_t *row = log + static_cast<size_t>(min(s0 + 32 * b + j, of.n_calls - 1)) * o.log_words;
+#pragma unroll
+      for (int r = 0; r < R; ++r) w[b][r] = row[min((r * kSelBlock + wave * 64) / 32 + half, o.log_words - 1)];
+    }
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      const int s = s0 + 32 * b;
+      if (s >= of.n_calls) break;                  // (uniform)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const unsigned calls = transpose_bits<32>(s + j < of.n_calls ? w[b][r] : 0u, j);
+        if (calls == 0) continue;
+        const int lo = __builtin_ctz(calls), hi = 31 - __builtin_clz(calls);
+        v_mri[r] = max(v_mri[r], of.t + s + lo - v_ts[r]);                  // Eq. 1
+        if (hi > lo) v_mri[r] = max(v_mri[r], longest_gap<32>(calls, lo, hi));
+        v_ts[r] = of.t + s + hi;                                            // Alg. 1
+      }
+    }
+  }
+  if (last) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = r * kSelBlock + tid;
+      if (i == o.last.n_old) {
+        v_ts[r] = o.last.t;
+        v_mri[r] = 0;
+        v_pos[r] = o.last.prompt_len + o.last.t - 1;
+      } else if ((active[i >> 5] >> (i & 31)) & 1u) {
+        v_mri[r] = max(v_mri[r], o.last.t - v_ts[r]);
+        v_ts[r] = o.last.t;
+      }
+    }
+    if (tid == 0) o.last.activation_counter[unit_l * 64] += *n_active;
+  }
+}
+
 // The selection for units of at most R * kSelBlock entries.  One block per unit, so what bounds it is the chain of its
 // steps (and the scores, at 4096 entries): memory is read once, at the start (TS, MRI and pos stay in registers, R
 // entries per thread), the keys lie in registers, every wave finds the threshold's digit for itself, and the
@@ -223,6 +335,8 @@ __device__ __forceinline__ unsigned wave_scan(unsigned v) {
 template <int R>
 __global__ __launch_bounds__(kSelBlock) void evict_select_held_kernel(const EvictArgs a) {
   extern __shared__ unsigned long long keys_lds[];      // score bit pattern of each candidate
+  __shared__ unsigned active[R * kSelBlock / 32];  // the last call's activations, a bit per entry
+  __shared__ unsigned n_active;
   __shared__ unsigned hist[3][256];                // of passes p, p + 1, p + 2: a barrier lies between the last reading
   __shared__ unsigned long long wave_key[2][kSelWaves];   // of one, its clearing and its next use
   __shared__ unsigned wave_kind[2][kSelWaves];     // keys of the wave in play: 0 none, 1 all wave_key, 2 several values
@@ -248,6 +362,7 @@ __global__ __launch_bounds__(kSelBlock) void evict_select_held_kernel(const Evic
     v_ts[r] = v_mri[r] = v_pos[r] = 0;
     if (slot < n) { v_ts[r] = ts[slot]; v_mri[r] = mri[slot]; v_pos[r] = pos[slot]; }
   }
+  if (a.todo.on) apply_outstanding<R>(a, unit, v_ts, v_mri, v_pos, active, &n_active);
   if (tid < 256) hist[0][tid] = hist[1][tid] = hist[2][tid] = 0;
   if (tid == 0) { small_n = 0; moved = 0; }
 
@@ -406,6 +521,9 @@ __global__ __launch_bounds__(kSelBlock) void evict_select_held_kernel(const Evic
     if (keep) {
       ts[dst] = v_ts[r]; mri[dst] = v_mri[r]; pos[dst] = v_pos[r];
       src_index[dst] = slot;
+    }
+    if (a.todo.on && slot >= a.budget && slot < n) {   // (places that no survivor takes: as the tracking leaves them)
+      ts[slot] = v_ts[r]; mri[slot] = v_mri[r]; pos[slot] = v_pos[r];
     }
     n_moved += static_cast<unsigned>(__popcll(__builtin_amdgcn_ballot_w64(keep && dst != static_cast<unsigned>(slot))));
   }
@@ -659,6 +777,7 @@ __global__ __launch_bounds__(kMoveBlock) void evict_move_kernel(const EvictArgs 
 }  // namespace
 
 int evict_lds_candidates() { return kLdsCandidates; }
+bool evict_applies_tracking(int n) { return n <= kLdsCandidates; }   // (entries held in registers)
 
 hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) {
   const int n_cand = a.n - a.window;
@@ -671,6 +790,16 @@ hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) 
     return hipErrorInvalidValue;
   const size_t lds = static_cast<size_t>(n_cand) * sizeof(unsigned long long);
   if (n_cand > kLdsCandidates && !a.ws.sel_keys) return hipErrorInvalidValue;
+  if (a.todo.on && (!evict_applies_tracking(a.n) || a.slots.prompt_len || !a.todo.bitlog || a.units / a.units_per_layer > kFlushLayers ||
+                    a.todo.log_words < (a.n + 31) / 32 || a.todo.log_slots < 1 || a.todo.last_layer >= a.units / a.units_per_layer))
+    return hipErrorInvalidValue;
+  if (a.todo.on && a.todo.last_layer >= 0) {
+    const TrackArgs &k = a.todo.last;
+    if (!k.compact || k.units != a.units_per_layer || !k.logits || !k.stat || k.group > kHeadPad || (k.group == kHeadPad && !k.cand_index) ||
+        k.n_old + 1 != a.n || !k.activation_counter ||
+        static_cast<long long>(fused_part_cap(k.n_old, k.n_parts)) * k.n_parts > k.p_stride)
+      return hipErrorInvalidValue;
+  }
   int n_blocks = a.units;                          // one per unit, or only the due sequences' units
   if (a.n_due > 0) {
     if (!a.slots.prompt_len || a.n_due > 8) return hipErrorInvalidValue;

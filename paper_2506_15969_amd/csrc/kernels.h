@@ -97,6 +97,18 @@ struct FlushArgs {
   } layer[kFlushLayers];
 };
 
+// The tracking that is outstanding when an eviction is due, applied by the selection itself (uniform batches): the
+// logged calls of every layer of the launch, and the call after them of one layer, whose candidate records are still
+// in the workspace.
+struct OutstandingArgs {
+  int32_t on;                       // 0: TS / MRI / pos are up to date
+  const uint32_t *bitlog;           // as in FlushArgs
+  int32_t log_words, log_slots, prompt_len;
+  FlushArgs::Layer layer[kFlushLayers];
+  int32_t last_layer;               // layer (of the launch) of the last call, -1: none
+  TrackArgs last;                   // (compact)
+};
+
 struct DecodeArgs {
   int32_t batch, n_q_heads, n_kv_heads, head_dim, group;
   int32_t capacity;       // C
@@ -150,7 +162,10 @@ struct EvictArgs {
   // i % n_kv_heads.  n_due = 0: one block per unit as usual.
   int32_t n_due;
   int32_t due_seq[8];
+  OutstandingArgs todo;
 };
+// Can the selection of n entries apply what is outstanding?
+bool evict_applies_tracking(int n);
 
 // The unit a block of an eviction launch works on.
 __host__ __device__ inline int32_t evict_unit_of(const EvictArgs &a, int32_t i) {

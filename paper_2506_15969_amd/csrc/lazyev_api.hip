@@ -324,6 +324,38 @@ hipError_t flush_tracking(lazyev_ctx *ctx) {
   return e;
 }
 
+// What is outstanding for the layers l0 .. l1 - 1, whose eviction of n entries is about to be launched: handed to the
+// selection where that can apply it (a.todo), else applied in launches of its own.  Other layers' calls stay where they are
+// in the first case.
+hipError_t outstanding_of(lazyev_ctx *ctx, int l0, int l1, int32_t n, lazyev::EvictArgs &a) {
+  const bool last = ctx->pend.valid && ctx->pend_layer >= l0 && ctx->pend_layer < l1;
+  if (!ctx->bitlog || ctx->slots_on || l1 - l0 > lazyev::kFlushLayers || !lazyev::evict_applies_tracking(n) ||
+      (ctx->pend.valid && !ctx->pend.compact) || (last && ctx->pend.n_old + 1 != n))
+    return flush_tracking(ctx);
+  lazyev::OutstandingArgs &o = a.todo;
+  o.on = 1;
+  o.bitlog = ctx->bitlog + static_cast<size_t>(l0) * ctx->log_slots * ctx->units * ctx->log_words;
+  o.log_words = ctx->log_words; o.log_slots = ctx->log_slots;
+  o.prompt_len = ctx->cfg.prompt_len;
+  for (int l = l0; l < l1; ++l) {
+    o.layer[l - l0].n_calls = ctx->log_n[l];
+    o.layer[l - l0].t = ctx->log_t[l];
+    o.layer[l - l0].n_old = ctx->log_n_old[l];
+  }
+  o.last_layer = last ? ctx->pend_layer - l0 : -1;
+  if (last) {
+    o.last = ctx->pend;
+    o.last.bitlog = nullptr;
+  }
+  return hipSuccess;
+}
+// ... and after that launch
+void outstanding_done(lazyev_ctx *ctx, int l0, int l1, const lazyev::EvictArgs &a) {
+  if (!a.todo.on) return;
+  for (int l = l0; l < l1; ++l) ctx->log_n[l] = 0;
+  if (a.todo.last_layer >= 0) ctx->pend.valid = 0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -740,10 +772,11 @@ static int evict_layer(lazyev_ctx *ctx, int32_t layer, int32_t t, int32_t *n_evi
     a.logits = ctx->last_logits; a.stat = ctx->last_stat;
     a.group = ctx->group; a.p_stride = ctx->last_p_stride;
   }
-  const hipError_t ef = flush_tracking(ctx);       // scores use TS and MRI of step t (Alg. 1 order)
+  const hipError_t ef = outstanding_of(ctx, layer, layer + 1, n, a);   // scores use TS and MRI of step t (Alg. 1 order)
   if (ef != hipSuccess) return fail_hip(ctx, ef);
   const hipError_t e = lazyev::launch_evict(a, ctx->stream, arm_events(ctx, 1));
   if (e != hipSuccess) return fail_hip(ctx, e);
+  outstanding_done(ctx, layer, layer + 1, a);
   if (n_evicted) *n_evicted = n - c.budget;
   ctx->n_evict_events[layer] += 1;
   ctx->n_evicted[layer] += n - c.budget;
@@ -822,10 +855,11 @@ int lazyev_evict_all(lazyev_ctx *ctx, int32_t t, int32_t *n_evicted) {
   a.n_kv_heads = c.n_kv_heads;
   a.slots = slots_of(ctx);
   fill_due(ctx, t, a);
-  const hipError_t ef = flush_tracking(ctx);       // scores use TS and MRI of step t (Alg. 1 order)
+  const hipError_t ef = outstanding_of(ctx, 0, L, n, a);   // scores use TS and MRI of step t (Alg. 1 order)
   if (ef != hipSuccess) return fail_hip(ctx, ef);
   const hipError_t e = lazyev::launch_evict(a, ctx->stream, arm_events(ctx, 1));
   if (e != hipSuccess) return fail_hip(ctx, e);
+  outstanding_done(ctx, 0, L, a);
   if (n_evicted) *n_evicted = n - c.budget;
   for (int l = 0; l < L; ++l) {
     ctx->n_evict_events[l] += 1;

@@ -1,0 +1,47 @@
+// What the decode kernel that leaves a call's candidate records and the kernels that read them share.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace lazyev {
+namespace {
+
+constexpr int kWaves = 4;               // stream waves of a block
+constexpr int kHeadPad = 8;             // logits and statistics are stored for 8 heads per unit
+// How a unit's n_sub sub-tiles of 16 entries are dealt to the kWaves * n_split waves of its
+// n_split blocks: wave wv (= kWaves * (n_split - 1 - split) + wave) takes wv, wv + kWaves * n_split,
+// ..., so the waves of a unit read one moving window of the cache together (measured against a
+// region of consecutive sub-tiles per block: 28.6 against 29.2 us per call on the 2048-entry
+// workload).  The unit's LAST block comes first in that order: when the sub-tiles do not divide
+// evenly its waves take the longer runs, and it is the block that finishes the unit,
+// so the other blocks' partials are on their way while it still streams.
+struct WaveMap { int first, step, cnt; };
+__host__ __device__ inline WaveMap fused_wave_map(int n_sub, int n_split, int split, int wave) {
+  WaveMap m;
+  m.first = (n_split - 1 - split) * kWaves + wave;
+  m.step = kWaves * n_split;
+  m.cnt = m.first < n_sub ? (n_sub - m.first + m.step - 1) / m.step : 0;
+  return m;
+}
+// Most sub-tiles one wave takes.
+__host__ __device__ inline int fused_wave_run(int n_sub, int n_split) {
+  return (n_sub + kWaves * n_split - 1) / (kWaves * n_split);
+}
+
+// Slots of a block's region of candidate records in a call with n_parts blocks per unit: one
+// for the count and one for each entry the block can own.
+__host__ __device__ inline int fused_part_cap(int n_old, int n_parts) {
+  const int n_sub = (n_old + 1 + 15) >> 4;
+  return fused_wave_run(n_sub, n_parts) * (kWaves * 16) + 1;
+}
+
+template <bool kPrecise>
+__device__ __forceinline__ float exp_of(float x) {
+  if constexpr (kPrecise) return expf(x);
+  else return __expf(x);
+}
+// The weight the activation test of Alg. 1 compares with alpha.
+template <bool kPrecise>
+__device__ __forceinline__ float weight_of(float s, float m, float invl) { return exp_of<kPrecise>(s - m) * invl; }
+
+}  // namespace
+}  // namespace lazyev

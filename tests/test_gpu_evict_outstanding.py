@@ -1,0 +1,48 @@
+"""Tracking that is outstanding when an eviction is due: applied by the selection itself, or by launches of its own
+(lazyev_stats before the eviction).  Same state bit for bit, places beyond the budget included."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(lazyev_lib, first_stats, per_layer, L, S, group, H, d, dtype, B, W, steps, prompt):
+    gen = torch.Generator(device="cuda").manual_seed(B + W + group)
+    eng = lazyev_lib.LazyEviction(L, S, group * H, H, d, B, W, prompt, 8.0 / (B + W), dtype=dtype)
+    eng.k_cache[:, :, :, :prompt].normal_(generator=gen)
+    eng.v_cache[:, :, :, :prompt].normal_(generator=gen)
+    eng.init()
+    out = torch.zeros((S, group * H, d), dtype=dtype, device="cuda")
+    events = 0
+    for t in range(1, steps + 1):
+        for layer in range(L):
+            q, kn, vn = (torch.empty((S, h, d), device="cuda").normal_(generator=gen).to(dtype) for h in (group * H, H, H))
+            q = (q.float() + 2.0 * eng.k_cache[layer, :, :, (7 * t) % prompt].float().repeat_interleave(group, dim=1)).to(dtype)
+            eng.decode_step(layer, t, q, kn, vn, out)
+        if first_stats:
+            eng.stats()
+        if per_layer:
+            events += sum(1 for layer in reversed(range(L)) if eng.evict(layer, t))
+        else:
+            events += 1 if eng.evict_all(t) else 0
+    st = eng.stats()
+    state = [x.clone() for x in (eng.ts, eng.mri, eng.pos)] + [eng.k_cache.float().clone(), out.float().clone()]
+    eng.close()
+    return events, st, state
+
+
+# the selection's instances hold 2, 3, 5 and 8 entries per thread (2048, 3072, 5120, 8192 entries); 32 calls are applied at a time, 128
+# (64 from 5 on) requested together, 256 logged
+@pytest.mark.parametrize("L,S,group,H,d,dtype,B,W,steps,prompt", [
+    (2, 2, 7, 2, 128, torch.bfloat16, 60, 3, 9, 60), (1, 1, 8, 1, 128, torch.bfloat16, 1000, 33, 66, 1000),
+    (3, 1, 4, 2, 64, torch.float32, 2010, 38, 38, 2010), (1, 2, 8, 1, 64, torch.bfloat16, 2000, 49, 49, 2000),
+    (2, 1, 7, 1, 128, torch.bfloat16, 2900, 130, 130, 2900), (1, 1, 1, 2, 128, torch.float32, 5000, 65, 65, 5000),
+    (1, 1, 7, 1, 128, torch.bfloat16, 8100, 92, 92, 8100), (1, 1, 3, 1, 128, torch.bfloat16, 8150, 43, 43, 8150),
+    (1, 1, 7, 1, 128, torch.bfloat16, 400, 270, 270, 400), (2, 1, 5, 1, 64, torch.float32, 90, 40, 80, 20)])
+@pytest.mark.parametrize("per_layer", [False, True])
+def test_selection_applies_what_is_outstanding(lazyev_lib, per_layer, L, S, group, H, d, dtype, B, W, steps, prompt):
+    runs = [_run(lazyev_lib, first, per_layer, L, S, group, H, d, dtype, B, W, steps, prompt) for first in (True, False)]
+    assert runs[0][0] == runs[1][0] > 0
+    assert runs[0][1] == runs[1][1]
+    for x, y in zip(runs[0][2], runs[1][2]):
+        assert torch.equal(x, y)
