@@ -35,12 +35,12 @@
 // NEXT launch carries, behind its stream blocks, as many tracking blocks (spread over the
 // compute units the same way) that apply the previous call's tracking from the stored logits
 // and statistics (>= alpha test over the query group, TS / MRI update, start of the appended
-// entry) while the new call streams; lazyev_evict and lazyev_stats apply what is pending
-// through track_kernel.  Logits and statistics are double-buffered.
+// entry) while the new call streams; lazyev_stats applies what is pending
+// through track_kernel, an eviction in its selection.  Logits and statistics are double-buffered.
 // In a uniform batch the tracking blocks do not touch TS / MRI themselves (a 128-byte line read
 // and written for every 4-byte word of an active entry, beside the stream): they leave one bit
 // per cache entry in the layer's activation log, and track_flush_kernel applies the logged calls
-// in step order before anything reads TS / MRI (TrackArgs::bitlog).
+// in step order before anything reads TS / MRI (TrackArgs::bitlog), or the selection of an eviction does.
 //
 // Candidate lists (kernel instances with kCompact; every call whose
 // logits nobody reads as such).  A block knows, once its four stream waves are done, its own
@@ -347,7 +347,8 @@ __device__ void track_count(const TrackArgs &k, int unit, int part, unsigned n_a
   }
 }
 
-// Tracking alone (lazyev_evict, lazyev_stats, or a caller that wants the weights at once).
+// Tracking alone (lazyev_stats, evictions with per-sequence timing or of more entries than the selection holds, or a caller
+// that wants the weights at once).
 template <bool kPrecise>
 __global__ __launch_bounds__(kBlock) void track_kernel(const TrackArgs k_all, int n_parts) {
   __shared__ unsigned cnt_lds[kWaves];

@@ -701,7 +701,7 @@ __global__ __launch_bounds__(kSelBlock) void evict_select_kernel(const EvictArgs
 
 // Moves rows of K (blockIdx.y = 0) or V (1): row j <- row src_index[j], j < budget.
 // Row parts are 256 bytes (16 lanes of 16 bytes; a whole row for bf16 with d = 128) or, for
-// shorter rows, 128 bytes.  A block of 1024 threads owns one part of every row of one unit and
+// shorter rows and few units, 128 bytes.  A block of 1024 threads owns one part of every row of one unit and
 // walks the rows in tiles of (1024 / LPP) * U; loads and stores are marked non-temporal (every
 // byte is touched once: measured 14 % faster than plain ones); inside a tile every load
 // completes before the first store (a destination row may be another thread's source row),
@@ -826,7 +826,11 @@ hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) 
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[1], stream);
   const int row_bytes = a.head_dim * (a.dtype == 0 ? 4 : 2);
-  if (row_bytes % 256 == 0) {
+  // Parts of 256 bytes where their blocks come to three quarters of the chip's compute units, else parts of 128 bytes and twice the
+  // blocks.  us, 256 / 128: 8 units x 4096 rows of 256 bytes 33.9 / 21.0, 48 x 1024 16.5 / 12.3, 64 x 2048 28.7 / 24.9, 96 x 2048 (192
+  // blocks) 43.0 / 41.8; 48 x 1024 rows of 512 bytes (192 blocks) 18.8 / 21.0.  (Parts of 64 bytes: 4 units x 144 2.4, as with 128;
+  // 32 x 1024 11.2 / 10.3.)
+  if (row_bytes % 256 == 0 && 2 * n_blocks * (row_bytes / 256) >= 192) {
     hipLaunchKernelGGL((evict_move_kernel<8, 16>), dim3(row_bytes / 256, 2, n_blocks), dim3(kMoveBlock),
                        0, stream, a, row_bytes);
   } else {
