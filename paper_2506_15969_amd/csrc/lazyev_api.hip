@@ -325,11 +325,16 @@ hipError_t flush_tracking(lazyev_ctx *ctx) {
 }
 
 // What is outstanding for the layers l0 .. l1 - 1, whose eviction of n entries is about to be launched: handed to the
-// selection where that can apply it (a.todo), else applied in launches of its own.  Other layers' calls stay where they are
-// in the first case.
+// selection where that can apply it (a.todo), else applied in launches of its own.  Where layers are evicted one by one,
+// the first one's launches apply the logged calls of all of them (28 layers of 128 units 58 us; each selection by itself 8 us more).
+// Of more units than the chip holds selection blocks at once (two per compute unit) launches of their own are the
+// faster, the chain of a selection block being what its launch waits for again and again (us, all three launches / the selection
+// alone: 256 units of 1152 entries x 128 calls 22 / 15, of 4160 x 64 37 / 28; 3584 units of 1152 x 128 107 / 142, 4608 of 4160 x 64 322 / 353).
+constexpr long long kSelectionUnits = 512;
 hipError_t outstanding_of(lazyev_ctx *ctx, int l0, int l1, int32_t n, lazyev::EvictArgs &a) {
   const bool last = ctx->pend.valid && ctx->pend_layer >= l0 && ctx->pend_layer < l1;
-  if (!ctx->bitlog || ctx->slots_on || l1 - l0 > lazyev::kFlushLayers || !lazyev::evict_applies_tracking(n) ||
+  if (!ctx->bitlog || ctx->slots_on || l1 - l0 != ctx->cfg.n_layers || l1 - l0 > lazyev::kFlushLayers ||
+      static_cast<long long>(l1 - l0) * ctx->units > kSelectionUnits || !lazyev::evict_applies_tracking(n) ||
       (ctx->pend.valid && !ctx->pend.compact) || (last && ctx->pend.n_old + 1 != n))
     return flush_tracking(ctx);
   lazyev::OutstandingArgs &o = a.todo;
