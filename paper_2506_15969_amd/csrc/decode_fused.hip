@@ -627,6 +627,7 @@ struct Kernarg {
 typedef const __attribute__((address_space(4))) DecodeArgs *const_args_t;
 template <typename T>
 __device__ __forceinline__ const DecodeArgs &args_from_here() {
+  static_assert(offsetof(Kernarg<T>, a) == 56, "five pointers, two lengths and the shape, then the block, aligned to 8 bytes");
   uintptr_t p = reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()) + offsetof(Kernarg<T>, a);
   __asm__ volatile("" : "+s"(p));                  // (nothing of it is read before this place)
   return *(const DecodeArgs *)reinterpret_cast<const_args_t>(p);
