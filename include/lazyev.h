@@ -157,7 +157,9 @@ int lazyev_prefill_track_seq(lazyev_ctx *ctx, int32_t layer, int32_t seq, const 
  * t must be the layer's previous step + 1 (first step is 1).
  * A call on a stream that is being captured into a HIP graph is recorded with the step, entry and
  * pointers it was made with, and the context goes on from there; every replay computes `out` and
- * the appended rows from what the pointers hold then.
+ * the appended rows from what the pointers hold then.  ts / mri / pos follow the order of the
+ * calls only if each captured call is replayed once, in its place: what a replay at another time
+ * tracks, and what is tracked of the calls around it, is unspecified (but within the buffers).
  * p_out (device, nullable): receives the fp32 probabilities the threshold test used, entries
  *   [0, N+1) of each row.
  * p_override (device, nullable): probabilities to threshold INSTEAD of the computed ones (the

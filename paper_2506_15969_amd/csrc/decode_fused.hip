@@ -297,11 +297,11 @@ __device__ __forceinline__ unsigned track_records(const TrackArgs &k, int unit, 
   for (int b = part; b < k.n_parts; b += step) {
     const size_t at = static_cast<size_t>(unit) * k.p_stride + static_cast<size_t>(b) * cap;
     const float *region = k.logits + at * kHeadPad;
-    const int n = *reinterpret_cast<const int32_t *>(region);
+    const int n = region_count(region, cap);
     auto track = [&](int r, auto eight) {          // (groups of eight have the index beside the records)
       const float4 sa = *reinterpret_cast<const float4 *>(region + static_cast<size_t>(1 + r) * kHeadPad);
       const float4 sb = *reinterpret_cast<const float4 *>(region + static_cast<size_t>(1 + r) * kHeadPad + 4);
-      const int i = decltype(eight)::value ? k.cand_index[at + 1 + r] : __float_as_int(sb.w);
+      const int i = record_entry(decltype(eight)::value ? k.cand_index[at + 1 + r] : __float_as_int(sb.w), k.n_old);
       const float s[kHeadPad] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, decltype(eight)::value ? sb.w : 0.f};
       n_act += track_one<kPrecise>(k, unit, i, s, m, invl, log_mask) ? 1u : 0u;
     };

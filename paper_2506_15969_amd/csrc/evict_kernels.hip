@@ -228,12 +228,12 @@ __device__ __forceinline__ unsigned last_call_bits(const TrackArgs &k, int unit,
   for (int b = wave; b < k.n_parts; b += kSelWaves) {
     const size_t at = static_cast<size_t>(unit) * k.p_stride + static_cast<size_t>(b) * cap;
     const float *region = k.logits + at * kHeadPad;
-    const int n = *reinterpret_cast<const int32_t *>(region);
+    const int n = region_count(region, cap);
     for (int r = lane; r < n; r += 64) {
       const float4 sa = *reinterpret_cast<const float4 *>(region + static_cast<size_t>(1 + r) * kHeadPad);
       const float4 sb = *reinterpret_cast<const float4 *>(region + static_cast<size_t>(1 + r) * kHeadPad + 4);
       const bool eight = k.group == kHeadPad;      // (groups of eight have the index beside the records)
-      const int i = eight ? k.cand_index[at + 1 + r] : __float_as_int(sb.w);
+      const int i = record_entry(eight ? k.cand_index[at + 1 + r] : __float_as_int(sb.w), k.n_old);
       const float s[kHeadPad] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
       bool act = false;
 #pragma unroll

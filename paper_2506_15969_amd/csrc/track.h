@@ -34,6 +34,16 @@ __host__ __device__ inline int fused_part_cap(int n_old, int n_parts) {
   return fused_wave_run(n_sub, n_parts) * (kWaves * 16) + 1;
 }
 
+// Records in a block's region, and the entry that one of them names.  A captured call may be replayed when
+// calls of other lengths, whose regions begin elsewhere, have used the buffer since, or may leave its own regions under a
+// call that is still to be tracked: a count or an index is then any word, and must not lead out of the buffers.
+__device__ __forceinline__ int region_count(const float *region, int cap) {
+  return min(*reinterpret_cast<const int32_t *>(region), cap - 1);   // (below zero: none)
+}
+__device__ __forceinline__ int record_entry(int word, int n_old) {   // (any other word: the appended entry, which starts in any case)
+  return static_cast<int>(min(static_cast<unsigned>(word), static_cast<unsigned>(n_old)));
+}
+
 template <bool kPrecise>
 __device__ __forceinline__ float exp_of(float x) {
   if constexpr (kPrecise) return expf(x);

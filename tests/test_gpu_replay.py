@@ -61,3 +61,55 @@ def test_replayed_calls(lazyev_lib, dtype, d, blocks, N, calls):
         assert eng.stats()["len"] == [N + calls + 1]
         assert bool(out[0].isfinite().all())
     eng.close()
+
+
+@pytest.mark.parametrize("how", ["evict", "stats"])
+@pytest.mark.parametrize("G", [7, 8])
+def test_replays_after_the_cache_has_grown(lazyev_lib, G, how):
+    """The candidate records of 250 entries over four blocks lie elsewhere than those of 257 and more: a call captured at 251
+    entries is replayed between eager calls up to 290, and right before what is outstanding is applied (by the
+    selection of an eviction, or by a launch of its own).  Outputs against fp64 softmax attention; every row of the cache
+    is the one its place (after an eviction, its position) says."""
+    S, H, N, W, budget = 2, 4, 250, 40, 280
+    stream = torch.cuda.Stream()
+    gen = torch.Generator(device="cuda").manual_seed(G)
+    q, kn, vn = (torch.empty((W + 1, S, h, 128), device="cuda").normal_(generator=gen).to(torch.bfloat16) for h in (H * G, H, H))
+    k, v = (torch.empty((S, H, N + W, 128), device="cuda").normal_(generator=gen).to(torch.bfloat16) for _ in range(2))
+    for all_rows, new in ((k, kn), (v, vn)):
+        all_rows[:, :, N:] = new[1:].permute(1, 2, 0, 3)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        eng = lazyev_lib.LazyEviction(1, S, H * G, H, 128, budget, W, N, 0.02, stream=stream)
+        eng.load_prompt(0, k[:, :, :N], v[:, :, :N])
+        eng.init()
+        eng.set_target_blocks(4 * S * H)
+        out = torch.zeros((W + 1, S, H * G, 128), dtype=torch.bfloat16, device="cuda")
+        graph = torch.cuda.CUDAGraph()
+        for t in range(1, W + 1):
+            if t == 2:                             # (its candidate records go to the second buffer, as those of the last call)
+                stream.synchronize()
+                with torch.cuda.graph(graph, stream=stream):
+                    eng.decode_step(0, t, q[t], kn[t], vn[t], out[t])
+                graph.replay()
+            else:
+                eng.decode_step(0, t, q[t], kn[t], vn[t], out[t])
+            if t % 3 == 0 or t == W:
+                graph.replay()
+        n = N + W
+        if how == "evict":
+            assert eng.evict(0, W) == n - budget
+            n = budget
+        assert eng.stats()["len"] == [n]
+        for t in range(1, W + 1):
+            p = torch.softmax(torch.matmul(k[:, :, :N + t].double(), q[t].double().view(S, H, G, 128).transpose(2, 3).contiguous()) / 128 ** 0.5, dim=2)
+            ref = torch.matmul(p.transpose(2, 3).contiguous(), v[:, :, :N + t].double()).view(S, H * G, 128)
+            err = (out[t].double() - ref).norm(dim=2) / ref.norm(dim=2)
+            assert float(err.max()) < 2 * 2.0 ** -8, (t, float(err.max()))   # (two roundings to bf16 of relative size 2^-9)
+        if how == "evict":
+            pos = eng.pos[0, :, :, :n].long()
+        else:                                      # (what the last call left for its entry's position is gone)
+            pos = torch.arange(n, device="cuda").expand(S, H, n).contiguous()
+        assert int(pos.min()) >= 0 and int(pos.max()) < N + W and bool((pos.diff(dim=2) > 0).all())
+        for cache, rows in ((eng.k_cache, k), (eng.v_cache, v)):
+            assert torch.equal(cache[0, :, :, :n], rows.gather(2, pos.unsqueeze(3).expand(-1, -1, -1, 128)))
+        eng.close()
