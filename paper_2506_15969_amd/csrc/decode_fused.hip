@@ -507,12 +507,13 @@ __device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, c
 // workspace's fault word and goes on.
 // The number is an argument, so a captured call has the same one in every replay and would find the records
 // of the replay before complete: a call that is being captured has its records cleared by a launch
-// before it (see lazyev_decode_step).
+// before it, and all captured calls have kSeqCaptured for their number, which no eager call has: an eager one would find
+// what a replay left complete as soon as the numbers had started over (see lazyev_decode_step).
 // A unit's blocks form groups of kMergeRadix; the last block of a group (its leader) merges the
 // group, and the unit's last block, a leader itself, merges what the other leaders hand over: one
 // hop for up to kMergeRadix blocks, two for up to kFusedSplitMax.  A hop is one memory round trip
 // whatever the number of records, because all of them are requested together.
-// The numbers run from 1 to 65535; before they start over the records are cleared (lazyev_decode_step).
+// The numbers of eager calls run from 1 to kSeqMax; before they start over the records are cleared.
 // Record of a block: for each of the four waves four rows of 64 words; row i holds the output
 // element 4 t + i of thread t (one store instruction of a wave writes 512
 // contiguous bytes), and the 16 bits beside it are a half of the maximum (rows 0 and 1) or the sum of thread t's head (each thread its own
@@ -524,7 +525,7 @@ constexpr int kRecWords = 4 * kBlock;
 // thread t's first word, as a byte offset
 __device__ __forceinline__ unsigned rec_at(int t) { return (static_cast<unsigned>(t >> 6) * (4 * 64) + (t & 63)) * 8u; }
 constexpr int kMergeRadix = 8;
-constexpr uint32_t kSeqMax = 0xFFFF;
+constexpr uint32_t kSeqMax = 0xFFFE, kSeqCaptured = 0xFFFF;
 
 __device__ __forceinline__ void rec_word_store(unsigned long long *p, float v, unsigned top) {
   __hip_atomic_store(p, (static_cast<unsigned long long>(top) << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
@@ -1547,6 +1548,7 @@ extern "C" int lazyev_timeline_read(unsigned long long *out, int n_words) {
 #endif
 int decode_fused_split_max() { return kFusedSplitMax; }
 uint32_t decode_fused_seq_max() { return kSeqMax; }
+uint32_t decode_fused_seq_captured() { return kSeqCaptured; }
 size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * sizeof(unsigned long long); }
 
 // Blocks per unit.  Measured on 28 query / 4 KV heads of 128 x bf16, us per call, unless it says otherwise:
@@ -1649,7 +1651,7 @@ hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent
   const int units = a.batch * a.n_kv_heads;
   if (a.group > kHeadPad || a.n_split < 1 ||
       a.n_split > kFusedSplitMax || a.n_split > a.rec_per_unit + 1 || !a.logits_out ||
-      !a.ws.part_rec || !a.ws.fault || a.seq == 0 || a.seq > kSeqMax ||
+      !a.ws.part_rec || !a.ws.fault || a.seq == 0 || a.seq > kSeqCaptured ||
       !a.stat_out || a.p_stride < (a.n_old + 16) / 16 * 16 ||
       (a.track.valid && (a.track.units != units || !a.track.logits || !a.track.stat ||
                          a.track.logits == a.logits_out || a.track.stat == a.stat_out)) ||

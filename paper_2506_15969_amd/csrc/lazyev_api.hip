@@ -40,9 +40,9 @@ struct lazyev_ctx {
   int last_hip_error;
   int device;                       // the device that was current at lazyev_init
   int32_t *static_scratch;          // that device's copy of `scratch` (see static_scratch_of)
-  uint32_t launch_seq;              // fused kernel: launches so far (the stamp of handed-over partials)
+  uint32_t launch_seq;              // fused kernel: number of the last eager launch (the stamp of handed-over partials)
   int32_t rec_per_unit;             // records of handed-over partials per unit ...
-  int32_t rec_clean;                // ... of which the first ones hold nothing but what launches of earlier numbers left
+  int32_t rec_clean;                // ... of which the first ones hold nothing but what eager launches of earlier numbers and replays left
   uint32_t spin_ticks;              // fused kernel: longest wait for such a partial, 10 ns ticks
   // fused kernel: the call whose tracking has not been applied yet, and the buffer pair in turn
   lazyev::TrackArgs pend;
@@ -597,25 +597,26 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
     // The number of this launch stamps the partials its blocks hand over; 0 is what a cleared record
     // holds.  Records are cleared before their first use (what lazyev_init did not clear, because only
     // lazyev_set_target_blocks asks for it; what the split + merge kernels wrote over), and
-    // when the numbers start over (every 65535 launches).  A call that is being captured will be launched with one
-    // number again and again: its records go back to 0 before each time (the default stream cannot
-    // be captured).
-    if (++ctx->launch_seq > lazyev::decode_fused_seq_max()) {
+    // when the numbers start over.  A call that is being captured will be launched with one number again and
+    // again, before and after any other call: its records go back to 0 before each time, and its number
+    // is one that no eager call has, whatever replays leave behind (the default stream cannot be captured).
+    const int32_t n_rec = a.n_split - 1;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (ctx->stream && n_rec > 0) {
+      const hipError_t ec = hipStreamIsCapturing(ctx->stream, &status);
+      if (ec != hipSuccess) return fail_hip(ctx, ec);
+    }
+    const bool captured = status != hipStreamCaptureStatusNone;
+    if (!captured && ++ctx->launch_seq > lazyev::decode_fused_seq_max()) {
       ctx->launch_seq = 1;
       ctx->rec_clean = 0;
     }
-    const int32_t n_rec = a.n_split - 1;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (ctx->stream && n_rec > 0) {
-      const hipError_t ec = hipStreamIsCapturing(ctx->stream, &capture);
-      if (ec != hipSuccess) return fail_hip(ctx, ec);
-    }
-    if (n_rec > ctx->rec_clean || (n_rec > 0 && capture != hipStreamCaptureStatusNone)) {
+    if (n_rec > ctx->rec_clean || captured) {
       const hipError_t ec = lazyev::launch_clear_records(ctx->ws.part_rec, ctx->units, a.rec_per_unit, n_rec, ctx->stream);
       if (ec != hipSuccess) return fail_hip(ctx, ec);
-      if (capture == hipStreamCaptureStatusNone) ctx->rec_clean = n_rec;   // (a captured launch has not run yet)
+      if (!captured) ctx->rec_clean = n_rec;       // (a captured launch has not run yet)
     }
-    a.seq = ctx->launch_seq;
+    a.seq = captured ? lazyev::decode_fused_seq_captured() : ctx->launch_seq;
     a.spin_ticks = ctx->spin_ticks;
   }
   a.activation_counter = ctx->ws.activations + static_cast<size_t>(layer) * ctx->units * lazyev::decode_slice_max();

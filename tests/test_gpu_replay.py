@@ -113,3 +113,48 @@ def test_replays_after_the_cache_has_grown(lazyev_lib, G, how):
         for cache, rows in ((eng.k_cache, k), (eng.v_cache, v)):
             assert torch.equal(cache[0, :, :, :n], rows.gather(2, pos.unsqueeze(3).expand(-1, -1, -1, 128)))
         eng.close()
+
+
+def test_replays_between_eager_calls_whose_numbers_start_over(lazyev_lib):
+    """Eager calls number their partials with 16 bits, a captured call leaves its partials with one number at every
+    replay: an early captured call is replayed before each eager call around the 65536th, whose outputs
+    are compared with fp64 softmax attention over what the cache holds."""
+    L, H, G, N, steps, captured_at = 64, 8, 2, 250, 1030, 10
+    stream = torch.cuda.Stream()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    k, v = (torch.empty((L, 1, H, N, 128), device="cuda").normal_(generator=gen).to(torch.bfloat16) for _ in range(2))
+    q, kn, vn = (torch.empty((5, 1, h, 128), device="cuda").normal_(generator=gen).to(torch.bfloat16) for h in (H * G, H, H))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        eng = lazyev_lib.LazyEviction(L, 1, H * G, H, 128, N + steps, 64, N, 0.05, stream=stream)
+        eng.k_cache[:, :, :, :N].copy_(k)
+        eng.v_cache[:, :, :, :N].copy_(v)
+        eng.init()
+        eng.set_target_blocks(4 * H)
+        out, out_replayed = (torch.zeros((1, H * G, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        graph, launches, wrong = torch.cuda.CUDAGraph(), 0, []
+        for t in range(1, steps + 1):
+            for layer in range(L):
+                x = (t + layer) % 4
+                if launches == captured_at:
+                    stream.synchronize()
+                    with torch.cuda.graph(graph, stream=stream):
+                        eng.decode_step(layer, t, q[4], kn[4], vn[4], out_replayed)
+                    graph.replay()
+                    launches += 1
+                    continue
+                near = 65526 <= launches < 65610
+                if near:
+                    graph.replay()
+                eng.decode_step(layer, t, q[x], kn[x], vn[x], out)
+                launches += 1
+                if near:
+                    n = N + t
+                    kd, vd = eng.k_cache[layer, 0, :, :n].double(), eng.v_cache[layer, 0, :, :n].double()
+                    p = torch.softmax(torch.matmul(kd, q[x, 0].double().view(H, G, 128).transpose(1, 2).contiguous()) / 128 ** 0.5, dim=1)
+                    ref = torch.matmul(p.transpose(1, 2).contiguous(), vd).view(H * G, 128)
+                    err = float(((out[0].double() - ref).norm(dim=1) / ref.norm(dim=1)).max())
+                    if not err < 2 * 2.0 ** -8:    # (bf16 weights and a bf16 result: two roundings of relative size 2^-9)
+                        wrong.append((launches, err))
+        assert launches > 65610 and not wrong, wrong
+        eng.close()
