@@ -232,7 +232,8 @@ __device__ __forceinline__ void track_load(const TrackArgs &k, int unit, int par
 
 // The activation test and the TS / MRI update of entry i (Alg. 1, Eq. 1); true if active.
 // log_mask (LDS, or null): the call is logged; an active entry then only sets its bit there.
-template <bool kPrecise>
+// kWeights: the caller may have asked for the weights or brought some (never with candidate records).
+template <bool kPrecise, bool kWeights>
 __device__ __forceinline__ bool track_one(const TrackArgs &k, int unit, int i, const float (&s)[kHeadPad],
                                           const float (&m)[kHeadPad], const float (&invl)[kHeadPad],
                                           unsigned *log_mask) {
@@ -247,8 +248,8 @@ __device__ __forceinline__ bool track_one(const TrackArgs &k, int unit, int i, c
     if (h < G) {
       float p = weight_of<kPrecise>(s[h], m[h], invl[h]);
       const size_t at = (head0 + h) * k.capacity + i;
-      if (k.p_out) k.p_out[at] = p;
-      if (k.p_override) p = k.p_override[at];
+      if (kWeights && k.p_out) k.p_out[at] = p;
+      if (kWeights && k.p_override) p = k.p_override[at];
       act = act || (p >= k.alpha);
     }
   }
@@ -282,7 +283,7 @@ __device__ __forceinline__ unsigned track_apply(const TrackArgs &k, int unit, in
     if (i >= n1) continue;
     const float s[kHeadPad] = {b.sa[r].x, b.sa[r].y, b.sa[r].z, b.sa[r].w,
                                b.sb[r].x, b.sb[r].y, b.sb[r].z, b.sb[r].w};
-    n_act += track_one<kPrecise>(k, unit, i, s, m, invl, log_mask) ? 1u : 0u;
+    n_act += track_one<kPrecise, true>(k, unit, i, s, m, invl, log_mask) ? 1u : 0u;
   }
   return n_act;
 }
@@ -303,7 +304,7 @@ __device__ __forceinline__ unsigned track_records(const TrackArgs &k, int unit, 
       const float4 sb = *reinterpret_cast<const float4 *>(region + static_cast<size_t>(1 + r) * kHeadPad + 4);
       const int i = record_entry(decltype(eight)::value ? k.cand_index[at + 1 + r] : __float_as_int(sb.w), k.n_old);
       const float s[kHeadPad] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, decltype(eight)::value ? sb.w : 0.f};
-      n_act += track_one<kPrecise>(k, unit, i, s, m, invl, log_mask) ? 1u : 0u;
+      n_act += track_one<kPrecise, false>(k, unit, i, s, m, invl, log_mask) ? 1u : 0u;
     };
     if (k.group == kHeadPad)
       for (int r = threadIdx.x; r < n; r += kBlock) track(r, std::true_type{});
@@ -1621,7 +1622,8 @@ hipError_t launch_track(const TrackArgs &k, hipStream_t stream) {
       k.p_stride < (k.n_old + 16) / 16 * 16)
     return hipErrorInvalidValue;
   if (k.compact && k.group == kHeadPad && !k.cand_index) return hipErrorInvalidValue;
-  if (k.compact && !decode_fused_compact_fits(k.n_old, k.n_parts, k.p_stride, k.group)) return hipErrorInvalidValue;
+  if (k.compact && (k.p_out || k.p_override || !decode_fused_compact_fits(k.n_old, k.n_parts, k.p_stride, k.group)))
+    return hipErrorInvalidValue;
   int n_parts = (k.n_old + 1 + 2 * kBlock - 1) / (2 * kBlock);   // about two entries per thread
   if (n_parts > 64) n_parts = 64;
   if (k.compact) n_parts = k.n_parts;              // one block per block of the call
@@ -1656,7 +1658,8 @@ hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent
       (a.track.valid && (a.track.units != units || !a.track.logits || !a.track.stat ||
                          a.track.logits == a.logits_out || a.track.stat == a.stat_out)) ||
       (a.track.valid && a.track.compact &&
-       !decode_fused_compact_fits(a.track.n_old, a.track.n_parts, a.track.p_stride, a.track.group)) ||
+       (a.track.p_out || a.track.p_override ||
+        !decode_fused_compact_fits(a.track.n_old, a.track.n_parts, a.track.p_stride, a.track.group))) ||
       (a.track.valid && a.track.bitlog &&
        (a.track.log_words < (a.track.capacity + 31) / 32 || a.track.log_words > decode_fused_log_words_max() ||
         a.track.log_unit_stride < a.track.log_words ||
