@@ -332,10 +332,13 @@ __device__ __forceinline__ void apply_outstanding(const EvictArgs &a, int unit, 
 // score in steps of 1 / 126 from 1 on (scores lie in 0 .. 2, weights in 0 .. 1), which tells keys apart better than their
 // leading byte: mostly one pass ends at the zeros or leaves at most kSmallSet keys.  The following digits are the
 // bytes, the highest first, of the keys still in play.
-template <int R>
+// kTodo: tracking is outstanding (a.todo).  Evictions without, those of many units among them, have an instance of their
+// own, as the registers of the other leave room for fewer blocks on a compute unit (3 entries per thread: 68 instead of 56): us,
+// tracking and row move included, one instance for both / this one, 2048 units of 432 entries 178 / 166, 3584 302 / 283.
+template <int R, bool kTodo>
 __global__ __launch_bounds__(kSelBlock) void evict_select_held_kernel(const EvictArgs a) {
   extern __shared__ unsigned long long keys_lds[];      // score bit pattern of each candidate
-  __shared__ unsigned active[R * kSelBlock / 32];  // the last call's activations, a bit per entry
+  __shared__ unsigned active[kTodo ? R * kSelBlock / 32 : 1];   // the last call's activations, a bit per entry
   __shared__ unsigned n_active;
   __shared__ unsigned hist[3][256];                // of passes p, p + 1, p + 2: a barrier lies between the last reading
   __shared__ unsigned long long wave_key[2][kSelWaves];   // of one, its clearing and its next use
@@ -362,7 +365,7 @@ __global__ __launch_bounds__(kSelBlock) void evict_select_held_kernel(const Evic
     v_ts[r] = v_mri[r] = v_pos[r] = 0;
     if (slot < n) { v_ts[r] = ts[slot]; v_mri[r] = mri[slot]; v_pos[r] = pos[slot]; }
   }
-  if (a.todo.on) apply_outstanding<R>(a, unit, v_ts, v_mri, v_pos, active, &n_active);
+  if constexpr (kTodo) apply_outstanding<R>(a, unit, v_ts, v_mri, v_pos, active, &n_active);
   if (tid < 256) hist[0][tid] = hist[1][tid] = hist[2][tid] = 0;
   if (tid == 0) { small_n = 0; moved = 0; }
 
@@ -522,7 +525,7 @@ __global__ __launch_bounds__(kSelBlock) void evict_select_held_kernel(const Evic
       ts[dst] = v_ts[r]; mri[dst] = v_mri[r]; pos[dst] = v_pos[r];
       src_index[dst] = slot;
     }
-    if (a.todo.on && slot >= a.budget && slot < n) {   // (places that no survivor takes: as the tracking leaves them)
+    if (kTodo && slot >= a.budget && slot < n) {   // (places that no survivor takes: as the tracking leaves them)
       ts[slot] = v_ts[r]; mri[slot] = v_mri[r]; pos[slot] = v_pos[r];
     }
     n_moved += static_cast<unsigned>(__popcll(__builtin_amdgcn_ballot_w64(keep && dst != static_cast<unsigned>(slot))));
@@ -810,14 +813,16 @@ hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) 
   if (ev) (void)hipEventRecord(ev[0], stream);
   // as few entries per thread as hold the unit (an instance of 8 for all: 1056 entries 12.4 instead of 7.2 us, 2112 13.0 instead of 10.0); beyond 8 and
   // its 64 KB of keys the passes go over memory
-  if (a.n <= 2 * kSelBlock)
-    hipLaunchKernelGGL(evict_select_held_kernel<2>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
-  else if (a.n <= 3 * kSelBlock)
-    hipLaunchKernelGGL(evict_select_held_kernel<3>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
-  else if (a.n <= 5 * kSelBlock)
-    hipLaunchKernelGGL(evict_select_held_kernel<5>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
-  else if (a.n <= kLdsCandidates)
-    hipLaunchKernelGGL(evict_select_held_kernel<8>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
+#define LAZYEV_SELECT(R) \
+  do { \
+    if (a.todo.on) hipLaunchKernelGGL((evict_select_held_kernel<R, true>), dim3(n_blocks), dim3(kSelBlock), lds, stream, a); \
+    else hipLaunchKernelGGL((evict_select_held_kernel<R, false>), dim3(n_blocks), dim3(kSelBlock), lds, stream, a); \
+  } while (0)
+  if (a.n <= 2 * kSelBlock) LAZYEV_SELECT(2);
+  else if (a.n <= 3 * kSelBlock) LAZYEV_SELECT(3);
+  else if (a.n <= 5 * kSelBlock) LAZYEV_SELECT(5);
+  else if (a.n <= kLdsCandidates) LAZYEV_SELECT(8);
+#undef LAZYEV_SELECT
   else if (n_cand <= kLdsCandidates)
     hipLaunchKernelGGL(evict_select_kernel<true>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
   else

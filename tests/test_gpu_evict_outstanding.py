@@ -46,3 +46,32 @@ def test_selection_applies_what_is_outstanding(lazyev_lib, per_layer, L, S, grou
     assert runs[0][1] == runs[1][1]
     for x, y in zip(runs[0][2], runs[1][2]):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("S,first", [(128, 64), (129, 64), (160, 32)])
+def test_many_units_as_several_contexts(lazyev_lib, S, first):
+    """512 units at once, 516 (tracking in launches of its own, the selection without) and 640: the same state, bit for bit,
+    as the same sequences in two contexts of at most 512 units each, whose calls have one block per unit as well."""
+    H, group, d, B, W, steps = 4, 2, 64, 70, 9, 27
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    rnd = lambda *shape: torch.empty(shape, device="cuda").normal_(generator=gen).to(torch.bfloat16)
+    k, v, q, kn, vn = rnd(S, H, B, d), rnd(S, H, B, d), rnd(steps, S, group * H, d), rnd(steps, S, H, d), rnd(steps, S, H, d)
+    q = (q.float() + 2.0 * k[:, :, 7].float().repeat_interleave(group, dim=1)).to(torch.bfloat16)
+    states = []
+    for parts in (((0, S),), ((0, first), (first, S))):
+        state = []
+        for a, b in parts:
+            eng = lazyev_lib.LazyEviction(1, b - a, group * H, H, d, B, W, B, 8.0 / (B + W))
+            eng.load_prompt(0, k[a:b], v[a:b])
+            eng.init()
+            eng.set_target_blocks((b - a) * H)
+            out = torch.zeros((b - a, group * H, d), dtype=torch.bfloat16, device="cuda")
+            for t in range(1, steps + 1):
+                eng.decode_step(0, t, q[t - 1, a:b].contiguous(), kn[t - 1, a:b].contiguous(), vn[t - 1, a:b].contiguous(), out)
+                assert eng.evict_all(t) == (W if t % W == 0 else 0)
+            assert eng.stats()["n_evict_events"] == [steps // W]
+            state.append([x[0].clone() for x in (eng.ts, eng.mri, eng.pos)] + [eng.k_cache[0, :, :, :B].clone(), out])
+            eng.close()
+        states.append([torch.cat(x) for x in zip(*state)])
+    for x, y in zip(*states):
+        assert torch.equal(x, y)
