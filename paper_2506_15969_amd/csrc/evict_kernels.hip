@@ -1,7 +1,7 @@
 // Lagged eviction of one layer (Sec. 4 "MRI-Centric Eviction", Eq. 3, Eq. 6, Alg. 1 of the
 // paper), as two kernels:
-//   select  one block per unit: applies the tracking that is outstanding (units whose entries fit its
-//           registers), scores every candidate entry (all but the last W) in binary64,
+//   select  one block per unit: applies the tracking that is outstanding (see evict_applies_tracking),
+//           scores every candidate entry (all but the last W) in binary64,
 //           finds the (B-W)-th largest score with an 8-bit radix select over the score bit
 //           patterns held in registers (beyond 8192 entries in LDS, beyond 8192 candidates in the
 //           workspace), breaks ties in favour of the more recent entry, prefix-scans
@@ -780,7 +780,17 @@ __global__ __launch_bounds__(kMoveBlock) void evict_move_kernel(const EvictArgs 
 }  // namespace
 
 int evict_lds_candidates() { return kLdsCandidates; }
-bool evict_applies_tracking(int n) { return n <= kLdsCandidates; }   // (entries held in registers)
+// Up to 3 entries per thread, and up to 5 from 32 units on.  One block applies all that is outstanding for its unit, a launch
+// of its own spreads a unit over several: with more entries the chain of the one block takes longer than the launches it
+// saves.  us for an eviction of 64 calls' tracking, launches of their own / in the selection: 4 units x 1064 22 / 19, x 2564 30 / 28,
+// x 4264 36.7 / 39.6, x 5264 46 / 52, x 8064 65 / 75; 32 units x 2564 40.2 / 36.6, x 4264 57.0 / 55.2, x 5264 69.5 / 71.5, x 8064
+// 89.5 / 94.3; 128 units x 4264 136 / 133, x 5264 164 / 166, x 8064 232 / 236; 256 units x 8064 418 / 415.
+// Of more units than the chip holds selection blocks at once (two per compute unit) the chain is what
+// the launch waits for again and again: 512 units of 432 entries 55 / 52, of 1152 118 / 113, of 2112 221 / 214; 768 73.3 / 72.4, 167 /
+// 162, 323 / 314; 1024 91.9 / 93.3, 216 / 211, 423 / 411; 2048 165 / 178, 402 / 410, 818 / 813; 3584 of 432 281 / 301.
+bool evict_applies_tracking(int n, int units) {
+  return (n <= 3 * kSelBlock || (n <= 5 * kSelBlock && units >= 32)) && units <= 512;
+}
 
 hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) {
   const int n_cand = a.n - a.window;
@@ -793,7 +803,7 @@ hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) 
     return hipErrorInvalidValue;
   const size_t lds = static_cast<size_t>(n_cand) * sizeof(unsigned long long);
   if (n_cand > kLdsCandidates && !a.ws.sel_keys) return hipErrorInvalidValue;
-  if (a.todo.on && (!evict_applies_tracking(a.n) || a.slots.prompt_len || !a.todo.bitlog || a.units / a.units_per_layer > kFlushLayers ||
+  if (a.todo.on && (!evict_applies_tracking(a.n, a.units) || a.slots.prompt_len || !a.todo.bitlog || a.units / a.units_per_layer > kFlushLayers ||
                     a.todo.log_words < (a.n + 31) / 32 || a.todo.log_slots < 1 || a.todo.last_layer >= a.units / a.units_per_layer))
     return hipErrorInvalidValue;
   if (a.todo.on && a.todo.last_layer >= 0) {
@@ -821,7 +831,8 @@ hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) 
   if (a.n <= 2 * kSelBlock) LAZYEV_SELECT(2);
   else if (a.n <= 3 * kSelBlock) LAZYEV_SELECT(3);
   else if (a.n <= 5 * kSelBlock) LAZYEV_SELECT(5);
-  else if (a.n <= kLdsCandidates) LAZYEV_SELECT(8);
+  else if (a.n <= kLdsCandidates)                  // (nothing outstanding: evict_applies_tracking)
+    hipLaunchKernelGGL((evict_select_held_kernel<8, false>), dim3(n_blocks), dim3(kSelBlock), lds, stream, a);
 #undef LAZYEV_SELECT
   else if (n_cand <= kLdsCandidates)
     hipLaunchKernelGGL(evict_select_kernel<true>, dim3(n_blocks), dim3(kSelBlock), lds, stream, a);

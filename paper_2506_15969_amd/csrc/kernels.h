@@ -164,8 +164,8 @@ struct EvictArgs {
   int32_t due_seq[8];
   OutstandingArgs todo;
 };
-// Can the selection of n entries apply what is outstanding?
-bool evict_applies_tracking(int n);
+// Does the selection of n entries of so many units (of all layers) apply what is outstanding?
+bool evict_applies_tracking(int n, int units);
 
 // The unit a block of an eviction launch works on.
 __host__ __device__ inline int32_t evict_unit_of(const EvictArgs &a, int32_t i) {

@@ -324,30 +324,26 @@ hipError_t flush_tracking(lazyev_ctx *ctx) {
   return e;
 }
 
-// What is outstanding for the layers l0 .. l1 - 1, whose eviction of n entries is about to be launched: handed to the
-// selection where that can apply it (a.todo), else applied in launches of its own.  Where layers are evicted one by one,
-// the first one's launches apply the logged calls of all of them (28 layers of 128 units 58 us; each selection by itself 8 us more).
-// Of more units than the chip holds selection blocks at once (two per compute unit) launches of their own are the
-// faster, the chain of a selection block being what its launch waits for again and again (us, all three launches / the selection
-// alone: 256 units of 1152 entries x 128 calls 22 / 15, of 4160 x 64 37 / 28; 3584 units of 1152 x 128 107 / 142, 4608 of 4160 x 64 322 / 353).
-constexpr long long kSelectionUnits = 512;
-hipError_t outstanding_of(lazyev_ctx *ctx, int l0, int l1, int32_t n, lazyev::EvictArgs &a) {
-  const bool last = ctx->pend.valid && ctx->pend_layer >= l0 && ctx->pend_layer < l1;
-  if (!ctx->bitlog || ctx->slots_on || l1 - l0 != ctx->cfg.n_layers || l1 - l0 > lazyev::kFlushLayers ||
-      static_cast<long long>(l1 - l0) * ctx->units > kSelectionUnits || !lazyev::evict_applies_tracking(n) ||
-      (ctx->pend.valid && !ctx->pend.compact) || (last && ctx->pend.n_old + 1 != n))
+// What is outstanding when an eviction of n entries is about to be launched: handed to the selection where that applies it
+// (a.todo), else applied in launches of its own.  Only where all layers are evicted at once: one by one, the first
+// one's launches apply the logged calls of all of them (28 layers of 128 units 58 us; each selection by itself 8 us more).
+hipError_t outstanding_of(lazyev_ctx *ctx, bool all_layers, int32_t n, lazyev::EvictArgs &a) {
+  const int L = ctx->cfg.n_layers;
+  const bool last = ctx->pend.valid;
+  if (!all_layers || !ctx->bitlog || ctx->slots_on || L > lazyev::kFlushLayers || !lazyev::evict_applies_tracking(n, a.units) ||
+      (last && (!ctx->pend.compact || ctx->pend.n_old + 1 != n)))
     return flush_tracking(ctx);
   lazyev::OutstandingArgs &o = a.todo;
   o.on = 1;
-  o.bitlog = ctx->bitlog + static_cast<size_t>(l0) * ctx->log_slots * ctx->units * ctx->log_words;
+  o.bitlog = ctx->bitlog;
   o.log_words = ctx->log_words; o.log_slots = ctx->log_slots;
   o.prompt_len = ctx->cfg.prompt_len;
-  for (int l = l0; l < l1; ++l) {
-    o.layer[l - l0].n_calls = ctx->log_n[l];
-    o.layer[l - l0].t = ctx->log_t[l];
-    o.layer[l - l0].n_old = ctx->log_n_old[l];
+  for (int l = 0; l < L; ++l) {
+    o.layer[l].n_calls = ctx->log_n[l];
+    o.layer[l].t = ctx->log_t[l];
+    o.layer[l].n_old = ctx->log_n_old[l];
   }
-  o.last_layer = last ? ctx->pend_layer - l0 : -1;
+  o.last_layer = last ? ctx->pend_layer : -1;
   if (last) {
     o.last = ctx->pend;
     o.last.bitlog = nullptr;
@@ -355,10 +351,10 @@ hipError_t outstanding_of(lazyev_ctx *ctx, int l0, int l1, int32_t n, lazyev::Ev
   return hipSuccess;
 }
 // ... and after that launch
-void outstanding_done(lazyev_ctx *ctx, int l0, int l1, const lazyev::EvictArgs &a) {
+void outstanding_done(lazyev_ctx *ctx, const lazyev::EvictArgs &a) {
   if (!a.todo.on) return;
-  for (int l = l0; l < l1; ++l) ctx->log_n[l] = 0;
-  if (a.todo.last_layer >= 0) ctx->pend.valid = 0;
+  std::fill(ctx->log_n.begin(), ctx->log_n.end(), 0);
+  ctx->pend.valid = 0;
 }
 
 }  // namespace
@@ -778,11 +774,11 @@ static int evict_layer(lazyev_ctx *ctx, int32_t layer, int32_t t, int32_t *n_evi
     a.logits = ctx->last_logits; a.stat = ctx->last_stat;
     a.group = ctx->group; a.p_stride = ctx->last_p_stride;
   }
-  const hipError_t ef = outstanding_of(ctx, layer, layer + 1, n, a);   // scores use TS and MRI of step t (Alg. 1 order)
+  const hipError_t ef = outstanding_of(ctx, c.n_layers == 1, n, a);   // scores use TS and MRI of step t (Alg. 1 order)
   if (ef != hipSuccess) return fail_hip(ctx, ef);
   const hipError_t e = lazyev::launch_evict(a, ctx->stream, arm_events(ctx, 1));
   if (e != hipSuccess) return fail_hip(ctx, e);
-  outstanding_done(ctx, layer, layer + 1, a);
+  outstanding_done(ctx, a);
   if (n_evicted) *n_evicted = n - c.budget;
   ctx->n_evict_events[layer] += 1;
   ctx->n_evicted[layer] += n - c.budget;
@@ -861,11 +857,11 @@ int lazyev_evict_all(lazyev_ctx *ctx, int32_t t, int32_t *n_evicted) {
   a.n_kv_heads = c.n_kv_heads;
   a.slots = slots_of(ctx);
   fill_due(ctx, t, a);
-  const hipError_t ef = outstanding_of(ctx, 0, L, n, a);   // scores use TS and MRI of step t (Alg. 1 order)
+  const hipError_t ef = outstanding_of(ctx, true, n, a);   // scores use TS and MRI of step t (Alg. 1 order)
   if (ef != hipSuccess) return fail_hip(ctx, ef);
   const hipError_t e = lazyev::launch_evict(a, ctx->stream, arm_events(ctx, 1));
   if (e != hipSuccess) return fail_hip(ctx, e);
-  outstanding_done(ctx, 0, L, a);
+  outstanding_done(ctx, a);
   if (n_evicted) *n_evicted = n - c.budget;
   for (int l = 0; l < L; ++l) {
     ctx->n_evict_events[l] += 1;

@@ -6,7 +6,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-def _run(lazyev_lib, first_stats, per_layer, L, S, group, H, d, dtype, B, W, steps, prompt):
+def _run(lazyev_lib, first_stats, per_layer, L, S, group, H, d, dtype, B, W, steps, prompt, last_layer=None):
     gen = torch.Generator(device="cuda").manual_seed(B + W + group)
     eng = lazyev_lib.LazyEviction(L, S, group * H, H, d, B, W, prompt, 8.0 / (B + W), dtype=dtype)
     eng.k_cache[:, :, :, :prompt].normal_(generator=gen)
@@ -14,8 +14,9 @@ def _run(lazyev_lib, first_stats, per_layer, L, S, group, H, d, dtype, B, W, ste
     eng.init()
     out = torch.zeros((S, group * H, d), dtype=dtype, device="cuda")
     events = 0
+    order = list(range(L)) if last_layer is None else [x for x in range(L) if x != last_layer] + [last_layer]
     for t in range(1, steps + 1):
-        for layer in range(L):
+        for layer in order:
             q, kn, vn = (torch.empty((S, h, d), device="cuda").normal_(generator=gen).to(dtype) for h in (group * H, H, H))
             q = (q.float() + 2.0 * eng.k_cache[layer, :, :, (7 * t) % prompt].float().repeat_interleave(group, dim=1)).to(dtype)
             eng.decode_step(layer, t, q, kn, vn, out)
@@ -44,6 +45,26 @@ def test_selection_applies_what_is_outstanding(lazyev_lib, per_layer, L, S, grou
     runs = [_run(lazyev_lib, first, per_layer, L, S, group, H, d, dtype, B, W, steps, prompt) for first in (True, False)]
     assert runs[0][0] == runs[1][0] > 0
     assert runs[0][1] == runs[1][1]
+    for x, y in zip(runs[0][2], runs[1][2]):
+        assert torch.equal(x, y)
+
+
+# the layer whose call is the last before the eviction is any of them; 5 entries per thread from 32 units on (31: launches of its own), up
+# to 5120 entries
+@pytest.mark.parametrize("last_layer", [0, 1, 2])
+def test_last_call_of_any_layer(lazyev_lib, last_layer):
+    args = (3, 2, 7, 2, 128, torch.bfloat16, 300, 40, 80, 300)
+    runs = [_run(lazyev_lib, first, False, *args, last_layer=last_layer) for first in (True, False)]
+    assert runs[0][0] == runs[1][0] > 0 and runs[0][1] == runs[1][1]
+    for x, y in zip(runs[0][2], runs[1][2]):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("L,S,H,B,W", [(1, 32, 1, 3020, 53), (1, 31, 1, 3020, 53), (2, 4, 4, 3019, 53), (1, 8, 4, 5055, 65), (1, 8, 4, 5056, 65),
+                                       (1, 8, 4, 4990, 129)])
+def test_five_entries_per_thread(lazyev_lib, L, S, H, B, W):
+    runs = [_run(lazyev_lib, first, False, L, S, 1, H, 64, torch.bfloat16, B, W, W, B) for first in (True, False)]
+    assert runs[0][0] == runs[1][0] > 0 and runs[0][1] == runs[1][1]
     for x, y in zip(runs[0][2], runs[1][2]):
         assert torch.equal(x, y)
 
