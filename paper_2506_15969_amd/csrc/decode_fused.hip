@@ -1552,15 +1552,41 @@ uint32_t decode_fused_seq_max() { return kSeqMax; }
 uint32_t decode_fused_seq_captured() { return kSeqCaptured; }
 size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * sizeof(unsigned long long); }
 
+// Of n > kMergeRadix blocks per unit, all or the whole groups of kMergeRadix among them.  A last group that is not whole makes its
+// blocks wait for the leaders' merges all the same, and the blocks of a unit lie on more XCDs; what it saves are rounds, i.e. sub-tiles of
+// the longest-running waves.  us per call, whole groups / all blocks:
+//   * bf16 rows, where a round is short: 20 units x 4200 .. 8200 entries 8 / 12 blocks (128) 11.4 / 11.8 .. 18.4 / 18.4, (64) 10.3 / 11.0
+//     .. 14.8 / 14.2, 28 x 8200 8 / 9 22.5 / 26.8, (64) 15.4 / 19.5, 23 x 8200 8 / 11 19.8 / 23.4, (64) 14.9 / 17.2, 14 x 8200 16 / 18 14.6 /
+//     16.6; the other way for long caches, where idle compute units cost more: 18 x 12000 8 / 14 26.6 / 25.5, (64) 20.4 /
+//     18.6, 24 x 16400 8 / 10 43.8 / 42.7, (64) 28.4 / 27.4.
+//   * fp32 rows of 128, where it is long: fewer than four fifths of the rounds pay.  20 x 4200 / 8200 / 12000 8 / 12 23.7 / 21.7, 40.3 /
+//     34.5, 56.6 / 47.9; 24 x 8200 8 / 10 42.3 / 40.0; 11 x 8200 16 / 23 26.2 / 24.5; 7 x 4200 32 / 36 14.3 / 13.2; but 28 x 8200 8
+//     / 9 44.5 / 49.6, 14 x 8200 16 / 18 27.4 / 29.2.
+//   * fp32 rows of 64 lie between: 18 x 8200 8 / 14 23.1 / 21.7, 20 x 8200 8 / 12 23.4 / 20.7, but where the units are no multiple of four
+//     (see BlockPlace) 22 x 8200 8 / 11 23.9 / 25.7; 11 x 6200 16 / 23 14.2 / 13.3 (64 x bf16 11.3 / 11.1).
+// Where the cache's length bounds the blocks, whole groups above it: 4 units x 4800, 32 / 38 / 40 blocks 13.9 / 12.6 / 12.5 (fp32 128),
+// 10.4 / 9.7 / 9.5 (fp32 64), 9.1 / 9.2 / 8.9 (bf16 64), 8.5 / 8.2 / 8.1 (bf16 128).
+static int groups_of(int units, int n_sub, int n, bool f32, int head_dim) {
+  const int part = n % kMergeRadix, whole = n - part;
+  if (part == 0) return n;
+  const int rounds = fused_wave_run(n_sub, n), rounds_whole = fused_wave_run(n_sub, whole);
+  bool all;
+  if (f32 && head_dim == 128)
+    all = 5 * rounds < 4 * rounds_whole || (whole == kMergeRadix && part > 1 && n_sub >= 768);
+  else if (whole == kMergeRadix)
+    all = (part > 1 && n_sub >= 640) || (f32 && 10 * rounds <= (units % 4 == 0 ? 7 : 6) * rounds_whole);
+  else
+    all = (f32 || head_dim == 64) && whole == 2 * kMergeRadix && 4 * rounds < 3 * rounds_whole;
+  return all ? n : whole;
+}
+
 // Blocks per unit.  Measured on 28 query / 4 KV heads of 128 x bf16, us per call, unless it says otherwise:
 //   * no more blocks than compute units: a second stream block on some of them holds up the whole
 //     launch (80 units x 2200 entries: 3 blocks per unit 17.4, 4 22.1; 48 units: 5 12.6, 6 16.6), and with
 //     two on all of them the bytes in flight only widen the spread of the blocks' ends (128 units x
 //     4144 entries: 44.5 with one, 46.4 with two).
 //   * only a long cache pays for the second hop that more than kMergeRadix blocks need (8 units x 2200
-//     entries: 8 blocks 8.9, 16 9.7, 32 9.8; x 6200 entries: 13.3, 11.6, 10.3), and then in whole groups, the leaders' merges
-//     being what it waits for (12 units x 8200: 8 blocks 17.1, 16 14.6, 21 16.0; 28 x 8200: 8 23.6, 9 27.5; 24 x 8200: 8 20.3,
-//     10 21.8), but for caches so long that idle compute units cost more (20 units x 16400: 8 38.8, 12 36.5; 24: 8 44.1, 10 43.1).
+//     entries: 8 blocks 6.9, 16 7.8, 32 7.4; x 6200 entries: 11.1, 10.5, 9.1), and then mostly in whole groups (see groups_of).
 //   * seven or eight blocks where they leave some compute units to the tracking (28 units x 1040 / 2060 / 4200
 //     entries: 6 blocks 7.25 / 9.52 / 14.6, 8 7.22 / 9.47 / 13.9); where they fill the chip to the last one, six up to some thousand
 //     entries (32 units x 1040 / 4100 / 6200: 6 blocks 7.1 / 15.0 / 20.1, 8 7.4 / 15.4 / 20.6; x 8200 / 12000 27.3 / 42.9, 8
@@ -1576,15 +1602,18 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //     x 600 12.6 / 14.8, x 2200 38.5 / 40.5, x 6200 115 / 119; 192 units 12.7 / 15.3, 39.9 / 42.1, 123 / 130; 240 units
 //     14.6 / 17.5, 48.7 / 50.7, 143 / 152), as it is for fp32 rows (192 units x 2200, 64 46.5 / 47.9, 128 84.2 / 89.1);
 //     so it is for bf16 rows of 64 (176 units x 2200 25.4 / 25.3).
-int decode_fused_split(int units, int n_sub, bool bf16_128) {
+int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   constexpr int kUnitsOfChip = 256;                // compute units of the chip that the figures above are from
   int n = kUnitsOfChip / units;
   if (n < 1) n = 1;
   if (n > kMergeRadix && n_sub <= kWaves * kMergeRadix * 8) n = kMergeRadix;
-  if (n > 6 && n <= kMergeRadix && n * units > 240 && n_sub < (n < kMergeRadix ? 512 : bf16_128 ? 480 : 112)) n = 6;
+  if (n > 6 && n <= kMergeRadix && n * units > 240 && n_sub < (n < kMergeRadix ? 512 : !f32 && head_dim == 128 ? 480 : 112)) n = 6;
   const int by_work = n_sub <= kWaves ? 1 : n_sub < 4 * kWaves ? 2 : (n_sub + kWaves) / (2 * kWaves);
-  if (n > by_work) n = by_work;
-  if (n > kMergeRadix && (n >= 2 * kMergeRadix || n == kMergeRadix + 1 || n_sub < 768)) n = n / kMergeRadix * kMergeRadix;
+  if (n > kMergeRadix) {
+    const int up = (by_work + kMergeRadix - 1) / kMergeRadix * kMergeRadix;
+    n = groups_of(units, n_sub, n < up ? n : up, f32, head_dim);
+  }
+  if (n > by_work && n <= kMergeRadix) n = by_work;
   const int n2 = 2 * kUnitsOfChip / units;
   if (units < kUnitsOfChip && n <= kMergeRadix && n_sub >= 32 * kWaves * n && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2 < by_work ? n2 : by_work;
   return n;

@@ -213,7 +213,7 @@ uint32_t decode_fused_seq_max();              // largest number of an eager laun
 uint32_t decode_fused_seq_captured();         // ... and the number of every captured one
 int decode_fused_records_needed(int units, int capacity);   // most records per unit that decode_fused_split asks for
 int decode_fused_records_held(int units, int capacity, size_t bytes);   // most records per unit of use that `bytes` hold for all units
-int decode_fused_split(int units, int n_sub, bool bf16_128);   // blocks per unit of a call over n_sub sub-tiles of 16 entries (rows of 128 x bf16, or others)
+int decode_fused_split(int units, int n_sub, bool f32, int head_dim);   // blocks per unit of a call over n_sub sub-tiles of 16 entries
 hipError_t launch_clear_records(unsigned long long *rec, int units, int rec_per_unit, int n_records, hipStream_t stream);
 hipError_t launch_track(const TrackArgs &k, hipStream_t stream);
 hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stream);
