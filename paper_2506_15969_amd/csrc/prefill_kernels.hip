@@ -634,8 +634,12 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
       __syncthreads();                             // the next stage is complete, this one no longer read
     };
     settle(ka);
-    do {                                           // (whole rounds: see settle; a stage too many works on nothing)
+    // Whole rounds (see settle); a stage too many works on nothing.  Narrow blocks of 128-byte rows end in the middle of one: their
+    // stages are two tiles each and few (us, whole rounds / this, 64 x bf16, 28 / 4 heads x 20 / 33 / 100 positions 11.0 / 10.8, 13.5 /
+    // 13.2, 17.6 / 17.4; 16 sequences x 20 / 33 11.5 / 11.3, 14.0 / 13.7; the same from 180 positions on).
+    do {
       stage(std::integral_constant<int, 0>{});
+      if (NB == 1 && R::kStage == 2 && it >= it_end) break;
       stage(std::integral_constant<int, 1>{});
     } while (it < it_end);
   }
