@@ -432,12 +432,8 @@ __global__ __launch_bounds__(kBlock) void track_flush_kernel(const FlushArgs f) 
 #pragma unroll
       for (int x = 0; x < kFlushWords; ++x) {
         const unsigned calls = transpose_bits<32>(s + j < of.n_calls ? w[b][x] : 0u, j);
-        if (calls == 0) continue;
-        const int lo = __builtin_ctz(calls), hi = 31 - __builtin_clz(calls);
-        mri[x] = max(mri[x], of.t + s + lo - ts[x]);                       // Eq. 1
-        if (hi > lo) mri[x] = max(mri[x], longest_gap<32>(calls, lo, hi));
-        ts[x] = of.t + s + hi;                                             // Alg. 1
-        touched[x] = true;
+        apply_calls(calls, of.t + s, ts[x], mri[x]);
+        touched[x] = touched[x] || calls != 0;
       }
     }
   }
@@ -520,7 +516,7 @@ __device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, c
 // contiguous bytes), and the 16 bits beside it are a half of the maximum (rows 0 and 1) or the sum of thread t's head (each thread its own
 // copy: what the reader needs of a head then never waits for another wave's store).  What a merge costs is the
 // instructions of single waves: with a word of its own, half of it the number, for each of the six values, a merge of seven
-// records was 42 loads and 42 comparisons, now 28 and 14, and with one exponential per record instead of two that wait for
+// records was 42 loads and 42 comparisons, now 28 loads, 14 exclusive ors and 7 comparisons, and with one exponential per record instead of two that wait for
 // those before (see Merge) 8 units x 2081 entries take 2074 us for 256 calls instead of 2218, 32 x 1040 241 for 32 instead of 256.
 constexpr int kRecWords = 4 * kBlock;
 // thread t's first word, as a byte offset
@@ -629,6 +625,7 @@ struct Kernarg {
 typedef const __attribute__((address_space(4))) DecodeArgs *const_args_t;
 template <typename T>
 __device__ __forceinline__ const DecodeArgs &args_from_here() {
+  // (that the compiler lays the kernel's own arguments out like this struct: tests/test_kernel_resources.py)
   static_assert(offsetof(Kernarg<T>, a) == 56, "five pointers, two lengths and the shape, then the block, aligned to 8 bytes");
   uintptr_t p = reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()) + offsetof(Kernarg<T>, a);
   __asm__ volatile("" : "+s"(p));                  // (nothing of it is read before this place)
@@ -794,9 +791,9 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
 
   // Two ways to a sub-tile's rows.  kFlat: they lie one after the other in the cache, so a scalar address and one 32-bit offset
   // per lane and load reach them, rows beyond the cache taken as its last one; the row to be appended is not there yet,
-  // and patch_k and patch_v put it in place when the unit's last sub-tile, which alone has it, is worked on.  Otherwise every load
+  // and is put in place (K in the staging area, V by patch_v) when the unit's last sub-tile, which alone has it, is worked on.  Otherwise every load
   // chooses the source of its row, 64 of the 230 vector instructions of a sub-tile.  Where the bytes set the time those cost
-  // nothing, and the patch at the end of the run does: us per pass, chosen / flat, 128 units x 2081 3009 / 3029, x 4129 of 80 (2 blocks a unit) 5766 / 5816;
+  // nothing, and the replacement at the end of the run does: us per pass, chosen / flat, 128 units x 2081 3009 / 3029, x 4129 of 80 (2 blocks a unit) 5766 / 5816;
   // with three blocks a unit or more, and for rows of 128 bytes, the latency of a sub-tile does: 8 units x 2081 1999 / 1950,
   // 48 units x 1000 1273 / 1254, 64 units x 1563 of 64 x bf16 1160 / 1090.  (fp32 rows: the products are longer than either, 840 / 842.)
   constexpr bool kFlat = !R::kF32 && (kSplit >= 3 || R::kBytes == 128);

@@ -248,9 +248,8 @@ __device__ __forceinline__ unsigned last_call_bits(const TrackArgs &k, int unit,
   return n_act;
 }
 
-// Applies what is outstanding to the entries in registers, entry r * kSelBlock + tid in place r (the same
-// updates as track_flush_kernel's and track_kernel's, which are the comments' place; launches of their own took 8 - 13 us
-// before every eviction).  A wave has 64 entries in a row, two words of a call: lane (half, j) brings word `half` of call
+// Applies what is outstanding to the entries in registers, entry r * kSelBlock + tid in place r: the updates of
+// track_flush_kernel and track_kernel.  A wave has 64 entries in a row, two words of a call: lane (half, j) brings word `half` of call
 // s + j, and after a transposition across the 32 lanes holds the 32 calls of entry 32 half + j.
 template <int R>
 __device__ __forceinline__ void apply_outstanding(const EvictArgs &a, int unit, int32_t (&v_ts)[R], int32_t (&v_mri)[R], int32_t (&v_pos)[R],
@@ -294,12 +293,7 @@ __device__ __forceinline__ void apply_outstanding(const EvictArgs &a, int unit, 
       if (s >= of.n_calls) break;                  // (uniform)
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const unsigned calls = transpose_bits<32>(s + j < of.n_calls ? w[b][r] : 0u, j);
-        if (calls == 0) continue;
-        const int lo = __builtin_ctz(calls), hi = 31 - __builtin_clz(calls);
-        v_mri[r] = max(v_mri[r], of.t + s + lo - v_ts[r]);                  // Eq. 1
-        if (hi > lo) v_mri[r] = max(v_mri[r], longest_gap<32>(calls, lo, hi));
-        v_ts[r] = of.t + s + hi;                                            // Alg. 1
+        apply_calls(transpose_bits<32>(s + j < of.n_calls ? w[b][r] : 0u, j), of.t + s, v_ts[r], v_mri[r]);
       }
     }
   }
