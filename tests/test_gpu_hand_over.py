@@ -105,3 +105,33 @@ def test_launch_numbers_start_over(lazyev_lib):
             n = B
     assert eng.stats()["last_step"] == [steps] * L
     eng.close()
+
+
+def test_records_left_a_whole_cycle_of_numbers_ago(lazyev_lib):
+    """Launch 100 has eight blocks per unit; all others up to the next one with that number (eager numbers run from 1 to
+    65534) have two, which leave six of its seven records as they are.  That launch, over other inputs, must not take
+    them for its own: they are cleared when the numbers start over."""
+    L, H, group, N, steps, period = 64, 8, 2, 500, 1030, 65534
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    eng = lazyev_lib.LazyEviction(L, 1, group * H, H, 128, N + steps, 64, N, 0.05)
+    eng.k_cache[:, :, :, :N].normal_(generator=gen)
+    eng.v_cache[:, :, :, :N].normal_(generator=gen)
+    eng.init()
+    q, kn, vn = (torch.empty((5, 1, h, 128), device="cuda").normal_(generator=gen).to(torch.bfloat16) for h in (group * H, H, H))
+    out = torch.zeros((1, group * H, 128), dtype=torch.bfloat16, device="cuda")
+    launches, checked = 0, []
+    for t in range(1, steps + 1):
+        for layer in range(L):
+            launches += 1
+            eight = launches in (100, period + 100)
+            x = launches % 5
+            eng.set_target_blocks((8 if eight else 2) * H)
+            eng.decode_step(layer, t, q[x], kn[x], vn[x], out)
+            if eight:
+                k, v = eng.k_cache[layer, 0, :, :N + t].double(), eng.v_cache[layer, 0, :, :N + t].double()
+                p = torch.softmax(torch.matmul(k, q[x, 0].double().view(H, group, 128).transpose(1, 2).contiguous()) / np.sqrt(128.0), dim=1)
+                ref = torch.matmul(p.transpose(1, 2).contiguous(), v).view(group * H, 128)
+                checked.append(float(((out[0].double() - ref).norm(dim=1) / ref.norm(dim=1)).max()))
+    assert len(checked) == 2 and max(checked) < 2 * 2.0 ** -8, checked   # (two roundings to bf16, as above)
+    assert eng.stats()["last_step"] == [steps] * L
+    eng.close()

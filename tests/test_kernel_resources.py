@@ -1,5 +1,6 @@
-"""Resources of the built kernels as the compiler left them in the library's own code objects: none uses scratch memory
-(a kernel that spills a register sets scratch up at every launch: 4 us a decode call when it happened)."""
+"""What the compiler left in the library's own code objects about the built kernels: none uses scratch memory
+(a kernel that spills a register sets scratch up at every launch: 4 us a decode call when it happened), and the
+arguments lie where the kernels take them to be."""
 import os
 import struct
 
@@ -38,11 +39,26 @@ def _kernels(elf):
             p = desc + (desc_len + 3) // 4 * 4
 
 
-def test_no_kernel_uses_scratch_memory():
+def _built_kernels():
     if not os.path.exists(LIB):
         pytest.fail("the library is not built (python -m paper_2506_15969_amd.build)")
     with open(LIB, "rb") as f:
-        kernels = [k for obj in _code_objects(f.read()) for k in _kernels(obj)]
+        return [k for obj in _code_objects(f.read()) for k in _kernels(obj)]
+
+
+def test_argument_block_lies_where_the_decode_kernel_reads_it():
+    """The kernel reads its last argument, the block, at a fixed place among its arguments: 56 bytes in, behind five pointers, two
+    lengths and the shape."""
+    fused = [k for k in _built_kernels() if "decode_fused_kernel" in k[".name"]]
+    assert len(fused) > 20
+    for k in fused:
+        explicit = [x for x in k[".args"] if not x[".value_kind"].startswith("hidden_")]
+        assert [x[".offset"] for x in explicit] == [0, 8, 16, 24, 32, 40, 44, 48, 56], (k[".name"], explicit)
+        assert [x[".size"] for x in explicit[:8]] == [8] * 5 + [4] * 3 and explicit[8][".value_kind"] == "by_value", k[".name"]
+
+
+def test_no_kernel_uses_scratch_memory():
+    kernels = _built_kernels()
     fused = [k for k in kernels if "decode_fused_kernel" in k[".name"]]
     assert len(fused) > 20 and len(kernels) > len(fused)   # (the notes were found)
     bad = {k[".name"]: (k[".private_segment_fixed_size"], k.get(".vgpr_spill_count")) for k in kernels
