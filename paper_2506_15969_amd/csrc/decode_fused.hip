@@ -1577,28 +1577,27 @@ static int groups_of(int units, int n_sub, int n, bool f32, int head_dim) {
   return all ? n : whole;
 }
 
-// Blocks per unit.  Measured on 28 query / 4 KV heads of 128 x bf16, us per call, unless it says otherwise:
-//   * no more blocks than compute units: a second stream block on some of them holds up the whole
-//     launch (80 units x 2200 entries: 3 blocks per unit 17.4, 4 22.1; 48 units: 5 12.6, 6 16.6), and with
-//     two on all of them the bytes in flight only widen the spread of the blocks' ends (128 units x
-//     4144 entries: 44.5 with one, 46.4 with two).
-//   * only a long cache pays for the second hop that more than kMergeRadix blocks need (8 units x 2200
-//     entries: 8 blocks 6.9, 16 7.8, 32 7.4; x 6200 entries: 11.1, 10.5, 9.1), and then mostly in whole groups (see groups_of).
-//   * seven or eight blocks where they leave some compute units to the tracking (28 units x 1040 / 2060 / 4200
-//     entries: 6 blocks 7.25 / 9.52 / 14.6, 8 7.22 / 9.47 / 13.9); where they fill the chip to the last one, six up to some thousand
-//     entries (32 units x 1040 / 4100 / 6200: 6 blocks 7.1 / 15.0 / 20.1, 8 7.4 / 15.4 / 20.6; x 8200 / 12000 27.3 / 42.9, 8
-//     26.2 / 39.0; 36 units x 6200 / 12000: 6 22.9 / 47.0, 7 25.1 / 44.8). The other row types have more to do per byte, or fewer bytes per entry:
-//     eight from about 1800 entries on (32 units x 2060 / 4100, 6 / 8: 64 x bf16 8.43 / 8.24, 11.6 / 10.9; 64 x fp32
-//     11.6 / 11.1, 18.0 / 16.6; 128 x fp32 19.2 / 18.7, 30.4 / 29.3; x 1016 12.6 / 13.3).
-//   * two sub-tiles or more per wave (8 units x 600 entries: 4 blocks 6.0, 5 6.0; x 350: 2 5.3, 4 5.5),
-//     but two blocks from a unit's fifth sub-tile on.
-//   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to
-//     two per compute unit (96 units x 6200 entries: 2 blocks per unit 61.8, 5 58.1; 144 units: 1 98.9, 3 88.5;
-//     with 2200 entries still 20.1 against 23.6 and 33.1 against 31.1: from 32 sub-tiles per wave on).
-//     From 171 units on that would be two blocks, and one is the better at every length (1 / 2 blocks, 172 units
-//     x 600 12.6 / 14.8, x 2200 38.5 / 40.5, x 6200 115 / 119; 192 units 12.7 / 15.3, 39.9 / 42.1, 123 / 130; 240 units
-//     14.6 / 17.5, 48.7 / 50.7, 143 / 152), as it is for fp32 rows (192 units x 2200, 64 46.5 / 47.9, 128 84.2 / 89.1);
-//     so it is for bf16 rows of 64 (176 units x 2200 25.4 / 25.3).
+// Blocks per unit.  us per call, 7 query heads to a KV head, 128 x bf16 unless it says otherwise (one layer again and again):
+//   * no more blocks than compute units: a second stream block on some of them holds up the whole launch (80
+//     units x 2200 entries: 3 blocks per unit 15.6, 4 20.6; 48 units: 5 10.5, 6 14.2), and with two on all of them
+//     the bytes in flight only widen the spread of the blocks' ends (128 units x 4144: 49.8 with one, 50.9 with two).
+//   * only a long cache pays for the second hop that more than kMergeRadix blocks need (8 units x 2200: 8 blocks 6.8,
+//     16 7.8, 32 7.4; x 6200: 10.8, 10.2, 9.2), and then mostly in whole groups (see groups_of).
+//   * seven or eight blocks where they leave some compute units to the tracking (28 units x 1040 / 2060 / 4200:
+//     6 blocks 6.3 / 8.3 / 13.1, 8 6.4 / 8.1 / 12.6); where they fill the chip to the last one, six up to some
+//     thousand entries (32 units x 1040 / 4100 / 6200: 6 blocks 6.0 / 13.7 / 18.9, 8 6.2 / 13.5 / 19.5; x 8200 /
+//     12000 26.4 / 40.2, 8 25.1 / 37.6; 36 units x 6200 / 12000: 6 21.8 / 43.9, 7 23.2 / 42.5).  The other row types
+//     have more to do per byte, or fewer bytes per entry: eight from about 1800 entries on (32 units x 2060 / 4100,
+//     6 / 8: 64 x bf16 8.1 / 8.1, 11.2 / 10.7; 64 x fp32 11.0 / 10.5, 17.2 / 15.5; 128 x fp32 18.3 / 17.1, 29.0 /
+//     26.8; the line is from 128 x fp32 x 1016, 12.6 / 13.3 then; 11.6 / 10.7 now).
+//   * two sub-tiles or more per wave (8 units x 600: 4 blocks 5.2, 5 5.4; x 350: 2 5.0, 3 4.9, 4 4.8), but two blocks
+//     from a unit's fifth sub-tile on (x 70: 1 4.1, 2 3.8; x 136: 1 4.7, 2 4.3, 3 4.3).
+//   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to two per
+//     compute unit (96 units x 6200: 2 blocks per unit 60.6, 5 57.0; 144 units: 1 96.9, 3 90.2; x 2200 18.5 against
+//     22.3 and 32.6 against 30.1: from 32 sub-tiles per wave on).  From 171 units on that would be two blocks,
+//     and one is the better (1 / 2 blocks, 172 units x 600 11.1 / 12.7, x 2200 35.8 / 36.7, x 6200 110 / 117; 192
+//     units 11.2 / 12.9, 36.6 / 38.2, 118 / 125; 240 units 12.5 / 15.2, 44.8 / 44.5, 139 / 143), as it is for fp32 rows
+//     (192 units x 2200, 64 43.8 / 44.4, 128 79.3 / 84.9); bf16 rows of 64 would gain from two (176 units x 2200 24.3 / 22.5).
 int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   constexpr int kUnitsOfChip = 256;                // compute units of the chip that the figures above are from
   int n = kUnitsOfChip / units;
