@@ -51,8 +51,8 @@ __device__ __forceinline__ int longest_gap(unsigned set, int lo, int hi) {
   return 1 + longest_run<N>(~set & ((1u << hi) - (1u << lo)));
 }
 
-// Alg. 1 (first loop) and Eq. 1 for one entry and up to 32 calls of consecutive steps: bit s of `calls` says that it was active at
-// step t + s.
+// Alg. 1 (first loop) and Eq. 1 for one entry and up to 32 calls of consecutive steps: bit s of `calls` says that it
+// was active at step t + s.
 __device__ __forceinline__ void apply_calls(unsigned calls, int32_t t, int32_t &ts, int32_t &mri) {
   if (calls == 0) return;
   const int lo = __builtin_ctz(calls), hi = 31 - __builtin_clz(calls);

@@ -494,30 +494,30 @@ __device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, c
 }
 
 // ------------------------------------------------------------------- hand-over of partials
-// A block hands its partial over to a block of a higher index as a record of 64-bit words, each =
-// 16 bits of the launch's number, 16 bits of the maximum or the sum, 32 bits of an output value, written and read with 64-bit
-// device-scope atomics.  A word that shows this launch's number holds this launch's values, whatever else is still on its way,
-// so the writer neither waits for its stores nor signals, and the reader needs no second round
-// trip after a flag: it reads the words it needs until all of them carry the number.  Blocks are
-// started in index order and a block waits for blocks of lower indices only, so every wait ends;
-// it is bounded all the same (spin_ticks of the 100 MHz counter), after which the block raises the
-// workspace's fault word and goes on.
-// The number is an argument, so a captured call has the same one in every replay and would find the records
-// of the replay before complete: a call that is being captured has its records cleared by a launch
-// before it, and all captured calls have kSeqCaptured for their number, which no eager call has: an eager one would find
-// what a replay left complete as soon as the numbers had started over (see lazyev_decode_step).
-// A unit's blocks form groups of kMergeRadix; the last block of a group (its leader) merges the
-// group, and the unit's last block, a leader itself, merges what the other leaders hand over: one
-// hop for up to kMergeRadix blocks, two for up to kFusedSplitMax.  A hop is one memory round trip
-// whatever the number of records, because all of them are requested together.
+// A block hands its partial over to a block of a higher index as a record of 64-bit words, each = 16 bits of the
+// launch's number, 16 bits of the maximum or the sum, 32 bits of an output value, written and read with 64-bit
+// device-scope atomics.  A word that shows this launch's number holds this launch's values, whatever else is still on
+// its way, so the writer neither waits for its stores nor signals, and the reader needs no second round trip after a
+// flag: it reads the words it needs until all of them carry the number.  Blocks are started in index order and a
+// block waits for blocks of lower indices only, so every wait ends; it is bounded all the same (spin_ticks of the 100
+// MHz counter), after which the block raises the workspace's fault word and goes on.
+// The number is an argument, so a captured call has the same one in every replay and would find the records of the
+// replay before complete: a call that is being captured has its records cleared by a launch before it, and all
+// captured calls have kSeqCaptured for their number, which no eager call has: an eager one would find what a replay
+// left complete as soon as the numbers had started over (see lazyev_decode_step).
+// A unit's blocks form groups of kMergeRadix; the last block of a group (its leader) merges the group, and the unit's
+// last block, a leader itself, merges what the other leaders hand over: one hop for up to kMergeRadix blocks, two for
+// up to kFusedSplitMax.  A hop is one memory round trip whatever the number of records, because all of them are
+// requested together.
 // The numbers of eager calls run from 1 to kSeqMax; before they start over the records are cleared.
-// Record of a block: for each of the four waves four rows of 64 words; row i holds the output
-// element 4 t + i of thread t (one store instruction of a wave writes 512
-// contiguous bytes), and the 16 bits beside it are a half of the maximum (rows 0 and 1) or the sum of thread t's head (each thread its own
-// copy: what the reader needs of a head then never waits for another wave's store).  What a merge costs is the
-// instructions of single waves: with a word of its own, half of it the number, for each of the six values, a merge of seven
-// records was 42 loads and 42 comparisons, now 28 loads, 14 exclusive ors and 7 comparisons, and with one exponential per record instead of two that wait for
-// those before (see Merge) 8 units x 2081 entries take 2074 us for 256 calls instead of 2218, 32 x 1040 241 for 32 instead of 256.
+// Record of a block: for each of the four waves four rows of 64 words; row i holds the output element 4 t + i of
+// thread t (one store instruction of a wave writes 512 contiguous bytes), and the 16 bits beside it are a half of the
+// maximum (rows 0 and 1) or the sum of thread t's head (each thread its own copy: what the reader needs of a head
+// then never waits for another wave's store).  What a merge costs is the instructions of single waves: with a word of
+// its own, half of it the number, for each of the six values, a merge of seven records was 42 loads and 42
+// comparisons, now 28 loads, 14 exclusive ors and 7 comparisons, and with one exponential per record instead of two
+// that wait for those before (see Merge) 8 units x 2081 entries take 2074 us for 256 calls instead of 2218, 32 x 1040
+// 241 for 32 instead of 256.
 constexpr int kRecWords = 4 * kBlock;
 // thread t's first word, as a byte offset
 __device__ __forceinline__ unsigned rec_at(int t) { return (static_cast<unsigned>(t >> 6) * (4 * 64) + (t & 63)) * 8u; }
@@ -537,7 +537,8 @@ __device__ __forceinline__ void rec_store(unsigned long long *rec, int t_own, co
 }
 // What one thread reads of another block's record: its four output elements, its head's max and sum.
 struct RecPart { unsigned long long w[4]; };
-// (rec, the same for the whole wave, is kept a scalar: with the four addresses of every record in vector registers seven records spill)
+// (rec, the same for the whole wave, is kept a scalar: with the four addresses of every record in vector registers
+// seven records spill)
 __device__ __forceinline__ void rec_load(RecPart &r, const unsigned long long *rec, unsigned at) {
   auto base = (const __attribute__((address_space(1))) char *)rec;
   __asm__ volatile("" : "+s"(base));
@@ -610,11 +611,12 @@ __global__ __launch_bounds__(kBlock) void clear_records_kernel(unsigned long lon
 }
 
 // ------------------------------------------------------------------------------- the kernel
-// The kernel's arguments as they lie in memory.  The argument block `a` is read through args_from_here only: left to itself the
-// compiler fetches words of it at the top of the kernel for whichever path needs them, and a stream wave, whose first
-// loads need none of them, waited there for such a fetch (its registers were used again), 0.5 us in every call; the queries took
-// another round trip behind it.  us per pass, before and now (queries from the leading arguments, the block read
-// behind the first loads): 64 units x 1563 entries of 64 x bf16 1283 -> 1188, 8 units x 2081 2385 -> 2218, 128 x 2081 3128 -> 3066.
+// The kernel's arguments as they lie in memory.  The argument block `a` is read through args_from_here only: left to
+// itself the compiler fetches words of it at the top of the kernel for whichever path needs them, and a stream wave,
+// whose first loads need none of them, waited there for such a fetch (its registers were used again), 0.5 us in every
+// call; the queries took another round trip behind it.  us per pass, before and now (queries from the leading
+// arguments, the block read behind the first loads): 64 units x 1563 entries of 64 x bf16 1283 -> 1188, 8 units x
+// 2081 2385 -> 2218, 128 x 2081 3128 -> 3066.
 template <typename T>
 struct Kernarg {
   const T *k_cache, *v_cache, *k_new, *v_new, *q;
@@ -789,17 +791,19 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     return P >= 0 && tau >= 1;
   };
 
-  // Two ways to a sub-tile's rows.  kFlat: they lie one after the other in the cache, so a scalar address and one 32-bit offset
-  // per lane and load reach them, rows beyond the cache taken as its last one; the row to be appended is not there yet,
-  // and is put in place (K in the staging area, V by patch_v) when the unit's last sub-tile, which alone has it, is worked on.  Otherwise every load
-  // chooses the source of its row, 64 of the 230 vector instructions of a sub-tile.  Where the bytes set the time those cost
-  // nothing, and the replacement at the end of the run does: us per pass, chosen / flat, 128 units x 2081 3009 / 3029, x 4129 of 80 (2 blocks a unit) 5766 / 5816;
-  // with three blocks a unit or more, and for rows of 128 bytes, the latency of a sub-tile does: 8 units x 2081 1999 / 1950,
-  // 48 units x 1000 1273 / 1254, 64 units x 1563 of 64 x bf16 1160 / 1090.  (fp32 rows: the products are longer than either, 840 / 842.)
+  // Two ways to a sub-tile's rows.  kFlat: they lie one after the other in the cache, so a scalar address and one
+  // 32-bit offset per lane and load reach them, rows beyond the cache taken as its last one; the row to be appended
+  // is not there yet, and is put in place (K in the staging area, V by patch_v) when the unit's last sub-tile, which
+  // alone has it, is worked on.  Otherwise every load chooses the source of its row, 64 of the 230 vector
+  // instructions of a sub-tile.  Where the bytes set the time those cost nothing, and the replacement at the end of
+  // the run does: us per pass, chosen / flat, 128 units x 2081 3009 / 3029, x 4129 of 80 (2 blocks a unit) 5766 /
+  // 5816; with three blocks a unit or more, and for rows of 128 bytes, the latency of a sub-tile does: 8 units x 2081
+  // 1999 / 1950, 48 units x 1000 1273 / 1254, 64 units x 1563 of 64 x bf16 1160 / 1090.  (fp32 rows: the products are
+  // longer than either, 840 / 842.)
   constexpr bool kFlat = !R::kF32 && (kSplit >= 3 || R::kBytes == 128);
-  // ... Such a wave's first sub-tile does not depend on the unit's length but for the clamp of its rows, so with per-sequence timing the
-  // length is worked out while that travels (its rows clamped to the unit's capacity): 48 units x 1000, a pass of
-  // continuous_batch's shapes, 1240 -> 1225 us.
+  // ... Such a wave's first sub-tile does not depend on the unit's length but for the clamp of its rows, so with
+  // per-sequence timing the length is worked out while that travels (its rows clamped to the unit's capacity): 48
+  // units x 1000, a pass of continuous_batch's shapes, 1240 -> 1225 us.
   if (slots_on && !(kFlat && wave < kWaves))
     if (!own_length()) return;
 
@@ -999,7 +1003,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     }
   };
   // kFlat, the unit's last sub-tile: the lanes whose row is the appended one, or beyond it, get V from where the wave
-  // has kept it in LDS since its start (K: see compute).  kPrecise: rows beyond count as zero: zero times an infinite element is NaN.
+  // has kept it in LDS since its start (K: see compute).  kPrecise: rows beyond count as zero: zero times an infinite
+  // element is NaN.
   auto patch_v = [&](SubTile &t, int left) {
     const char *row = reinterpret_cast<const char *>(new_lds[wave]) + R::kBytes;
 #pragma unroll
@@ -1549,20 +1554,21 @@ uint32_t decode_fused_seq_max() { return kSeqMax; }
 uint32_t decode_fused_seq_captured() { return kSeqCaptured; }
 size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * sizeof(unsigned long long); }
 
-// Of n > kMergeRadix blocks per unit, all or the whole groups of kMergeRadix among them.  A last group that is not whole makes its
-// blocks wait for the leaders' merges all the same, and the blocks of a unit lie on more XCDs; what it saves are rounds, i.e. sub-tiles of
-// the longest-running waves.  us per call, whole groups / all blocks:
-//   * bf16 rows, where a round is short: 20 units x 4200 .. 8200 entries 8 / 12 blocks (128) 11.4 / 11.8 .. 18.4 / 18.4, (64) 10.3 / 11.0
-//     .. 14.8 / 14.2, 28 x 8200 8 / 9 22.5 / 26.8, (64) 15.4 / 19.5, 23 x 8200 8 / 11 19.8 / 23.4, (64) 14.9 / 17.2, 14 x 8200 16 / 18 14.6 /
-//     16.6; the other way for long caches, where idle compute units cost more: 18 x 12000 8 / 14 26.6 / 25.5, (64) 20.4 /
-//     18.6, 24 x 16400 8 / 10 43.8 / 42.7, (64) 28.4 / 27.4.
-//   * fp32 rows of 128, where it is long: fewer than four fifths of the rounds pay.  20 x 4200 / 8200 / 12000 8 / 12 23.7 / 21.7, 40.3 /
-//     34.5, 56.6 / 47.9; 24 x 8200 8 / 10 42.3 / 40.0; 11 x 8200 16 / 23 26.2 / 24.5; 7 x 4200 32 / 36 14.3 / 13.2; but 28 x 8200 8
-//     / 9 44.5 / 49.6, 14 x 8200 16 / 18 27.4 / 29.2.
-//   * fp32 rows of 64 lie between: 18 x 8200 8 / 14 23.1 / 21.7, 20 x 8200 8 / 12 23.4 / 20.7, but where the units are no multiple of four
-//     (see BlockPlace) 22 x 8200 8 / 11 23.9 / 25.7; 11 x 6200 16 / 23 14.2 / 13.3 (64 x bf16 11.3 / 11.1).
-// Where the cache's length bounds the blocks, whole groups above it: 4 units x 4800, 32 / 38 / 40 blocks 13.9 / 12.6 / 12.5 (fp32 128),
-// 10.4 / 9.7 / 9.5 (fp32 64), 9.1 / 9.2 / 8.9 (bf16 64), 8.5 / 8.2 / 8.1 (bf16 128).
+// Of n > kMergeRadix blocks per unit, all or the whole groups of kMergeRadix among them.  A last group that is not
+// whole makes its blocks wait for the leaders' merges all the same, and the blocks of a unit lie on more XCDs; what
+// it saves are rounds, i.e. sub-tiles of the longest-running waves.  us per call, whole groups / all blocks:
+//   * bf16 rows, where a round is short: 20 units x 4200 .. 8200 entries 8 / 12 blocks (128) 11.4 / 11.8 .. 18.4 /
+//     18.4, (64) 10.3 / 11.0 .. 14.8 / 14.2, 28 x 8200 8 / 9 22.5 / 26.8, (64) 15.4 / 19.5, 23 x 8200 8 / 11 19.8 /
+//     23.4, (64) 14.9 / 17.2, 14 x 8200 16 / 18 14.6 / 16.6; the other way for long caches, where idle compute units
+//     cost more: 18 x 12000 8 / 14 26.6 / 25.5, (64) 20.4 / 18.6, 24 x 16400 8 / 10 43.8 / 42.7, (64) 28.4 / 27.4.
+//   * fp32 rows of 128, where it is long: fewer than four fifths of the rounds pay.  20 x 4200 / 8200 / 12000 8 / 12
+//     23.7 / 21.7, 40.3 / 34.5, 56.6 / 47.9; 24 x 8200 8 / 10 42.3 / 40.0; 11 x 8200 16 / 23 26.2 / 24.5; 7 x 4200 32
+//     / 36 14.3 / 13.2; but 28 x 8200 8 / 9 44.5 / 49.6, 14 x 8200 16 / 18 27.4 / 29.2.
+//   * fp32 rows of 64 lie between: 18 x 8200 8 / 14 23.1 / 21.7, 20 x 8200 8 / 12 23.4 / 20.7, but where the units
+//     are no multiple of four (see BlockPlace) 22 x 8200 8 / 11 23.9 / 25.7; 11 x 6200 16 / 23 14.2 / 13.3 (64 x bf16
+//     11.3 / 11.1).
+// Where the cache's length bounds the blocks, whole groups above it: 4 units x 4800, 32 / 38 / 40 blocks 13.9 / 12.6
+// / 12.5 (fp32 128), 10.4 / 9.7 / 9.5 (fp32 64), 9.1 / 9.2 / 8.9 (bf16 64), 8.5 / 8.2 / 8.1 (bf16 128).
 static int groups_of(int units, int n_sub, int n, bool f32, int head_dim) {
   const int part = n % kMergeRadix, whole = n - part;
   if (part == 0) return n;
@@ -1577,27 +1583,29 @@ static int groups_of(int units, int n_sub, int n, bool f32, int head_dim) {
   return all ? n : whole;
 }
 
-// Blocks per unit.  us per call, 7 query heads to a KV head, 128 x bf16 unless it says otherwise (one layer again and again):
-//   * no more blocks than compute units: a second stream block on some of them holds up the whole launch (80
-//     units x 2200 entries: 3 blocks per unit 15.6, 4 20.6; 48 units: 5 10.5, 6 14.2), and with two on all of them
-//     the bytes in flight only widen the spread of the blocks' ends (128 units x 4144: 49.8 with one, 50.9 with two).
+// Blocks per unit.  us per call, 7 query heads to a KV head, 128 x bf16 unless it says otherwise (one layer again and
+// again):
+//   * no more blocks than compute units: a second stream block on some of them holds up the whole launch (80 units x
+//     2200 entries: 3 blocks per unit 15.6, 4 20.6; 48 units: 5 10.5, 6 14.2), and with two on all of them the bytes
+//     in flight only widen the spread of the blocks' ends (128 units x 4144: 49.8 with one, 50.9 with two).
 //   * only a long cache pays for the second hop that more than kMergeRadix blocks need (8 units x 2200: 8 blocks 6.8,
 //     16 7.8, 32 7.4; x 6200: 10.8, 10.2, 9.2), and then mostly in whole groups (see groups_of).
-//   * seven or eight blocks where they leave some compute units to the tracking (28 units x 1040 / 2060 / 4200:
-//     6 blocks 6.3 / 8.3 / 13.1, 8 6.4 / 8.1 / 12.6); where they fill the chip to the last one, six up to some
-//     thousand entries (32 units x 1040 / 4100 / 6200: 6 blocks 6.0 / 13.7 / 18.9, 8 6.2 / 13.5 / 19.5; x 8200 /
-//     12000 26.4 / 40.2, 8 25.1 / 37.6; 36 units x 6200 / 12000: 6 21.8 / 43.9, 7 23.2 / 42.5).  The other row types
-//     have more to do per byte, or fewer bytes per entry: eight from about 1800 entries on (32 units x 2060 / 4100,
-//     6 / 8: 64 x bf16 8.1 / 8.1, 11.2 / 10.7; 64 x fp32 11.0 / 10.5, 17.2 / 15.5; 128 x fp32 18.3 / 17.1, 29.0 /
-//     26.8; the line is from 128 x fp32 x 1016, 12.6 / 13.3 then; 11.6 / 10.7 now).
+//   * seven or eight blocks where they leave some compute units to the tracking (28 units x 1040 / 2060 / 4200: 6
+//     blocks 6.3 / 8.3 / 13.1, 8 6.4 / 8.1 / 12.6); where they fill the chip to the last one, six up to some thousand
+//     entries (32 units x 1040 / 4100 / 6200: 6 blocks 6.0 / 13.7 / 18.9, 8 6.2 / 13.5 / 19.5; x 8200 / 12000 26.4 /
+//     40.2, 8 25.1 / 37.6; 36 units x 6200 / 12000: 6 21.8 / 43.9, 7 23.2 / 42.5).  The other row types have more to
+//     do per byte, or fewer bytes per entry: eight from about 1800 entries on (32 units x 2060 / 4100, 6 / 8: 64 x
+//     bf16 8.1 / 8.1, 11.2 / 10.7; 64 x fp32 11.0 / 10.5, 17.2 / 15.5; 128 x fp32 18.3 / 17.1, 29.0 / 26.8; the line
+//     is from 128 x fp32 x 1016, 12.6 / 13.3 then; 11.6 / 10.7 now).
 //   * two sub-tiles or more per wave (8 units x 600: 4 blocks 5.2, 5 5.4; x 350: 2 5.0, 3 4.9, 4 4.8), but two blocks
 //     from a unit's fifth sub-tile on (x 70: 1 4.1, 2 3.8; x 136: 1 4.7, 2 4.3, 3 4.3).
 //   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to two per
 //     compute unit (96 units x 6200: 2 blocks per unit 60.6, 5 57.0; 144 units: 1 96.9, 3 90.2; x 2200 18.5 against
-//     22.3 and 32.6 against 30.1: from 32 sub-tiles per wave on).  From 171 units on that would be two blocks,
-//     and one is the better (1 / 2 blocks, 172 units x 600 11.1 / 12.7, x 2200 35.8 / 36.7, x 6200 110 / 117; 192
-//     units 11.2 / 12.9, 36.6 / 38.2, 118 / 125; 240 units 12.5 / 15.2, 44.8 / 44.5, 139 / 143), as it is for fp32 rows
-//     (192 units x 2200, 64 43.8 / 44.4, 128 79.3 / 84.9); bf16 rows of 64 would gain from two (176 units x 2200 24.3 / 22.5).
+//     22.3 and 32.6 against 30.1: from 32 sub-tiles per wave on).  From 171 units on that would be two blocks, and
+//     one is the better (1 / 2 blocks, 172 units x 600 11.1 / 12.7, x 2200 35.8 / 36.7, x 6200 110 / 117; 192 units
+//     11.2 / 12.9, 36.6 / 38.2, 118 / 125; 240 units 12.5 / 15.2, 44.8 / 44.5, 139 / 143), as it is for fp32 rows
+//     (192 units x 2200, 64 43.8 / 44.4, 128 79.3 / 84.9); bf16 rows of 64 would gain from two (176 units x 2200 24.3
+//     / 22.5).
 int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   constexpr int kUnitsOfChip = 256;                // compute units of the chip that the figures above are from
   int n = kUnitsOfChip / units;

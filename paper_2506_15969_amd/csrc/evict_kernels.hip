@@ -212,8 +212,8 @@ __device__ __forceinline__ unsigned wave_scan(unsigned v) {
   return v;
 }
 
-// The records of the last call before the eviction (Alg. 1, first loop): bits of the active entries.  Wave w takes the regions
-// w, w + 16, ... of the unit.
+// The records of the last call before the eviction (Alg. 1, first loop): bits of the active entries.  Wave w takes
+// the regions w, w + 16, ... of the unit.
 template <bool kPrecise>
 __device__ __forceinline__ unsigned last_call_bits(const TrackArgs &k, int unit, unsigned *active) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -249,8 +249,8 @@ __device__ __forceinline__ unsigned last_call_bits(const TrackArgs &k, int unit,
 }
 
 // Applies what is outstanding to the entries in registers, entry r * kSelBlock + tid in place r: the updates of
-// track_flush_kernel and track_kernel.  A wave has 64 entries in a row, two words of a call: lane (half, j) brings word `half` of call
-// s + j, and after a transposition across the 32 lanes holds the 32 calls of entry 32 half + j.
+// track_flush_kernel and track_kernel.  A wave has 64 entries in a row, two words of a call: lane (half, j) brings
+// word `half` of call s + j, and after a transposition across the 32 lanes holds the 32 calls of entry 32 half + j.
 template <int R>
 __device__ __forceinline__ void apply_outstanding(const EvictArgs &a, int unit, int32_t (&v_ts)[R], int32_t (&v_mri)[R], int32_t (&v_pos)[R],
                                                   unsigned *active, unsigned *n_active) {
@@ -315,20 +315,21 @@ __device__ __forceinline__ void apply_outstanding(const EvictArgs &a, int unit, 
   }
 }
 
-// The selection for units of at most R * kSelBlock entries.  One block per unit, so what bounds it is the chain of its
-// steps (and the scores, at 4096 entries): memory is read once, at the start (TS, MRI and pos stay in registers, R
-// entries per thread), the keys lie in registers, every wave finds the threshold's digit for itself, and the
+// The selection for units of at most R * kSelBlock entries.  One block per unit, so what bounds it is the chain of
+// its steps (and the scores, at 4096 entries): memory is read once, at the start (TS, MRI and pos stay in registers,
+// R entries per thread), the keys lie in registers, every wave finds the threshold's digit for itself, and the
 // destinations of all entries come from one exchange of counts.  us, before (keys in LDS, shuffles of 16 waves
 // queueing up at it for ANDs, ORs and scans, a pass over TS / MRI / pos per 1024 entries at the end, as
-// evict_select_kernel still has it) and now: 144 entries 9.2 -> 5.3, 1056 15.6 -> 7.2, 2112 17.5 -> 10.0, 256 units of 4160
-// 29.6 -> 17.1.
-// The first digit is 0 for the score 0 (the usual threshold: the entries that were never re-activated) and the
-// score in steps of 1 / 126 from 1 on (scores lie in 0 .. 2, weights in 0 .. 1), which tells keys apart better than their
+// evict_select_kernel still has it) and now: 144 entries 9.2 -> 5.3, 1056 15.6 -> 7.2, 2112 17.5 -> 10.0, 256 units
+// of 4160 29.6 -> 17.1.
+// The first digit is 0 for the score 0 (the usual threshold: the entries that were never re-activated) and the score
+// in steps of 1 / 126 from 1 on (scores lie in 0 .. 2, weights in 0 .. 1), which tells keys apart better than their
 // leading byte: mostly one pass ends at the zeros or leaves at most kSmallSet keys.  The following digits are the
 // bytes, the highest first, of the keys still in play.
-// kTodo: tracking is outstanding (a.todo).  Evictions without, those of many units among them, have an instance of their
-// own, as the registers of the other leave room for fewer blocks on a compute unit (3 entries per thread: 68 instead of 56): us,
-// tracking and row move included, one instance for both / this one, 2048 units of 432 entries 178 / 166, 3584 302 / 283.
+// kTodo: tracking is outstanding (a.todo).  Evictions without, those of many units among them, have an instance of
+// their own, as the registers of the other leave room for fewer blocks on a compute unit (3 entries per thread: 68
+// instead of 56): us, tracking and row move included, one instance for both / this one, 2048 units of 432 entries
+// 178 / 166, 3584 302 / 283.
 template <int R, bool kTodo>
 __global__ __launch_bounds__(kSelBlock) void evict_select_held_kernel(const EvictArgs a) {
   extern __shared__ unsigned long long keys_lds[];      // score bit pattern of each candidate
@@ -774,13 +775,14 @@ __global__ __launch_bounds__(kMoveBlock) void evict_move_kernel(const EvictArgs 
 }  // namespace
 
 int evict_lds_candidates() { return kLdsCandidates; }
-// Up to 3 entries per thread, and up to 5 from 32 units on.  One block applies all that is outstanding for its unit, a launch
-// of its own spreads a unit over several: with more entries the chain of the one block takes longer than the launches it
-// saves.  us for an eviction of 64 calls' tracking, launches of their own / in the selection: 4 units x 1064 22 / 19, x 2564 30 / 28,
-// x 4264 36.7 / 39.6, x 5264 46 / 52, x 8064 65 / 75; 32 units x 2564 40.2 / 36.6, x 4264 57.0 / 55.2, x 5264 69.5 / 71.5, x 8064
-// 89.5 / 94.3; 128 units x 4264 136 / 133, x 5264 164 / 166, x 8064 232 / 236; 256 units x 8064 418 / 415.
-// Of more units than the chip holds selection blocks at once (two per compute unit) the chain is what
-// the launch waits for again and again: 512 units of 432 entries 55 / 52, of 1152 118 / 113, of 2112 221 / 214; 768 73.3 / 72.4, 167 /
+// Up to 3 entries per thread, and up to 5 from 32 units on.  One block applies all that is outstanding for its unit,
+// a launch of its own spreads a unit over several: with more entries the chain of the one block takes longer than the
+// launches it saves.  us for an eviction of 64 calls' tracking, launches of their own / in the selection: 4 units x
+// 1064 22 / 19, x 2564 30 / 28, x 4264 36.7 / 39.6, x 5264 46 / 52, x 8064 65 / 75; 32 units x 2564 40.2 / 36.6, x
+// 4264 57.0 / 55.2, x 5264 69.5 / 71.5, x 8064 89.5 / 94.3; 128 units x 4264 136 / 133, x 5264 164 / 166, x 8064 232
+// / 236; 256 units x 8064 418 / 415.
+// Of more units than the chip holds selection blocks at once (two per compute unit) the chain is what the launch waits
+// for again and again: 512 units of 432 / 1152 / 2112 entries 55 / 52, 118 / 113, 221 / 214; 768 73.3 / 72.4, 167 /
 // 162, 323 / 314; 1024 91.9 / 93.3, 216 / 211, 423 / 411; 2048 165 / 178, 402 / 410, 818 / 813; 3584 of 432 281 / 301.
 bool evict_applies_tracking(int n, int units) {
   return (n <= 3 * kSelBlock || (n <= 5 * kSelBlock && units >= 32)) && units <= 512;
@@ -815,8 +817,8 @@ hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) 
     n_blocks = a.units / a.units_per_layer * a.n_due * a.n_kv_heads;
   }
   if (ev) (void)hipEventRecord(ev[0], stream);
-  // as few entries per thread as hold the unit (an instance of 8 for all: 1056 entries 12.4 instead of 7.2 us, 2112 13.0 instead of 10.0); beyond 8 and
-  // its 64 KB of keys the passes go over memory
+  // as few entries per thread as hold the unit (an instance of 8 for all: 1056 entries 12.4 instead of 7.2 us, 2112
+  // 13.0 instead of 10.0); beyond 8 and its 64 KB of keys the passes go over memory
 #define LAZYEV_SELECT(R) \
   do { \
     if (a.todo.on) hipLaunchKernelGGL((evict_select_held_kernel<R, true>), dim3(n_blocks), dim3(kSelBlock), lds, stream, a); \
@@ -836,10 +838,10 @@ hipError_t launch_evict(const EvictArgs &a, hipStream_t stream, hipEvent_t *ev) 
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[1], stream);
   const int row_bytes = a.head_dim * (a.dtype == 0 ? 4 : 2);
-  // Parts of 256 bytes where their blocks come to three quarters of the chip's compute units, else parts of 128 bytes and twice the
-  // blocks.  us, 256 / 128: 8 units x 4096 rows of 256 bytes 33.9 / 21.0, 48 x 1024 16.5 / 12.3, 64 x 2048 28.7 / 24.9, 96 x 2048 (192
-  // blocks) 43.0 / 41.8; 48 x 1024 rows of 512 bytes (192 blocks) 18.8 / 21.0.  (Parts of 64 bytes: 4 units x 144 2.4, as with 128;
-  // 32 x 1024 11.2 / 10.3.)
+  // Parts of 256 bytes where their blocks come to three quarters of the chip's compute units, else parts of 128 bytes
+  // and twice the blocks.  us, 256 / 128: 8 units x 4096 rows of 256 bytes 33.9 / 21.0, 48 x 1024 16.5 / 12.3, 64 x
+  // 2048 28.7 / 24.9, 96 x 2048 (192 blocks) 43.0 / 41.8; 48 x 1024 rows of 512 bytes (192 blocks) 18.8 / 21.0.
+  // (Parts of 64 bytes: 4 units x 144 2.4, as with 128; 32 x 1024 11.2 / 10.3.)
   if (row_bytes % 256 == 0 && 2 * n_blocks * (row_bytes / 256) >= 192) {
     hipLaunchKernelGGL((evict_move_kernel<8, 16>), dim3(row_bytes / 256, 2, n_blocks), dim3(kMoveBlock),
                        0, stream, a, row_bytes);

@@ -75,8 +75,8 @@ struct Rows {
   // from, b = -(m + log2 l) / c2 (c2 = scale log2 e, m = r c2).
   static constexpr bool kApart = !(sizeof(T) == 2 && D == 128);
   static constexpr int kTiles = kK == 8 ? 2 : 4;   // tiles a wave keeps in registers where there is work for all
-  // waves per SIMD the registers are held to: in the second kernel, and in the first (128 x bf16: 128 registers just suffice for
-  // four; three 1086, four 1070 us for both kernels, 128 units x 2048 positions)
+  // waves per SIMD the registers are held to: in the second kernel, and in the first (128 x bf16: 128 registers just
+  // suffice for four; three 1086, four 1070 us for both kernels, 128 units x 2048 positions)
   static constexpr int waves(int nb) { return nb == 1 ? 4 : kF32 ? 2 : 3; }
   static constexpr int stats_waves(int nb) { return nb == 1 || !kF32 ? 4 : 2; }
 };
@@ -177,15 +177,14 @@ __device__ __forceinline__ float rounded_product(float x, float c2) {
 // first make signalling NaNs quiet)
 __device__ __forceinline__ float max_f32(float a, float b) { return __builtin_fmaxf(a, b); }
 
-// One key tile against the wave's NB query tiles in the statistics kernel.  Logits are kept in units of
-// log 2 (scaled by c2 = scale * log2(e)), so a weight is one multiply-add and one v_exp_f32.  Every lane sums
-// ITS four key rows of every tile (the four lanes of a query column are merged once, at the end): no
-// cross-lane traffic inside the loop.  The reference m of a query need not be its maximum: a
-// floating-point sum is as exact relative to any reference within the range of the exponent, so there is no
-// running maximum, only a look whether the weights leave the range (first: there is no reference
-// yet; where all logits of the first tile are -inf it is the lowest finite number, and the first other logit
-// raises it).  limit: kFar, or, once some reference of the wave is beyond kHuge, a number that every sum exceeds.  mask: the tile may hold keys newer than a query or
-// positions beyond the prompt.
+// One key tile against the wave's NB query tiles in the statistics kernel.  Logits are kept in units of log 2 (scaled
+// by c2 = scale * log2(e)), so a weight is one multiply-add and one v_exp_f32.  Every lane sums ITS four key rows of
+// every tile (the four lanes of a query column are merged once, at the end): no cross-lane traffic inside the loop.
+// The reference m of a query need not be its maximum: a floating-point sum is as exact relative to any reference
+// within the range of the exponent, so there is no running maximum, only a look whether the weights leave the range
+// (first: there is no reference yet; where all logits of the first tile are -inf it is the lowest finite number, and
+// the first other logit raises it).  limit: kFar, or, once some reference of the wave is beyond kHuge, a number that
+// every sum exceeds.  mask: the tile may hold keys newer than a query or positions beyond the prompt.
 template <typename T, int D, int NB, bool kFirst>
 __device__ __forceinline__ void stats_tiles(bool mask, const u32x4_t (&ka)[Rows<T, D>::kK], const u32x4_t (&qb)[NB][Rows<T, D>::kK],
                                             float c2, int key0, int query0, int P, float (&r)[NB], float (&m)[NB], float (&l)[NB], float &limit) {
@@ -572,8 +571,9 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
               }
             }
           } else {
-            // (masked in place and then one maximum for both: with a maximum on either way the 16 of them are copied around every
-            // stage, 1105 instead of 1040 us for 128 units x 2048 positions; with the products' differences above it is the other way, 31.8 / 30.6)
+            // (masked in place and then one maximum for both: with a maximum on either way the 16 of them are copied
+            // around every stage, 1105 instead of 1040 us for 128 units x 2048 positions; with the products'
+            // differences above it is the other way, 31.8 / 30.6)
             float lw[4 * NB];
 #pragma unroll
             for (int n = 0; n < NB; ++n)
@@ -634,9 +634,10 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
       __syncthreads();                             // the next stage is complete, this one no longer read
     };
     settle(ka);
-    // Whole rounds (see settle); a stage too many works on nothing.  Narrow blocks of 128-byte rows end in the middle of one: their
-    // stages are two tiles each and few (us, whole rounds / this, 64 x bf16, 28 / 4 heads x 20 / 33 / 100 positions 11.0 / 10.8, 13.5 /
-    // 13.2, 17.6 / 17.4; 16 sequences x 20 / 33 11.5 / 11.3, 14.0 / 13.7; the same from 180 positions on).
+    // Whole rounds (see settle); a stage too many works on nothing.  Narrow blocks of 128-byte rows end in the middle
+    // of one: their stages are two tiles each and few (us, whole rounds / this, 64 x bf16, 28 / 4 heads x 20 / 33 /
+    // 100 positions 11.0 / 10.8, 13.5 / 13.2, 17.6 / 17.4; 16 sequences x 20 / 33 11.5 / 11.3, 14.0 / 13.7; the same
+    // from 180 positions on).
     do {
       stage(std::integral_constant<int, 0>{});
       if (NB == 1 && R::kStage == 2 && it >= it_end) break;
