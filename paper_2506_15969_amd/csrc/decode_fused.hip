@@ -20,12 +20,10 @@
 // What follows the stream is serial code of single waves, where instructions, not bytes, set
 // the time: no branches where a select does, addresses worked out beforehand.
 //
-// Partials of a unit.  One block: its partial is the result.  More (decode_fused_split): a block hands
-// its partial to the last block of its group of up to eight as a record of stamped 64-bit words, the
-// groups' last blocks hand theirs to the unit's last block, which finishes the unit (see
-// "hand-over" below): no acknowledgement is waited for, nothing is signalled, one memory round trip
-// a hop.  (Until this replaced a ticket counter for more than four blocks, whose holder loaded four
-// partials per round trip: 8 units x 2112 entries 14.8 -> 8.6 us per call, 32 x 1056 9.1 -> 6.9, with block_place.)
+// Partials of a unit.  One block: its partial is the result.  More (decode_fused_split): they are handed over as records of
+// stamped 64-bit words (see "hand-over" below): no acknowledgement is waited for, nothing is signalled, one memory
+// round trip.  Up to eight blocks: the unit's last one merges the others' records with its own partial.  More: blocks
+// of their own behind the stream blocks do (merge_columns), so that few units can have the whole chip.
 // The partials are merged in an order that depends on the split alone, and the finishing block
 // leaves the unit's softmax statistics (max, 1 / sum per head) for the tracking.
 //
@@ -106,7 +104,8 @@ __device__ __forceinline__ BlockPlace block_place(int b, int n_split, int units)
     return {b - first, split};
   }
   if (n_split == 1) return {b, 0};
-  return {b % units, b / units};
+  const int split = wave_div(b, units);
+  return {b - split * units, split};
 }
 
 #ifdef LAZYEV_TIMELINE
@@ -159,6 +158,13 @@ __device__ __forceinline__ float max_over_lane_groups(float x) {
   r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+
+// The same over the eight lanes c, c + 8, ..., c + 56 (a rotation of 8 within the rows of 16 lanes comes first).
+__device__ __forceinline__ float lane_8_on(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float sum_over_eight(float x) { return sum_over_lane_groups(x + lane_8_on(x)); }
+__device__ __forceinline__ float max_over_eight(float x) { return max_over_lane_groups(fmaxf(x, lane_8_on(x))); }
 
 // What the kernel needs to know of a row type: bf16 or fp32, 64 or 128 elements.
 template <typename T, int D>
@@ -505,11 +511,12 @@ __device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, c
 // replay before complete: a call that is being captured has its records cleared by a launch before it, and all
 // captured calls have kSeqCaptured for their number, which no eager call has: an eager one would find what a replay
 // left complete as soon as the numbers had started over (see lazyev_decode_step).
-// A unit's blocks form groups of kMergeRadix; the last block of a group (its leader) merges the group, and the unit's
-// last block, a leader itself, merges what the other leaders hand over: one hop for up to kMergeRadix blocks, two for
-// up to kFusedSplitMax.  A hop is one memory round trip whatever the number of records, because all of them are
-// requested together.
-// The numbers of eager calls run from 1 to kSeqMax; before they start over the records are cleared.
+// One hop for any number of blocks: up to kPairMax, the unit's last block merges what the others hand over; of more, all
+// hand over and blocks behind the stream blocks merge (merge_columns).  (Before, the last of every eight blocks merged
+// those and handed over in turn: the second hop took 1.5 us, and seven records are 28 loads for every thread of the one
+// block that merges.  us per call, 8 units x 2080 entries 6.65 (8 blocks) -> 5.4 (32), 4 x 3000 7.8 (8) -> 5.5 (32), 16 x
+// 4000 10.8 (8) -> 8.7 (16), 2 units of 128 x bf16 x 12000 9.7 (64) -> 8.3 (64), 8 x 2080 of 128 x fp32 15.4 (8) -> 8.0
+// (32); 220 random shapes of 1 .. 60 units x 130 .. 24000 entries 0.93 of the time.)
 // Record of a block: for each of the four waves four rows of 64 words; row i holds the output element 4 t + i of
 // thread t (one store instruction of a wave writes 512 contiguous bytes), and the 16 bits beside it are a half of the
 // maximum (rows 0 and 1) or the sum of thread t's head (each thread its own copy: what the reader needs of a head
@@ -521,7 +528,7 @@ __device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, c
 constexpr int kRecWords = 4 * kBlock;
 // thread t's first word, as a byte offset
 __device__ __forceinline__ unsigned rec_at(int t) { return (static_cast<unsigned>(t >> 6) * (4 * 64) + (t & 63)) * 8u; }
-constexpr int kMergeRadix = 8;
+constexpr int kPairMax = 8;             // blocks of a unit whose last one finishes it
 constexpr uint32_t kSeqMax = 0xFFFE, kSeqCaptured = 0xFFFF;
 
 __device__ __forceinline__ void rec_word_store(unsigned long long *p, float v, unsigned top) {
@@ -674,6 +681,92 @@ __device__ __forceinline__ int shape_units(unsigned s) { return static_cast<int>
 __device__ __forceinline__ int shape_split(unsigned s) { return static_cast<int>((s >> 16) & 127u); }
 __device__ __forceinline__ int shape_group(unsigned s) { return static_cast<int>((s >> 23) & 7u) + 1; }
 __device__ __forceinline__ bool shape_slots(unsigned s) { return (s >> 26) & 1u; }
+// Does the sequence of a unit take this step?  (per-sequence timing)
+__device__ __forceinline__ bool takes_part(const DecodeArgs &a, int unit) {
+  const int seq = unit / a.n_kv_heads;
+  return a.slots.prompt_len[seq] >= 0 && a.t - a.slots.t0[seq] >= 1;
+}
+// Waves of a block that merge, each 32 output elements, and blocks of them per unit.  What a wave reads, 256 bytes of every
+// record, passes through its compute unit's L1 at 64 bytes a cycle: with eight waves a block 32 records a unit took 0.2 us
+// more (8 units x 2080: 5.67 / 5.50), 16 records 0.3.
+__host__ __device__ constexpr int merge_waves(int n_split) { return n_split <= 16 ? 4 : 2; }
+template <int D>
+__host__ __device__ constexpr int merge_blocks(int group, int waves) { return (group * (D / 32) + waves - 1) / waves; }
+// The output elements 32 columns .. + 31 of a unit of n blocks (kPairMax < n <= 8 N), merged by one wave: lane (c, g)
+// reads the elements 4 c .. 4 c + 3 of the records g, g + 8, ..., and the eight lanes of a column merge across the wave,
+// with no LDS and no barrier.  What bounds it is the chain partial stored - seen - loaded - stored, 1.4 us from the last
+// block's end to the launch's.  First one word of every record is looked at, until half of them are there: blocks of
+// equal work end close together, and a look at all words of 32 records is 16 loads that hold up the ones that will find them
+// (from the first record on: 8 units x 2080 5.96 / 5.92, 4 x 3000 6.46 / 6.03; only when all are there 6.5 / 6.7).
+// Before that the wave sleeps for what a run of sub-tiles takes at least, 0.5 us each (128-byte rows 0.25) from the third on: the
+// looks go to memory, where they are in the stream's way (16 units x 24000 39.6 -> 38.8).
+// It waits for blocks of lower indices only, like any reader of records, but for as long as a whole run takes: until the
+// first records are there the limit is 64 times the one for the others.
+template <typename T, int D, int N, typename Args>
+__device__ __forceinline__ void merge_columns(const Args &a, int unit, int G, int n, int run, int columns) {
+  constexpr bool kPrecise = Rows<T, D>::kPrecise;
+  const int lane = static_cast<int>(threadIdx.x) & 63, c = lane & 7, g = lane >> 3;
+  const int t_own = columns * 8 + c;
+  const unsigned long long *recs = a.part_rec + static_cast<size_t>(unit) * a.rec_per_unit * kRecWords;
+  const unsigned long long t_start = wall_clock64();
+  const unsigned quiet = run > 2 ? static_cast<unsigned>(run - 2) * (Rows<T, D>::kBytes >= 256 ? 50 : 25) : 0u;
+  while (wall_clock64() - t_start < quiet) __builtin_amdgcn_s_sleep(4);
+  unsigned long long t_first = 0;
+  {
+    auto base = (const __attribute__((address_space(1))) char *)recs;
+    __asm__ volatile("" : "+s"(base));
+    const unsigned at = static_cast<unsigned>(min(lane, n - 1)) * (kRecWords * 8) + rec_at(columns * 8);
+    for (;;) {
+      const unsigned long long w = __hip_atomic_load((const __attribute__((address_space(1))) unsigned long long *)(base + at),
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__popcll(__builtin_amdgcn_ballot_w64(lane < n && static_cast<unsigned>(w >> 48) == a.seq)) >= n - n / 2) break;
+      const unsigned long long now = wall_clock64();
+      if (t_first == 0) t_first = now;
+      if (now - t_first >= 64ull * a.spin_ticks) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  STAMP(2);
+  t_first = 0;
+  RecPart r[N];
+  for (;;) {
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      rec_load(r[j], recs, rec_at(t_own) + static_cast<unsigned>(min(8 * j + g, n - 1)) * (kRecWords * 8));
+    bool ok = true;
+#pragma unroll
+    for (int j = 0; j < N; ++j) ok = ok & rec_valid(r[j], a.seq);
+    if (__builtin_amdgcn_ballot_w64(!ok) == 0) break;
+    const unsigned long long now = wall_clock64();
+    if (t_first == 0) t_first = now;
+    if (now - t_first >= a.spin_ticks) {
+      atomicOr(a.fault, 1);
+      break;
+    }
+  }
+  STAMP(3);
+  Merge<kPrecise> mg;
+  float m = rec_max(r[0]);
+#pragma unroll
+  for (int j = 1; j < N; ++j) m = fmaxf(m, rec_max(r[j]));
+  mg.m = max_over_eight(m);
+  float l = 0.f;
+  f32x4_t o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+#pragma clang fp contract(off)
+    const bool mine = 8 * j + g < n;
+    const float f = exp_of<kPrecise>(rec_max(r[j]) - mg.m);
+    const f32x4_t x = rec_values(r[j]);
+    l = fmaf(mine ? rec_sum(r[j]) : 0.f, f, l);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = fmaf(mine ? x[i] : 0.f, f, o[i]);
+  }
+  mg.l = sum_over_eight(l);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) mg.o[i] = sum_over_eight(o[i]);
+  if (g == 0) write_unit_row<T, D>(a, unit, G, mg, 4 * t_own, 4 * t_own / D);
+}
 // kCompact: this call leaves candidate lists instead of every logit.
 // The leading scalar arguments repeat what a stream wave needs to request its queries and first sub-tile
 // (the same values are in `a`): scalar kernel arguments are handed to a wave in registers at its
@@ -690,9 +783,11 @@ __device__ __forceinline__ bool shape_slots(unsigned s) { return (s >> 26) & 1u;
 // tracking block per compute unit: these instances keep to 128 registers per lane); a launch of
 // more blocks, and fp32 rows of 128 elements (up to 230 registers), run four-wave blocks whose
 // stream waves build their own lists.
+// Launches with merging blocks have none either: their lists are built while the records travel (with list waves 20 units
+// x 10500 of 64 x bf16 18.6 us, 13.7 without).
 // kSplit > 0: the instance is for units of exactly kSplit blocks (1 .. 8, with list waves).  What
 // precedes and follows the stream is serial code of single waves, and a split known at compile time takes the
-// second hop, the loads of a variable number of records and the divisions by the split out of it
+// loads of a variable number of records and the divisions by the split out of it
 // (us per call with an instance of its own / with the one for any split: 32 units x 600 entries, 3 blocks 6.4
 // / 7.7, 4 6.3 / 7.2, 6 6.5 / 7.0).
 template <typename T, int D, bool kCompact, bool kLong = false, bool kListWaves = false, int kSplit = 0>
@@ -718,12 +813,16 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
 #ifdef LAZYEV_TIMELINE
   STAMPV(6, xcc_id());
 #endif
-  if (static_cast<int>(blockIdx.x) >= n_split * units_call) {
+  const int n_stream = n_split * units_call;
+  const bool merged = kSplit == 0 && n_split > kPairMax;   // a unit's partials are merged by blocks of their own
+  const int per_merge = merge_waves(n_split);
+  const int n_merge = merged ? merge_blocks<D>(G, per_merge) * units_call : 0;
+  if (static_cast<int>(blockIdx.x) >= n_stream + n_merge) {
     // tracking of the previous call: n_split blocks per unit, spread over the compute units
     // like the stream blocks
     if (kListWaves && threadIdx.x >= kBlock) return;  // (the tracking has no use for list waves)
     const DecodeArgs &a = args_from_here<T>();
-    const int tb = blockIdx.x - n_split * units_call;
+    const int tb = blockIdx.x - n_stream - n_merge;
     const int n_track = a.n_track;
     const BlockPlace at = block_place<kSplit>(tb, n_track, units_call);
     const int unit = at.unit, part = at.split;
@@ -770,6 +869,22 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // wave-uniform: scalar branches below
+  if (merged && static_cast<int>(blockIdx.x) >= n_stream) {
+    const BlockPlace at = block_place<0>(blockIdx.x - n_stream, 2, units_call);
+    const int columns = at.split * per_merge + wave;
+    if (wave >= per_merge || columns >= G * (D / 32)) return;
+    if (slots_on && !takes_part(args_from_here<T>(), at.unit)) return;
+    CallArgs<T> a;
+    a.read();
+    const int run = fused_wave_run((n_old_call + 16) >> 4, n_split);
+    STAMP(1);
+    if (n_split <= 8) merge_columns<T, D, 1>(a, at.unit, G, n_split, run, columns);
+    else if (n_split <= 16) merge_columns<T, D, 2>(a, at.unit, G, n_split, run, columns);
+    else if (n_split <= 32) merge_columns<T, D, 4>(a, at.unit, G, n_split, run, columns);
+    else merge_columns<T, D, 8>(a, at.unit, G, n_split, run, columns);
+    STAMP(5);
+    return;
+  }
   if (kCompact && tid == 0) cand_total = 0;        // (the block barrier after the stream orders it)
   if constexpr (kLong) {                           // (here the waves add to it while they stream)
     if (tid < kWaves * kHeadPad) run_lse[tid / kHeadPad][tid % kHeadPad] = -INFINITY;   // nothing seen yet
@@ -799,8 +914,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   // the run does: us per pass, chosen / flat, 128 units x 2081 3009 / 3029, x 4129 of 80 (2 blocks a unit) 5766 /
   // 5816; with three blocks a unit or more, and for rows of 128 bytes, the latency of a sub-tile does: 8 units x 2081
   // 1999 / 1950, 48 units x 1000 1273 / 1254, 64 units x 1563 of 64 x bf16 1160 / 1090.  (fp32 rows: the products are
-  // longer than either, 840 / 842.)
-  constexpr bool kFlat = !R::kF32 && (kSplit >= 3 || R::kBytes == 128);
+  // longer than either, 840 / 842.  The instances for any split with long runs or all logits have no registers left for it.)
+  constexpr bool kFlat = !R::kF32 && ((kSplit == 0 && kCompact && !kLong) || kSplit >= 3 || R::kBytes == 128);
   // ... Such a wave's first sub-tile does not depend on the unit's length but for the clamp of its rows, so with
   // per-sequence timing the length is worked out while that travels (its rows clamped to the unit's capacity): 48
   // units x 1000, a pass of continuous_batch's shapes, 1240 -> 1225 us.
@@ -1412,12 +1527,10 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     for (int i = 0; i < 4; ++i) v_own[i] = fmaf(f, x[i], v_own[i]);
     l_own = fmaf(f, lsum_lds[w][h_own], l_own);
   }
-  const bool finisher = split == n_split - 1;      // the unit's last block
-  const int group0 = split / kMergeRadix * kMergeRadix;   // the blocks group0 .. of this block's group
-  const bool leader = finisher || split - group0 == kMergeRadix - 1;
+  const bool finisher = !merged && split == n_split - 1;      // the unit's last block
   const int t_own = ec >> 2;                       // (threads beyond the group's rows read a valid place)
   unsigned long long *recs = a.part_rec + static_cast<size_t>(unit) * a.rec_per_unit * kRecWords;
-  if (!leader && e0 < G * D) rec_store(recs + static_cast<size_t>(split) * kRecWords, tid, v_own, mb_own, l_own, a.seq);
+  if (!finisher && e0 < G * D) rec_store(recs + static_cast<size_t>(split) * kRecWords, tid, v_own, mb_own, l_own, a.seq);
   // what only the NEXT launch needs, while the partial travels: the appended row and this wave's
   // candidate list (list waves, where the block has them, do both meanwhile)
   if constexpr (!kListWaves) {
@@ -1428,25 +1541,12 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
       run_scan(sp);
     }
   }
-  if (leader) {
-    constexpr int kIn = kSplit > 1 ? kSplit - 1 : kMergeRadix - 1;   // (instances of a fixed split have one group)
-    const int n_in = kSplit > 0 ? kSplit - 1 : split - group0;
-    const Merge<kPrecise> mg = merge_records<kIn, kPrecise>(a, recs + static_cast<size_t>(group0) * kRecWords, kRecWords, n_in, t_own,
-                                        mb_own, l_own, v_own);
-    const f32x4_t o4 = {mg.o[0], mg.o[1], mg.o[2], mg.o[3]};
-    if (kSplit > 0 || n_split <= kMergeRadix) {
-      STAMP(4);
-      write_unit_row<T, D>(a, unit, G, mg, e0, h_own);
-    } else if (!finisher) {
-      if (e0 < G * D) rec_store(recs + static_cast<size_t>(split) * kRecWords, tid, o4, mg.m, mg.l, a.seq);
-    } else {
-      // the other leaders' records (blocks kMergeRadix - 1, 2 kMergeRadix - 1, ...)
-      const Merge<kPrecise> all = merge_records<kFusedSplitMax / kMergeRadix - 1, kPrecise>(
-          a, recs + static_cast<size_t>(kMergeRadix - 1) * kRecWords, kMergeRadix * kRecWords, group0 / kMergeRadix, t_own,
-          mg.m, mg.l, o4);
-      STAMP(4);
-      write_unit_row<T, D>(a, unit, G, all, e0, h_own);
-    }
+  if (finisher) {
+    constexpr int kIn = kSplit > 1 ? kSplit - 1 : kPairMax - 1;
+    const int n_in = kSplit > 0 ? kSplit - 1 : n_split - 1;
+    const Merge<kPrecise> mg = merge_records<kIn, kPrecise>(a, recs, kRecWords, n_in, t_own, mb_own, l_own, v_own);
+    STAMP(4);
+    write_unit_row<T, D>(a, unit, G, mg, e0, h_own);
   }
   if (kCompact) {
     __syncthreads();                               // cand_total is complete
@@ -1491,9 +1591,11 @@ hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) 
   // list waves (blocks of eight waves) where every block of the launch is resident at once: two
   // such blocks fit a compute unit
   constexpr bool kList = !Rows<T, D>::kWide;
-  const int n_blocks = sb + (a.track.valid ? a.n_track * units : 0);
-  const bool resident = n_blocks <= 2 * compute_units();
-  const dim3 grid(n_blocks), block(kBlock), block_l(kList ? 2 * kBlock : kBlock);
+  const bool merged = a.n_split > kPairMax;
+  const int merge = merged ? merge_blocks<D>(a.group, merge_waves(a.n_split)) * units : 0;
+  const int tracking = a.track.valid ? a.n_track * units : 0;
+  const bool resident = !merged && sb + tracking <= 2 * compute_units();
+  const dim3 grid(sb + merge + tracking), block(kBlock), block_l(kList ? 2 * kBlock : kBlock);
 #define LAZYEV_LAUNCH(block, ...) \
   hipLaunchKernelGGL((decode_fused_kernel<T, D, __VA_ARGS__>), grid, block, lds_all, stream, kc, vc, kn, vn, q, a.n_old, a.capacity, shape, a)
 #define LAZYEV_SPLIT(n) \
@@ -1501,7 +1603,7 @@ hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) 
     if (long_run) LAZYEV_LAUNCH(block_l, true, true, kList, n); \
     else LAZYEV_LAUNCH(block_l, true, false, kList, n); \
     break;
-  if (a.variant == 6 && resident) {
+  if (a.variant == 6 && resident) {   // (n_split <= kPairMax)
     switch (a.n_split) {
       LAZYEV_SPLIT(1)
       LAZYEV_SPLIT(2)
@@ -1511,9 +1613,6 @@ hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) 
       LAZYEV_SPLIT(6)
       LAZYEV_SPLIT(7)
       LAZYEV_SPLIT(8)
-      default:
-        if (long_run) LAZYEV_LAUNCH(block_l, true, true, kList, 0);
-        else LAZYEV_LAUNCH(block_l, true, false, kList, 0);
     }
   } else if (a.variant == 6 && a.n_split == 1) {
     // (more than 256 units: no blocks to wait for, no divisions; with the instance for any split 320 units x 64 entries
@@ -1554,33 +1653,36 @@ uint32_t decode_fused_seq_max() { return kSeqMax; }
 uint32_t decode_fused_seq_captured() { return kSeqCaptured; }
 size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * sizeof(unsigned long long); }
 
-// Of n > kMergeRadix blocks per unit, all or the whole groups of kMergeRadix among them.  A last group that is not
-// whole makes its blocks wait for the leaders' merges all the same, and the blocks of a unit lie on more XCDs; what
-// it saves are rounds, i.e. sub-tiles of the longest-running waves.  us per call, whole groups / all blocks:
-//   * bf16 rows, where a round is short: 20 units x 4200 .. 8200 entries 8 / 12 blocks (128) 11.4 / 11.8 .. 18.4 /
-//     18.4, (64) 10.3 / 11.0 .. 14.8 / 14.2, 28 x 8200 8 / 9 22.5 / 26.8, (64) 15.4 / 19.5, 23 x 8200 8 / 11 19.8 /
-//     23.4, (64) 14.9 / 17.2, 14 x 8200 16 / 18 14.6 / 16.6; the other way for long caches, where idle compute units
-//     cost more: 18 x 12000 8 / 14 26.6 / 25.5, (64) 20.4 / 18.6, 24 x 16400 8 / 10 43.8 / 42.7, (64) 28.4 / 27.4.
-//   * fp32 rows of 128, where it is long: fewer than four fifths of the rounds pay.  20 x 4200 / 8200 / 12000 8 / 12
-//     23.7 / 21.7, 40.3 / 34.5, 56.6 / 47.9; 24 x 8200 8 / 10 42.3 / 40.0; 11 x 8200 16 / 23 26.2 / 24.5; 7 x 4200 32
-//     / 36 14.3 / 13.2; but 28 x 8200 8 / 9 44.5 / 49.6, 14 x 8200 16 / 18 27.4 / 29.2.
-//   * fp32 rows of 64 lie between: 18 x 8200 8 / 14 23.1 / 21.7, 20 x 8200 8 / 12 23.4 / 20.7, but where the units
-//     are no multiple of four (see BlockPlace) 22 x 8200 8 / 11 23.9 / 25.7; 11 x 6200 16 / 23 14.2 / 13.3 (64 x bf16
-//     11.3 / 11.1).
-// Where the cache's length bounds the blocks, whole groups above it: 4 units x 4800, 32 / 38 / 40 blocks 13.9 / 12.6
-// / 12.5 (fp32 128), 10.4 / 9.7 / 9.5 (fp32 64), 9.1 / 9.2 / 8.9 (bf16 64), 8.5 / 8.2 / 8.1 (bf16 128).
-static int groups_of(int units, int n_sub, int n, bool f32, int head_dim) {
-  const int part = n % kMergeRadix, whole = n - part;
-  if (part == 0) return n;
-  const int rounds = fused_wave_run(n_sub, n), rounds_whole = fused_wave_run(n_sub, whole);
-  bool all;
-  if (f32 && head_dim == 128)
-    all = 5 * rounds < 4 * rounds_whole || (whole == kMergeRadix && part > 1 && n_sub >= 768);
-  else if (whole == kMergeRadix)
-    all = (part > 1 && n_sub >= 640) || (f32 && 10 * rounds <= (units % 4 == 0 ? 7 : 6) * rounds_whole);
-  else
-    all = (f32 || head_dim == 64) && whole == 2 * kMergeRadix && 4 * rounds < 3 * rounds_whole;
-  return all ? n : whole;
+// Blocks per unit where there is room for more than kPairMax of them (`most`) and the cache has more than 43 sub-tiles;
+// 0: kPairMax or fewer (decode_fused_split).  us per call, 4 query heads to a KV head, one count / another:
+//   * all that there is room for up to 15: 20 units x 2000 / 8200 / 20000 entries 8 / 12 8.1 / 7.0, 18.0 / 16.7, 44.0 /
+//     41.6 (64 x bf16 8.1 / 6.8, 14.5 / 12.1, 30.7 / 27.9; 128 x fp32 14.5 / 12.5, x 4000 22.5 / 18.8); but eleven of
+//     22, which lie on the XCDs unevenly, only while the call is a chain: 22 units x 2000 / 4000 / 8200 8 / 11 8.4 / 7.8,
+//     11.8 / 12.4, 19.3 / 20.2 (64 x bf16 x 4000 / 8200 10.3 / 9.6, 14.9 / 15.3; fp32 rows have enough to do at any
+//     length); nine of 28 gain 4 % at 1000 entries, nothing at 2000, and lose 6 % where the sequences' lengths differ.
+//   * beyond, 16, 24, 32, 48 or 64 (a merging wave reads a record per lane and eight blocks): 12 units x 2000 / 8200 16 /
+//     21 6.0 / 6.3, 11.6 / 13.2; 10 units x 8200 24 / 25 10.3 / 12.0; 6 units x 8200 32 / 42 8.0 / 9.0; of 11 and 12 units
+//     20 for long caches: 11 x 12000 16 / 20 17.1 / 16.8 (64 x bf16 13.5 / 10.9, fp32 (64) 20.7 / 16.6, (128) 33.9 / 31.4).
+//   * more than 16 once a wave has two sub-tiles to do: 8 units x 1500 16 / 24 5.5 / 5.5, x 2000 16 / 32 5.9 / 5.6, 10
+//     units x 4000 16 / 24 7.6 / 7.3; fp32 rows, whose sub-tiles take longer, before: 6 units x 1500 16 / 24 (64) 6.6 / 6.0,
+//     (128) 9.0 / 7.7.
+//   * more than 32 from three on: 4 units x 4000 / 6000 / 12000 32 / 64 6.0 / 6.3, 6.5 / 6.4, 9.0 / 8.4; 5 units x 8200 32 /
+//     51 8.5 / 8.2; 4 units of 128 x fp32 x 3000 32 / 48 9.2 / 8.6, x 4000 32 / 64 9.5 / 8.9.
+static int merged_split(int n_sub, bool f32, int head_dim, int most) {
+  const int by_length = (n_sub + kWaves - 1) / kWaves;
+  if (most <= kPairMax || n_sub < 44) return 0;
+  if (most == 9) return 0;
+  if (most == 11 && !f32 && n_sub > (head_dim == 64 ? 320 : 160)) return 0;
+  int n = most;
+  if (most >= 16) {
+    const bool wide = f32 && head_dim == 128;
+    if (most >= 20 && most < 24 && n_sub >= 500) n = 20;
+    else if (most < 24 || n_sub < (f32 ? 80 : 112)) n = 16;
+    else if (most < 32) n = 24;
+    else if (most < 48 || n_sub < (wide && most == kFusedSplitMax ? 180 : 376)) n = 32;
+    else n = most / 16 * 16;
+  }
+  return n < by_length ? n : by_length;
 }
 
 // Blocks per unit.  us per call, 7 query heads to a KV head, 128 x bf16 unless it says otherwise (one layer again and
@@ -1588,8 +1690,7 @@ static int groups_of(int units, int n_sub, int n, bool f32, int head_dim) {
 //   * no more blocks than compute units: a second stream block on some of them holds up the whole launch (80 units x
 //     2200 entries: 3 blocks per unit 15.6, 4 20.6; 48 units: 5 10.5, 6 14.2), and with two on all of them the bytes
 //     in flight only widen the spread of the blocks' ends (128 units x 4144: 49.8 with one, 50.9 with two).
-//   * only a long cache pays for the second hop that more than kMergeRadix blocks need (8 units x 2200: 8 blocks 6.8,
-//     16 7.8, 32 7.4; x 6200: 10.8, 10.2, 9.2), and then mostly in whole groups (see groups_of).
+//   * more than eight where there is room: merged_split.
 //   * seven or eight blocks where they leave some compute units to the tracking (28 units x 1040 / 2060 / 4200: 6
 //     blocks 6.3 / 8.3 / 13.1, 8 6.4 / 8.1 / 12.6); where they fill the chip to the last one, six up to some thousand
 //     entries (32 units x 1040 / 4100 / 6200: 6 blocks 6.0 / 13.7 / 18.9, 8 6.2 / 13.5 / 19.5; x 8200 / 12000 26.4 /
@@ -1597,8 +1698,10 @@ static int groups_of(int units, int n_sub, int n, bool f32, int head_dim) {
 //     do per byte, or fewer bytes per entry: eight from about 1800 entries on (32 units x 2060 / 4100, 6 / 8: 64 x
 //     bf16 8.1 / 8.1, 11.2 / 10.7; 64 x fp32 11.0 / 10.5, 17.2 / 15.5; 128 x fp32 18.3 / 17.1, 29.0 / 26.8; the line
 //     is from 128 x fp32 x 1016, 12.6 / 13.3 then; 11.6 / 10.7 now).
-//   * two sub-tiles or more per wave (8 units x 600: 4 blocks 5.2, 5 5.4; x 350: 2 5.0, 3 4.9, 4 4.8), but two blocks
-//     from a unit's fifth sub-tile on (x 70: 1 4.1, 2 3.8; x 136: 1 4.7, 2 4.3, 3 4.3).
+//   * two sub-tiles or more per wave (8 units x 500: 4 blocks 5.1, 8 5.4; x 350: 2 5.0, 3 4.9, 4 4.8), but two blocks
+//     from a unit's fifth sub-tile on (x 70: 1 4.1, 2 3.8; x 136: 1 4.7, 2 4.3, 3 4.3).  A sub-tile of fp32 rows takes longer
+//     than a record more: 4 units x 130 2 / 3 blocks (64) 5.2 / 4.8, (128) 8.4 / 6.9; x 200 2 / 4 5.6 / 5.2, 8.7 / 7.3; x 400
+//     (64) 4 / 7 5.9 / 6.0, (128) 4 / 7 8.9 / 8.1; x 500 4 / 5 6.4 / 6.0, 10.3 / 9.1.
 //   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to two per
 //     compute unit (96 units x 6200: 2 blocks per unit 60.6, 5 57.0; 144 units: 1 96.9, 3 90.2; x 2200 18.5 against
 //     22.3 and 32.6 against 30.1: from 32 sub-tiles per wave on).  From 171 units on that would be two blocks, and
@@ -1610,29 +1713,32 @@ int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   constexpr int kUnitsOfChip = 256;                // compute units of the chip that the figures above are from
   int n = kUnitsOfChip / units;
   if (n < 1) n = 1;
-  if (n > kMergeRadix && n_sub <= kWaves * kMergeRadix * 8) n = kMergeRadix;
-  if (n > 6 && n <= kMergeRadix && n * units > 240 && n_sub < (n < kMergeRadix ? 512 : !f32 && head_dim == 128 ? 480 : 112)) n = 6;
-  const int by_work = n_sub <= kWaves ? 1 : n_sub < 4 * kWaves ? 2 : (n_sub + kWaves) / (2 * kWaves);
-  if (n > kMergeRadix) {
-    const int up = (by_work + kMergeRadix - 1) / kMergeRadix * kMergeRadix;
-    n = groups_of(units, n_sub, n < up ? n : up, f32, head_dim);
-  }
-  if (n > by_work && n <= kMergeRadix) n = by_work;
+  const int merged = merged_split(n_sub, f32, head_dim, n < kFusedSplitMax ? n : kFusedSplitMax);
+  if (merged > kPairMax) return merged;
+  if (n > kPairMax) n = kPairMax;
+  if (n > 6 && n * units > 240 && n_sub < (n < kPairMax ? 512 : !f32 && head_dim == 128 ? 480 : 112)) n = 6;
+  int by_work = n_sub <= kWaves ? 1 : n_sub < 4 * kWaves ? 2 : n_sub < 44 ? (n_sub + kWaves) / (2 * kWaves) : kPairMax;
+  if (f32 && n_sub <= (head_dim == 128 ? 32 : 16)) by_work = (n_sub + kWaves - 1) / kWaves;
+  else if (f32 && n_sub < 44) by_work = head_dim == 128 ? (n_sub + 7) / 8 : (n_sub + 6) / 7;
+  if (n > by_work) n = by_work;
   const int n2 = 2 * kUnitsOfChip / units;
-  if (units < kUnitsOfChip && n <= kMergeRadix && n_sub >= 32 * kWaves * n && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2 < by_work ? n2 : by_work;
+  // (28 units x 17000 of 128 x bf16: 8 blocks 48.0, 18 50.8; x 20000 56.1, 55.3; 128 x fp32 x 17000 96.8, 93.7)
+  if (units < kUnitsOfChip && n_sub >= (n == kPairMax && !f32 && head_dim == 128 ? 1200 : 32 * kWaves * n) && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2;
   return n;
 }
 
-// A unit of n blocks hands over n - 1 records.  decode_fused_split has at most 512 blocks for all units together (4 MB
-// of records); lazyev_set_target_blocks may ask for more, as far as the area that is there anyway holds them.
+// A unit of n blocks hands over n - 1 records, or n to blocks that merge them; an area is sized for the larger number.
+// decode_fused_split has at most 512 blocks for all units together (4 MB of records); lazyev_set_target_blocks may ask for
+// more, as far as the area that is there anyway holds them.
+int decode_fused_records_of(int n_split) { return n_split > 1 ? n_split : 0; }
 int decode_fused_records_needed(int units, int capacity) {
   const int by_length = ((capacity + 15) / 16 + 3) / 4, by_units = (2 * 256 + units - 1) / units;
   const int n = by_length < by_units ? by_length : by_units;
-  return (n < kFusedSplitMax ? n : kFusedSplitMax) - 1;
+  return decode_fused_records_of(n < kFusedSplitMax ? n : kFusedSplitMax);
 }
 int decode_fused_records_held(int units, int capacity, size_t bytes) {
   const int by_length = ((capacity + 15) / 16 + 3) / 4;
-  const int most = (by_length < kFusedSplitMax ? by_length : kFusedSplitMax) - 1;
+  const int most = decode_fused_records_of(by_length < kFusedSplitMax ? by_length : kFusedSplitMax);
   const size_t n = bytes / (decode_fused_record_bytes() * units);
   return n < static_cast<size_t>(most) ? static_cast<int>(n) : most;
 }
@@ -1685,7 +1791,7 @@ hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stre
 hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) {
   const int units = a.batch * a.n_kv_heads;
   if (a.group > kHeadPad || a.n_split < 1 ||
-      a.n_split > kFusedSplitMax || a.n_split > a.rec_per_unit + 1 || !a.logits_out ||
+      a.n_split > kFusedSplitMax || decode_fused_records_of(a.n_split) > a.rec_per_unit || a.n_track < 1 || !a.logits_out ||
       !a.ws.part_rec || !a.ws.fault || a.seq == 0 || a.seq > kSeqCaptured ||
       !a.stat_out || a.p_stride < (a.n_old + 16) / 16 * 16 ||
       (a.track.valid && (a.track.units != units || !a.track.logits || !a.track.stat ||

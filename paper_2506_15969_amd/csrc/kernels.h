@@ -129,7 +129,7 @@ struct DecodeArgs {
   const float *p_override;
   Workspace ws;
   unsigned long long *activation_counter;   // this layer's [units][slice_max] counters
-  int32_t rec_per_unit;                     // fused kernel: records per unit in ws.part_rec (a unit can have one block more)
+  int32_t rec_per_unit;                     // fused kernel: records per unit in ws.part_rec (decode_fused_records_of)
   int32_t n_track;                          // fused kernel: tracking blocks per unit (when a call is tracked)
   uint32_t seq;                             // fused kernel: number of this launch (1 .. decode_fused_seq_max, or that of captured calls), the stamp of its records
   uint32_t spin_ticks;                      // fused kernel: longest wait for a record, in 10 ns ticks
@@ -211,6 +211,7 @@ bool decode_fused_compact_fits(int n_old, int n_split, int p_stride, int group);
 size_t decode_fused_record_bytes();           // one stamped record
 uint32_t decode_fused_seq_max();              // largest number of an eager launch (the stamp has 16 bits) ...
 uint32_t decode_fused_seq_captured();         // ... and the number of every captured one
+int decode_fused_records_of(int n_split);     // most records that a unit of so many blocks hands over
 int decode_fused_records_needed(int units, int capacity);   // most records per unit that decode_fused_split asks for
 int decode_fused_records_held(int units, int capacity, size_t bytes);   // most records per unit of use that `bytes` hold for all units
 int decode_fused_split(int units, int n_sub, bool f32, int head_dim);   // blocks per unit of a call over n_sub sub-tiles of 16 entries

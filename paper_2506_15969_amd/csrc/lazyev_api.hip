@@ -535,7 +535,7 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
     if (n_split > (n_sub + 3) / 4) n_split = (n_sub + 3) / 4;
     if (n_split > lazyev::decode_fused_split_max()) n_split = lazyev::decode_fused_split_max();
     a.rec_per_unit = ctx->rec_per_unit;
-    if (n_split > a.rec_per_unit + 1) n_split = a.rec_per_unit + 1;
+    while (n_split > 1 && lazyev::decode_fused_records_of(n_split) > a.rec_per_unit) --n_split;
     if (n_split < 1) n_split = 1;
     a.n_split = n_split;
     a.n_track = n_split;
@@ -596,7 +596,7 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
     // when the numbers start over.  A call that is being captured will be launched with one number again and
     // again, before and after any other call: its records go back to 0 before each time, and its number
     // is one that no eager call has, whatever replays leave behind (the default stream cannot be captured).
-    const int32_t n_rec = a.n_split - 1;
+    const int32_t n_rec = lazyev::decode_fused_records_of(a.n_split);
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (ctx->stream && n_rec > 0) {
       const hipError_t ec = hipStreamIsCapturing(ctx->stream, &status);

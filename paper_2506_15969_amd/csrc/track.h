@@ -5,8 +5,26 @@
 namespace lazyev {
 namespace {
 
+// x / y for 0 <= x < 2^24, y > 0, the same in all lanes of a wave: the compiler's own sequence for a divisor that it does
+// not know is some thirty instructions, in a chain.  The rounded quotient is off by one at most.
+__host__ __device__ inline int wave_div(int x, int y) {
+#ifdef __HIP_DEVICE_COMPILE__
+  if (!__builtin_constant_p(y)) {
+    int q = __builtin_amdgcn_readfirstlane(static_cast<int>(static_cast<float>(x) * __builtin_amdgcn_rcpf(static_cast<float>(y))));
+    const int r = x - q * y;
+    q += r >= y ? 1 : 0;
+    return q - (r < 0 ? 1 : 0);
+  }
+#endif
+  return x / y;
+}
+
 constexpr int kWaves = 4;               // stream waves of a block
 constexpr int kHeadPad = 8;             // logits and statistics are stored for 8 heads per unit
+// Most sub-tiles one wave takes.
+__host__ __device__ inline int fused_wave_run(int n_sub, int n_split) {
+  return wave_div(n_sub + kWaves * n_split - 1, kWaves * n_split);
+}
 // How a unit's n_sub sub-tiles of 16 entries are dealt to the kWaves * n_split waves of its
 // n_split blocks: wave wv (= kWaves * (n_split - 1 - split) + wave) takes wv, wv + kWaves * n_split,
 // ..., so the waves of a unit read one moving window of the cache together (measured against a
@@ -19,12 +37,9 @@ __host__ __device__ inline WaveMap fused_wave_map(int n_sub, int n_split, int sp
   WaveMap m;
   m.first = (n_split - 1 - split) * kWaves + wave;
   m.step = kWaves * n_split;
-  m.cnt = m.first < n_sub ? (n_sub - m.first + m.step - 1) / m.step : 0;
+  const int run = fused_wave_run(n_sub, n_split);
+  m.cnt = m.first + (run - 1) * m.step < n_sub ? run : run - 1;
   return m;
-}
-// Most sub-tiles one wave takes.
-__host__ __device__ inline int fused_wave_run(int n_sub, int n_split) {
-  return (n_sub + kWaves * n_split - 1) / (kWaves * n_split);
 }
 
 // Slots of a block's region of candidate records in a call with n_parts blocks per unit: one

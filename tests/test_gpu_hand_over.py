@@ -1,5 +1,5 @@
-"""Partials of a unit handed over between its blocks: one hop for up to 8 blocks (an instance of the
-kernel each), two for up to 64, the groups' leaders at 7, 15, ... and a last group of any size."""
+"""Partials of a unit handed over between its blocks: up to 8 blocks (an instance of the kernel each) to the unit's last
+one, up to 64 to blocks that merge them, one, two, four or eight records per lane."""
 import numpy as np
 import pytest
 import torch
@@ -36,7 +36,7 @@ def _run(lazyev_lib, blocks, N, steps, group):
     return state
 
 
-@pytest.mark.parametrize("N,group,blocks", [(4080, 7, (1, 2, 3, 5, 6, 7, 8, 9, 15, 16, 17, 24, 63, 64, 0)),
+@pytest.mark.parametrize("N,group,blocks", [(4080, 7, (1, 2, 3, 5, 6, 7, 8, 9, 15, 16, 17, 24, 32, 33, 63, 64, 0)),
                                             (150, 4, (1, 2, 3, 0)), (3, 1, (1, 0)), (62, 7, (2, 0))])
 def test_every_number_of_blocks_gives_the_same_result(lazyev_lib, N, group, blocks):
     """Outputs against fp64 softmax attention; TS / MRI / pos equal whatever the split (a decision

@@ -58,7 +58,7 @@ def test_row_types_against_the_general_kernels(lazyev_lib, dtype, d, group, N):
 @pytest.mark.parametrize("dtype,d", [("fp32", 64), ("fp32", 128), ("bf16", 64)])
 @pytest.mark.parametrize("blocks", [1, 2, 3, 8, 9, 33])
 def test_row_types_with_every_kind_of_split(lazyev_lib, dtype, d, blocks):
-    """One, several and two hops' worth of blocks per unit; a single block streams a long run."""
+    """One, several and merged blocks per unit; a single block streams a long run."""
     dt = torch.float32 if dtype == "fp32" else torch.bfloat16
     runs = [_run(lazyev_lib, v, dt, d, 1, 8, 2, 2300, 4, 4000, 64, blocks=b) for v, b in ((0, 0), (1, blocks))]
     _compare(*runs, dt)
