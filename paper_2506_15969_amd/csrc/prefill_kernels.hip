@@ -662,7 +662,9 @@ __global__ __launch_bounds__(kBlock, (Rows<T, D>::waves(NB))) void prefill_track
 }
 
 // The segments of every key joined in order (Eq. 1): between two segments lies the gap from the last activation
-// before to the first one in it.
+// before to the first one in it.  What bounds it is the chain of its loads: the records of kJoin segments are
+// requested together (4 sequences, 32 / 8 heads of 64 x 499 positions, all three kernels: one after the other 29.5 us, 27.1 now).
+constexpr int kJoin = 8;
 __global__ __launch_bounds__(kBlock) void prefill_join_kernel(const PrefillArgs a) {
   const int units = a.batch * a.n_kv_heads, P = a.prompt_len;
   const int spans = (P + kBlock - 1) / kBlock;
@@ -671,12 +673,18 @@ __global__ __launch_bounds__(kBlock) void prefill_join_kernel(const PrefillArgs 
   if (key < P) {
     int32_t ts = key + 1 - P, mri = 0;             // born at its own step
     // (the first segment that a block of its wave's keys worked on)
-    for (int z = key / a.seg_block * (a.seg_block / 16) / a.seg_tiles; z < a.segments; ++z) {
-      const int4 s = a.seg[(static_cast<size_t>(z) * units + unit) * P + key];
-      if (s.x == INT_MAX) continue;
-      mri = max(mri, max(s.x - ts, s.z));
-      ts = s.y;
-      n_act += static_cast<unsigned>(s.w);
+    for (int z0 = key / a.seg_block * (a.seg_block / 16) / a.seg_tiles; z0 < a.segments; z0 += kJoin) {
+      int4 s[kJoin];
+#pragma unroll
+      for (int j = 0; j < kJoin; ++j)              // (beyond the last segment: that one once more)
+        s[j] = a.seg[(static_cast<size_t>(min(z0 + j, a.segments - 1)) * units + unit) * P + key];
+#pragma unroll
+      for (int j = 0; j < kJoin; ++j) {
+        if (z0 + j >= a.segments || s[j].x == INT_MAX) continue;
+        mri = max(mri, max(s[j].x - ts, s[j].z));
+        ts = s[j].y;
+        n_act += static_cast<unsigned>(s[j].w);
+      }
     }
     a.ts[static_cast<size_t>(unit) * a.capacity + key] = ts;
     a.mri[static_cast<size_t>(unit) * a.capacity + key] = mri;
