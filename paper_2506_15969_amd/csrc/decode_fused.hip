@@ -1697,7 +1697,8 @@ static int merged_split(int n_sub, bool f32, int head_dim, int most) {
 //     40.2, 8 25.1 / 37.6; 36 units x 6200 / 12000: 6 21.8 / 43.9, 7 23.2 / 42.5).  The other row types have more to
 //     do per byte, or fewer bytes per entry: eight from about 1800 entries on (32 units x 2060 / 4100, 6 / 8: 64 x
 //     bf16 8.1 / 8.1, 11.2 / 10.7; 64 x fp32 11.0 / 10.5, 17.2 / 15.5; 128 x fp32 18.3 / 17.1, 29.0 / 26.8; the line
-//     is from 128 x fp32 x 1016, 12.6 / 13.3 then; 11.6 / 10.7 now).
+//     is from 128 x fp32 x 1016), and before that where they take a round of sub-tiles less (128 x fp32 x 860 / 960 / 1100 /
+//     1300, 6 / 8 12.3 / 10.9, 12.3 / 11.0, 12.9 / 13.3, 14.6 / 13.5; 64 x fp32 x 960 / 1300 7.9 / 8.0, 9.0 / 8.4).
 //   * two sub-tiles or more per wave (8 units x 500: 4 blocks 5.1, 8 5.4; x 350: 2 5.0, 3 4.9, 4 4.8), but two blocks
 //     from a unit's fifth sub-tile on (x 70: 1 4.1, 2 3.8; x 136: 1 4.7, 2 4.3, 3 4.3).  A sub-tile of fp32 rows takes longer
 //     than a record more: 4 units x 130 2 / 3 blocks (64) 5.2 / 4.8, (128) 8.4 / 6.9; x 200 2 / 4 5.6 / 5.2, 8.7 / 7.3; x 400
@@ -1716,7 +1717,8 @@ int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   const int merged = merged_split(n_sub, f32, head_dim, n < kFusedSplitMax ? n : kFusedSplitMax);
   if (merged > kPairMax) return merged;
   if (n > kPairMax) n = kPairMax;
-  if (n > 6 && n * units > 240 && n_sub < (n < kPairMax ? 512 : !f32 && head_dim == 128 ? 480 : 112)) n = 6;
+  const bool fewer = f32 && n == kPairMax && (head_dim == 128 || n_sub > 72) && fused_wave_run(n_sub, n) < fused_wave_run(n_sub, 6);
+  if (n > 6 && n * units > 240 && n_sub < (n < kPairMax ? 512 : !f32 && head_dim == 128 ? 480 : 112) && !fewer) n = 6;
   int by_work = n_sub <= kWaves ? 1 : n_sub < 4 * kWaves ? 2 : n_sub < 44 ? (n_sub + kWaves) / (2 * kWaves) : kPairMax;
   if (f32 && n_sub <= (head_dim == 128 ? 32 : 16)) by_work = (n_sub + kWaves - 1) / kWaves;
   else if (f32 && n_sub < 44) by_work = head_dim == 128 ? (n_sub + 7) / 8 : (n_sub + 6) / 7;
