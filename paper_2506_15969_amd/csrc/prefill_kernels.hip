@@ -712,18 +712,21 @@ hipError_t launch_rows(PrefillArgs a, hipStream_t stream) {
     return hipGetLastError();
   }
   // Blocks of four waves with NB key tiles each, or with one each where that does not fill the chip.  The
-  // queries are cut into segments where the blocks are fewer than eight per compute unit (wide) or two (narrow):
+  // queries are cut into segments where the blocks are fewer than eight per compute unit:
   // early keys have all queries to walk, one after the other, and with one block for that the chip ends
   // on the few blocks of the earliest keys.  One segment / cut, us for both kernels: 32 units x 1024 positions
   // 267 / 112, 8 units x 8192 2129 / 1146, 128 units x 600 230 / 169; from 2048 blocks on nothing is gained
-  // (128 units x 4096, 4096 blocks asked for instead: 2966 / 2900).  A segment is two query tiles at
-  // least (wide: four).
+  // (128 units x 4096, 4096 blocks asked for instead: 2966 / 2900).  A segment is a query tile at
+  // least (wide: two): what a block walks one after the other costs more than the records of more segments.  us for the
+  // three kernels, 512 narrow blocks of two query tiles and wide ones of four / like this: 28 / 4 heads of 128 x bf16 x 33
+  // positions 12.7 / 10.4, x 164 16.4 / 13.0, 2 sequences x 1500 102 / 74, x 2600 258 / 184, 16 x 250 37.9 / 30.1, 8 x 600 59.7 /
+  // 55.4; 4 sequences of 32 / 8 heads of 64 x bf16 x 499 27.7 / 26.0; fp32 rows of 128, 2 x 300 46.0 / 39.5.
   const long long n_it = (a.prompt_len + 15) / 16;
   const long long most = n_it / 4 < a.segments ? n_it / 4 : a.segments;        // (what the workspace holds records for)
   const bool use_wide = units * wide * (most < 1 ? 1 : most) >= 512;
-  const long long per_unit = use_wide ? wide : narrow, want = use_wide ? 2048 : 512;
+  const long long per_unit = use_wide ? wide : narrow, want = 2048;
   long long z = (want + units * per_unit - 1) / (units * per_unit);
-  if (z > (use_wide ? n_it / 4 : n_it / 2)) z = use_wide ? n_it / 4 : n_it / 2;
+  if (z > (use_wide ? n_it / 2 : n_it)) z = use_wide ? n_it / 2 : n_it;
   if (z > a.segments) z = a.segments;
   if (z <= 1) {
     const dim3 grid(static_cast<unsigned>(units * per_unit));
