@@ -701,7 +701,11 @@ hipError_t launch_rows(PrefillArgs a, hipStream_t stream) {
   const long long units = static_cast<long long>(a.batch) * a.n_kv_heads;
   const long long wide = (a.prompt_len + kWaves * 16 * NB - 1) / (kWaves * 16 * NB), narrow = (a.prompt_len + kWaves * 16 - 1) / (kWaves * 16);
   if (units * a.group * narrow > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  if (units * a.group * wide >= 512)
+  // Wide blocks where there are eight per compute unit; with fewer the last of them leave more of the chip idle than their
+  // products save (us for the three kernels, narrow from 512 / 2048 wide blocks down: 28 / 4 heads of 128 x bf16, 8
+  // sequences x 600 positions 55.6 / 48.4, 2 x 2600 185 / 169, 32 x 60 19.0 / 16.1; 8 of 32 / 8 heads of 64 x 300 29.2 / 23.2;
+  // from 4096 down: 32 x 600 154 / 203).
+  if (units * a.group * wide >= 2048)
     hipLaunchKernelGGL((prefill_stats_kernel<T, D, NB>), dim3(static_cast<unsigned>(units * a.group * wide)), dim3(kBlock), 0, stream, a);
   else
     hipLaunchKernelGGL((prefill_stats_kernel<T, D, 1>), dim3(static_cast<unsigned>(units * a.group * narrow)), dim3(kBlock), 0, stream, a);
