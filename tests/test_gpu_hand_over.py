@@ -135,3 +135,36 @@ def test_records_left_a_whole_cycle_of_numbers_ago(lazyev_lib):
     assert len(checked) == 2 and max(checked) < 2 * 2.0 ** -8, checked   # (two roundings to bf16, as above)
     assert eng.stats()["last_step"] == [steps] * L
     eng.close()
+
+
+@pytest.mark.parametrize("group,blocks", [(7, 16), (8, 33), (1, 17), (5, 9)])
+def test_merged_blocks_of_sequences_of_their_own_lengths(lazyev_lib, group, blocks):
+    """More than eight blocks per unit with per-sequence timing: a full cache, one of fewer sub-tiles than the unit has
+    waves, and an empty slot, whose rows of the output stay as they are.  Against fp64 softmax attention."""
+    H, N, steps, lens = 2, 2300, 3, (2300, 70, -1)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    eng = lazyev_lib.LazyEviction(1, 3, group * H, H, 128, N + 100, 64, N, 8.0 / N)
+    eng.k_cache[:, :, :, :N].normal_(generator=gen)
+    eng.v_cache[:, :, :, :N].normal_(generator=gen)
+    eng.init()
+    for s, n in enumerate(lens):
+        if n < 0:
+            eng.retire(s)
+        else:
+            eng.admit(s, n, 0)
+    eng.set_target_blocks(blocks * 3 * H)
+    for t in range(1, steps + 1):
+        q, kn, vn = (torch.empty((3, h, 128), device="cuda").normal_(generator=gen).to(torch.bfloat16) for h in (group * H, H, H))
+        out = torch.full((3, group * H, 128), 7.0, dtype=torch.bfloat16, device="cuda")
+        eng.decode_step(0, t, q, kn, vn, out)
+        for s, n in enumerate(lens):
+            if n < 0:
+                assert bool((out[s] == 7.0).all())
+                continue
+            k, v = eng.k_cache[0, s, :, :n + t].double(), eng.v_cache[0, s, :, :n + t].double()
+            p = torch.softmax(torch.matmul(q[s].double().view(H, group, 128), k.transpose(1, 2).contiguous()) / np.sqrt(128.0), dim=-1)
+            ref = torch.matmul(p, v).view(group * H, 128)
+            err = float(((out[s].double() - ref).norm(dim=1) / ref.norm(dim=1)).max())
+            assert err < 2 * 2.0 ** -8, (s, t, err)   # (two roundings to bf16, as above)
+    eng.stats()
+    eng.close()
