@@ -32,12 +32,12 @@
 // kernels, before (a running maximum with two exponentials per weight, an exponential and a comparison per
 // weight in the second kernel, rows of 64 and fp32 rows on a kernel without matrix instructions) and now, calls back to
 // back (3 % from box to box; the other figures in this file are against 1190 - 1223 us for 2048 positions in their own runs):
-//   32 sequences, 28 / 4 heads of 128, bf16   600 positions 292 -> 166, 2048 positions 1370 -> 1050
+//   32 sequences, 28 / 4 heads of 128, bf16   600 positions 292 -> 154, 2048 positions 1370 -> 1050
 //   16 sequences, 40 / 8 heads of 128, bf16  4096 positions 3520 -> 2760
-//    8 sequences, 28 / 4 heads of 128, bf16  1024 positions 350 -> 110
-//    1 sequence,  28 / 4 heads of 128, bf16    33 positions 22.9 -> 13.0,  400 positions 141 -> 23.6
-//    4 sequences, 32 / 8 heads of  64, bf16   499 positions 5470 -> 30
-//    2 sequences, 28 / 4 heads of 128, fp32   300 positions 10880 -> 48
+//    8 sequences, 28 / 4 heads of 128, bf16  1024 positions 350 -> 100
+//    1 sequence,  28 / 4 heads of 128, bf16    33 positions 22.9 -> 10.4,  400 positions 141 -> 19.7
+//    4 sequences, 32 / 8 heads of  64, bf16   499 positions 5470 -> 26
+//    2 sequences, 28 / 4 heads of 128, fp32   300 positions 10880 -> 39
 // (Of the first two 1158 -> 1050 and 2960 -> 2760 by loops without a way out of their middle, whose stages therefore waited for their own
 // request, by masks and maxima in place instead of copies of 16 registers a stage, and by four waves per SIMD in the first kernel.
 // The clock falls as the matrix cores get busier, 1.98 -> 1.87 GHz under the profiler: 16 % fewer cycles were 12 % of the time.)
