@@ -207,7 +207,7 @@ struct TrackBatch {
 // Entry that thread `tid` of part `part` (of n_parts) handles in round r: the parts own the
 // 16-entry sub-tiles exactly as the stream blocks of a launch with n_parts blocks per unit do
 // (fused_wave_map), so a tracking block that runs on the XCD of the stream block with the same
-// index finds the logits that block wrote in its L2.  Beyond the part's share: a number no
+// index (see places_of) finds the logits that block wrote in its L2.  Beyond the part's share: a number no
 // cache reaches.
 __device__ __forceinline__ int track_entry(int n_sub, int part, int n_parts, int r) {
   const int j = r * (kBlock / 16) + (static_cast<int>(threadIdx.x) >> 4);   // wave j % kWaves, its sub-tile j / kWaves
@@ -690,8 +690,17 @@ __device__ __forceinline__ bool takes_part(const DecodeArgs &a, int unit) {
 // record, passes through its compute unit's L1 at 64 bytes a cycle: with eight waves a block 32 records a unit took 0.2 us
 // more (8 units x 2080: 5.67 / 5.50), 16 records 0.3.
 __host__ __device__ constexpr int merge_waves(int n_split) { return n_split <= 16 ? 4 : 2; }
-template <int D>
-__host__ __device__ constexpr int merge_blocks(int group, int waves) { return (group * (D / 32) + waves - 1) / waves; }
+__host__ __device__ constexpr int merge_blocks(int head_dim, int group, int waves) { return (group * (head_dim / 32) + waves - 1) / waves; }
+// Where a launch's blocks that do not stream begin: the merging blocks, if there are any, and the tracking blocks.  Blocks go to
+// the eight XCDs round robin, and a tracking block reads the logits that the stream block of its number has just written
+// (see track_entry): the tracking blocks of a launch with merging blocks begin at a multiple of eight, up to seven blocks
+// before them do nothing.  us per call, right behind the merging blocks / like this: 5 units x 19000 entries of 128 x
+// bf16 14.4 / 12.6, 25 x 4000 14.6 / 12.9, 19 x 8200 18.5 / 16.3; 9 x 24000 of 64 x bf16 18.0 / 14.8; 10 x 13000 of 64 x fp32 18.5 / 15.8;
+// 15 x 13000 of 128 x fp32 41.9 / 37.3.
+struct Places { int merge, track; };
+__host__ __device__ inline Places places_of(int n_stream, int n_merge) {
+  return {n_stream, n_merge > 0 ? (n_stream + n_merge + 7) & ~7 : n_stream};
+}
 // The output elements 32 columns .. + 31 of a unit of n blocks (kPairMax < n <= 8 N), merged by one wave: lane (c, g)
 // reads the elements 4 c .. 4 c + 3 of the records g, g + 8, ..., and the eight lanes of a column merge across the wave,
 // with no LDS and no barrier.  What bounds it is the chain partial stored - seen - loaded - stored, 1.4 us from the last
@@ -816,13 +825,13 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   const int n_stream = n_split * units_call;
   const bool merged = kSplit == 0 && n_split > kPairMax;   // a unit's partials are merged by blocks of their own
   const int per_merge = merge_waves(n_split);
-  const int n_merge = merged ? merge_blocks<D>(G, per_merge) * units_call : 0;
-  if (static_cast<int>(blockIdx.x) >= n_stream + n_merge) {
+  const Places places = places_of(n_stream, merged ? merge_blocks(D, G, per_merge) * units_call : 0);
+  if (static_cast<int>(blockIdx.x) >= places.track) {
     // tracking of the previous call: n_split blocks per unit, spread over the compute units
     // like the stream blocks
     if (kListWaves && threadIdx.x >= kBlock) return;  // (the tracking has no use for list waves)
     const DecodeArgs &a = args_from_here<T>();
-    const int tb = blockIdx.x - n_stream - n_merge;
+    const int tb = blockIdx.x - places.track;
     const int n_track = a.n_track;
     const BlockPlace at = block_place<kSplit>(tb, n_track, units_call);
     const int unit = at.unit, part = at.split;
@@ -869,10 +878,10 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // wave-uniform: scalar branches below
-  if (merged && static_cast<int>(blockIdx.x) >= n_stream) {
-    const BlockPlace at = block_place<0>(blockIdx.x - n_stream, 2, units_call);
+  if (merged && static_cast<int>(blockIdx.x) >= places.merge) {
+    const BlockPlace at = block_place<0>(blockIdx.x - places.merge, 2, units_call);
     const int columns = at.split * per_merge + wave;
-    if (wave >= per_merge || columns >= G * (D / 32)) return;
+    if (wave >= per_merge || columns >= G * (D / 32)) return;   // (the blocks before the tracking blocks among them)
     if (slots_on && !takes_part(args_from_here<T>(), at.unit)) return;
     CallArgs<T> a;
     a.read();
@@ -1592,10 +1601,10 @@ hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) 
   // such blocks fit a compute unit
   constexpr bool kList = !Rows<T, D>::kWide;
   const bool merged = a.n_split > kPairMax;
-  const int merge = merged ? merge_blocks<D>(a.group, merge_waves(a.n_split)) * units : 0;
+  const Places places = places_of(sb, merged ? merge_blocks(D, a.group, merge_waves(a.n_split)) * units : 0);
   const int tracking = a.track.valid ? a.n_track * units : 0;
   const bool resident = !merged && sb + tracking <= 2 * compute_units();
-  const dim3 grid(sb + merge + tracking), block(kBlock), block_l(kList ? 2 * kBlock : kBlock);
+  const dim3 grid(places.track + tracking), block(kBlock), block_l(kList ? 2 * kBlock : kBlock);
 #define LAZYEV_LAUNCH(block, ...) \
   hipLaunchKernelGGL((decode_fused_kernel<T, D, __VA_ARGS__>), grid, block, lds_all, stream, kc, vc, kn, vn, q, a.n_old, a.capacity, shape, a)
 #define LAZYEV_SPLIT(n) \
@@ -1727,6 +1736,13 @@ int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   // (28 units x 17000 of 128 x bf16: 8 blocks 48.0, 18 50.8; x 20000 56.1, 55.3; 128 x fp32 x 17000 96.8, 93.7)
   if (units < kUnitsOfChip && n_sub >= (n == kPairMax && !f32 && head_dim == 128 ? 1200 : 32 * kWaves * n) && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2;
   return n;
+}
+
+void decode_fused_places(int units, int n_split, int group, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track) {
+  *n_merge = n_split > kPairMax ? merge_blocks(head_dim, group, merge_waves(n_split)) * units : 0;
+  const Places p = places_of(units * n_split, *n_merge);
+  *merge = p.merge;
+  *track = p.track;
 }
 
 // A unit of n blocks hands over n - 1 records, or n to blocks that merge them; an area is sized for the larger number.
