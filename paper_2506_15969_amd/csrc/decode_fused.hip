@@ -670,17 +670,18 @@ struct CallArgs {
     p = (P *)g;
   }
 };
-// Units, blocks per unit, query heads per unit and whether sequences have their own timing, in one scalar argument
+// Units, blocks per unit, query heads per unit, whether sequences have their own timing and whether there are merging blocks, in one scalar argument
 // (what a wave is handed in registers at its start is limited to a few words).
 static_assert(kFusedSplitMax < 128, "seven bits");
-inline unsigned pack_shape(int units, int n_split, int group, bool slots) {
+inline unsigned pack_shape(int units, int n_split, int group, bool slots, bool merged) {
   return static_cast<unsigned>(units) | (static_cast<unsigned>(n_split) << 16) | (static_cast<unsigned>(group - 1) << 23) |
-         (slots ? 1u << 26 : 0u);
+         (slots ? 1u << 26 : 0u) | (merged ? 1u << 27 : 0u);
 }
 __device__ __forceinline__ int shape_units(unsigned s) { return static_cast<int>(s & 0xFFFFu); }
 __device__ __forceinline__ int shape_split(unsigned s) { return static_cast<int>((s >> 16) & 127u); }
 __device__ __forceinline__ int shape_group(unsigned s) { return static_cast<int>((s >> 23) & 7u) + 1; }
 __device__ __forceinline__ bool shape_slots(unsigned s) { return (s >> 26) & 1u; }
+__device__ __forceinline__ bool shape_merged(unsigned s) { return (s >> 27) & 1u; }
 // Does the sequence of a unit take this step?  (per-sequence timing)
 __device__ __forceinline__ bool takes_part(const DecodeArgs &a, int unit) {
   const int seq = unit / a.n_kv_heads;
@@ -823,7 +824,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   STAMPV(6, xcc_id());
 #endif
   const int n_stream = n_split * units_call;
-  const bool merged = kSplit == 0 && n_split > kPairMax;   // a unit's partials are merged by blocks of their own
+  const bool merged = kSplit == 0 && shape_merged(shape);   // a unit's partials are merged by blocks of their own
   const int per_merge = merge_waves(n_split);
   const Places places = places_of(n_stream, merged ? merge_blocks(D, G, per_merge) * units_call : 0);
   if (static_cast<int>(blockIdx.x) >= places.track) {
@@ -1551,9 +1552,14 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     }
   }
   if (finisher) {
-    constexpr int kIn = kSplit > 1 ? kSplit - 1 : kPairMax - 1;
+    constexpr int kIn = kSplit > 1 ? kSplit - 1 : kSplit == 1 ? 1 : R::kWide ? 18 : 9;
     const int n_in = kSplit > 0 ? kSplit - 1 : n_split - 1;
-    const Merge<kPrecise> mg = merge_records<kIn, kPrecise>(a, recs, kRecWords, n_in, t_own, mb_own, l_own, v_own);
+    Merge<kPrecise> mg = merge_records<kIn, kPrecise>(a, recs, kRecWords, min(n_in, kIn), t_own, mb_own, l_own, v_own);
+    if constexpr (kSplit == 0) {                   // (at most 18 records where the split is the library's own)
+      for (int j = kIn; j < n_in; j += kIn)
+        mg = merge_records<kIn, kPrecise>(a, recs + static_cast<size_t>(j) * kRecWords, kRecWords, min(n_in - j, kIn), t_own, mg.m, mg.l,
+                                          f32x4_t{mg.o[0], mg.o[1], mg.o[2], mg.o[3]});
+    }
     STAMP(4);
     write_unit_row<T, D>(a, unit, G, mg, e0, h_own);
   }
@@ -1583,6 +1589,30 @@ int compute_units() {
   return n;
 }
 
+// Four-wave blocks that the chip holds at once in a launch whose waves run over `run` sub-tiles: by their LDS, which is
+// handed out in pieces of 1280 bytes of 160 KB, and by their registers.
+int fused_slots(int run, bool f32, int head_dim) {
+  const int stationary = 17056 + (f32 ? 0 : head_dim == 64 ? 1024 : 2048);   // (what is not logit_lds)
+  const int lds = kWaves * (run < kRunMax ? run : kRunMax) * 16 * kHeadPad * static_cast<int>(sizeof(float)) + stationary;
+  const int by_lds = 160 * 1024 / ((lds + 1279) / 1280 * 1280), by_registers = f32 && head_dim == 128 ? 2 : 4;
+  return compute_units() * (by_lds < by_registers ? by_lds : by_registers);
+}
+
+// Merging blocks of a launch: for units of more than kPairMax blocks, where they fit the chip beside the stream blocks or all but
+// a few do.  With
+// two stream blocks on every compute unit (long caches) they would start only when stream blocks end, before the tracking blocks,
+// and hold their places until the unit's last block is there: that one merges then.  us per call, merging blocks / its last
+// block: 53 units x 13000 / 20000 entries, 9 blocks, 128 x bf16 70.6 / 69.2, 109.9 / 105.9 (7 or 8 query heads to a KV head 52 x
+// 20000 115.9 / 106.9), 128 x fp32 (7) 139.3 / 135.6, 64 x fp32 (7) 117.8 / 114.3; 28 x 24000, 18 blocks, 128 x bf16 (5) 70.4 / 66.4, 128 x fp32
+// 127.2 / 125.5; but with three blocks to a compute unit 53 x 8200 of 128 x bf16 44.5 / 46.2, of 64 x fp32 45.4 / 47.0, 28 x 17000
+// of 64 x fp32 52.7 / 55.5; and with a tenth of a block per compute unit too many 52 x 8200 of 128 x fp32, one query head to a KV head,
+// 76.0 / 80.2, 53 x 16000 of 128 x bf16 79.0 / 80.6 (54 x 24000, more than that, 130 / 126).
+int merging_blocks(int units, int n_sub, int n_split, int group, bool f32, int head_dim) {
+  if (n_split <= kPairMax) return 0;
+  const long long n = static_cast<long long>(merge_blocks(head_dim, group, merge_waves(n_split))) * units;
+  return static_cast<long long>(n_split) * units + n <= fused_slots(fused_wave_run(n_sub, n_split), f32, head_dim) + compute_units() / 10 ? static_cast<int>(n) : 0;
+}
+
 template <typename T, int D>
 hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) {
   if (ev) (void)hipEventRecord(ev[0], stream);
@@ -1595,15 +1625,15 @@ hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) 
   const T *kc = static_cast<const T *>(a.k_cache), *vc = static_cast<const T *>(a.v_cache);
   const T *kn = static_cast<const T *>(a.k_new), *vn = static_cast<const T *>(a.v_new);
   const T *q = static_cast<const T *>(a.q);
-  const unsigned shape = pack_shape(units, a.n_split, a.group, a.slots.prompt_len != nullptr);
+  const int n_merge = merging_blocks(units, n_sub, a.n_split, a.group, Rows<T, D>::kF32, D);
+  const unsigned shape = pack_shape(units, a.n_split, a.group, a.slots.prompt_len != nullptr, n_merge > 0);
   const bool long_run = fused_wave_run(n_sub, a.n_split) > kRunMax;
   // list waves (blocks of eight waves) where every block of the launch is resident at once: two
   // such blocks fit a compute unit
   constexpr bool kList = !Rows<T, D>::kWide;
-  const bool merged = a.n_split > kPairMax;
-  const Places places = places_of(sb, merged ? merge_blocks(D, a.group, merge_waves(a.n_split)) * units : 0);
+  const Places places = places_of(sb, n_merge);
   const int tracking = a.track.valid ? a.n_track * units : 0;
-  const bool resident = !merged && sb + tracking <= 2 * compute_units();
+  const bool resident = a.n_split <= kPairMax && sb + tracking <= 2 * compute_units();
   const dim3 grid(places.track + tracking), block(kBlock), block_l(kList ? 2 * kBlock : kBlock);
 #define LAZYEV_LAUNCH(block, ...) \
   hipLaunchKernelGGL((decode_fused_kernel<T, D, __VA_ARGS__>), grid, block, lds_all, stream, kc, vc, kn, vn, q, a.n_old, a.capacity, shape, a)
@@ -1738,8 +1768,8 @@ int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   return n;
 }
 
-void decode_fused_places(int units, int n_split, int group, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track) {
-  *n_merge = n_split > kPairMax ? merge_blocks(head_dim, group, merge_waves(n_split)) * units : 0;
+void decode_fused_places(int units, int n_sub, int n_split, int group, bool f32, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track) {
+  *n_merge = merging_blocks(units, n_sub, n_split, group, f32, head_dim);
   const Places p = places_of(units * n_split, *n_merge);
   *merge = p.merge;
   *track = p.track;

@@ -216,7 +216,7 @@ int decode_fused_records_needed(int units, int capacity);   // most records per 
 int decode_fused_records_held(int units, int capacity, size_t bytes);   // most records per unit of use that `bytes` hold for all units
 int decode_fused_split(int units, int n_sub, bool f32, int head_dim);   // blocks per unit of a call over n_sub sub-tiles of 16 entries
 // block numbers at which a launch's merging blocks (n_merge of them, 0: none) and its tracking blocks begin
-void decode_fused_places(int units, int n_split, int group, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track);
+void decode_fused_places(int units, int n_sub, int n_split, int group, bool f32, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track);
 hipError_t launch_clear_records(unsigned long long *rec, int units, int rec_per_unit, int n_records, hipStream_t stream);
 hipError_t launch_track(const TrackArgs &k, hipStream_t stream);
 hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stream);

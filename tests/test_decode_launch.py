@@ -5,26 +5,33 @@ import ctypes as C
 import pytest
 
 
-def _places(lib, units, n_split, group, d):
-    fn = getattr(lib, "_ZN6lazyev19decode_fused_placesEiiiiPiS0_S0_")   # lazyev::decode_fused_places (kernels.h)
-    fn.restype = None
+def _places(lib, units, n_sub, n_split, group, f32, d):
+    fn = getattr(lib, "_ZN6lazyev19decode_fused_placesEiiiibiPiS0_S0_")   # lazyev::decode_fused_places (kernels.h)
+    fn.restype, fn.argtypes = None, [C.c_int] * 4 + [C.c_bool, C.c_int] + [C.POINTER(C.c_int32)] * 3
     merge, n_merge, track = C.c_int32(-1), C.c_int32(-1), C.c_int32(-1)
-    fn(units, n_split, group, d, C.byref(merge), C.byref(n_merge), C.byref(track))
+    fn(units, n_sub, n_split, group, f32, d, C.byref(merge), C.byref(n_merge), C.byref(track))
     return merge.value, n_merge.value, track.value
 
 
+@pytest.mark.parametrize("f32", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("group", range(1, 9))
-def test_tracking_blocks_run_on_the_xcds_of_the_stream_blocks(lazyev_lib, d, group):
+@pytest.mark.parametrize("group", [1, 2, 4, 5, 7, 8])
+def test_merging_and_tracking_blocks(lazyev_lib, d, group, f32):
     """Blocks go to the eight XCDs in turn: tracking block i is on the XCD of stream block i where the tracking blocks begin at
-    a multiple of eight.  No two kinds of blocks overlap, and no more than seven blocks are left empty."""
+    a multiple of eight.  No two kinds of blocks overlap, and no more than seven blocks are left empty.  Merging blocks are
+    there where at most one stream block is on a compute unit, and never where two of long runs are on each."""
     for units in range(1, 65):
         for n_split in range(1, 65):
             stream = units * n_split
-            merge, n_merge, track = _places(lazyev_lib.lib, units, n_split, group, d)
-            if n_split <= 8:
-                assert (n_merge, track) == (0, stream)
-                continue
-            # a wave merges 32 output elements, a block has two or four such waves
-            assert n_merge % units == 0 and group * (d // 32) <= n_merge // units * (4 if n_split <= 16 else 2) < group * (d // 32) + 4
-            assert merge == stream and 0 <= track - (stream + n_merge) < 8 and track % 8 == 0
+            for run in (1, 15, 30):
+                merge, n_merge, track = _places(lazyev_lib.lib, units, 4 * n_split * run, n_split, group, f32, d)
+                if n_split <= 8 or (run == 30 and stream > 512 + 25):
+                    assert n_merge == 0
+                if n_split > 8 and stream <= 256:  # (compute units of the chip, and what is assumed without one)
+                    assert n_merge > 0
+                if n_merge == 0:
+                    assert track == stream
+                    continue
+                # a wave merges 32 output elements, a block has two or four such waves
+                assert n_merge % units == 0 and group * (d // 32) <= n_merge // units * (4 if n_split <= 16 else 2) < group * (d // 32) + 4
+                assert merge == stream and 0 <= track - (stream + n_merge) < 8 and track % 8 == 0

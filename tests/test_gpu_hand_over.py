@@ -168,3 +168,37 @@ def test_merged_blocks_of_sequences_of_their_own_lengths(lazyev_lib, group, bloc
             assert err < 2 * 2.0 ** -8, (s, t, err)   # (two roundings to bf16, as above)
     eng.stats()
     eng.close()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("fp32", 64), ("fp32", 128)])
+@pytest.mark.parametrize("batch,blocks,N", [(30, 9, 10500), (30, 10, 11600), (28, 11, 13000), (15, 19, 22500), (18, 32, 10500)])
+def test_more_than_eight_blocks_where_the_chip_is_full(lazyev_lib, dtype, d, batch, blocks, N):
+    """Units of more than eight blocks in launches of more than two stream blocks per compute unit: the unit's last block merges,
+    nine records at a time (fp32 rows of 128: eighteen), a round that is not full, a whole one, one more record, and several.  Outputs of sampled sequences against fp64 softmax attention; TS / MRI / pos as with three
+    blocks a unit."""
+    H, group, steps = 2, 3, 3
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    states = []
+    for b in (3, blocks):
+        gen = torch.Generator(device="cuda").manual_seed(13)
+        eng = lazyev_lib.LazyEviction(1, batch, group * H, H, d, N + 100, 64, N, 8.0 / N, dtype=dt)
+        eng.k_cache[:, :, :, :N].normal_(generator=gen)
+        eng.v_cache[:, :, :, :N].normal_(generator=gen)
+        eng.init()
+        eng.set_target_blocks(b * batch * H)
+        out = torch.zeros((batch, group * H, d), dtype=dt, device="cuda")
+        for t in range(1, steps + 1):
+            q, kn, vn = (torch.empty((batch, h, d), device="cuda").normal_(generator=gen).to(dt) for h in (group * H, H, H))
+            eng.decode_step(0, t, q, kn, vn, out)
+            for s in (0, batch - 1):
+                k, v = eng.k_cache[0, s, :, :N + t].double(), eng.v_cache[0, s, :, :N + t].double()
+                p = torch.softmax(torch.matmul(q[s].double().view(H, group, d), k.transpose(1, 2).contiguous()) * d ** -0.5, dim=-1)
+                ref = torch.matmul(p, v).view(group * H, d)
+                err = float(((out[s].double() - ref).norm(dim=1) / ref.norm(dim=1)).max())
+                # (bf16: two roundings, as above; fp32: sums of some thousand terms)
+                assert err < (1e-5 if dt == torch.float32 else 2 * 2.0 ** -8), (b, s, t, err)
+        eng.stats()
+        states.append([x[0, :, :, :N + steps].clone() for x in (eng.ts, eng.mri, eng.pos)])
+        eng.close()
+    for x, y in zip(*states):
+        assert torch.equal(x, y)
