@@ -670,18 +670,20 @@ struct CallArgs {
     p = (P *)g;
   }
 };
-// Units, blocks per unit, query heads per unit, whether sequences have their own timing and whether there are merging blocks, in one scalar argument
+// Units, blocks per unit, query heads per unit, whether sequences have their own timing, whether there are merging blocks and whether
+// they come last, in one scalar argument
 // (what a wave is handed in registers at its start is limited to a few words).
 static_assert(kFusedSplitMax < 128, "seven bits");
-inline unsigned pack_shape(int units, int n_split, int group, bool slots, bool merged) {
+inline unsigned pack_shape(int units, int n_split, int group, bool slots, bool merged, bool merge_last) {
   return static_cast<unsigned>(units) | (static_cast<unsigned>(n_split) << 16) | (static_cast<unsigned>(group - 1) << 23) |
-         (slots ? 1u << 26 : 0u) | (merged ? 1u << 27 : 0u);
+         (slots ? 1u << 26 : 0u) | (merged ? 1u << 27 : 0u) | (merge_last ? 1u << 28 : 0u);
 }
 __device__ __forceinline__ int shape_units(unsigned s) { return static_cast<int>(s & 0xFFFFu); }
 __device__ __forceinline__ int shape_split(unsigned s) { return static_cast<int>((s >> 16) & 127u); }
 __device__ __forceinline__ int shape_group(unsigned s) { return static_cast<int>((s >> 23) & 7u) + 1; }
 __device__ __forceinline__ bool shape_slots(unsigned s) { return (s >> 26) & 1u; }
 __device__ __forceinline__ bool shape_merged(unsigned s) { return (s >> 27) & 1u; }
+__device__ __forceinline__ bool shape_merge_last(unsigned s) { return (s >> 28) & 1u; }
 // Does the sequence of a unit take this step?  (per-sequence timing)
 __device__ __forceinline__ bool takes_part(const DecodeArgs &a, int unit) {
   const int seq = unit / a.n_kv_heads;
@@ -698,9 +700,12 @@ __host__ __device__ constexpr int merge_blocks(int head_dim, int group, int wave
 // before them do nothing.  us per call, right behind the merging blocks / like this: 5 units x 19000 entries of 128 x
 // bf16 14.4 / 12.6, 25 x 4000 14.6 / 12.9, 19 x 8200 18.5 / 16.3; 9 x 24000 of 64 x bf16 18.0 / 14.8; 10 x 13000 of 64 x fp32 18.5 / 15.8;
 // 15 x 13000 of 128 x fp32 41.9 / 37.3.
+// merge_last (see merges_last): the tracking blocks, as many as stream blocks, come before the merging blocks.
 struct Places { int merge, track; };
-__host__ __device__ inline Places places_of(int n_stream, int n_merge) {
-  return {n_stream, n_merge > 0 ? (n_stream + n_merge + 7) & ~7 : n_stream};
+__host__ __device__ inline Places places_of(int n_stream, int n_merge, bool merge_last) {
+  if (n_merge == 0) return {n_stream, n_stream};
+  const int track = (n_stream + (merge_last ? 0 : n_merge) + 7) & ~7;
+  return {merge_last ? track + n_stream : n_stream, track};
 }
 // The output elements 32 columns .. + 31 of a unit of n blocks (kPairMax < n <= 8 N), merged by one wave: lane (c, g)
 // reads the elements 4 c .. 4 c + 3 of the records g, g + 8, ..., and the eight lanes of a column merge across the wave,
@@ -826,8 +831,8 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   const int n_stream = n_split * units_call;
   const bool merged = kSplit == 0 && shape_merged(shape);   // a unit's partials are merged by blocks of their own
   const int per_merge = merge_waves(n_split);
-  const Places places = places_of(n_stream, merged ? merge_blocks(D, G, per_merge) * units_call : 0);
-  if (static_cast<int>(blockIdx.x) >= places.track) {
+  const Places places = places_of(n_stream, merged ? merge_blocks(D, G, per_merge) * units_call : 0, shape_merge_last(shape));
+  if (static_cast<int>(blockIdx.x) >= places.track && static_cast<int>(blockIdx.x) < places.track + n_stream) {
     // tracking of the previous call: n_split blocks per unit, spread over the compute units
     // like the stream blocks
     if (kListWaves && threadIdx.x >= kBlock) return;  // (the tracking has no use for list waves)
@@ -879,10 +884,11 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // wave-uniform: scalar branches below
-  if (merged && static_cast<int>(blockIdx.x) >= places.merge) {
+  if (merged && static_cast<int>(blockIdx.x) >= n_stream) {
+    if (static_cast<int>(blockIdx.x) < places.merge) return;
     const BlockPlace at = block_place<0>(blockIdx.x - places.merge, 2, units_call);
     const int columns = at.split * per_merge + wave;
-    if (wave >= per_merge || columns >= G * (D / 32)) return;   // (the blocks before the tracking blocks among them)
+    if (wave >= per_merge || columns >= G * (D / 32)) return;   // (a block between the merging and the tracking blocks among them)
     if (slots_on && !takes_part(args_from_here<T>(), at.unit)) return;
     CallArgs<T> a;
     a.read();
@@ -1613,6 +1619,19 @@ int merging_blocks(int units, int n_sub, int n_split, int group, bool f32, int h
   return static_cast<long long>(n_split) * units + n <= fused_slots(fused_wave_run(n_sub, n_split), f32, head_dim) + compute_units() / 10 ? static_cast<int>(n) : 0;
 }
 
+// Do they come behind the tracking blocks?  They have nothing to do until the stream ends, but where not all blocks fit the chip
+// at once they hold places that tracking blocks then wait for until others of their kind end, and the blocks of a unit get
+// out of step.  us per call, merging blocks first / last: 25 units x 19000 entries of 128 x fp32 (600 blocks for 512 places)
+// 99.2 / 93.0, 17 x 19000 (7 heads, 629) 66.5 / 61.2, 20 x 13000 of 128 x bf16 (8 heads, 640) 29.8 / 27.1.  First where all fit, or all but
+// a tenth of the places: they start later otherwise (8 x 8200 of 128 x bf16 8.8 / 9.0, 20 x 10500 of 64 x bf16 13.5 / 13.9, 14 x
+// 19000 of 128 x fp32, 560 blocks, 55.3 / 56.4), and where two stream blocks on a compute unit leave the tracking blocks no places
+// in any order (56 x 8200 of 128 x bf16 45.9 / 48.0).  Only with tracking blocks in the launch: their number is taken as that of the stream
+// blocks.
+bool merges_last(int n_stream, int n_tracking, int n_merge, int run, bool f32, int head_dim) {
+  const long long slots = fused_slots(run, f32, head_dim), others = static_cast<long long>(n_stream) + n_tracking;
+  return n_merge > 0 && n_tracking > 0 && others <= slots && 10 * (others + n_merge) > 11 * slots;
+}
+
 template <typename T, int D>
 hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) {
   if (ev) (void)hipEventRecord(ev[0], stream);
@@ -1626,15 +1645,16 @@ hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) 
   const T *kn = static_cast<const T *>(a.k_new), *vn = static_cast<const T *>(a.v_new);
   const T *q = static_cast<const T *>(a.q);
   const int n_merge = merging_blocks(units, n_sub, a.n_split, a.group, Rows<T, D>::kF32, D);
-  const unsigned shape = pack_shape(units, a.n_split, a.group, a.slots.prompt_len != nullptr, n_merge > 0);
   const bool long_run = fused_wave_run(n_sub, a.n_split) > kRunMax;
   // list waves (blocks of eight waves) where every block of the launch is resident at once: two
   // such blocks fit a compute unit
   constexpr bool kList = !Rows<T, D>::kWide;
-  const Places places = places_of(sb, n_merge);
-  const int tracking = a.track.valid ? a.n_track * units : 0;
+  const int tracking = a.track.valid ? sb : 0;     // (n_track is n_split)
+  const bool merge_last = merges_last(sb, tracking, n_merge, run, Rows<T, D>::kF32, D);
+  const Places places = places_of(sb, n_merge, merge_last);
+  const unsigned shape = pack_shape(units, a.n_split, a.group, a.slots.prompt_len != nullptr, n_merge > 0, merge_last);
   const bool resident = a.n_split <= kPairMax && sb + tracking <= 2 * compute_units();
-  const dim3 grid(places.track + tracking), block(kBlock), block_l(kList ? 2 * kBlock : kBlock);
+  const dim3 grid((merge_last ? places.merge + n_merge : places.track + tracking)), block(kBlock), block_l(kList ? 2 * kBlock : kBlock);
 #define LAZYEV_LAUNCH(block, ...) \
   hipLaunchKernelGGL((decode_fused_kernel<T, D, __VA_ARGS__>), grid, block, lds_all, stream, kc, vc, kn, vn, q, a.n_old, a.capacity, shape, a)
 #define LAZYEV_SPLIT(n) \
@@ -1768,9 +1788,10 @@ int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   return n;
 }
 
-void decode_fused_places(int units, int n_sub, int n_split, int group, bool f32, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track) {
+void decode_fused_places(int units, int n_sub, int n_split, int group, bool tracking, bool f32, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track) {
+  const int sb = units * n_split;
   *n_merge = merging_blocks(units, n_sub, n_split, group, f32, head_dim);
-  const Places p = places_of(units * n_split, *n_merge);
+  const Places p = places_of(sb, *n_merge, merges_last(sb, tracking ? sb : 0, *n_merge, fused_wave_run(n_sub, n_split), f32, head_dim));
   *merge = p.merge;
   *track = p.track;
 }
@@ -1839,7 +1860,7 @@ hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stre
 hipError_t launch_decode_fused(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) {
   const int units = a.batch * a.n_kv_heads;
   if (a.group > kHeadPad || a.n_split < 1 ||
-      a.n_split > kFusedSplitMax || decode_fused_records_of(a.n_split) > a.rec_per_unit || a.n_track < 1 || !a.logits_out ||
+      a.n_split > kFusedSplitMax || decode_fused_records_of(a.n_split) > a.rec_per_unit || a.n_track != a.n_split || !a.logits_out ||
       !a.ws.part_rec || !a.ws.fault || a.seq == 0 || a.seq > kSeqCaptured ||
       !a.stat_out || a.p_stride < (a.n_old + 16) / 16 * 16 ||
       (a.track.valid && (a.track.units != units || !a.track.logits || !a.track.stat ||

@@ -130,7 +130,7 @@ struct DecodeArgs {
   Workspace ws;
   unsigned long long *activation_counter;   // this layer's [units][slice_max] counters
   int32_t rec_per_unit;                     // fused kernel: records per unit in ws.part_rec (decode_fused_records_of)
-  int32_t n_track;                          // fused kernel: tracking blocks per unit (when a call is tracked)
+  int32_t n_track;                          // fused kernel: tracking blocks per unit (when a call is tracked), as many as stream blocks
   uint32_t seq;                             // fused kernel: number of this launch (1 .. decode_fused_seq_max, or that of captured calls), the stamp of its records
   uint32_t spin_ticks;                      // fused kernel: longest wait for a record, in 10 ns ticks
   // fused kernel: where this call's logits and statistics go, and the previous call to track
@@ -215,8 +215,8 @@ int decode_fused_records_of(int n_split);     // most records that a unit of so 
 int decode_fused_records_needed(int units, int capacity);   // most records per unit that decode_fused_split asks for
 int decode_fused_records_held(int units, int capacity, size_t bytes);   // most records per unit of use that `bytes` hold for all units
 int decode_fused_split(int units, int n_sub, bool f32, int head_dim);   // blocks per unit of a call over n_sub sub-tiles of 16 entries
-// block numbers at which a launch's merging blocks (n_merge of them, 0: none) and its tracking blocks begin
-void decode_fused_places(int units, int n_sub, int n_split, int group, bool f32, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track);
+// block numbers at which a launch's merging blocks (n_merge of them, 0: none) and, if it has any, its tracking blocks begin
+void decode_fused_places(int units, int n_sub, int n_split, int group, bool tracking, bool f32, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track);
 hipError_t launch_clear_records(unsigned long long *rec, int units, int rec_per_unit, int n_records, hipStream_t stream);
 hipError_t launch_track(const TrackArgs &k, hipStream_t stream);
 hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stream);

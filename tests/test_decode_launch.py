@@ -5,11 +5,11 @@ import ctypes as C
 import pytest
 
 
-def _places(lib, units, n_sub, n_split, group, f32, d):
-    fn = getattr(lib, "_ZN6lazyev19decode_fused_placesEiiiibiPiS0_S0_")   # lazyev::decode_fused_places (kernels.h)
-    fn.restype, fn.argtypes = None, [C.c_int] * 4 + [C.c_bool, C.c_int] + [C.POINTER(C.c_int32)] * 3
+def _places(lib, units, n_sub, n_split, group, tracking, f32, d):
+    fn = getattr(lib, "_ZN6lazyev19decode_fused_placesEiiiibbiPiS0_S0_")   # lazyev::decode_fused_places (kernels.h)
+    fn.restype, fn.argtypes = None, [C.c_int] * 4 + [C.c_bool, C.c_bool, C.c_int] + [C.POINTER(C.c_int32)] * 3
     merge, n_merge, track = C.c_int32(-1), C.c_int32(-1), C.c_int32(-1)
-    fn(units, n_sub, n_split, group, f32, d, C.byref(merge), C.byref(n_merge), C.byref(track))
+    fn(units, n_sub, n_split, group, tracking, f32, d, C.byref(merge), C.byref(n_merge), C.byref(track))
     return merge.value, n_merge.value, track.value
 
 
@@ -24,7 +24,7 @@ def test_merging_and_tracking_blocks(lazyev_lib, d, group, f32):
         for n_split in range(1, 65):
             stream = units * n_split
             for run in (1, 15, 30):
-                merge, n_merge, track = _places(lazyev_lib.lib, units, 4 * n_split * run, n_split, group, f32, d)
+                merge, n_merge, track = _places(lazyev_lib.lib, units, 4 * n_split * run, n_split, group, True, f32, d)
                 if n_split <= 8 or (run == 30 and stream > 512 + 25):
                     assert n_merge == 0
                 if n_split > 8 and stream <= 256:  # (compute units of the chip, and what is assumed without one)
@@ -34,4 +34,9 @@ def test_merging_and_tracking_blocks(lazyev_lib, d, group, f32):
                     continue
                 # a wave merges 32 output elements, a block has two or four such waves
                 assert n_merge % units == 0 and group * (d // 32) <= n_merge // units * (4 if n_split <= 16 else 2) < group * (d // 32) + 4
-                assert merge == stream and 0 <= track - (stream + n_merge) < 8 and track % 8 == 0
+                assert track % 8 == 0
+                if merge == stream:
+                    assert 0 <= track - (stream + n_merge) < 8
+                else:                              # merging blocks last, behind as many tracking blocks as stream blocks
+                    assert _places(lazyev_lib.lib, units, 4 * n_split * run, n_split, group, False, f32, d)[0] == stream
+                    assert 0 <= track - stream < 8 and merge == track + stream and 2 * stream + n_merge > 563

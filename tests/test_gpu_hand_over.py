@@ -202,3 +202,37 @@ def test_more_than_eight_blocks_where_the_chip_is_full(lazyev_lib, dtype, d, bat
         eng.close()
     for x, y in zip(*states):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("dtype,d,batch,blocks,N", [("fp32", 128, 12, 10, 2000), ("fp32", 128, 9, 13, 2000),
+                                                    ("bf16", 128, 10, 12, 13000), ("bf16", 64, 12, 10, 11700), ("fp32", 64, 12, 10, 11700)])
+def test_merging_blocks_behind_the_tracking_blocks(lazyev_lib, dtype, d, batch, blocks, N):
+    """Launches of more blocks than the chip holds at once, whose merging blocks come last (the first call tracks nothing, so its
+    merging blocks come first).  Outputs of sampled sequences against fp64
+    softmax attention; TS / MRI / pos and the activations as with three blocks a unit."""
+    H, group, steps = 2, 8, 4
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    states = []
+    for b in (3, blocks):
+        gen = torch.Generator(device="cuda").manual_seed(17)
+        eng = lazyev_lib.LazyEviction(1, batch, group * H, H, d, N + 100, 64, N, 8.0 / N, dtype=dt)
+        eng.k_cache[:, :, :, :N].normal_(generator=gen)
+        eng.v_cache[:, :, :, :N].normal_(generator=gen)
+        eng.init()
+        eng.set_target_blocks(b * batch * H)
+        out = torch.zeros((batch, group * H, d), dtype=dt, device="cuda")
+        for t in range(1, steps + 1):
+            q, kn, vn = (torch.empty((batch, h, d), device="cuda").normal_(generator=gen).to(dt) for h in (group * H, H, H))
+            eng.decode_step(0, t, q, kn, vn, out)
+            for s in (0, batch - 1):
+                k, v = eng.k_cache[0, s, :, :N + t].double(), eng.v_cache[0, s, :, :N + t].double()
+                p = torch.softmax(torch.matmul(q[s].double().view(H, group, d), k.transpose(1, 2).contiguous()) * d ** -0.5, dim=-1)
+                ref = torch.matmul(p, v).view(group * H, d)
+                err = float(((out[s].double() - ref).norm(dim=1) / ref.norm(dim=1)).max())
+                # (bf16: two roundings, as above; fp32: sums of some thousand terms)
+                assert err < (1e-5 if dt == torch.float32 else 2 * 2.0 ** -8), (b, s, t, err)
+        states.append([eng.stats()["n_activations"]] + [x[0, :, :, :N + steps].clone() for x in (eng.ts, eng.mri, eng.pos)])
+        eng.close()
+    assert states[0][0] == states[1][0]
+    for x, y in zip(states[0][1:], states[1][1:]):
+        assert torch.equal(x, y)
