@@ -713,10 +713,12 @@ __host__ __device__ inline Places places_of(int n_stream, int n_merge, bool merg
 // block's end to the launch's.  First one word of every record is looked at, until half of them are there: blocks of
 // equal work end close together, and a look at all words of 32 records is 16 loads that hold up the ones that will find them
 // (from the first record on: 8 units x 2080 5.96 / 5.92, 4 x 3000 6.46 / 6.03; only when all are there 6.5 / 6.7).
-// Before that the wave sleeps for what a run of sub-tiles takes at least, 0.5 us each (128-byte rows 0.25) from the third on: the
-// looks go to memory, where they are in the stream's way (16 units x 24000 39.6 -> 38.8).
-// It waits for blocks of lower indices only, like any reader of records, but for as long as a whole run takes: until the
-// first records are there the limit is 64 times the one for the others.
+// Before that the wave sleeps for what a run of sub-tiles takes at least, 0.5 us each (128-byte rows 0.25) from the third on, and
+// looks at one word of one record where the run is long: the looks go to memory, where they are in the stream's way (16 units x
+// 24000 39.6 -> 38.8 with the sleep; 15 x 24000 of 128 x fp32 72.6 -> 71.8, 20 x 24000 of 128 x bf16 49.4 -> 49.1 with the single word; shorter runs
+// lose by it, 9 x 13000 of 64 x bf16 10.1 / 10.4).
+// It waits for blocks of lower indices only, like any reader of records, but for as long as a whole run takes: the limit of
+// the single word and that of the looks until half of the records are there are 64 times the one for the others.
 template <typename T, int D, int N, typename Args>
 __device__ __forceinline__ void merge_columns(const Args &a, int unit, int G, int n, int run, int columns) {
   constexpr bool kPrecise = Rows<T, D>::kPrecise;
@@ -730,6 +732,19 @@ __device__ __forceinline__ void merge_columns(const Args &a, int unit, int G, in
   {
     auto base = (const __attribute__((address_space(1))) char *)recs;
     __asm__ volatile("" : "+s"(base));
+    // (long runs: a single word until the record of the unit's first block is there)
+    while (run > kRunMax) {
+      unsigned long long w = 0;
+      if (lane == 0)
+        w = __hip_atomic_load((const __attribute__((address_space(1))) unsigned long long *)(base + rec_at(columns * 8)), __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
+      if (__builtin_amdgcn_ballot_w64(static_cast<unsigned>(w >> 48) == a.seq) != 0) break;
+      const unsigned long long now = wall_clock64();
+      if (t_first == 0) t_first = now;
+      if (now - t_first >= 64ull * a.spin_ticks) break;
+      __builtin_amdgcn_s_sleep(16);
+    }
+    t_first = 0;
     const unsigned at = static_cast<unsigned>(min(lane, n - 1)) * (kRecWords * 8) + rec_at(columns * 8);
     for (;;) {
       const unsigned long long w = __hip_atomic_load((const __attribute__((address_space(1))) unsigned long long *)(base + at),

@@ -37,7 +37,7 @@ def _run(lazyev_lib, blocks, N, steps, group):
 
 
 @pytest.mark.parametrize("N,group,blocks", [(4080, 7, (1, 2, 3, 5, 6, 7, 8, 9, 15, 16, 17, 24, 32, 33, 63, 64, 0)),
-                                            (150, 4, (1, 2, 3, 0)), (3, 1, (1, 0)), (62, 7, (2, 0))])
+                                            (150, 4, (1, 2, 3, 0)), (3, 1, (1, 0)), (62, 7, (2, 0)), (13000, 7, (8, 9, 16))])
 def test_every_number_of_blocks_gives_the_same_result(lazyev_lib, N, group, blocks):
     """Outputs against fp64 softmax attention; TS / MRI / pos equal whatever the split (a decision
     within rounding of alpha could differ: about one in 1e7, of 1e5 here)."""
