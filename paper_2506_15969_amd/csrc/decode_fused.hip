@@ -1730,10 +1730,12 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 // Blocks per unit where there is room for more than kPairMax of them (`most`) and the cache has more than 43 sub-tiles;
 // 0: kPairMax or fewer (decode_fused_split).  us per call, 4 query heads to a KV head, one count / another:
 //   * all that there is room for up to 15: 20 units x 2000 / 8200 / 20000 entries 8 / 12 8.1 / 7.0, 18.0 / 16.7, 44.0 /
-//     41.6 (64 x bf16 8.1 / 6.8, 14.5 / 12.1, 30.7 / 27.9; 128 x fp32 14.5 / 12.5, x 4000 22.5 / 18.8); but eleven of
-//     22, which lie on the XCDs unevenly, only while the call is a chain: 22 units x 2000 / 4000 / 8200 8 / 11 8.4 / 7.8,
-//     11.8 / 12.4, 19.3 / 20.2 (64 x bf16 x 4000 / 8200 10.3 / 9.6, 14.9 / 15.3; fp32 rows have enough to do at any
-//     length); nine of 28 gain 4 % at 1000 entries, nothing at 2000, and lose 6 % where the sequences' lengths differ.
+//     41.6 (64 x bf16 8.1 / 6.8, 14.5 / 12.1, 30.7 / 27.9; 128 x fp32 14.5 / 12.5, x 4000 22.5 / 18.8).  22 units x 2000 / 8200 /
+//     13000 / 19500 8 / 11 7.7 / 6.7, 18.6 / 17.8, 30.6 / 27.8, 46.4 / 43.0 (64 x bf16 x 2000 / 13000 7.9 / 6.8, 22.1 / 19.1; two blocks to a
+//     compute unit, 23, x 24000 53.3 / 52.7 with 11, 64 x bf16 34.0 / 35.5, but with 7 heads 34.8 / 34.3).  28 units x 1000 / 2000 / 8200 / 16000 8
+//     / 9 6.2 / 5.8, 7.8 / 7.1, 21.6 / 21.7, 46.4 / 45.4 (7 heads); fp32 (64) 7.7 / 6.9, 9.8 / 8.9, 24.1 / 23.1, 51.9 / 50.1;
+//     sequences of their own lengths 6.6 / 6.0, 7.6 / 7.0, 18.4 / 18.2, 37.2 / 37.8.  Nine only until two blocks to a compute
+//     unit take over: 26 units x 24000 9 / 19 63.7 / 61.5, fp32 (64) 71.3 / 63.5, (128) x 17000 88.7 / 86.2.
 //   * beyond, 16, 24, 32, 48 or 64 (a merging wave reads a record per lane and eight blocks): 12 units x 2000 / 8200 16 /
 //     21 6.0 / 6.3, 11.6 / 13.2; 10 units x 8200 24 / 25 10.3 / 12.0; 6 units x 8200 32 / 42 8.0 / 9.0; of 11 and 12 units
 //     20 for long caches: 11 x 12000 16 / 20 17.1 / 16.8 (64 x bf16 13.5 / 10.9, fp32 (64) 20.7 / 16.6, (128) 33.9 / 31.4).
@@ -1742,11 +1744,11 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //     (128) 9.0 / 7.7.
 //   * more than 32 from three on: 4 units x 4000 / 6000 / 12000 32 / 64 6.0 / 6.3, 6.5 / 6.4, 9.0 / 8.4; 5 units x 8200 32 /
 //     51 8.5 / 8.2; 4 units of 128 x fp32 x 3000 32 / 48 9.2 / 8.6, x 4000 32 / 64 9.5 / 8.9.
+static int two_per_compute_unit_from(bool f32, int head_dim) { return !f32 && head_dim == 128 ? 1200 : 1024; }
 static int merged_split(int n_sub, bool f32, int head_dim, int most) {
   const int by_length = (n_sub + kWaves - 1) / kWaves;
   if (most <= kPairMax || n_sub < 44) return 0;
-  if (most == 9) return 0;
-  if (most == 11 && !f32 && n_sub > (head_dim == 64 ? 320 : 160)) return 0;
+  if (most == kPairMax + 1 && n_sub >= two_per_compute_unit_from(f32, head_dim)) return 0;
   int n = most;
   if (most >= 16) {
     const bool wide = f32 && head_dim == 128;
@@ -1799,7 +1801,7 @@ int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   if (n > by_work) n = by_work;
   const int n2 = 2 * kUnitsOfChip / units;
   // (28 units x 17000 of 128 x bf16: 8 blocks 48.0, 18 50.8; x 20000 56.1, 55.3; 128 x fp32 x 17000 96.8, 93.7)
-  if (units < kUnitsOfChip && n_sub >= (n == kPairMax && !f32 && head_dim == 128 ? 1200 : 32 * kWaves * n) && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2;
+  if (units < kUnitsOfChip && n_sub >= (n == kPairMax ? two_per_compute_unit_from(f32, head_dim) : 32 * kWaves * n) && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2;
   return n;
 }
 

@@ -40,3 +40,14 @@ def test_merging_and_tracking_blocks(lazyev_lib, d, group, f32):
                 else:                              # merging blocks last, behind as many tracking blocks as stream blocks
                     assert _places(lazyev_lib.lib, units, 4 * n_split * run, n_split, group, False, f32, d)[0] == stream
                     assert 0 <= track - stream < 8 and merge == track + stream and 2 * stream + n_merge > 563
+
+
+@pytest.mark.parametrize("d,f32", [(128, False), (64, False), (64, True), (128, True)])
+def test_nine_to_fifteen_blocks_where_there_is_room(lazyev_lib, d, f32):
+    """As many blocks a unit as the chip has room for (up to fifteen), from 44 sub-tiles to
+    16384 entries: never a part of the chip idle for a rule about one number of units."""
+    fn = getattr(lazyev_lib.lib, "_ZN6lazyev18decode_fused_splitEiibi")    # lazyev::decode_fused_split (kernels.h)
+    fn.restype, fn.argtypes = C.c_int, [C.c_int, C.c_int, C.c_bool, C.c_int]
+    for units in range(17, 29):
+        for n_sub in (44, 63, 64, 128, 161, 321, 513, 640, 1023):
+            assert fn(units, n_sub, f32, d) == min(256 // units, (n_sub + 3) // 4), (units, n_sub)
