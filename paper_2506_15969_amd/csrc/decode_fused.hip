@@ -1642,7 +1642,11 @@ int merging_blocks(int units, int n_sub, int n_split, int group, bool f32, int h
 // 19000 of 128 x fp32, 560 blocks, 55.3 / 56.4), and where two stream blocks on a compute unit leave the tracking blocks no places
 // in any order (56 x 8200 of 128 x bf16 45.9 / 48.0).  Only with tracking blocks in the launch: their number is taken as that of the stream
 // blocks.
-bool merges_last(int n_stream, int n_tracking, int n_merge, int run, bool f32, int head_dim) {
+// First with sequences of their own lengths: places become free where short ones end, and tracking blocks that start there are
+// less in the way of the others' streams than from the start on; last / first, 7 query heads, 16 units x 20000 32.9 / 28.7, 20 x 16000 32.7 /
+// 29.0, 24 x 12000 30.2 / 27.6, 28 x 12000 34.1 / 29.8 (4 heads 30.5 / 28.7).
+bool merges_last(int n_stream, int n_tracking, int n_merge, int run, bool f32, int head_dim, bool own_lengths) {
+  if (own_lengths) return false;
   const long long slots = fused_slots(run, f32, head_dim), others = static_cast<long long>(n_stream) + n_tracking;
   return n_merge > 0 && n_tracking > 0 && others <= slots && 10 * (others + n_merge) > 11 * slots;
 }
@@ -1665,7 +1669,7 @@ hipError_t launch_rows(const DecodeArgs &a, hipStream_t stream, hipEvent_t *ev) 
   // such blocks fit a compute unit
   constexpr bool kList = !Rows<T, D>::kWide;
   const int tracking = a.track.valid ? sb : 0;     // (n_track is n_split)
-  const bool merge_last = merges_last(sb, tracking, n_merge, run, Rows<T, D>::kF32, D);
+  const bool merge_last = merges_last(sb, tracking, n_merge, run, Rows<T, D>::kF32, D, a.slots.prompt_len != nullptr);
   const Places places = places_of(sb, n_merge, merge_last);
   const unsigned shape = pack_shape(units, a.n_split, a.group, a.slots.prompt_len != nullptr, n_merge > 0, merge_last);
   const bool resident = a.n_split <= kPairMax && sb + tracking <= 2 * compute_units();
@@ -1735,7 +1739,7 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //     compute unit, 23, x 24000 53.3 / 52.7 with 11, 64 x bf16 34.0 / 35.5, but with 7 heads 34.8 / 34.3).  28 units x 1000 / 2000 / 8200 / 16000 8
 //     / 9 6.2 / 5.8, 7.8 / 7.1, 21.6 / 21.7, 46.4 / 45.4 (7 heads); fp32 (64) 7.7 / 6.9, 9.8 / 8.9, 24.1 / 23.1, 51.9 / 50.1;
 //     sequences of their own lengths 6.6 / 6.0, 7.6 / 7.0, 18.4 / 18.2, 37.2 / 37.8.  Nine only until two blocks to a compute
-//     unit take over: 26 units x 24000 9 / 19 63.7 / 61.5, fp32 (64) 71.3 / 63.5, (128) x 17000 88.7 / 86.2.
+//     unit take over: 28 units x 18500 of their own lengths 9 / 18 43.8 / 41.6, 26 units x 24000 9 / 19 63.7 / 61.5 (64 x bf16 40.6 / 39.7, x 16300 28.0 / 29.0), fp32 (64) 71.3 / 63.5, (128) x 17000 88.7 / 86.2.
 //   * beyond, 16, 24, 32, 48 or 64 (a merging wave reads a record per lane and eight blocks): 12 units x 2000 / 8200 16 /
 //     21 6.0 / 6.3, 11.6 / 13.2; 10 units x 8200 24 / 25 10.3 / 12.0; 6 units x 8200 32 / 42 8.0 / 9.0; of 11 and 12 units
 //     20 for long caches: 11 x 12000 16 / 20 17.1 / 16.8 (64 x bf16 13.5 / 10.9, fp32 (64) 20.7 / 16.6, (128) 33.9 / 31.4).
@@ -1744,11 +1748,11 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //     (128) 9.0 / 7.7.
 //   * more than 32 from three on: 4 units x 4000 / 6000 / 12000 32 / 64 6.0 / 6.3, 6.5 / 6.4, 9.0 / 8.4; 5 units x 8200 32 /
 //     51 8.5 / 8.2; 4 units of 128 x fp32 x 3000 32 / 48 9.2 / 8.6, x 4000 32 / 64 9.5 / 8.9.
-static int two_per_compute_unit_from(bool f32, int head_dim) { return !f32 && head_dim == 128 ? 1200 : 1024; }
-static int merged_split(int n_sub, bool f32, int head_dim, int most) {
+static int two_per_compute_unit_from(bool f32, bool own_lengths) { return f32 || own_lengths ? 1024 : 1200; }
+static int merged_split(int n_sub, bool f32, int head_dim, bool own_lengths, int most) {
   const int by_length = (n_sub + kWaves - 1) / kWaves;
   if (most <= kPairMax || n_sub < 44) return 0;
-  if (most == kPairMax + 1 && n_sub >= two_per_compute_unit_from(f32, head_dim)) return 0;
+  if (most == kPairMax + 1 && n_sub >= two_per_compute_unit_from(f32, own_lengths)) return 0;
   int n = most;
   if (most >= 16) {
     const bool wide = f32 && head_dim == 128;
@@ -1786,11 +1790,11 @@ static int merged_split(int n_sub, bool f32, int head_dim, int most) {
 //     11.2 / 12.9, 36.6 / 38.2, 118 / 125; 240 units 12.5 / 15.2, 44.8 / 44.5, 139 / 143), as it is for fp32 rows
 //     (192 units x 2200, 64 43.8 / 44.4, 128 79.3 / 84.9); bf16 rows of 64 would gain from two (176 units x 2200 24.3
 //     / 22.5).
-int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
+int decode_fused_split(int units, int n_sub, bool f32, int head_dim, bool own_lengths) {
   constexpr int kUnitsOfChip = 256;                // compute units of the chip that the figures above are from
   int n = kUnitsOfChip / units;
   if (n < 1) n = 1;
-  const int merged = merged_split(n_sub, f32, head_dim, n < kFusedSplitMax ? n : kFusedSplitMax);
+  const int merged = merged_split(n_sub, f32, head_dim, own_lengths, n < kFusedSplitMax ? n : kFusedSplitMax);
   if (merged > kPairMax) return merged;
   if (n > kPairMax) n = kPairMax;
   const bool fewer = f32 && n == kPairMax && (head_dim == 128 || n_sub > 72) && fused_wave_run(n_sub, n) < fused_wave_run(n_sub, 6);
@@ -1801,14 +1805,14 @@ int decode_fused_split(int units, int n_sub, bool f32, int head_dim) {
   if (n > by_work) n = by_work;
   const int n2 = 2 * kUnitsOfChip / units;
   // (28 units x 17000 of 128 x bf16: 8 blocks 48.0, 18 50.8; x 20000 56.1, 55.3; 128 x fp32 x 17000 96.8, 93.7)
-  if (units < kUnitsOfChip && n_sub >= (n == kPairMax ? two_per_compute_unit_from(f32, head_dim) : 32 * kWaves * n) && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2;
+  if (units < kUnitsOfChip && n_sub >= (n == kPairMax ? two_per_compute_unit_from(f32, own_lengths) : 32 * kWaves * n) && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2;
   return n;
 }
 
-void decode_fused_places(int units, int n_sub, int n_split, int group, bool tracking, bool f32, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track) {
+void decode_fused_places(int units, int n_sub, int n_split, int group, bool tracking, bool f32, int head_dim, bool own_lengths, int32_t *merge, int32_t *n_merge, int32_t *track) {
   const int sb = units * n_split;
   *n_merge = merging_blocks(units, n_sub, n_split, group, f32, head_dim);
-  const Places p = places_of(sb, *n_merge, merges_last(sb, tracking ? sb : 0, *n_merge, fused_wave_run(n_sub, n_split), f32, head_dim));
+  const Places p = places_of(sb, *n_merge, merges_last(sb, tracking ? sb : 0, *n_merge, fused_wave_run(n_sub, n_split), f32, head_dim, own_lengths));
   *merge = p.merge;
   *track = p.track;
 }

@@ -214,9 +214,10 @@ uint32_t decode_fused_seq_captured();         // ... and the number of every cap
 int decode_fused_records_of(int n_split);     // most records that a unit of so many blocks hands over
 int decode_fused_records_needed(int units, int capacity);   // most records per unit that decode_fused_split asks for
 int decode_fused_records_held(int units, int capacity, size_t bytes);   // most records per unit of use that `bytes` hold for all units
-int decode_fused_split(int units, int n_sub, bool f32, int head_dim);   // blocks per unit of a call over n_sub sub-tiles of 16 entries
+// blocks per unit of a call over n_sub sub-tiles of 16 entries (own_lengths: with per-sequence timing, of its longest sequence)
+int decode_fused_split(int units, int n_sub, bool f32, int head_dim, bool own_lengths);
 // block numbers at which a launch's merging blocks (n_merge of them, 0: none) and, if it has any, its tracking blocks begin
-void decode_fused_places(int units, int n_sub, int n_split, int group, bool tracking, bool f32, int head_dim, int32_t *merge, int32_t *n_merge, int32_t *track);
+void decode_fused_places(int units, int n_sub, int n_split, int group, bool tracking, bool f32, int head_dim, bool own_lengths, int32_t *merge, int32_t *n_merge, int32_t *track);
 hipError_t launch_clear_records(unsigned long long *rec, int units, int rec_per_unit, int n_records, hipStream_t stream);
 hipError_t launch_track(const TrackArgs &k, hipStream_t stream);
 hipError_t launch_track_flush(const FlushArgs &f, int n_layers, hipStream_t stream);

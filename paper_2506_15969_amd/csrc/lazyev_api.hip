@@ -531,7 +531,7 @@ int lazyev_decode_step(lazyev_ctx *ctx, int32_t layer, int32_t t, const void *q,
     // fused kernel: n_split blocks of four waves per unit, every wave a run of 16-entry sub-tiles
     const int n_sub = (n_old + 1 + 15) / 16;
     int n_split = (ctx->target_blocks + ctx->units / 2) / ctx->units;
-    if (!ctx->target_blocks_set) n_split = lazyev::decode_fused_split(ctx->units, n_sub, c.dtype == LAZYEV_DTYPE_FP32, c.head_dim);
+    if (!ctx->target_blocks_set) n_split = lazyev::decode_fused_split(ctx->units, n_sub, c.dtype == LAZYEV_DTYPE_FP32, c.head_dim, ctx->slots_on);
     if (n_split > (n_sub + 3) / 4) n_split = (n_sub + 3) / 4;
     if (n_split > lazyev::decode_fused_split_max()) n_split = lazyev::decode_fused_split_max();
     a.rec_per_unit = ctx->rec_per_unit;

@@ -5,11 +5,11 @@ import ctypes as C
 import pytest
 
 
-def _places(lib, units, n_sub, n_split, group, tracking, f32, d):
-    fn = getattr(lib, "_ZN6lazyev19decode_fused_placesEiiiibbiPiS0_S0_")   # lazyev::decode_fused_places (kernels.h)
-    fn.restype, fn.argtypes = None, [C.c_int] * 4 + [C.c_bool, C.c_bool, C.c_int] + [C.POINTER(C.c_int32)] * 3
+def _places(lib, units, n_sub, n_split, group, tracking, f32, d, own_lengths=False):
+    fn = getattr(lib, "_ZN6lazyev19decode_fused_placesEiiiibbibPiS0_S0_")   # lazyev::decode_fused_places (kernels.h)
+    fn.restype, fn.argtypes = None, [C.c_int] * 4 + [C.c_bool, C.c_bool, C.c_int, C.c_bool] + [C.POINTER(C.c_int32)] * 3
     merge, n_merge, track = C.c_int32(-1), C.c_int32(-1), C.c_int32(-1)
-    fn(units, n_sub, n_split, group, tracking, f32, d, C.byref(merge), C.byref(n_merge), C.byref(track))
+    fn(units, n_sub, n_split, group, tracking, f32, d, own_lengths, C.byref(merge), C.byref(n_merge), C.byref(track))
     return merge.value, n_merge.value, track.value
 
 
@@ -46,8 +46,23 @@ def test_merging_and_tracking_blocks(lazyev_lib, d, group, f32):
 def test_nine_to_fifteen_blocks_where_there_is_room(lazyev_lib, d, f32):
     """As many blocks a unit as the chip has room for (up to fifteen), from 44 sub-tiles to
     16384 entries: never a part of the chip idle for a rule about one number of units."""
-    fn = getattr(lazyev_lib.lib, "_ZN6lazyev18decode_fused_splitEiibi")    # lazyev::decode_fused_split (kernels.h)
-    fn.restype, fn.argtypes = C.c_int, [C.c_int, C.c_int, C.c_bool, C.c_int]
+    fn = getattr(lazyev_lib.lib, "_ZN6lazyev18decode_fused_splitEiibib")    # lazyev::decode_fused_split (kernels.h)
+    fn.restype, fn.argtypes = C.c_int, [C.c_int, C.c_int, C.c_bool, C.c_int, C.c_bool]
     for units in range(17, 29):
         for n_sub in (44, 63, 64, 128, 161, 321, 513, 640, 1023):
-            assert fn(units, n_sub, f32, d) == min(256 // units, (n_sub + 3) // 4), (units, n_sub)
+            assert fn(units, n_sub, f32, d, False) == min(256 // units, (n_sub + 3) // 4), (units, n_sub)
+
+
+@pytest.mark.parametrize("group", [1, 4, 7, 8])
+def test_sequences_of_their_own_lengths(lazyev_lib, group):
+    """Merging blocks stay before the tracking blocks, at every length; two blocks per compute unit from 16384 entries on where
+    nine have room."""
+    fn = getattr(lazyev_lib.lib, "_ZN6lazyev18decode_fused_splitEiibib")
+    fn.restype, fn.argtypes = C.c_int, [C.c_int, C.c_int, C.c_bool, C.c_int, C.c_bool]
+    for units in range(4, 29):
+        for n_sub in (128, 321, 640, 751, 1023, 1024, 1199, 1500):
+            n = fn(units, n_sub, False, 128, True)
+            if units > 25:
+                assert n == (512 // units if n_sub >= 1024 else 9)
+            merge, n_merge, track = _places(lazyev_lib.lib, units, n_sub, n, group, True, False, 128, own_lengths=True)
+            assert merge == units * n and 0 <= track - (merge + n_merge) < 8
