@@ -1817,10 +1817,11 @@ void decode_fused_places(int units, int n_sub, int n_split, int group, bool trac
   *track = p.track;
 }
 
-// A unit of n blocks hands over n - 1 records, or n to blocks that merge them; an area is sized for the larger number.
-// decode_fused_split has at most 512 blocks for all units together (4 MB of records); lazyev_set_target_blocks may ask for
-// more, as far as the area that is there anyway holds them.
-int decode_fused_records_of(int n_split) { return n_split > 1 ? n_split : 0; }
+// A unit of up to kPairMax blocks hands over a record less than it has blocks, one of more a record each (also where its last
+// block merges and hands over none: which it is differs from call to call).  With decode_fused_split's two blocks per
+// compute unit that is an area of 4.5 MB at most; lazyev_set_target_blocks may ask for more, as far as the area that is there
+// anyway holds them.
+int decode_fused_records_of(int n_split) { return n_split > kPairMax ? n_split : n_split - 1; }
 int decode_fused_records_needed(int units, int capacity) {
   const int by_length = ((capacity + 15) / 16 + 3) / 4, by_units = (2 * 256 + units - 1) / units;
   const int n = by_length < by_units ? by_length : by_units;

@@ -66,3 +66,15 @@ def test_sequences_of_their_own_lengths(lazyev_lib, group):
                 assert n == (512 // units if n_sub >= 1024 else 9)
             merge, n_merge, track = _places(lazyev_lib.lib, units, n_sub, n, group, True, False, 128, own_lengths=True)
             assert merge == units * n and 0 <= track - (merge + n_merge) < 8
+
+
+def test_records_of_a_split(lazyev_lib):
+    """A record less than blocks up to eight blocks a unit, from nine on one each; an area of 512 blocks and a record more per unit
+    at most."""
+    of, needed = (getattr(lazyev_lib.lib, n) for n in ("_ZN6lazyev23decode_fused_records_ofEi", "_ZN6lazyev27decode_fused_records_neededEii"))
+    assert [of(n) for n in range(1, 65)] == list(range(8)) + list(range(9, 65))
+    for units in range(1, 1025):
+        assert needed(units, 30000) == of(min(64, -(-512 // units))) and units * needed(units, 30000) < 512 + 64
+        for n_sub in (1, 40, 100, 500, 1100, 1800):
+            split = getattr(lazyev_lib.lib, "_ZN6lazyev18decode_fused_splitEiibib")
+            assert of(split(units, n_sub, False, 128, False)) <= needed(units, 16 * n_sub)
