@@ -1,5 +1,5 @@
 """Partials of a unit handed over between its blocks: up to 8 blocks (an instance of the kernel each) to the unit's last
-one, up to 64 to blocks that merge them, one, two, four or eight records per lane."""
+one, up to 64 to blocks that merge them, two, four or eight records per lane."""
 import numpy as np
 import pytest
 import torch
@@ -107,11 +107,12 @@ def test_launch_numbers_start_over(lazyev_lib):
     eng.close()
 
 
-def test_records_left_a_whole_cycle_of_numbers_ago(lazyev_lib):
-    """Launch 100 has eight blocks per unit; all others up to the next one with that number (eager numbers run from 1 to
-    65534) have two, which leave six of its seven records as they are.  That launch, over other inputs, must not take
-    them for its own: they are cleared when the numbers start over."""
-    L, H, group, N, steps, period = 64, 8, 2, 500, 1030, 65534
+@pytest.mark.parametrize("many,N", [(8, 500), (17, 1100)])
+def test_records_left_a_whole_cycle_of_numbers_ago(lazyev_lib, many, N):
+    """Launch 100 has eight blocks per unit, or seventeen, whose records other blocks merge; all others up to the next one with
+    that number (eager numbers run from 1 to 65534) have two, which leave all but the first of its seven or seventeen records as
+    they are.  That launch, over other inputs, must not take them for its own: they are cleared when the numbers start over."""
+    L, H, group, steps, period = 64, 8, 2, 1030, 65534
     gen = torch.Generator(device="cuda").manual_seed(4)
     eng = lazyev_lib.LazyEviction(L, 1, group * H, H, 128, N + steps, 64, N, 0.05)
     eng.k_cache[:, :, :, :N].normal_(generator=gen)
@@ -123,11 +124,11 @@ def test_records_left_a_whole_cycle_of_numbers_ago(lazyev_lib):
     for t in range(1, steps + 1):
         for layer in range(L):
             launches += 1
-            eight = launches in (100, period + 100)
+            looked_at = launches in (100, period + 100)
             x = launches % 5
-            eng.set_target_blocks((8 if eight else 2) * H)
+            eng.set_target_blocks((many if looked_at else 2) * H)
             eng.decode_step(layer, t, q[x], kn[x], vn[x], out)
-            if eight:
+            if looked_at:
                 k, v = eng.k_cache[layer, 0, :, :N + t].double(), eng.v_cache[layer, 0, :, :N + t].double()
                 p = torch.softmax(torch.matmul(k, q[x, 0].double().view(H, group, 128).transpose(1, 2).contiguous()) / np.sqrt(128.0), dim=1)
                 ref = torch.matmul(p.transpose(1, 2).contiguous(), v).view(group * H, 128)
@@ -137,11 +138,12 @@ def test_records_left_a_whole_cycle_of_numbers_ago(lazyev_lib):
     eng.close()
 
 
-@pytest.mark.parametrize("group,blocks", [(7, 16), (8, 33), (1, 17), (5, 9)])
-def test_merged_blocks_of_sequences_of_their_own_lengths(lazyev_lib, group, blocks):
+@pytest.mark.parametrize("group,blocks,N", [(7, 16, 2300), (8, 33, 2300), (1, 17, 2300), (5, 9, 2300), (8, 40, 33300)])
+def test_merged_blocks_of_sequences_of_their_own_lengths(lazyev_lib, group, blocks, N):
     """More than eight blocks per unit with per-sequence timing: a full cache, one of fewer sub-tiles than the unit has
-    waves, and an empty slot, whose rows of the output stay as they are.  Against fp64 softmax attention."""
-    H, N, steps, lens = 2, 2300, 3, (2300, 70, -1)
+    waves, and an empty slot, whose rows of the output stay as they are; launches that fit the chip, and one that does not.  Against
+    fp64 softmax attention."""
+    H, steps, lens = 2, 3, (N, 70, -1)
     gen = torch.Generator(device="cuda").manual_seed(11)
     eng = lazyev_lib.LazyEviction(1, 3, group * H, H, 128, N + 100, 64, N, 8.0 / N)
     eng.k_cache[:, :, :, :N].normal_(generator=gen)
@@ -236,3 +238,40 @@ def test_merging_blocks_behind_the_tracking_blocks(lazyev_lib, dtype, d, batch, 
     assert states[0][0] == states[1][0]
     for x, y in zip(states[0][1:], states[1][1:]):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("fp32", 64)])
+@pytest.mark.parametrize("blocks,N", [(9, 2200), (17, 2200), (33, 2200), (9, 11700)])
+def test_merging_blocks_report_a_wait_that_ends(lazyev_lib, dtype, d, blocks, N):
+    """Both waits of a merging block, and the one on a single word before them in long runs, with the limit at 0: a block gives
+    up as soon as a look finds a record missing.  Every kernel still ends, the next lazyev_stats says so once, and with the
+    limit back the outputs are right again (against fp64 softmax attention)."""
+    H, group, batch, steps = 2, 4, 2, 12
+    dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(19)
+    eng = lazyev_lib.LazyEviction(1, batch, group * H, H, d, N + 100, 64, N, 8.0 / N, dtype=dt)
+    eng.k_cache[:, :, :, :N].normal_(generator=gen)
+    eng.v_cache[:, :, :, :N].normal_(generator=gen)
+    eng.init()
+    eng.set_target_blocks(blocks * batch * H)
+    out = torch.zeros((batch, group * H, d), dtype=dt, device="cuda")
+    eng.set_spin_ticks(0)
+    for t in range(1, steps + 1):
+        if t == steps - 1:
+            torch.cuda.synchronize()
+            with pytest.raises(lazyev_lib.LazyevError) as err:
+                eng.stats()
+            assert err.value.code == lazyev_lib.EEXCHANGE
+            eng.set_spin_ticks(2000000)
+            assert eng.stats()["len"][0] == N + t - 1        # reported once
+        q, kn, vn = (torch.empty((batch, h, d), device="cuda").normal_(generator=gen).to(dt) for h in (group * H, H, H))
+        eng.decode_step(0, t, q, kn, vn, out)
+        if t >= steps - 1:
+            k, v = eng.k_cache[0, :, :, :N + t].double(), eng.v_cache[0, :, :, :N + t].double()
+            p = torch.softmax(torch.matmul(q.double().view(batch, H, group, d), k.transpose(2, 3).contiguous()) * d ** -0.5, dim=-1)
+            ref = torch.matmul(p, v).view(batch, group * H, d)
+            err = float(((out.double() - ref).norm(dim=-1) / ref.norm(dim=-1)).max())
+            # (bf16: two roundings, as above; fp32: sums of some thousand terms)
+            assert err < (1e-5 if dt == torch.float32 else 2 * 2.0 ** -8), (t, err)
+    assert eng.stats()["len"][0] == N + steps
+    eng.close()

@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 ROWS = [("fp32", 64), ("fp32", 128), ("bf16", 64)]
 
 
-def _run(lazyev_lib, variant, dtype, d, place, value, N, H=2, G=4, S=2, steps=2):
+def _run(lazyev_lib, variant, dtype, d, place, value, N, H=2, G=4, S=2, steps=2, blocks=0):
     gen = torch.Generator(device="cuda").manual_seed(N)
     eng = lazyev_lib.LazyEviction(1, S, H * G, H, d, N + 40, 8, N, 0.01, dtype=dtype)
     eng.k_cache[:, :, :, :N].normal_(generator=gen)
@@ -31,8 +31,8 @@ def _run(lazyev_lib, variant, dtype, d, place, value, N, H=2, G=4, S=2, steps=2)
         eng.k_cache[0, 0, 0, N // 3] *= value
     eng.init()
     eng.set_variant(variant)
-    if N > 2000:                                   # one block per unit: runs whose logits leave LDS in segments
-        eng.set_target_blocks(S * H)
+    if N > 2000 or blocks:                         # one block per unit: runs whose logits leave LDS in segments
+        eng.set_target_blocks(max(blocks, 1) * S * H)
     out = torch.zeros((steps, S, H * G, d), dtype=dtype, device="cuda")
     for t in range(1, steps + 1):
         eng.decode_step(0, t, q[t - 1], kn[t - 1], vn[t - 1], out[t - 1])
@@ -45,10 +45,11 @@ def _run(lazyev_lib, variant, dtype, d, place, value, N, H=2, G=4, S=2, steps=2)
 @pytest.mark.parametrize("dtype,d", ROWS)
 @pytest.mark.parametrize("place", ["cached V", "first V", "appended V", "cached K", "query"])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
-@pytest.mark.parametrize("N", [3, 15, 64, 333, 2600])
-def test_infinite_elements(lazyev_lib, dtype, d, place, value, N):
+@pytest.mark.parametrize("N,blocks", [(3, 0), (15, 0), (64, 0), (333, 0), (2600, 0), (2600, 9), (2600, 17), (2600, 33)])
+def test_infinite_elements(lazyev_lib, dtype, d, place, value, N, blocks):
+    """(Of more than eight blocks a unit, blocks of their own merge the partials, two, four or eight records a lane.)"""
     dt = torch.float32 if dtype == "fp32" else torch.bfloat16
-    (want, state0, act0), (got, state1, act1) = (_run(lazyev_lib, v, dt, d, place, value, N) for v in (0, 1))
+    (want, state0, act0), (got, state1, act1) = (_run(lazyev_lib, v, dt, d, place, value, N, blocks=blocks) for v in (0, 1))
     assert torch.equal(got.isnan(), want.isnan())
     assert torch.equal(got.isposinf(), want.isposinf()) and torch.equal(got.isneginf(), want.isneginf())
     assert (want.isposinf().any() and want.isneginf().any()) if place.endswith("V") and value == float("inf") else want.isnan().any()
@@ -61,11 +62,11 @@ def test_infinite_elements(lazyev_lib, dtype, d, place, value, N):
 
 @pytest.mark.parametrize("dtype,d", ROWS + [("bf16", 128)])
 @pytest.mark.parametrize("value", [1e8, 1e12, 1e25])
-@pytest.mark.parametrize("N", [3, 64, 333, 2600])
-def test_large_logits(lazyev_lib, dtype, d, value, N):
+@pytest.mark.parametrize("N,blocks", [(3, 0), (64, 0), (333, 0), (2600, 0), (2600, 9), (2600, 17), (2600, 33)])
+def test_large_logits(lazyev_lib, dtype, d, value, N, blocks):
     """A key with logits so large that their rounding exceeds the range of an exponential."""
     dt = torch.float32 if dtype == "fp32" else torch.bfloat16
-    (want, state0, act0), (got, state1, act1) = (_run(lazyev_lib, v, dt, d, "large K", value, N) for v in (0, 1))
+    (want, state0, act0), (got, state1, act1) = (_run(lazyev_lib, v, dt, d, "large K", value, N, blocks=blocks) for v in (0, 1))
     assert bool(want.isfinite().all()) and bool(got.isfinite().all())
     tol = (N + 2) * 2.0 ** -23 if dt == torch.float32 else 2.0 ** -6
     assert float((got - want).abs().max()) < tol * max(1.0, float(want.abs().max()))
@@ -73,7 +74,7 @@ def test_large_logits(lazyev_lib, dtype, d, value, N):
 
 
 @pytest.mark.parametrize("dtype,d", ROWS + [("bf16", 128)])
-@pytest.mark.parametrize("N,blocks", [(40, 0), (333, 0), (333, 1), (700, 3), (2600, 1)])
+@pytest.mark.parametrize("N,blocks", [(40, 0), (333, 0), (333, 1), (700, 3), (2600, 1), (2600, 9), (2600, 17), (2600, 33)])
 def test_entries_without_weight(lazyev_lib, dtype, d, N, blocks):
     """Runs of entries whose logits are -inf in every head, long enough to fill whole sub-tiles, a wave's first ones among
     them: softmax in 64 bits over the others, and no activation of theirs."""
