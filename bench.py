@@ -173,6 +173,94 @@ def prefill_track_mode(args):
     eng.close()
 
 
+def timeline_sample(a):
+    """The stamps of one launch (rows of eight words per block, see decode_fused.hip) as microseconds from the start of its
+    first stream block, by kind of block; rows that other launches left are not taken.  None: no block of the launch ended."""
+    import numpy as np
+    kind, launch = a[:, 7] & 255, a[:, 7] >> 8
+    mine = (launch == launch[0]) & (launch[0] > 0)
+    stream = mine & ((kind == 1) | (kind == 2))
+    if not stream.any():
+        return None
+    origin = a[stream, 0].min()
+
+    def us(rows, words):
+        return (a[rows][:, words] - origin) / 100.0
+    return {"stream": us(stream, list(range(6))), "finishes": kind[stream] == 2, "xcd": a[stream, 6], "block": np.nonzero(stream)[0],
+            "merging": us(mine & (kind == 3), [0, 2, 3, 5]), "tracking": us(mine & (kind == 4), [0, 5])}
+
+
+def timeline_summary(samples, n_units):
+    """What --timeline prints of its samples.  A unit is finished by its last block or, of more than eight, mostly by merging
+    blocks: then no stream block has seen other partials."""
+    import numpy as np
+    names = ["block start", "first sub-tile multiplied", "end of wave 0's stream", "all four waves done",
+             "partials complete (finishing blocks)", "block end"]
+
+    def q(x):
+        if np.size(x) == 0:
+            return {}
+        return {"min": round(float(np.min(x)), 2), "p50": round(float(np.median(x)), 2),
+                "p90": round(float(np.percentile(x, 90)), 2), "max": round(float(np.max(x)), 2)}
+
+    def per_launch(x, f):
+        x = [f(v) for v in x if len(v)]
+        return round(float(np.mean(x)), 2) if x else None
+
+    def at(sample, i):                             # (only finishing blocks leave stamp 4)
+        return sample["stream"][sample["finishes"], i] if i == 4 else sample["stream"][:, i]
+    st = np.concatenate([s["stream"] for s in samples])
+    fin = np.concatenate([s["finishes"] for s in samples])
+    merging = np.concatenate([s["merging"] for s in samples])
+    tracking = np.concatenate([s["tracking"] for s in samples])
+    res = {"what": "in-kernel timeline of decode_fused_kernel, microseconds from the start of the launch's "
+                   "first block, over the stream blocks of %d launches" % len(samples),
+           "stamps": {n: dict(q(np.concatenate([at(s, i) for s in samples])),
+                              mean_of_per_launch_max=per_launch([at(s, i) for s in samples], np.max),
+                              mean_of_per_launch_min=per_launch([at(s, i) for s in samples], np.min))
+                      for i, n in enumerate(names)},
+           "finisher_tail_us (block end - end of its stream)": q((st[:, 5] - st[:, 2])[fin]),
+           "merging_blocks": {n: q(merging[:, i]) for i, n in enumerate(
+               ["start", "half of the unit's records there", "all there", "end"])},
+           # (the tracking blocks of the launch apply the PREVIOUS call's tracking; the first call of a
+           # layer has none)
+           "tracking_blocks": {"start": q(tracking[:, 0]), "end": q(tracking[:, 1])}}
+    # Which blocks end their stream late: by the XCD they ran on, by their place among the unit's
+    # blocks, and how far the blocks of one unit lie apart.
+    xcd = np.concatenate([s["xcd"] for s in samples])
+    blk = np.concatenate([s["block"] for s in samples])
+    n_split = max(1, int(samples[0]["stream"].shape[0]) // n_units)   # (the first blocks of all units, then the second ones, ...)
+    res["stream_end_by_xcd"] = {str(int(x)): {"blocks_per_launch": round(float((xcd == x).sum()) / len(samples), 1),
+                                              "mean": round(float(st[xcd == x, 2].mean()), 2)}
+                                for x in np.unique(xcd)}
+    res["stream_end_by_block_of_the_unit"] = {str(j): round(float(st[blk // n_units == j, 2].mean()), 2)
+                                              for j in range(n_split)}
+    res["xcd_of_block_index_mod_8"] = {str(j): sorted(int(x) for x in np.unique(xcd[blk % 8 == j])) for j in range(8)}
+    per_unit = [s["stream"][:, 2].reshape(-1, n_units).T for s in samples]
+    res["spread_of_a_unit's_blocks (latest - earliest stream end)"] = q(
+        np.concatenate([u.max(axis=1) - u.min(axis=1) for u in per_unit]))
+    res["finishing_blocks"] = {"partials complete - all four waves done": q((st[:, 4] - st[:, 3])[fin]),
+                               "block end - partials complete": q((st[:, 5] - st[:, 4])[fin]),
+                               "stream end": q(st[fin, 2])}
+    res["other_blocks"] = {"block end - all four waves done": q((st[:, 5] - st[:, 3])[~fin]),
+                           "stream end": q(st[~fin, 2])}
+    # the stream block that ends last: did it stream longest, or did it wait for another block's partial?
+    last = [int(np.argmax(s["stream"][:, 5])) for s in samples]
+    waited = [s["stream"][i, 4] - s["stream"][i, 3] for i, s in zip(last, samples) if s["finishes"][i]]
+    res["last_block_of_a_launch"] = {
+        "is_the_block_whose_stream_ended_last": round(float(np.mean([int(i == int(np.argmax(s["stream"][:, 2]))) for i, s in zip(last, samples)])), 2),
+        "finishes_its_unit": round(float(np.mean([float(s["finishes"][i]) for i, s in zip(last, samples)])), 2),
+        "stream end": q(np.array([s["stream"][i, 2] for i, s in zip(last, samples)])),
+        "partials complete - all four waves done": q(np.array(waited)),
+        "block end - end of its stream": q(np.array([s["stream"][i, 5] - s["stream"][i, 2] for i, s in zip(last, samples)]))}
+    res["per_launch"] = {"stream_end_sigma": round(float(np.mean([s["stream"][:, 2].std() for s in samples])), 2),
+                         "mean_stream_end": round(float(np.mean([s["stream"][:, 2].mean() for s in samples])), 2),
+                         "latest_stream_end": round(float(np.mean([s["stream"][:, 2].max() for s in samples])), 2),
+                         "last merging block's end - latest stream end": per_launch(
+                             [s["merging"][:, 3] - s["stream"][:, 2].max() for s in samples], np.max)}
+    return res
+
+
 def timeline_mode(args):
     """--timeline: where the time of one decode launch goes.  Runs the workload's shapes (4 layers,
     prompt = budget, so the cache is at its budget) on the instrumented build of the library
@@ -210,76 +298,15 @@ def timeline_mode(args):
         if t > steps // 2:                            # the stamps of the step's last launch
             torch.cuda.synchronize()
             assert read(buf, NB * 8) == 0
-            a = np.frombuffer(buf, dtype=np.uint64).reshape(NB, 8).astype(np.int64)
-            live = a[:, 0] > 0
-            stream = live & (a[:, 3] >= a[:, 0]) & (a[:, 2] >= a[:, 0])
-            if stream.any():
-                origin = a[stream, 0].min()
-                trk = a[live & ~stream]
-                trk = trk[trk[:, 5] >= trk[:, 0]]
-                samples.append(((a[stream][:, :6] - origin) / 100.0, a[stream][:, 7],
-                                (trk[:, [0, 5]] - origin) / 100.0, a[stream][:, 6],
-                                np.nonzero(stream)[0]))
+            sample = timeline_sample(np.frombuffer(buf, dtype=np.uint64).reshape(NB, 8).astype(np.int64))
+            if sample is not None:
+                samples.append(sample)
         eng.evict_all(t)                              # (fires where the schedule says so)
     n1 = eng.stats()["len"][0]
-    names = ["block start", "first sub-tile multiplied", "end of wave 0's stream", "all four waves done",
-             "partials complete (finishing blocks)", "block end"]
-
-    def q(x):
-        return {"min": round(float(np.min(x)), 2), "p50": round(float(np.median(x)), 2),
-                "p90": round(float(np.percentile(x, 90)), 2), "max": round(float(np.max(x)), 2)}
-
-    def at(sample, i):                             # (only finishing blocks leave stamp 4)
-        return sample[0][:, i][sample[1] == 1] if i == 4 else sample[0][:, i]
-    res = {"what": "in-kernel timeline of decode_fused_kernel, microseconds from the start of the launch's "
-                   "first block, over the stream blocks of %d launches" % len(samples),
-           "config": {"workload": "%s-prompt%d" % (base.name, P), "layers": L, "entries_per_unit_at_the_end": n1,
-                      "stream_blocks_per_launch": int(samples[0][0].shape[0])},
-           "stamps": {n: dict(q(np.concatenate([at(s, i) for s in samples])),
-                              mean_of_per_launch_max=round(float(np.mean([at(s, i).max() for s in samples])), 2),
-                              mean_of_per_launch_min=round(float(np.mean([at(s, i).min() for s in samples])), 2))
-                      for i, n in enumerate(names)},
-           "finisher_tail_us (block end - end of its stream)":
-               q(np.concatenate([(s[0][:, 5] - s[0][:, 2])[s[1] == 1] for s in samples])),
-           # (the tracking blocks of the launch apply the PREVIOUS call's tracking; the first call of a
-           # layer has none)
-           "tracking_blocks": ({"start": q(np.concatenate([s[2][:, 0] for s in samples])),
-                                "end": q(np.concatenate([s[2][:, 1] for s in samples]))}
-                               if sum(len(s[2]) for s in samples) else {})}
-    # Which blocks end their stream late: by the XCD they ran on, by their place among the unit's
-    # blocks, and how far the blocks of one unit lie apart.
-    end = np.concatenate([s[0][:, 2] for s in samples])
-    xcd = np.concatenate([s[3] for s in samples])
-    blk = np.concatenate([s[4] for s in samples])
-    n_units = cfg.batch * cfg.n_kv_heads            # (the first blocks of all units, then the second ones, ...)
-    n_split = max(1, int(samples[0][0].shape[0]) // n_units)
-    res["stream_end_by_xcd"] = {str(int(x)): {"blocks_per_launch": round(float((xcd == x).sum()) / len(samples), 1),
-                                              "mean": round(float(end[xcd == x].mean()), 2)}
-                                for x in np.unique(xcd)}
-    res["stream_end_by_block_of_the_unit"] = {str(j): round(float(end[blk // n_units == j].mean()), 2)
-                                              for j in range(n_split)}
-    res["xcd_of_block_index_mod_8"] = {str(j): sorted(int(x) for x in np.unique(xcd[blk % 8 == j])) for j in range(8)}
-    per_unit = [s[0][:, 2].reshape(n_split, -1).T for s in samples]
-    res["spread_of_a_unit's_blocks (latest - earliest stream end)"] = q(
-        np.concatenate([u.max(axis=1) - u.min(axis=1) for u in per_unit]))
-    fin = np.concatenate([s[1] == 1 for s in samples])
-    st = np.concatenate([s[0] for s in samples])
-    res["finishing_blocks"] = {"partials complete - all four waves done": q((st[:, 4] - st[:, 3])[fin]),
-                               "block end - partials complete": q((st[:, 5] - st[:, 4])[fin]),
-                               "stream end": q(st[fin, 2])}
-    res["other_blocks"] = {"block end - all four waves done": q((st[:, 5] - st[:, 3])[~fin]),
-                           "stream end": q(st[~fin, 2])}
-    # the block that ends a launch: did it stream longest, or did it wait for another block's partial?
-    last = [int(np.argmax(s[0][:, 5])) for s in samples]
-    res["last_block_of_a_launch"] = {
-        "is_the_block_whose_stream_ended_last": round(float(np.mean([int(i == int(np.argmax(s[0][:, 2]))) for i, s in zip(last, samples)])), 2),
-        "finishes_its_unit": round(float(np.mean([float(s[1][i] == 1) for i, s in zip(last, samples)])), 2),
-        "stream end": q(np.array([s[0][i, 2] for i, s in zip(last, samples)])),
-        "partials complete - all four waves done": q(np.array([s[0][i, 4] - s[0][i, 3] for i, s in zip(last, samples)])),
-        "block end - end of its stream": q(np.array([s[0][i, 5] - s[0][i, 2] for i, s in zip(last, samples)]))}
-    res["per_launch"] = {"stream_end_sigma": round(float(np.mean([s[0][:, 2].std() for s in samples])), 2),
-                         "mean_stream_end": round(float(np.mean([s[0][:, 2].mean() for s in samples])), 2),
-                         "latest_stream_end": round(float(np.mean([s[0][:, 2].max() for s in samples])), 2)}
+    res = timeline_summary(samples, cfg.batch * cfg.n_kv_heads)
+    res["config"] = {"workload": "%s-prompt%d" % (base.name, P), "layers": L, "entries_per_unit_at_the_end": n1,
+                     "stream_blocks_per_launch": int(samples[0]["stream"].shape[0]),
+                     "merging_blocks_per_launch": int(samples[0]["merging"].shape[0])}
     print(json.dumps(res))
     eng.close()
 

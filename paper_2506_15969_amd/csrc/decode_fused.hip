@@ -111,9 +111,10 @@ __device__ __forceinline__ BlockPlace block_place(int b, int n_split, int units)
 #ifdef LAZYEV_TIMELINE
 // Measuring build only (liblazyev_timeline.so, see build.py): every block of the LAST launch
 // leaves time stamps of the constant 100 MHz counter: 0 block start, 1 first sub-tile multiplied,
-// 2 end of wave 0's stream, 3 all four waves done, 4 all partials there, 5 block end; word 6: the XCD the
-// block ran on (hardware register XCC_ID); word 7: 1 if the block finished its unit.  Read with
-// lazyev_timeline_read.
+// 2 end of wave 0's stream, 3 all four waves done, 4 all partials there, 5 block end (a merging block: 2 half of the unit's
+// records there, 3 all there; a tracking block: 0 and 5 only); word 6: the XCD the block ran on (hardware register XCC_ID);
+// word 7: 1 a stream block, 2 one that finished its unit, 3 a merging block, 4 a tracking block, and the launch's number times
+// 256 (rows of another number are an earlier launch's).  Read with lazyev_timeline_read.
 __device__ unsigned long long lz_stamp[2048 * 8];
 #define STAMP(i) do { if (threadIdx.x == 0 && blockIdx.x < 2048) lz_stamp[blockIdx.x * 8 + (i)] = wall_clock64(); } while (0)
 #define STAMPV(i, v) do { if (threadIdx.x == 0 && blockIdx.x < 2048) lz_stamp[blockIdx.x * 8 + (i)] = (v); } while (0)
@@ -894,6 +895,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
       }
     }
     track_count(k, unit, part, n_act, cnt_lds);
+    STAMPV(7, 4 | (static_cast<unsigned long long>(a.seq) << 8));
     STAMP(5);
     return;
   }
@@ -908,11 +910,11 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     CallArgs<T> a;
     a.read();
     const int run = fused_wave_run((n_old_call + 16) >> 4, n_split);
-    STAMP(1);
     if (n_split <= 8) merge_columns<T, D, 1>(a, at.unit, G, n_split, run, columns);
     else if (n_split <= 16) merge_columns<T, D, 2>(a, at.unit, G, n_split, run, columns);
     else if (n_split <= 32) merge_columns<T, D, 4>(a, at.unit, G, n_split, run, columns);
     else merge_columns<T, D, 8>(a, at.unit, G, n_split, run, columns);
+    STAMPV(7, 3 | (static_cast<unsigned long long>(a.seq) << 8));
     STAMP(5);
     return;
   }
@@ -1591,7 +1593,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
                                                    static_cast<size_t>(split) * fused_part_cap(n_old, n_split)) * kHeadPad) =
           static_cast<int32_t>(cand_total);
   }
-  STAMPV(7, static_cast<unsigned long long>(finisher));
+  STAMPV(7, (finisher ? 2 : 1) | (static_cast<unsigned long long>(a.seq) << 8));
   STAMP(5);
 }
 
