@@ -571,10 +571,10 @@ __device__ __forceinline__ f32x4_t rec_values(const RecPart &r) {
   return f32x4_t{value(0), value(1), value(2), value(3)};
 }
 
-// What one thread needs of n <= N records at rec, rec + stride, ..., all requested together, again
+// What one thread needs of n <= N records, one behind the other, all requested together, again
 // until every word carries the launch's number; then the records and (m, l, o) merged in this order.
 template <int N, bool kPrecise, typename Args>
-__device__ __forceinline__ Merge<kPrecise> merge_records(const Args &a, const unsigned long long *rec, int stride, int n,
+__device__ __forceinline__ Merge<kPrecise> merge_records(const Args &a, const unsigned long long *rec, int n,
                                                int t_own, float m, float l, const f32x4_t &o) {
   Merge<kPrecise> mg;
   if (n == 0) {                                    // uniform
@@ -589,7 +589,7 @@ __device__ __forceinline__ Merge<kPrecise> merge_records(const Args &a, const un
   for (;;) {
 #pragma unroll
     for (int j = 0; j < N; ++j)                    // (beyond n: the last record once more, no branches among the loads)
-      rec_load(r[j], rec + min(j, n - 1) * stride, at);
+      rec_load(r[j], rec + min(j, n - 1) * kRecWords, at);
     bool ok = true;
 #pragma unroll
     for (int j = 0; j < N; ++j) ok = ok & rec_valid(r[j], a.seq);
@@ -910,8 +910,7 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
     CallArgs<T> a;
     a.read();
     const int run = fused_wave_run((n_old_call + 16) >> 4, n_split);
-    if (n_split <= 8) merge_columns<T, D, 1>(a, at.unit, G, n_split, run, columns);
-    else if (n_split <= 16) merge_columns<T, D, 2>(a, at.unit, G, n_split, run, columns);
+    if (n_split <= 16) merge_columns<T, D, 2>(a, at.unit, G, n_split, run, columns);
     else if (n_split <= 32) merge_columns<T, D, 4>(a, at.unit, G, n_split, run, columns);
     else merge_columns<T, D, 8>(a, at.unit, G, n_split, run, columns);
     STAMPV(7, 3 | (static_cast<unsigned long long>(a.seq) << 8));
@@ -1577,10 +1576,10 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
   if (finisher) {
     constexpr int kIn = kSplit > 1 ? kSplit - 1 : kSplit == 1 ? 1 : R::kWide ? 18 : 9;
     const int n_in = kSplit > 0 ? kSplit - 1 : n_split - 1;
-    Merge<kPrecise> mg = merge_records<kIn, kPrecise>(a, recs, kRecWords, min(n_in, kIn), t_own, mb_own, l_own, v_own);
+    Merge<kPrecise> mg = merge_records<kIn, kPrecise>(a, recs, min(n_in, kIn), t_own, mb_own, l_own, v_own);
     if constexpr (kSplit == 0) {                   // (at most 18 records where the split is the library's own)
       for (int j = kIn; j < n_in; j += kIn)
-        mg = merge_records<kIn, kPrecise>(a, recs + static_cast<size_t>(j) * kRecWords, kRecWords, min(n_in - j, kIn), t_own, mg.m, mg.l,
+        mg = merge_records<kIn, kPrecise>(a, recs + static_cast<size_t>(j) * kRecWords, min(n_in - j, kIn), t_own, mg.m, mg.l,
                                           f32x4_t{mg.o[0], mg.o[1], mg.o[2], mg.o[3]});
     }
     STAMP(4);
