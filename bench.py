@@ -207,8 +207,9 @@ def timeline_summary(samples, n_units):
         x = [f(v) for v in x if len(v)]
         return round(float(np.mean(x)), 2) if x else None
 
-    def at(sample, i):                             # (only finishing blocks leave stamp 4)
-        return sample["stream"][sample["finishes"], i] if i == 4 else sample["stream"][:, i]
+    def at(sample, i):                             # (only finishing blocks leave stamp 4; a wave without a sub-tile leaves no stamp 1)
+        x = sample["stream"]
+        return x[sample["finishes"], i] if i == 4 else x[x[:, 1] >= x[:, 0], i] if i == 1 else x[:, i]
     st = np.concatenate([s["stream"] for s in samples])
     fin = np.concatenate([s["finishes"] for s in samples])
     merging = np.concatenate([s["merging"] for s in samples])

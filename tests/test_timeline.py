@@ -15,6 +15,7 @@ def _stamps(n_split, units, merging, tracking, launch, at):
         fin = b >= n_stream - units and not merging
         a[b] = [at + b, at + 170, at + 500 + b, at + 550 + b, at + 700 if fin else 33, at + 800 if fin else at + 600 + b, b % 8,
                 (2 if fin else 1) | (launch << 8)]
+    a[1, 1] = 0                                    # (its first wave has no sub-tile)
     for b in range(n_stream, n_stream + merging):
         a[b] = [at + 20, 44, at + 640, at + 680, 55, at + 720, b % 8, 3 | (launch << 8)]
     for b in range(n_stream + merging, n_stream + merging + tracking):
@@ -32,6 +33,7 @@ def test_summary_by_kind_of_block(n_split, merging):
     res = bench.timeline_summary(samples, units)
     assert len(res["stream_end_by_block_of_the_unit"]) == n_split
     assert res["stamps"]["end of wave 0's stream"]["max"] == pytest.approx(5.0 + (n_split * units - 1) / 100)
+    assert res["stamps"]["first sub-tile multiplied"]["min"] == 1.7
     assert res["tracking_blocks"]["end"]["max"] == 3.0
     if merging:
         assert res["merging_blocks"]["all there"]["max"] == 6.8 and res["finishing_blocks"]["stream end"] == {}
