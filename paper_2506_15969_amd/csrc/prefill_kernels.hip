@@ -704,8 +704,11 @@ hipError_t launch_rows(PrefillArgs a, hipStream_t stream) {
   // Wide blocks where there are eight per compute unit; with fewer the last of them leave more of the chip idle than their
   // products save (us for the three kernels, narrow from 512 / 2048 wide blocks down: 28 / 4 heads of 128 x bf16, 8
   // sequences x 600 positions 55.6 / 48.4, 2 x 2600 185 / 169, 32 x 60 19.0 / 16.1; 8 of 32 / 8 heads of 64 x 300 29.2 / 23.2;
-  // from 4096 down: 32 x 600 154 / 203).
-  if (units * a.group * wide >= 2048)
+  // from 4096 down: 32 x 600 154 / 203).  128 x bf16 already where the narrow ones are sixteen per compute unit: wide / narrow, 4
+  // heads to a KV head, 64 units x 1500 193 / 237 (6144 narrow blocks), 128 x 600 95.8 / 108 (5120), 32 x 2000 174 / 181 (4096); 42 x
+  // 1300 of 7 heads 128 / 121 (3528); the other types gain from narrow ones up to there (64 x bf16 x 1500 181 / 182, 600 84 / 75).
+  constexpr bool kProductsLong = D == 128 && sizeof(T) == 2;
+  if (units * a.group * wide >= 2048 || (kProductsLong && units * a.group * narrow >= 4096))
     hipLaunchKernelGGL((prefill_stats_kernel<T, D, NB>), dim3(static_cast<unsigned>(units * a.group * wide)), dim3(kBlock), 0, stream, a);
   else
     hipLaunchKernelGGL((prefill_stats_kernel<T, D, 1>), dim3(static_cast<unsigned>(units * a.group * narrow)), dim3(kBlock), 0, stream, a);
@@ -725,12 +728,25 @@ hipError_t launch_rows(PrefillArgs a, hipStream_t stream) {
   // three kernels, 512 narrow blocks of two query tiles and wide ones of four / like this: 28 / 4 heads of 128 x bf16 x 33
   // positions 12.7 / 10.4, x 164 16.4 / 13.0, 2 sequences x 1500 102 / 74, x 2600 258 / 184, 16 x 250 37.9 / 30.1, 8 x 600 59.7 /
   // 55.4; 4 sequences of 32 / 8 heads of 64 x bf16 x 499 27.7 / 26.0; fp32 rows of 128, 2 x 300 46.0 / 39.5.
+  // Where narrow blocks have fewer than 32 tiles of queries to walk, over all heads (fp32 rows: 16), 1024 of them (1024 / 2048, one head to a KV
+  // head: 128 x bf16, 32 units x 250 14.5 / 16.0, 192 x 164 15.6 / 17.0; 64 x bf16, 64 x 164 13.1 / 14.5; but 8 units x 2600 71.3 / 66.6, three heads
+  // 111 / 95.9; 48 of fp32 (128) x 250, three heads 47.0 / 43.8, 96 x 100, four heads 33.6 / 31.7).  Likewise segments of four tiles at least for wide
+  // blocks below 40 tiles (four / two, one head: 128 x bf16, 96 units x 400 24.4 / 28.2, 64 x bf16 21.1 / 25.2, 64 x fp32, 48 x 400 34.4 /
+  // 36.5; but four heads, 48 x 400 32.7 / 29.4; fp32 rows of 128, one head, 48 x 300 38.7 / 35.6).
+  // Up to three query tiles are cut only where what is walked costs more than the third launch, which one segment does
+  // without: 32 units, one segment / cut, 128 x bf16 x 33 1 / 2 / 4 / 7 heads 7.8 / 9.4, 8.6 / 9.4, 10.2 / 9.8, 13.5 / 11.6; x 20 7 heads equal;
+  // fp32 (64) x 33 1 / 2 / 4 heads 9.2 / 10.2, equal, 12.7 / 10.9; with 256 blocks of one segment 12.0 / 13.0 (128 x bf16 x 33, 4 heads).
+  // Wide blocks where 512 of them would have four query tiles each (a.segments: what the workspace holds records for): from
+  // 512 of two tiles on, narrow / wide instead, 24 units of 128 x bf16 x 400 21.3 / 25.7, 12 of 128 x fp32 x 400 45.2 / 57.6, 24 of 64 x
+  // fp32 x 400 39.9 / 54.8 (96 of 64 x bf16 x 250 25.6 / 22.7).
   const long long n_it = (a.prompt_len + 15) / 16;
-  const long long most = n_it / 4 < a.segments ? n_it / 4 : a.segments;        // (what the workspace holds records for)
+  const long long most = n_it / 4 < a.segments ? n_it / 4 : a.segments;
   const bool use_wide = units * wide * (most < 1 ? 1 : most) >= 512;
-  const long long per_unit = use_wide ? wide : narrow, want = 2048;
+  const long long per_unit = use_wide ? wide : narrow, want = use_wide || a.group * n_it >= (sizeof(T) == 4 ? 16 : 32) ? 2048 : 1024;
   long long z = (want + units * per_unit - 1) / (units * per_unit);
-  if (z > (use_wide ? n_it / 2 : n_it)) z = use_wide ? n_it / 2 : n_it;
+  const long long least = !use_wide ? 1 : a.group * n_it < 40 && !(sizeof(T) == 4 && D == 128) ? 4 : 2;    // query tiles of a segment
+  if (z > n_it / least) z = n_it / least;
+  if (n_it <= 3 && a.group * (n_it - 1) < (sizeof(T) == 4 ? 4 : 8) * (units * per_unit > 128 ? 2 : 1)) z = 1;
   if (z > a.segments) z = a.segments;
   if (z <= 1) {
     const dim3 grid(static_cast<unsigned>(units * per_unit));

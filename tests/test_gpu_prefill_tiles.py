@@ -8,9 +8,12 @@ import torch
 pytestmark = pytest.mark.gpu
 
 ROWS = [("bf16", 128), ("bf16", 64), ("fp32", 64), ("fp32", 128)]
-# (sequences, KV heads, group, positions): the last five are shapes of the wide tiles, with and without segments
+# (sequences, KV heads, group, positions): of up to three query tiles in one segment and cut; many narrow blocks of few tiles;
+# the last eight are shapes of the wide tiles (the first two of them not in all kernels and types), with and without segments
 SHAPES = [(1, 1, 1, 1), (1, 1, 2, 15), (2, 1, 3, 16), (1, 2, 5, 17), (1, 1, 7, 63), (1, 1, 4, 64), (1, 1, 8, 65),
           (2, 2, 4, 255), (1, 1, 6, 257), (1, 1, 8, 2100),
+          (1, 2, 1, 47), (2, 2, 3, 40), (3, 2, 8, 33), (64, 2, 8, 34), (40, 8, 7, 20), (64, 3, 1, 164), (64, 1, 3, 170),
+          (32, 8, 4, 200), (16, 8, 2, 330), (48, 2, 1, 400),
           (64, 8, 1, 70), (16, 4, 8, 300), (8, 4, 7, 513), (64, 2, 3, 129), (128, 16, 1, 33)]
 
 
