@@ -23,18 +23,20 @@ extern "C" {
  *     64..256; default 128).
  *   lazyev_set_target_blocks: stream blocks per layer call the single-launch attention kernel
  *     aims for, taken literally: each unit gets round(n_blocks / units) blocks, at least one
- *     and at most 64, and no more than the workspace has records for: one per block but the last,
- *     8 KB each, in the area of the vector-ALU kernel's partials (30 blocks for units of 2112
- *     entries, 7 query heads of 128; never fewer than the library's own choice).  Until this is called the library sizes the split from the number of units
- *     and the cache length (about one block per compute unit).
+ *     and at most 64, and no more than the workspace has records for: one per block, for up to
+ *     eight blocks one less, 8 KB each, in the area of the vector-ALU kernel's partials (29 blocks
+ *     for units of 2112 entries, 7 query heads of 128; never fewer than the library's own choice).
+ *     Until this is called the library sizes the split from the number of units and the cache
+ *     length (about one block per compute unit).
  * Errors: EINVAL. */
 int lazyev_set_chunk(lazyev_ctx *ctx, int32_t chunk);
 int lazyev_set_target_blocks(lazyev_ctx *ctx, int32_t n_blocks);
 
 /* Tuning knob: attention kernel.
  *   0  vector-ALU split kernel + merge kernel (any supported shape), tracking in the same call;
- *   4  one launch: MFMA stream blocks, the block that finishes a unit last merges the partials
- *      into the output; the tracking rides with the next launch (any supported shape).  A block
+ *   4  one launch: MFMA stream blocks; a unit's last block merges the partials into the output,
+ *      or, of more than eight blocks where there is room on the chip, blocks of their own do;
+ *      the tracking rides with the next launch (any supported shape).  A stream block
  *      leaves only the logits of entries that can still reach alpha for the tracking; it leaves
  *      all of them when the caller passes p_out / p_override or with LAZYEV_SCORE_CURRENT_ATTENTION;
  *   5  kernel 4 leaving every logit of a call in the workspace for the tracking, 6 kernel 4
@@ -44,9 +46,14 @@ int lazyev_set_target_blocks(lazyev_ctx *ctx, int32_t n_blocks);
  * 2 and 3 are not assigned.  Errors: EINVAL. */
 int lazyev_set_variant(lazyev_ctx *ctx, int32_t variant);
 
-/* Kernel 4, units of several blocks: the last block of a group waits for the partial results of the
- * others; the wait is bounded by `ticks` of the GPU's constant 100 MHz counter (default 2000000
- * = 20 ms; a block only waits for blocks started before it, so the bound is not reached).  When it is, the block
+/* Kernel 4, units of several blocks: the block that merges a unit's partials (see variant 4) waits
+ * for those of the others.  Every wait is bounded.  For the partials themselves, at most 18 at a
+ * time, the bound is `ticks` of the GPU's constant 100 MHz counter (default 2000000 = 20 ms).  A
+ * merging block of its own starts with the stream: it sleeps for the time the stream takes at
+ * least (up to half a microsecond for every 16 entries that a wave reads, whatever `ticks` is), then waits
+ * until half of the unit's partials are there, and in long caches for the first one before that,
+ * each for 64 * `ticks` at most (1.28 s by default), and then for all of them.  A block only
+ * waits for blocks started before it, so no bound is reached.  When the last one is, the block
  * goes on with what it has and the next lazyev_stats returns LAZYEV_EEXCHANGE.  0 makes a block
  * give up when its first look finds a partial missing (a test of that path).  Errors: EINVAL. */
 int lazyev_set_spin_ticks(lazyev_ctx *ctx, uint32_t ticks);
