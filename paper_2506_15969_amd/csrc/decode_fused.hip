@@ -23,8 +23,9 @@
 // Partials of a unit.  One block: its partial is the result.  More (decode_fused_split): they are handed over as records of
 // stamped 64-bit words (see "hand-over" below): no acknowledgement is waited for, nothing is signalled, one memory
 // round trip.  Up to eight blocks: the unit's last one merges the others' records with its own partial.  More: blocks
-// of their own behind the stream blocks do (merge_columns), so that few units can have the whole chip.
-// The partials are merged in an order that depends on the split alone, and the finishing block
+// of their own behind the stream blocks do (merge_columns), so that few units can have the whole chip, or the unit's last
+// block again where the chip is full (merging_blocks).
+// The partials are merged in an order that depends on the split and on who merges alone, and the finishing block
 // leaves the unit's softmax statistics (max, 1 / sum per head) for the tracking.
 //
 // Tracking.  The activation test of Alg. 1 needs p = exp(s - m) / l with the statistics of the
@@ -513,11 +514,12 @@ __device__ __forceinline__ void write_unit_row(const Args &a, int unit, int G, c
 // captured calls have kSeqCaptured for their number, which no eager call has: an eager one would find what a replay
 // left complete as soon as the numbers had started over (see lazyev_decode_step).
 // One hop for any number of blocks: up to kPairMax, the unit's last block merges what the others hand over; of more, all
-// hand over and blocks behind the stream blocks merge (merge_columns).  (Before, the last of every eight blocks merged
+// hand over and blocks behind the stream blocks merge (merge_columns), or the last block merges nine at a time
+// (merging_blocks).  (Before, the last of every eight blocks merged
 // those and handed over in turn: the second hop took 1.5 us, and seven records are 28 loads for every thread of the one
 // block that merges.  us per call, 8 units x 2080 entries 6.65 (8 blocks) -> 5.4 (32), 4 x 3000 7.8 (8) -> 5.5 (32), 16 x
-// 4000 10.8 (8) -> 8.7 (16), 2 units of 128 x bf16 x 12000 9.7 (64) -> 8.3 (64), 8 x 2080 of 128 x fp32 15.4 (8) -> 8.0
-// (32); 220 random shapes of 1 .. 60 units x 130 .. 24000 entries 0.93 of the time.)
+// 4000 10.8 (8) -> 8.7 (16), 2 units of 128 x bf16 x 12000 9.7 (64) -> 8.3 (64), 8 x 2080 of 128 x fp32 15.0 (8) -> 8.8
+// (32), with 7 query heads 14.9 -> 9.1; 220 random shapes of 1 .. 60 units x 130 .. 24000 entries 0.93 of the time.)
 // Record of a block: for each of the four waves four rows of 64 words; row i holds the output element 4 t + i of
 // thread t (one store instruction of a wave writes 512 contiguous bytes), and the 16 bits beside it are a half of the
 // maximum (rows 0 and 1) or the sum of thread t's head (each thread its own copy: what the reader needs of a head
@@ -1780,8 +1782,10 @@ static int merged_split(int n_sub, bool f32, int head_dim, bool own_lengths, int
 //     bf16 8.1 / 8.1, 11.2 / 10.7; 64 x fp32 11.0 / 10.5, 17.2 / 15.5; 128 x fp32 18.3 / 17.1, 29.0 / 26.8; the line
 //     is from 128 x fp32 x 1016), and before that where they take a round of sub-tiles less (128 x fp32 x 860 / 960 / 1100 /
 //     1300, 6 / 8 12.3 / 10.9, 12.3 / 11.0, 12.9 / 13.3, 14.6 / 13.5; 64 x fp32 x 960 / 1300 7.9 / 8.0, 9.0 / 8.4).
-//   * two sub-tiles or more per wave (8 units x 500: 4 blocks 5.1, 8 5.4; x 350: 2 5.0, 3 4.9, 4 4.8), but two blocks
-//     from a unit's fifth sub-tile on (x 70: 1 4.1, 2 3.8; x 136: 1 4.7, 2 4.3, 3 4.3).  A sub-tile of fp32 rows takes longer
+//   * below 44 sub-tiles two of them or more per wave (8 units x 500: 4 blocks 5.1, 8 5.4; x 350: 2 5.0, 3 4.9, 4 4.8), but two
+//     blocks from a unit's fifth sub-tile on (x 70: 1 4.1, 2 3.8; x 136: 1 4.7, 2 4.3, 3 4.3); from 44 on as many as there is
+//     room for, up to eight: bf16 rows do not mind (30 units x 704 4 / 6 / 8 blocks 5.8 / 6.0 / 5.7, x 850 6.1 / 6.1 / 6.4, 64 x bf16
+//     6.3 / 6.3 / 6.1, 6.6 / 6.4 / 6.8), fp32 rows gain ((64) 7.6 / 7.2 / 6.8, 8.1 / 7.4 / 7.3, (128) 11.9 / 10.9 / 10.1, 12.6 / 11.7 / 10.2).  A sub-tile of fp32 rows takes longer
 //     than a record more: 4 units x 130 2 / 3 blocks (64) 5.2 / 4.8, (128) 8.4 / 6.9; x 200 2 / 4 5.6 / 5.2, 8.7 / 7.3; x 400
 //     (64) 4 / 7 5.9 / 6.0, (128) 4 / 7 8.9 / 8.1; x 500 4 / 5 6.4 / 6.0, 10.3 / 9.1.
 //   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to two per
