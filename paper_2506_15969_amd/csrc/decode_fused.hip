@@ -1599,17 +1599,12 @@ __global__ __launch_bounds__(kListWaves ? 2 * kBlock : kBlock, (Rows<T, D>::kWid
 }
 
 // ------------------------------------------------------------------------------- host side
-// Compute units of the current device (asked once).
+// Compute units of the current device (asked once; 256, the whole chip's, without one).
 int compute_units() {
-  static int n = 0;
-  if (n == 0) {
+  static const int n = [] {
     int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      n = v;
-    else
-      n = 256;
-  }
+    return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0 ? v : 256;
+  }();
   return n;
 }
 
@@ -1796,21 +1791,21 @@ static int merged_split(int n_sub, bool f32, int head_dim, bool own_lengths, int
 //     (192 units x 2200, 64 43.8 / 44.4, 128 79.3 / 84.9); bf16 rows of 64 would gain from two (176 units x 2200 24.3
 //     / 22.5).
 int decode_fused_split(int units, int n_sub, bool f32, int head_dim, bool own_lengths) {
-  constexpr int kUnitsOfChip = 256;                // compute units of the chip that the figures above are from
-  int n = kUnitsOfChip / units;
+  const int chip = compute_units();                // (the figures above are from 256)
+  int n = chip / units;
   if (n < 1) n = 1;
   const int merged = merged_split(n_sub, f32, head_dim, own_lengths, n < kFusedSplitMax ? n : kFusedSplitMax);
   if (merged > kPairMax) return merged;
   if (n > kPairMax) n = kPairMax;
   const bool fewer = f32 && n == kPairMax && (head_dim == 128 || n_sub > 72) && fused_wave_run(n_sub, n) < fused_wave_run(n_sub, 6);
-  if (n > 6 && n * units > 240 && n_sub < (n < kPairMax ? 512 : !f32 && head_dim == 128 ? 480 : 112) && !fewer) n = 6;
+  if (n > 6 && 16 * n * units > 15 * chip && n_sub < (n < kPairMax ? 512 : !f32 && head_dim == 128 ? 480 : 112) && !fewer) n = 6;
   int by_work = n_sub <= kWaves ? 1 : n_sub < 4 * kWaves ? 2 : n_sub < 44 ? (n_sub + kWaves) / (2 * kWaves) : kPairMax;
   if (f32 && n_sub <= (head_dim == 128 ? 32 : 16)) by_work = (n_sub + kWaves - 1) / kWaves;
   else if (f32 && n_sub < 44) by_work = head_dim == 128 ? (n_sub + 7) / 8 : (n_sub + 6) / 7;
   if (n > by_work) n = by_work;
-  const int n2 = 2 * kUnitsOfChip / units;
+  const int n2 = 2 * chip / units;
   // (28 units x 17000 of 128 x bf16: 8 blocks 48.0, 18 50.8; x 20000 56.1, 55.3; 128 x fp32 x 17000 96.8, 93.7)
-  if (units < kUnitsOfChip && n_sub >= (n == kPairMax ? two_per_compute_unit_from(f32, own_lengths) : 32 * kWaves * n) && 10 * n2 * units >= 10 * 2 * n * units + 2 * kUnitsOfChip) n = n2;
+  if (units < chip && n_sub >= (n == kPairMax ? two_per_compute_unit_from(f32, own_lengths) : 32 * kWaves * n) && 10 * n2 * units >= 10 * 2 * n * units + 2 * chip) n = n2;
   return n;
 }
 
@@ -1828,7 +1823,7 @@ void decode_fused_places(int units, int n_sub, int n_split, int group, bool trac
 // anyway holds them.
 int decode_fused_records_of(int n_split) { return n_split > kPairMax ? n_split : n_split - 1; }
 int decode_fused_records_needed(int units, int capacity) {
-  const int by_length = ((capacity + 15) / 16 + 3) / 4, by_units = (2 * 256 + units - 1) / units;
+  const int by_length = ((capacity + 15) / 16 + 3) / 4, by_units = (2 * 256 + units - 1) / units;   // (of the whole chip: without a device too)
   const int n = by_length < by_units ? by_length : by_units;
   return decode_fused_records_of(n < kFusedSplitMax ? n : kFusedSplitMax);
 }
