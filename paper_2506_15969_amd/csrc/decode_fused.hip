@@ -1737,7 +1737,7 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //     compute unit, 23, x 24000 53.3 / 52.7 with 11, 64 x bf16 34.0 / 35.5, but with 7 heads 34.8 / 34.3).  28 units x 1000 / 2000 / 8200 / 16000 8
 //     / 9 6.2 / 5.8, 7.8 / 7.1, 21.6 / 21.7, 46.4 / 45.4 (7 heads); fp32 (64) 7.7 / 6.9, 9.8 / 8.9, 24.1 / 23.1, 51.9 / 50.1;
 //     sequences of their own lengths 6.6 / 6.0, 7.6 / 7.0, 18.4 / 18.2, 37.2 / 37.8.  Nine only until two blocks to a compute
-//     unit take over: 28 units x 18500 of their own lengths 9 / 18 43.8 / 41.6, 26 units x 24000 9 / 19 63.7 / 61.5 (64 x bf16 40.6 / 39.7, x 16300 28.0 / 29.0), fp32 (64) 71.3 / 63.5, (128) x 17000 88.7 / 86.2.
+//     unit take over, and of 128 x bf16 nine and ten from 46 sub-tiles on (24 units x 690 / 722 6 / 10 5.8 / 6.0, 6.2 / 6.2): 28 units x 18500 of their own lengths 9 / 18 43.8 / 41.6, 26 units x 24000 9 / 19 63.7 / 61.5 (64 x bf16 40.6 / 39.7, x 16300 28.0 / 29.0), fp32 (64) 71.3 / 63.5, (128) x 17000 88.7 / 86.2.
 //   * beyond, 16, 24, 32, 48 or 64 (a merging wave reads a record per lane and eight blocks): 12 units x 2000 / 8200 16 /
 //     21 6.0 / 6.3, 11.6 / 13.2; 10 units x 8200 24 / 25 10.3 / 12.0; 6 units x 8200 32 / 42 8.0 / 9.0; of 11 and 12 units
 //     20 for long caches: 11 x 12000 16 / 20 17.1 / 16.8 (64 x bf16 13.5 / 10.9, fp32 (64) 20.7 / 16.6, (128) 33.9 / 31.4).
@@ -1749,7 +1749,7 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 static int two_per_compute_unit_from(bool f32, bool own_lengths) { return f32 || own_lengths ? 1024 : 1200; }
 static int merged_split(int n_sub, bool f32, int head_dim, bool own_lengths, int most) {
   const int by_length = (n_sub + kWaves - 1) / kWaves;
-  if (most <= kPairMax || n_sub < 44) return 0;
+  if (most <= kPairMax || n_sub < (most <= kPairMax + 2 && !f32 && head_dim == 128 ? 46 : 44)) return 0;
   if (most == kPairMax + 1 && n_sub >= two_per_compute_unit_from(f32, own_lengths)) return 0;
   int n = most;
   if (most >= 16) {
@@ -1777,10 +1777,10 @@ static int merged_split(int n_sub, bool f32, int head_dim, bool own_lengths, int
 //     bf16 8.1 / 8.1, 11.2 / 10.7; 64 x fp32 11.0 / 10.5, 17.2 / 15.5; 128 x fp32 18.3 / 17.1, 29.0 / 26.8; the line
 //     is from 128 x fp32 x 1016), and before that where they take a round of sub-tiles less (128 x fp32 x 860 / 960 / 1100 /
 //     1300, 6 / 8 12.3 / 10.9, 12.3 / 11.0, 12.9 / 13.3, 14.6 / 13.5; 64 x fp32 x 960 / 1300 7.9 / 8.0, 9.0 / 8.4).
-//   * below 44 sub-tiles two of them or more per wave (8 units x 500: 4 blocks 5.1, 8 5.4; x 350: 2 5.0, 3 4.9, 4 4.8), but two
-//     blocks from a unit's fifth sub-tile on (x 70: 1 4.1, 2 3.8; x 136: 1 4.7, 2 4.3, 3 4.3); from 44 on as many as there is
-//     room for, up to eight: bf16 rows do not mind (30 units x 704 4 / 6 / 8 blocks 5.8 / 6.0 / 5.7, x 850 6.1 / 6.1 / 6.4, 64 x bf16
-//     6.3 / 6.3 / 6.1, 6.6 / 6.4 / 6.8), fp32 rows gain ((64) 7.6 / 7.2 / 6.8, 8.1 / 7.4 / 7.3, (128) 11.9 / 10.9 / 10.1, 12.6 / 11.7 / 10.2).  A sub-tile of fp32 rows takes longer
+//   * two sub-tiles or more per wave up to 48 (8 units x 500: 4 blocks 5.1, 8 5.4; x 350: 2 5.0, 3 4.9, 4 4.8), but two
+//     blocks from a unit's fifth sub-tile on (x 70: 1 4.1, 2 3.8; x 136: 1 4.7, 2 4.3, 3 4.3).  Beyond 48 as many as there is room
+//     for, up to eight: six take a third round (30 units x 690 / 760 / 790 6 / 8 6.3 / 6.6, 6.7 / 6.7, 6.8 / 6.7, 64 x bf16 6.1 / 6.4, 6.6 / 6.4, 6.7
+//     / 6.5, fp32 (64) 7.1 / 7.4, 7.5 / 7.4, 7.9 / 7.4, (128) 10.5 / 10.8, 10.5 / 10.7, 12.1 / 10.9).  A sub-tile of fp32 rows takes longer
 //     than a record more: 4 units x 130 2 / 3 blocks (64) 5.2 / 4.8, (128) 8.4 / 6.9; x 200 2 / 4 5.6 / 5.2, 8.7 / 7.3; x 400
 //     (64) 4 / 7 5.9 / 6.0, (128) 4 / 7 8.9 / 8.1; x 500 4 / 5 6.4 / 6.0, 10.3 / 9.1.
 //   * where one block per compute unit leaves a good part of the chip idle and the cache is long, up to two per
@@ -1799,7 +1799,7 @@ int decode_fused_split(int units, int n_sub, bool f32, int head_dim, bool own_le
   if (n > kPairMax) n = kPairMax;
   const bool fewer = f32 && n == kPairMax && (head_dim == 128 || n_sub > 72) && fused_wave_run(n_sub, n) < fused_wave_run(n_sub, 6);
   if (n > 6 && 16 * n * units > 15 * chip && n_sub < (n < kPairMax ? 512 : !f32 && head_dim == 128 ? 480 : 112) && !fewer) n = 6;
-  int by_work = n_sub <= kWaves ? 1 : n_sub < 4 * kWaves ? 2 : n_sub < 44 ? (n_sub + kWaves) / (2 * kWaves) : kPairMax;
+  int by_work = n_sub <= kWaves ? 1 : n_sub < 4 * kWaves ? 2 : n_sub <= 48 ? (n_sub + kWaves) / (2 * kWaves) : kPairMax;
   if (f32 && n_sub <= (head_dim == 128 ? 32 : 16)) by_work = (n_sub + kWaves - 1) / kWaves;
   else if (f32 && n_sub < 44) by_work = head_dim == 128 ? (n_sub + 7) / 8 : (n_sub + 6) / 7;
   if (n > by_work) n = by_work;

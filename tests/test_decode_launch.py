@@ -44,13 +44,16 @@ def test_merging_and_tracking_blocks(lazyev_lib, d, group, f32):
 
 @pytest.mark.parametrize("d,f32", [(128, False), (64, False), (64, True), (128, True)])
 def test_nine_to_fifteen_blocks_where_there_is_room(lazyev_lib, d, f32):
-    """As many blocks a unit as the chip has room for (up to fifteen), from 44 sub-tiles to
-    16384 entries: never a part of the chip idle for a rule about one number of units."""
+    """As many blocks a unit as the chip has room for (up to fifteen), from 44 sub-tiles (nine and ten of 128 x bf16: 46) to
+    16384 entries: never a part of the chip idle for a rule about one number of units.  Below, and of up to eight blocks up to 48 sub-tiles, six."""
     fn = getattr(lazyev_lib.lib, "_ZN6lazyev18decode_fused_splitEiibib")    # lazyev::decode_fused_split (kernels.h)
     fn.restype, fn.argtypes = C.c_int, [C.c_int, C.c_int, C.c_bool, C.c_int, C.c_bool]
     for units in range(17, 29):
         for n_sub in (44, 63, 64, 128, 161, 321, 513, 640, 1023):
-            assert fn(units, n_sub, f32, d, False) == min(256 // units, (n_sub + 3) // 4), (units, n_sub)
+            want = 6 if n_sub < 46 and units > 23 and not f32 and d == 128 else min(256 // units, (n_sub + 3) // 4)
+            assert fn(units, n_sub, f32, d, False) == want, (units, n_sub)
+    for units in (29, 30):
+        assert [fn(units, n_sub, f32, d, False) for n_sub in (44, 46, 48, 49, 60, 100)] == [6, 6, 6, 8, 8, 8]
 
 
 @pytest.mark.parametrize("group", [1, 4, 7, 8])
