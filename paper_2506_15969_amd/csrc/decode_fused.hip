@@ -1618,8 +1618,7 @@ int fused_slots(int run, bool f32, int head_dim) {
 }
 
 // Merging blocks of a launch: for units of more than kPairMax blocks, where they fit the chip beside the stream blocks or all but
-// a few do.  With
-// two stream blocks on every compute unit (long caches) they would start only when stream blocks end, before the tracking blocks,
+// a few do.  With two stream blocks on every compute unit (long caches) they would start only when stream blocks end, before the tracking blocks,
 // and hold their places until the unit's last block is there: that one merges then.  us per call, merging blocks / its last
 // block: 53 units x 13000 / 20000 entries, 9 blocks, 128 x bf16 70.6 / 69.2, 109.9 / 105.9 (7 or 8 query heads to a KV head 52 x
 // 20000 115.9 / 106.9), 128 x fp32 (7) 139.3 / 135.6, 64 x fp32 (7) 117.8 / 114.3; 28 x 24000, 18 blocks, 128 x bf16 (5) 70.4 / 66.4, 128 x fp32
@@ -1629,7 +1628,8 @@ int fused_slots(int run, bool f32, int head_dim) {
 int merging_blocks(int units, int n_sub, int n_split, int group, bool f32, int head_dim) {
   if (n_split <= kPairMax) return 0;
   const long long n = static_cast<long long>(merge_blocks(head_dim, group, merge_waves(n_split))) * units;
-  return static_cast<long long>(n_split) * units + n <= fused_slots(fused_wave_run(n_sub, n_split), f32, head_dim) + compute_units() / 10 ? static_cast<int>(n) : 0;
+  const int slots = fused_slots(fused_wave_run(n_sub, n_split), f32, head_dim);
+  return static_cast<long long>(n_split) * units + n <= slots + compute_units() / 10 ? static_cast<int>(n) : 0;
 }
 
 // Do they come behind the tracking blocks?  They have nothing to do until the stream ends, but where not all blocks fit the chip
@@ -1640,9 +1640,10 @@ int merging_blocks(int units, int n_sub, int n_split, int group, bool f32, int h
 // 19000 of 128 x fp32, 560 blocks, 55.3 / 56.4), and where two stream blocks on a compute unit leave the tracking blocks no places
 // in any order (56 x 8200 of 128 x bf16 45.9 / 48.0).  Only with tracking blocks in the launch: their number is taken as that of the stream
 // blocks.
-// First with sequences of their own lengths: places become free where short ones end, and tracking blocks that start there are
-// less in the way of the others' streams than from the start on; last / first, 7 query heads, 16 units x 20000 32.9 / 28.7, 20 x 16000 32.7 /
-// 29.0, 24 x 12000 30.2 / 27.6, 28 x 12000 34.1 / 29.8 (4 heads 30.5 / 28.7).
+// First with sequences of their own lengths: places become free where short ones end, and the tracking blocks, which update TS and
+// MRI themselves there, then start in those instead of beside the streams from the start on (that this is why is not shown); last /
+// first, 7 query heads, 16 units x 20000 32.9 / 28.7, 20 x 16000 32.7 / 29.0, 24 x 12000 30.2 / 27.6, 28 x 12000 34.1 / 29.8 (4
+// heads 30.5 / 28.7).
 bool merges_last(int n_stream, int n_tracking, int n_merge, int run, bool f32, int head_dim, bool own_lengths) {
   if (own_lengths) return false;
   const long long slots = fused_slots(run, f32, head_dim), others = static_cast<long long>(n_stream) + n_tracking;
@@ -1734,10 +1735,12 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //   * all that there is room for up to 15: 20 units x 2000 / 8200 / 20000 entries 8 / 12 8.1 / 7.0, 18.0 / 16.7, 44.0 /
 //     41.6 (64 x bf16 8.1 / 6.8, 14.5 / 12.1, 30.7 / 27.9; 128 x fp32 14.5 / 12.5, x 4000 22.5 / 18.8).  22 units x 2000 / 8200 /
 //     13000 / 19500 8 / 11 7.7 / 6.7, 18.6 / 17.8, 30.6 / 27.8, 46.4 / 43.0 (64 x bf16 x 2000 / 13000 7.9 / 6.8, 22.1 / 19.1; two blocks to a
-//     compute unit, 23, x 24000 53.3 / 52.7 with 11, 64 x bf16 34.0 / 35.5, but with 7 heads 34.8 / 34.3).  28 units x 1000 / 2000 / 8200 / 16000 8
-//     / 9 6.2 / 5.8, 7.8 / 7.1, 21.6 / 21.7, 46.4 / 45.4 (7 heads); fp32 (64) 7.7 / 6.9, 9.8 / 8.9, 24.1 / 23.1, 51.9 / 50.1;
-//     sequences of their own lengths 6.6 / 6.0, 7.6 / 7.0, 18.4 / 18.2, 37.2 / 37.8.  Nine only until two blocks to a compute
-//     unit take over, and of 128 x bf16 nine and ten from 46 sub-tiles on (24 units x 690 / 722 6 / 10 5.8 / 6.0, 6.2 / 6.2): 28 units x 18500 of their own lengths 9 / 18 43.8 / 41.6, 26 units x 24000 9 / 19 63.7 / 61.5 (64 x bf16 40.6 / 39.7, x 16300 28.0 / 29.0), fp32 (64) 71.3 / 63.5, (128) x 17000 88.7 / 86.2.
+//     compute unit, 23, x 24000 53.3 / 52.7 with 11, 64 x bf16 34.0 / 35.5, but with 7 heads 34.8 / 34.3).  28 units x 1000 / 2000 /
+//     8200 / 16000 8 / 9 6.2 / 5.8, 7.8 / 7.1, 21.6 / 21.7, 46.4 / 45.4 (7 heads); fp32 (64) 7.7 / 6.9, 9.8 / 8.9, 24.1 / 23.1, 51.9 /
+//     50.1; sequences of their own lengths 6.6 / 6.0, 7.6 / 7.0, 18.4 / 18.2, 37.2 / 37.8.
+//   * of 128 x bf16 nine and ten from 46 sub-tiles on: 24 units x 690 / 722 6 / 10 5.8 / 6.0, 6.2 / 6.2.  Nine until two blocks to a
+//     compute unit take over: 26 units x 16300 / 24000 9 / 19 42.6 / 44.0, 63.7 / 61.5 (64 x bf16 28.0 / 29.0, 40.6 / 39.7, fp32 (64) 47.1 /
+//     46.4, 71.3 / 63.5, (128) 84.0 / 82.8, 127 / 119), 28 x 18500 of their own lengths 9 / 18 43.8 / 41.6.
 //   * beyond, 16, 24, 32, 48 or 64 (a merging wave reads a record per lane and eight blocks): 12 units x 2000 / 8200 16 /
 //     21 6.0 / 6.3, 11.6 / 13.2; 10 units x 8200 24 / 25 10.3 / 12.0; 6 units x 8200 32 / 42 8.0 / 9.0; of 11 and 12 units
 //     20 for long caches: 11 x 12000 16 / 20 17.1 / 16.8 (64 x bf16 13.5 / 10.9, fp32 (64) 20.7 / 16.6, (128) 33.9 / 31.4).
@@ -1805,14 +1808,16 @@ int decode_fused_split(int units, int n_sub, bool f32, int head_dim, bool own_le
   if (n > by_work) n = by_work;
   const int n2 = 2 * chip / units;
   // (28 units x 17000 of 128 x bf16: 8 blocks 48.0, 18 50.8; x 20000 56.1, 55.3; 128 x fp32 x 17000 96.8, 93.7)
-  if (units < chip && n_sub >= (n == kPairMax ? two_per_compute_unit_from(f32, own_lengths) : 32 * kWaves * n) && 10 * n2 * units >= 10 * 2 * n * units + 2 * chip) n = n2;
+  const int two_from = n == kPairMax ? two_per_compute_unit_from(f32, own_lengths) : 32 * kWaves * n;
+  if (units < chip && n_sub >= two_from && 10 * n2 * units >= 10 * 2 * n * units + 2 * chip) n = n2;
   return n;
 }
 
-void decode_fused_places(int units, int n_sub, int n_split, int group, bool tracking, bool f32, int head_dim, bool own_lengths, int32_t *merge, int32_t *n_merge, int32_t *track) {
-  const int sb = units * n_split;
+void decode_fused_places(int units, int n_sub, int n_split, int group, bool tracking, bool f32, int head_dim, bool own_lengths,
+                         int32_t *merge, int32_t *n_merge, int32_t *track) {
+  const int sb = units * n_split, run = fused_wave_run(n_sub, n_split);
   *n_merge = merging_blocks(units, n_sub, n_split, group, f32, head_dim);
-  const Places p = places_of(sb, *n_merge, merges_last(sb, tracking ? sb : 0, *n_merge, fused_wave_run(n_sub, n_split), f32, head_dim, own_lengths));
+  const Places p = places_of(sb, *n_merge, merges_last(sb, tracking ? sb : 0, *n_merge, run, f32, head_dim, own_lengths));
   *merge = p.merge;
   *track = p.track;
 }

@@ -176,8 +176,8 @@ def test_merged_blocks_of_sequences_of_their_own_lengths(lazyev_lib, group, bloc
 @pytest.mark.parametrize("batch,blocks,N", [(30, 9, 10500), (30, 10, 11600), (28, 11, 13000), (15, 19, 22500), (18, 32, 10500)])
 def test_more_than_eight_blocks_where_the_chip_is_full(lazyev_lib, dtype, d, batch, blocks, N):
     """Units of more than eight blocks in launches of more than two stream blocks per compute unit: the unit's last block merges,
-    nine records at a time (fp32 rows of 128: eighteen), a round that is not full, a whole one, one more record, and several.  Outputs of sampled sequences against fp64 softmax attention; TS / MRI / pos as with three
-    blocks a unit."""
+    nine records at a time (fp32 rows of 128: eighteen), a round that is not full, a whole one, one more record, and several.  Outputs
+    of sampled sequences against fp64 softmax attention; TS / MRI / pos as with three blocks a unit."""
     H, group, steps = 2, 3, 3
     dt = torch.float32 if dtype == "fp32" else torch.bfloat16
     states = []
