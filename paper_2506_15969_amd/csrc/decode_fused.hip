@@ -1741,14 +1741,19 @@ size_t decode_fused_record_bytes() { return static_cast<size_t>(kRecWords) * siz
 //   * of 128 x bf16 nine and ten from 46 sub-tiles on: 24 units x 690 / 722 6 / 10 5.8 / 6.0, 6.2 / 6.2.  Nine until two blocks to a
 //     compute unit take over: 26 units x 16300 / 24000 9 / 19 42.6 / 44.0, 63.7 / 61.5 (64 x bf16 28.0 / 29.0, 40.6 / 39.7, fp32 (64) 47.1 /
 //     46.4, 71.3 / 63.5, (128) 84.0 / 82.8, 127 / 119), 28 x 18500 of their own lengths 9 / 18 43.8 / 41.6.
-//   * beyond, 16, 24, 32, 48 or 64 (a merging wave reads a record per lane and eight blocks): 12 units x 2000 / 8200 16 /
-//     21 6.0 / 6.3, 11.6 / 13.2; 10 units x 8200 24 / 25 10.3 / 12.0; 6 units x 8200 32 / 42 8.0 / 9.0; of 11 and 12 units
-//     20 for long caches: 11 x 12000 16 / 20 17.1 / 16.8 (64 x bf16 13.5 / 10.9, fp32 (64) 20.7 / 16.6, (128) 33.9 / 31.4).
-//   * more than 16 once a wave has two sub-tiles to do: 8 units x 1500 16 / 24 5.5 / 5.5, x 2000 16 / 32 5.9 / 5.6, 10
-//     units x 4000 16 / 24 7.6 / 7.3; fp32 rows, whose sub-tiles take longer, before: 6 units x 1500 16 / 24 (64) 6.6 / 6.0,
-//     (128) 9.0 / 7.7.
-//   * more than 32 from three on: 4 units x 4000 / 6000 / 12000 32 / 64 6.0 / 6.3, 6.5 / 6.4, 9.0 / 8.4; 5 units x 8200 32 /
-//     51 8.5 / 8.2; 4 units of 128 x fp32 x 3000 32 / 48 9.2 / 8.6, x 4000 32 / 64 9.5 / 8.9.
+//   * all up to 28 where a wave would have two sub-tiles or more to do with 16, and these otherwise (8 units x 1500 16 / 24 5.5 /
+//     5.5, 10 units x 2000 24 / 25 5.7 / 5.6; fp32 rows, whose sub-tiles take longer, before: 6 units x 1500 16 / 24 (64) 6.6 / 6.0, (128) 9.0 /
+//     7.7): 11 units x 4000 / 8200 / 24000 16 / 23 7.1 / 6.7, 10.7 / 9.9, 29.1 / 26.0 (64 x bf16 7.1 / 6.8, 9.3 / 8.4, 21.2 / 16.9, fp32 (64) 8.9
+//     / 8.1, 13.6 / 11.4, 34.6 / 28.2, (128) 13.6 / 11.9, 23.0 / 19.4, 61.0 / 50.0); 15 units x 8200 / 24000 fp32 16 / 17 (64) 14.7 / 14.3, 38.9 /
+//     38.1, (128) 25.7 / 24.7, 72.3 / 68.2; 9 units x 4000 / 8200 / 24000 24 / 28 6.5 / 6.4, 9.0 / 8.6, 21.1 / 21.5 (fp32 (128) 11.3 / 11.3, 18.2 /
+//     16.9, 42.4 / 40.9).  But a merging wave reads a record per lane and eight blocks: of bf16 rows 16 instead of 17 and 18 (15 units x
+//     4000 / 13000 7.6 / 7.7, 19.4 / 19.8), up to 500 sub-tiles instead of 19 (13 units x 4000 / 8200 7.2 / 7.4, 11.7 / 11.5), up to 240
+//     instead of 21 and 23 (12 units x 2000 16 / 21 5.7 / 5.6, with 7 heads 5.8 / 5.8).
+//   * beyond, 32 for 6 and 7 units (6 units x 8200 32 / 42 7.1 / 7.6, 7 units 32 / 36 7.7 / 8.0; fp32 rows of 6 units 42 from 500 sub-tiles on: x
+//     8200 / 19000 (64) 9.4 / 9.0, 15.4 / 14.7, (128) 14.6 / 13.7, 26.3 / 24.4); 48 and 64, of fp32 rows 51 and 64, for fewer units once a
+//     wave has three to do: 4 units x 4000 / 6000 / 12000 32 / 64 6.0 / 6.3, 6.5 / 6.4, 9.0 / 8.4; 5 units x 8200 / 13000 32 / 48 6.9 / 7.1,
+//     9.0 / 8.5 (64 x bf16 7.3 / 7.5, 8.4 / 8.4), fp32 rows 32 / 51 (64) 9.4 / 8.5, 11.7 / 10.3, (128) 14.4 / 12.0, 18.8 / 16.3; 4 units of
+//     128 x fp32 x 3000 32 / 48 9.2 / 8.6, x 4000 32 / 64 9.5 / 8.9.
 static int two_per_compute_unit_from(bool f32, bool own_lengths) { return f32 || own_lengths ? 1024 : 1200; }
 static int merged_split(int n_sub, bool f32, int head_dim, bool own_lengths, int most) {
   const int by_length = (n_sub + kWaves - 1) / kWaves;
@@ -1756,12 +1761,12 @@ static int merged_split(int n_sub, bool f32, int head_dim, bool own_lengths, int
   if (most == kPairMax + 1 && n_sub >= two_per_compute_unit_from(f32, own_lengths)) return 0;
   int n = most;
   if (most >= 16) {
-    const bool wide = f32 && head_dim == 128;
-    if (most >= 20 && most < 24 && n_sub >= 500) n = 20;
-    else if (most < 24 || n_sub < (f32 ? 80 : 112)) n = 16;
-    else if (most < 32) n = 24;
-    else if (most < 48 || n_sub < (wide && most == kFusedSplitMax ? 180 : 376)) n = 32;
-    else n = most / 16 * 16;
+    if (n_sub < (f32 ? 80 : 112)) n = 16;
+    else if (most < 24) n = f32 || (most > 18 && n_sub >= (most > 20 ? 240 : 500)) ? most : 16;
+    else if (most < 32) n = most;
+    else if (most < 48) n = f32 && most >= 40 && n_sub >= 500 ? most : 32;
+    else if (n_sub < (f32 && head_dim == 128 && most == kFusedSplitMax ? 180 : !f32 && most < kFusedSplitMax ? 700 : 376)) n = 32;
+    else n = f32 ? most : most / 16 * 16;
   }
   return n < by_length ? n : by_length;
 }

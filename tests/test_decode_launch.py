@@ -56,6 +56,20 @@ def test_nine_to_fifteen_blocks_where_there_is_room(lazyev_lib, d, f32):
         assert [fn(units, n_sub, f32, d, False) for n_sub in (44, 46, 48, 49, 60, 100)] == [6, 6, 6, 8, 8, 8]
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_sixteen_to_twentyeight_blocks_where_there_is_room(lazyev_lib, d):
+    """fp32 rows: all that there is room for, whatever the number of units, once a wave has two sub-tiles to do with 16.  bf16 rows: so
+    from 500 sub-tiles on, but for 17 and 18."""
+    fn = getattr(lazyev_lib.lib, "_ZN6lazyev18decode_fused_splitEiibib")
+    fn.restype, fn.argtypes = C.c_int, [C.c_int, C.c_int, C.c_bool, C.c_int, C.c_bool]
+    for units in range(9, 17):
+        for n_sub in (128, 300, 500, 1000, 1500):
+            most = 256 // units
+            assert fn(units, n_sub, True, d, False) == most
+            if n_sub >= 500:
+                assert fn(units, n_sub, False, d, False) == (16 if most in (17, 18) else most)
+
+
 @pytest.mark.parametrize("group", [1, 4, 7, 8])
 def test_sequences_of_their_own_lengths(lazyev_lib, group):
     """Merging blocks stay before the tracking blocks, at every length; two blocks per compute unit from 16384 entries on where
